@@ -1,6 +1,6 @@
-"""MI355X-native SAAP decode hot path (arXiv 2502.08246): thin Python binding over libsaap.so.
+"""MI355X-native SAAP decode hot path (arXiv 2502.08246): thin binding over libsaap.so.
 
-The package holds the HIP sources (csrc/), their build script and a ctypes binding whose
+The package holds the HIP sources (csrc/), their build script and a binding whose
 functions carry the names of the C entry points.  Every step runs in the HIP kernels; torch
 is used for device memory and streams only.  There is no CPU fallback: calling an operation
 without the built library or without a GPU raises.

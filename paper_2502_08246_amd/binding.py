@@ -1,12 +1,17 @@
-"""ctypes binding of libsaap.so (declared in include/saap.h).
+"""Binding of libsaap.so (declared in include/saap.h) to torch tensors.
 
 Argument marshalling only: shapes are read off the tensors, pointers and the current HIP
 stream are handed to the C entry points, status codes become exceptions.  Outputs are
 allocated with torch (device memory) unless the caller passes them in.
+
+The calls a program makes for every prompt, token or training step (NATIVE) are C++ functions on
+torch tensors (csrc/native.cpp): marshalled here a call held the host for 10 to 15 us, as long as its
+kernels take.  The others go through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 import torch
@@ -22,7 +27,18 @@ WS_HEADER_BYTES = 65536
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libsaap.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
 _lib = None
+_native = None
+
+NATIVE = (
+    "assign_keys", "build_bucket_index", "build_windowed_index", "quantize_kv",
+    "classify_queries", "select_buckets", "select_buckets_from_logits", "build_visit_plan", "select_buckets_planned",
+    "sparse_decode_attention", "sparse_decode_attention_fp8", "windowed_decode_attention", "windowed_decode_attention_fp8",
+    "dense_decode_attention", "dense_decode_attention_fp8", "select_attend", "select_attend_fp8",
+    "planned_decode_attention", "planned_decode_attention_fp8", "prefill_sparse_attention",
+    "append_keys", "append_keys_fp8", "window_push", "window_push_fp8", "adam_update",
+)
 
 EXPORTS = (
     "saap_workspace_bytes", "saap_workspace_reset", "saap_status_string", "saap_device_compute_units",
@@ -115,37 +131,30 @@ def workspace_bytes(op: int, **shape) -> int:
     return int(load_library().saap_workspace_bytes(op, ctypes.byref(sh)))
 
 
-class _Workspace:
-    """Device scratch handed to the calls.  Zero-filled once at allocation, which is what the
-    header of arrival counters needs; grown (and zero-filled again) on demand.
-
-    A HIP graph that captured a call holds the RAW ADDRESS of the buffer it was given.  A buffer that has
-    been handed out is therefore never freed: when a larger one replaces it, the old one is kept alive, so a
-    graph captured earlier still replays into memory that belongs to the workspace.  Growing while the
-    current stream is capturing is refused (allocating there would also break the capture): run the call
-    once eagerly first, or pass ws= explicitly."""
-
-    def __init__(self):
-        self.buf = None
-        self.retired = []
-
-    def get(self, nbytes: int, device) -> torch.Tensor:
-        if self.buf is None or self.buf.numel() < nbytes or self.buf.device != torch.device(device):
-            if torch.cuda.is_current_stream_capturing():
-                raise RuntimeError("the shared SAAP workspace would have to grow during stream capture: call the "
-                                   "operation once eagerly before capturing, or pass ws=")
-            if self.buf is not None:
-                self.retired.append(self.buf)
-            self.buf = torch.zeros(max(nbytes, WS_HEADER_BYTES), dtype=torch.uint8, device=device)
-        return self.buf
-
-
-_default_ws = _Workspace()
+def native():
+    """The native call layer (csrc/native.cpp), built first if absent."""
+    global _native
+    if _native is None:
+        load_library()
+        if not os.path.exists(_NATIVE_PATH):
+            from . import build as _build
+            _build.build_native()
+        _native = importlib.import_module("._native", __package__)
+    return _native
 
 
 def workspace(nbytes: int, device) -> torch.Tensor:
-    """The binding's shared workspace buffer, at least nbytes long."""
-    return _default_ws.get(nbytes, device)
+    """The shared workspace buffer of the device, at least nbytes long.
+
+    It is zero-filled when it is made, which is what the header of arrival counters needs, and replaced by a larger one
+    on demand.  A HIP graph that captured a call holds the RAW ADDRESS of the buffer it was given, so a buffer that has
+    been handed out is never freed: a graph captured earlier still replays into memory that belongs to the workspace.
+    Growing while the current stream is capturing is refused (allocating there would also break the capture): run the
+    call once eagerly first, or pass ws= explicitly."""
+    device = torch.device(device)
+    if device.type != "cuda":
+        raise ValueError("SAAP workspaces live in GPU memory; there is no CPU path")
+    return native().workspace(int(nbytes), torch.cuda.current_device() if device.index is None else device.index)
 
 
 def _ws(op, device, ws, **shape):
@@ -182,132 +191,6 @@ def mfma_rate_probe(operands: torch.Tensor, iters: int, sink: torch.Tensor, wgs_
     return flop.value
 
 
-def assign_keys(x, centroids, bias=None, out=None, ws=None):
-    """x [S,Hkv,N,d], centroids [Hkv,B,d], bias [Hkv,B] fp32 or None -> bucket_ids int32 [S,Hkv,N]."""
-    S, Hkv, N, d = x.shape
-    B = centroids.shape[1]
-    if centroids.shape != (Hkv, B, d) or centroids.dtype != x.dtype:
-        raise ValueError("centroids must be [Hkv,B,d] in the dtype of x")
-    ids = out if out is not None else torch.empty(S, Hkv, N, dtype=torch.int32, device=x.device)
-    ws, wsb = _ws(OP_ASSIGN_KEYS, x.device, ws, S=S, Hkv=Hkv, N=N, B=B, d=d)
-    st = load_library().saap_assign_keys(_ptr(x), _ptr(centroids), _ptr(bias), _ptr(ids), _i32(S), _i32(Hkv),
-                                         _i32(N), _i32(B), _i32(d), _i32(_dtype_code(x)), _ptr(ws), wsb, _stream())
-    _check("saap_assign_keys", st)
-    return ids
-
-
-def build_bucket_index(bucket_ids, K, V, B, slack=0, ws=None):
-    """-> off [S,Hkv,B+1], len [S,Hkv,B], idx [S,Hkv,Ncap] (int32), Ksorted, Vsorted [S,Hkv,Ncap,d]."""
-    S, Hkv, N, d = K.shape
-    Ncap = N + B * slack
-    dev = K.device
-    off = torch.empty(S, Hkv, B + 1, dtype=torch.int32, device=dev)
-    ln = torch.empty(S, Hkv, B, dtype=torch.int32, device=dev)
-    idx = torch.empty(S, Hkv, Ncap, dtype=torch.int32, device=dev)
-    alloc = torch.zeros if slack > 0 else torch.empty
-    Ks = alloc(S, Hkv, Ncap, d, dtype=K.dtype, device=dev)
-    Vs = alloc(S, Hkv, Ncap, d, dtype=K.dtype, device=dev)
-    ws, wsb = _ws(OP_BUILD_BUCKET_INDEX, dev, ws, S=S, Hkv=Hkv, N=N, B=B)
-    st = load_library().saap_build_bucket_index(_ptr(bucket_ids), _ptr(K), _ptr(V), _ptr(off), _ptr(ln), _ptr(idx),
-                                                _ptr(Ks), _ptr(Vs), _i32(S), _i32(Hkv), _i32(N), _i32(Ncap), _i32(B),
-                                                _i32(d), _i32(_dtype_code(K)), _i32(slack), _ptr(ws), wsb, _stream())
-    _check("saap_build_bucket_index", st)
-    return off, ln, idx, Ks, Vs
-
-
-def append_keys(x_new, k_new, v_new, pos_new, centroids, bias, off, ln, idx, Ks, Vs, overflow_flag=None, new_ids=None,
-                ws=None):
-    """In-place append of one key per (sequence, KV head). -> (new_bucket_ids [S,Hkv], overflow_flag [1])."""
-    S, Hkv, d = x_new.shape
-    B = centroids.shape[1]
-    Ncap = idx.shape[2]
-    dev = x_new.device
-    if new_ids is None:
-        new_ids = torch.empty(S, Hkv, dtype=torch.int32, device=dev)
-    if overflow_flag is None:
-        overflow_flag = torch.zeros(4, dtype=torch.int32, device=dev)
-    ws, wsb = _ws(OP_APPEND_KEYS, dev, ws, S=S, Hkv=Hkv, B=B)
-    st = load_library().saap_append_keys(_ptr(x_new), _ptr(k_new), _ptr(v_new), _ptr(pos_new), _ptr(centroids),
-                                         _ptr(bias), _ptr(off), _ptr(ln), _ptr(idx), _ptr(Ks), _ptr(Vs),
-                                         _ptr(new_ids), _ptr(overflow_flag), _i32(S), _i32(Hkv), _i32(Ncap), _i32(B),
-                                         _i32(d), _i32(_dtype_code(x_new)), _ptr(ws), wsb, _stream())
-    _check("saap_append_keys", st)
-    return new_ids, overflow_flag
-
-
-def _bf16_only(name, *tensors):
-    for t in tensors:
-        if t.dtype != torch.bfloat16:
-            raise TypeError(f"{name}: bf16 features and rows expected, got {t.dtype}")
-
-
-def append_keys_fp8(x_new, k_new, v_new, pos_new, centroids, bias, off, ln, idx, K8, V8, kscale, vscale,
-                    overflow_flag=None, new_ids=None, ws=None):
-    """append_keys on an 8-bit cache (K8, V8 uint8 with the scales of quantize_kv), in place."""
-    _bf16_only("append_keys_fp8", x_new, k_new, v_new, centroids)
-    S, Hkv, d = x_new.shape
-    B = centroids.shape[1]
-    Ncap = idx.shape[2]
-    dev = x_new.device
-    if new_ids is None:
-        new_ids = torch.empty(S, Hkv, dtype=torch.int32, device=dev)
-    if overflow_flag is None:
-        overflow_flag = torch.zeros(4, dtype=torch.int32, device=dev)
-    ws, wsb = _ws(OP_APPEND_KEYS, dev, ws, S=S, Hkv=Hkv, B=B)
-    st = load_library().saap_append_keys_fp8(
-        _ptr(x_new), _ptr(k_new), _ptr(v_new), _ptr(pos_new), _ptr(centroids), _ptr(bias), _ptr(off), _ptr(ln),
-        _ptr(idx), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(new_ids), _ptr(overflow_flag), _i32(S),
-        _i32(Hkv), _i32(Ncap), _i32(B), _i32(d), _ptr(ws), wsb, _stream())
-    _check("saap_append_keys_fp8", st)
-    return new_ids, overflow_flag
-
-
-def window_push_fp8(x_new, k_new, v_new, pos_new, centroids, bias, off, ln, idx, K8, V8, kscale, vscale, resident_ids,
-                    n_sink, n_recent, overflow_flag=None, new_ids=None, ws=None):
-    """window_push on an 8-bit cache (K8, V8 uint8 with the scales of quantize_kv), in place."""
-    _bf16_only("window_push_fp8", x_new, k_new, v_new, centroids)
-    S, Hkv, d = x_new.shape
-    B = centroids.shape[1]
-    Ncap = idx.shape[2]
-    dev = x_new.device
-    if new_ids is None:
-        new_ids = torch.empty(S, Hkv, dtype=torch.int32, device=dev)
-    if overflow_flag is None:
-        overflow_flag = torch.zeros(4, dtype=torch.int32, device=dev)
-    ws, wsb = _ws(OP_WINDOW_PUSH, dev, ws, S=S, Hkv=Hkv, B=B)
-    st = load_library().saap_window_push_fp8(
-        _ptr(x_new), _ptr(k_new), _ptr(v_new), _ptr(pos_new), _ptr(centroids), _ptr(bias), _ptr(off), _ptr(ln),
-        _ptr(idx), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(resident_ids), _ptr(new_ids),
-        _ptr(overflow_flag), _i32(S), _i32(Hkv), _i32(Ncap), _i32(B), _i32(d), _i32(n_sink), _i32(n_recent), _ptr(ws),
-        wsb, _stream())
-    _check("saap_window_push_fp8", st)
-    return new_ids, overflow_flag
-
-
-def classify_queries(xq, W1, b1, W2, b2, Hkv, output_kind=PROBS, out=None, ws=None):
-    """xq [S,Hq,d]; W1 [Hw,hidden,d]; W2 [Hw,B,hidden]; b1,b2 fp32 or None -> scores fp32 [S,Hq,B].
-    W1 = None: the one-layer model z = W2 x + b2 with W2 [Hw,B,d]."""
-    S, Hq, d = xq.shape
-    if W1 is None:
-        Hw, B, hidden = W2.shape[0], W2.shape[1], 0
-        if W2.shape != (Hw, B, d) or W2.dtype != xq.dtype:
-            raise ValueError("one-layer model: W2 must be [Hw,B,d] in xq's dtype")
-        b1 = None
-    else:
-        Hw, hidden, _ = W1.shape
-        B = W2.shape[1]
-        if W2.shape != (Hw, B, hidden) or W1.dtype != xq.dtype or W2.dtype != xq.dtype:
-            raise ValueError("W1 [Hw,hidden,d] and W2 [Hw,B,hidden] must match xq's dtype")
-    scores = out if out is not None else torch.empty(S, Hq, B, dtype=torch.float32, device=xq.device)
-    ws, wsb = _ws(OP_CLASSIFY_QUERIES, xq.device, ws, S=S, Hq=Hq, hidden=hidden)
-    st = load_library().saap_classify_queries(_ptr(xq), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(b2), _i32(Hw),
-                                              _ptr(scores), _i32(S), _i32(Hq), _i32(Hkv), _i32(d), _i32(hidden),
-                                              _i32(B), _i32(_dtype_code(xq)), _i32(output_kind), _ptr(ws), wsb,
-                                              _stream())
-    _check("saap_classify_queries", st)
-    return scores
-
-
 def classify_select(xq, W1, b1, W2, b2, Hkv, nprobe, off=None, ln=None, resident_run=-1, want_plan=False, logits=None,
                     probs=None, out=None, plan=None, ws=None):
     """classify_queries (logits) + the group selection in one call. -> (logits [S,Hq,B], selected [S,Hkv,nprobe], plan
@@ -333,52 +216,6 @@ def classify_select(xq, W1, b1, W2, b2, Hkv, nprobe, off=None, ln=None, resident
     return logits, sel, plan
 
 
-def select_buckets(scores, Hkv, nprobe, mode=GROUP_SUM, out=None, ws=None):
-    """scores fp32 [S,Hq,B] -> selected int32 [S,Hkv,nprobe] (GROUP_SUM) or [S,Hq,nprobe] (INDEPENDENT)."""
-    S, Hq, B = scores.shape
-    lists = Hq if mode == INDEPENDENT else Hkv
-    sel = out if out is not None else torch.empty(S, lists, nprobe, dtype=torch.int32, device=scores.device)
-    ws, wsb = _ws(OP_SELECT_BUCKETS, scores.device, ws)
-    st = load_library().saap_select_buckets(_ptr(scores), _ptr(sel), _i32(S), _i32(Hq), _i32(Hkv), _i32(B),
-                                            _i32(nprobe), _i32(mode), _ptr(ws), wsb, _stream())
-    _check("saap_select_buckets", st)
-    return sel
-
-
-def select_buckets_from_logits(logits, Hkv, nprobe, mode=GROUP_SUM, probs=None, out=None, ws=None):
-    """logits fp32 [S,Hq,B] (classify_queries with LOGITS) -> selected; `probs` (optional fp32 [S,Hq,B]) receives
-    the softmax the selection was made from."""
-    S, Hq, B = logits.shape
-    lists = Hq if mode == INDEPENDENT else Hkv
-    sel = out if out is not None else torch.empty(S, lists, nprobe, dtype=torch.int32, device=logits.device)
-    ws, wsb = _ws(OP_SELECT_BUCKETS, logits.device, ws)
-    st = load_library().saap_select_buckets_from_logits(_ptr(logits), _ptr(probs), _ptr(sel), _i32(S), _i32(Hq),
-                                                        _i32(Hkv), _i32(B), _i32(nprobe), _i32(mode), _ptr(ws), wsb,
-                                                        _stream())
-    _check("saap_select_buckets_from_logits", st)
-    return sel
-
-
-def sparse_decode_attention(q, Ks, Vs, off, ln, selected, scale, mode=GROUP_SUM, out_dtype=torch.float32,
-                            out=None, lse=None, ws=None):
-    """q [S,Hq,d]; Ks,Vs [S,Hkv,Ncap,d]; off,ln from build_bucket_index; selected from select_buckets
-    -> out [S,Hq,d] (out_dtype), lse fp32 [S,Hq]."""
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = Ks.shape
-    B = ln.shape[2]
-    nprobe = selected.shape[2]
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=mode)
-    st = load_library().saap_sparse_decode_attention(
-        _ptr(q), _ptr(Ks), _ptr(Vs), _ptr(off), _ptr(ln), _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0),
-        _i32(nprobe), _i32(mode), ctypes.c_float(scale), _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S),
-        _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(B), _i32(d), _i32(_dtype_code(q)), _ptr(ws), wsb, _stream())
-    _check("saap_sparse_decode_attention", st)
-    return out, lse
-
-
 def visit_plan_ints(S, Hq, Hkv, nruns, mode=GROUP_SUM) -> int:
     """int32 elements of the visit plan of S*Hkv (GROUP_SUM) or S*Hq (INDEPENDENT) lists of nruns runs."""
     nbytes = int(load_library().saap_visit_plan_bytes(int(S), int(Hq), int(Hkv), int(nruns), int(mode)))
@@ -394,95 +231,6 @@ def _plan_buffer(plan, S, Hq, Hkv, nruns, mode, device):
     elif plan.dtype != torch.int32 or plan.numel() < n:
         raise ValueError(f"plan must be int32 with at least {n} elements")
     return plan
-
-
-def build_visit_plan(selected, off, ln, Hq, mode=GROUP_SUM, resident_run=-1, plan=None):
-    """selected int32 [S,lists,nprobe]; off [S,Hkv,runs+1], ln [S,Hkv,runs] -> plan (int32, flat)."""
-    S, _, nprobe = selected.shape
-    Hkv, runs = ln.shape[1], ln.shape[2]
-    nruns = nprobe + (1 if resident_run >= 0 else 0)
-    plan = _plan_buffer(plan, S, Hq, Hkv, nruns, mode, ln.device)
-    st = load_library().saap_build_visit_plan(_ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _ptr(off), _ptr(ln),
-                                              _i32(nprobe), _i32(mode), _i32(resident_run), _ptr(plan), _i32(S), _i32(Hq),
-                                              _i32(Hkv), _i32(runs), _stream())
-    _check("saap_build_visit_plan", st)
-    return plan
-
-
-def select_buckets_planned(scores, off, ln, Hkv, nprobe, input_kind=PROBS, mode=GROUP_SUM, resident_run=-1, probs=None,
-                           out=None, plan=None, ws=None):
-    """select_buckets (PROBS) or select_buckets_from_logits (LOGITS) that also writes the lists' visit plan.
-    -> (selected, plan)."""
-    S, Hq, B = scores.shape
-    lists = Hq if mode == INDEPENDENT else Hkv
-    sel = out if out is not None else torch.empty(S, lists, nprobe, dtype=torch.int32, device=scores.device)
-    plan = _plan_buffer(plan, S, Hq, Hkv, nprobe + (1 if resident_run >= 0 else 0), mode, scores.device)
-    ws, wsb = _ws(OP_SELECT_BUCKETS, scores.device, ws)
-    st = load_library().saap_select_buckets_planned(
-        _ptr(scores), _i32(input_kind), _ptr(probs), _ptr(off), _ptr(ln), _i32(resident_run), _ptr(sel), _ptr(plan),
-        _i32(S), _i32(Hq), _i32(Hkv), _i32(B), _i32(nprobe), _i32(mode), _ptr(ws), wsb, _stream())
-    _check("saap_select_buckets_planned", st)
-    return sel, plan
-
-
-def planned_decode_attention(q, Ks, Vs, plan, nruns, scale, mode=GROUP_SUM, out_dtype=torch.float32, out=None, lse=None,
-                             ws=None):
-    """q [S,Hq,d]; Ks,Vs [S,Hkv,Ncap,d]; plan from select_buckets_planned / build_visit_plan -> out, lse."""
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = Ks.shape
-    dev = q.device
-    _plan_buffer(plan, S, Hq, Hkv, nruns, mode, dev)
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_PLANNED_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=mode)
-    st = load_library().saap_planned_decode_attention(
-        _ptr(q), _ptr(Ks), _ptr(Vs), _ptr(plan), _i32(nruns), _i32(mode), ctypes.c_float(scale), _ptr(out),
-        _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(d), _i32(_dtype_code(q)),
-        _ptr(ws), wsb, _stream())
-    _check("saap_planned_decode_attention", st)
-    return out, lse
-
-
-def planned_decode_attention_fp8(q, K8, V8, kscale, vscale, plan, nruns, scale, mode=GROUP_SUM, out_dtype=torch.float32,
-                                 out=None, lse=None, ws=None):
-    """planned_decode_attention on a cache written by quantize_kv; q bf16 [S,Hq,d]."""
-    if q.dtype != torch.bfloat16 or K8.dtype != torch.uint8 or V8.dtype != torch.uint8:
-        raise TypeError("q must be bf16, K8 and V8 uint8")
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = K8.shape
-    dev = q.device
-    _plan_buffer(plan, S, Hq, Hkv, nruns, mode, dev)
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_PLANNED_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=mode)
-    st = load_library().saap_planned_decode_attention_fp8(
-        _ptr(q), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(plan), _i32(nruns), _i32(mode),
-        ctypes.c_float(scale), _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap),
-        _i32(d), _ptr(ws), wsb, _stream())
-    _check("saap_planned_decode_attention_fp8", st)
-    return out, lse
-
-
-def prefill_sparse_attention(q, K, V, Ks, Vs, off, ln, idx, selected, pos0, n_sink, n_recent, scale,
-                             out_dtype=torch.float32, out=None, lse=None, ws=None):
-    """q [S,Tq,Hq,d]; position-ordered K,V [S,Hkv,Nt,d]; Ks,Vs,off,ln,idx from build_bucket_index over them;
-    selected int32 [S,Hkv,Tq,nprobe]; pos0 int32 [S] -> out [S,Tq,Hq,d], lse fp32 [S,Tq,Hq]."""
-    S, Tq, Hq, d = q.shape
-    _, Hkv, Nt, _ = K.shape
-    Ncap = Ks.shape[2]
-    B = ln.shape[2]
-    nprobe = selected.shape[3]
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Tq, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Tq, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_PREFILL_SPARSE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, N=Tq, nprobe=nprobe)
-    st = load_library().saap_prefill_sparse_attention(
-        _ptr(q), _ptr(K), _ptr(V), _ptr(Ks), _ptr(Vs), _ptr(off), _ptr(ln), _ptr(idx),
-        _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _ptr(pos0), _i32(nprobe), _i32(n_sink), _i32(n_recent),
-        ctypes.c_float(scale), _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Tq),
-        _i32(Nt), _i32(Ncap), _i32(B), _i32(d), _i32(_dtype_code(q)), _ptr(ws), wsb, _stream())
-    _check("saap_prefill_sparse_attention", st)
-    return out, lse
 
 
 def sparse_decode_attention_noalloc(q, Ks, Vs, off, ln, selected, scale, out, lse, mode=GROUP_SUM):
@@ -617,227 +365,6 @@ def fold_batch_norm(W1, b1, gamma, beta, running_mean, running_var, eps=1e-5, ou
     return W1o, b1o
 
 
-def adam_update(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e-8):
-    """One Adam step on one fp32 tensor, in place (param, m, v)."""
-    for t in (param, grad, m, v):
-        if t.dtype != torch.float32 or t.numel() != param.numel():
-            raise TypeError("adam_update works on fp32 tensors of one size")
-    st = load_library().saap_adam_update(_ptr(param), _ptr(grad), _ptr(m), _ptr(v), ctypes.c_size_t(param.numel()),
-                                         _i32(step), ctypes.c_float(lr), ctypes.c_float(beta1), ctypes.c_float(beta2),
-                                         ctypes.c_float(eps), _stream())
-    _check("saap_adam_update", st)
-
-
-def quantize_kv(Ks, Vs, ws=None):
-    """Ks, Vs [S,Hkv,Ncap,d] (bucket-sorted) -> K8, V8 uint8 [S,Hkv,Ncap,d] (OCP FP8 E4M3 codes),
-    kscale, vscale fp32 [S,Hkv] (one power of two per unit)."""
-    S, Hkv, Ncap, d = Ks.shape
-    dev = Ks.device
-    K8 = torch.empty(S, Hkv, Ncap, d, dtype=torch.uint8, device=dev)
-    V8 = torch.empty(S, Hkv, Ncap, d, dtype=torch.uint8, device=dev)
-    ks = torch.empty(S, Hkv, dtype=torch.float32, device=dev)
-    vs = torch.empty(S, Hkv, dtype=torch.float32, device=dev)
-    if ws is None:
-        ws = workspace(WS_HEADER_BYTES, dev)
-    st = load_library().saap_quantize_kv(_ptr(Ks), _ptr(Vs), _ptr(K8), _ptr(V8), _ptr(ks), _ptr(vs), _i32(S), _i32(Hkv),
-                                         _i32(Ncap), _i32(d), _i32(_dtype_code(Ks)), _ptr(ws),
-                                         ctypes.c_size_t(ws.numel()), _stream())
-    _check("saap_quantize_kv", st)
-    return K8, V8, ks, vs
-
-
-def sparse_decode_attention_fp8(q, K8, V8, kscale, vscale, off, ln, selected, scale, mode=GROUP_SUM,
-                                out_dtype=torch.float32, out=None, lse=None, ws=None):
-    """sparse_decode_attention on a cache written by quantize_kv; q bf16 [S,Hq,d]."""
-    if q.dtype != torch.bfloat16 or K8.dtype != torch.uint8 or V8.dtype != torch.uint8:
-        raise TypeError("q must be bf16, K8 and V8 uint8")
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = K8.shape
-    B = ln.shape[2]
-    nprobe = selected.shape[2]
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=mode)
-    st = load_library().saap_sparse_decode_attention_fp8(
-        _ptr(q), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(off), _ptr(ln),
-        _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _i32(nprobe), _i32(mode), ctypes.c_float(scale),
-        _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(B), _i32(d),
-        _ptr(ws), wsb, _stream())
-    _check("saap_sparse_decode_attention_fp8", st)
-    return out, lse
-
-
-def select_attend(logits, q, Ks, Vs, off, ln, nprobe, scale, out_dtype=torch.float32, selected=None, out=None,
-                  lse=None, ws=None, resident_run=-1):
-    """select_buckets_from_logits + sparse_decode_attention in one call (one launch where the library can):
-    logits fp32 [S,Hq,B] -> (selected int32 [S,Hkv,nprobe], out [S,Hq,d], lse fp32 [S,Hq]).  With
-    resident_run = B (an index from build_windowed_index: off [S,Hkv,B+2], ln [S,Hkv,B+1]) the always-visited run
-    is attended too, as by windowed_decode_attention."""
-    if resident_run >= 0:
-        return _select_attend_windowed(logits, q, Ks, Vs, off, ln, nprobe, resident_run, scale, out_dtype, selected, out,
-                                       lse, ws)
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = Ks.shape
-    B = ln.shape[2]
-    dev = q.device
-    selected = selected if selected is not None else torch.empty(S, Hkv, nprobe, dtype=torch.int32, device=dev)
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=GROUP_SUM)
-    st = load_library().saap_select_attend(
-        _ptr(logits), _ptr(q), _ptr(Ks), _ptr(Vs), _ptr(off), _ptr(ln), _i32(nprobe), ctypes.c_float(scale),
-        _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S),
-        _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(B), _i32(d), _i32(_dtype_code(q)), _ptr(ws), wsb, _stream())
-    _check("saap_select_attend", st)
-    return selected, out, lse
-
-
-def _select_attend_windowed(logits, q, Ks, Vs, off, ln, nprobe, resident_run, scale, out_dtype, selected, out, lse, ws):
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = Ks.shape
-    B = ln.shape[2] - 1
-    dev = q.device
-    selected = selected if selected is not None else torch.empty(S, Hkv, nprobe, dtype=torch.int32, device=dev)
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=GROUP_SUM)
-    st = load_library().saap_select_attend_windowed(
-        _ptr(logits), _ptr(q), _ptr(Ks), _ptr(Vs), _ptr(off), _ptr(ln), _i32(nprobe), _i32(resident_run),
-        ctypes.c_float(scale), _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _ptr(out), _i32(_dtype_code(out)),
-        _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(B), _i32(d), _i32(_dtype_code(q)), _ptr(ws), wsb,
-        _stream())
-    _check("saap_select_attend_windowed", st)
-    return selected, out, lse
-
-
-def select_attend_fp8(logits, q, K8, V8, kscale, vscale, off, ln, nprobe, scale, out_dtype=torch.float32,
-                      selected=None, out=None, lse=None, ws=None):
-    """select_attend on a cache written by quantize_kv; q bf16 [S,Hq,d]."""
-    if q.dtype != torch.bfloat16 or K8.dtype != torch.uint8 or V8.dtype != torch.uint8:
-        raise TypeError("q must be bf16, K8 and V8 uint8")
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = K8.shape
-    B = ln.shape[2]
-    dev = q.device
-    selected = selected if selected is not None else torch.empty(S, Hkv, nprobe, dtype=torch.int32, device=dev)
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=GROUP_SUM)
-    st = load_library().saap_select_attend_fp8(
-        _ptr(logits), _ptr(q), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(off), _ptr(ln), _i32(nprobe),
-        ctypes.c_float(scale), _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _ptr(out), _i32(_dtype_code(out)),
-        _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(B), _i32(d), _ptr(ws), wsb, _stream())
-    _check("saap_select_attend_fp8", st)
-    return selected, out, lse
-
-
-def dense_decode_attention_fp8(q, K8, V8, kscale, vscale, scale, off=None, ln=None, out_dtype=torch.float32,
-                               out=None, lse=None, ws=None):
-    """dense_decode_attention on 8-bit K/V (packed, or a bucket-sorted cache with off/ln); q bf16."""
-    if q.dtype != torch.bfloat16 or K8.dtype != torch.uint8 or V8.dtype != torch.uint8:
-        raise TypeError("q must be bf16, K8 and V8 uint8")
-    S, Hq, d = q.shape
-    _, Hkv, N, _ = K8.shape
-    B = ln.shape[2] if ln is not None else 0
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_DENSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv)
-    st = load_library().saap_dense_decode_attention_fp8(
-        _ptr(q), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(off), _ptr(ln), _i32(B), ctypes.c_float(scale),
-        _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(N), _i32(d), _ptr(ws), wsb,
-        _stream())
-    _check("saap_dense_decode_attention_fp8", st)
-    return out, lse
-
-
-def build_windowed_index(bucket_ids, K, V, B, slack, n_sink, n_recent, ws=None):
-    """Index with a resident run of W = n_sink + n_recent slots behind the B buckets.
-    -> off [S,Hkv,B+2], len [S,Hkv,B+1], idx [S,Hkv,Ncap], Ksorted, Vsorted [S,Hkv,Ncap,d], resident_ids [S,Hkv,W]."""
-    S, Hkv, N, d = K.shape
-    W = n_sink + n_recent
-    Ncap = max(N - W, 0) + B * slack + W
-    dev = K.device
-    off = torch.empty(S, Hkv, B + 2, dtype=torch.int32, device=dev)
-    ln = torch.empty(S, Hkv, B + 1, dtype=torch.int32, device=dev)
-    idx = torch.empty(S, Hkv, Ncap, dtype=torch.int32, device=dev)
-    Ks = torch.zeros(S, Hkv, Ncap, d, dtype=K.dtype, device=dev)
-    Vs = torch.zeros(S, Hkv, Ncap, d, dtype=K.dtype, device=dev)
-    res = torch.empty(S, Hkv, max(W, 1), dtype=torch.int32, device=dev)[:, :, :W]
-    ws, wsb = _ws(OP_BUILD_BUCKET_INDEX, dev, ws, S=S, Hkv=Hkv, N=N, B=B)
-    st = load_library().saap_build_windowed_index(
-        _ptr(bucket_ids), _ptr(K), _ptr(V), _ptr(off), _ptr(ln), _ptr(idx), _ptr(Ks), _ptr(Vs), _ptr(res), _i32(S),
-        _i32(Hkv), _i32(N), _i32(Ncap), _i32(B), _i32(d), _i32(_dtype_code(K)), _i32(slack), _i32(n_sink),
-        _i32(n_recent), _ptr(ws), wsb, _stream())
-    _check("saap_build_windowed_index", st)
-    return off, ln, idx, Ks, Vs, res
-
-
-def window_push(x_new, k_new, v_new, pos_new, centroids, bias, off, ln, idx, Ks, Vs, resident_ids, n_sink, n_recent,
-                overflow_flag=None, new_ids=None, ws=None):
-    """In-place push of one key per (sequence, KV head) into the resident run; the displaced key moves
-    to its bucket. -> (new_bucket_ids [S,Hkv], overflow_flag)."""
-    S, Hkv, d = x_new.shape
-    B = centroids.shape[1]
-    Ncap = idx.shape[2]
-    dev = x_new.device
-    if new_ids is None:
-        new_ids = torch.empty(S, Hkv, dtype=torch.int32, device=dev)
-    if overflow_flag is None:
-        overflow_flag = torch.zeros(4, dtype=torch.int32, device=dev)
-    ws, wsb = _ws(OP_WINDOW_PUSH, dev, ws, S=S, Hkv=Hkv, B=B)
-    st = load_library().saap_window_push(
-        _ptr(x_new), _ptr(k_new), _ptr(v_new), _ptr(pos_new), _ptr(centroids), _ptr(bias), _ptr(off), _ptr(ln),
-        _ptr(idx), _ptr(Ks), _ptr(Vs), _ptr(resident_ids), _ptr(new_ids), _ptr(overflow_flag), _i32(S), _i32(Hkv),
-        _i32(Ncap), _i32(B), _i32(d), _i32(_dtype_code(x_new)), _i32(n_sink), _i32(n_recent), _ptr(ws), wsb, _stream())
-    _check("saap_window_push", st)
-    return new_ids, overflow_flag
-
-
-def windowed_decode_attention(q, Ks, Vs, off, ln, selected, resident_run, scale, mode=GROUP_SUM,
-                              out_dtype=torch.float32, out=None, lse=None, ws=None):
-    """sparse_decode_attention over the selected buckets plus the always-visited run `resident_run`
-    (-1 for none); off [S,Hkv,runs+1], ln [S,Hkv,runs]."""
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = Ks.shape
-    runs = ln.shape[2]
-    nprobe = selected.shape[2]
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=mode)
-    st = load_library().saap_windowed_decode_attention(
-        _ptr(q), _ptr(Ks), _ptr(Vs), _ptr(off), _ptr(ln), _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0),
-        _i32(nprobe), _i32(mode), _i32(resident_run), ctypes.c_float(scale), _ptr(out), _i32(_dtype_code(out)),
-        _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap), _i32(runs), _i32(d), _i32(_dtype_code(q)), _ptr(ws),
-        wsb, _stream())
-    _check("saap_windowed_decode_attention", st)
-    return out, lse
-
-
-def windowed_decode_attention_fp8(q, K8, V8, kscale, vscale, off, ln, selected, resident_run, scale, mode=GROUP_SUM,
-                                  out_dtype=torch.float32, out=None, lse=None, ws=None):
-    """windowed_decode_attention on a cache written by quantize_kv; q bf16 [S,Hq,d]."""
-    if q.dtype != torch.bfloat16 or K8.dtype != torch.uint8 or V8.dtype != torch.uint8:
-        raise TypeError("q must be bf16, K8 and V8 uint8")
-    S, Hq, d = q.shape
-    _, Hkv, Ncap, _ = K8.shape
-    runs = ln.shape[2]
-    nprobe = selected.shape[2]
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_SPARSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv, mode=mode)
-    st = load_library().saap_windowed_decode_attention_fp8(
-        _ptr(q), _ptr(K8), _ptr(V8), _ptr(kscale), _ptr(vscale), _ptr(off), _ptr(ln),
-        _ptr(selected) if nprobe > 0 else ctypes.c_void_p(0), _i32(nprobe), _i32(mode), _i32(resident_run),
-        ctypes.c_float(scale), _ptr(out), _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(Ncap),
-        _i32(runs), _i32(d), _ptr(ws), wsb, _stream())
-    _check("saap_windowed_decode_attention_fp8", st)
-    return out, lse
-
-
 def recompact_index(off, ln, idx, Ks, Vs, slack_new, Ncap_new, resident=False, overflow_flag=None):
     """Fresh slack behind every bucket without re-assignment. -> (off_new, idx_new, Ks_new, Vs_new, overflow_flag);
     ln stays valid."""
@@ -884,18 +411,17 @@ def lloyd_iterations(x, centroids, iters, normalize=True):
     return c
 
 
-def dense_decode_attention(q, K, V, scale, off=None, ln=None, out_dtype=torch.float32, out=None, lse=None, ws=None):
-    """q [S,Hq,d]; K,V [S,Hkv,N,d] (packed, or a bucket-sorted cache with off/ln) -> out, lse."""
-    S, Hq, d = q.shape
-    _, Hkv, N, _ = K.shape
-    B = ln.shape[2] if ln is not None else 0
-    dev = q.device
-    out = out if out is not None else torch.empty(S, Hq, d, dtype=out_dtype, device=dev)
-    lse = lse if lse is not None else torch.empty(S, Hq, dtype=torch.float32, device=dev)
-    ws, wsb = _ws(OP_DENSE_DECODE_ATTENTION, dev, ws, S=S, Hq=Hq, Hkv=Hkv)
-    st = load_library().saap_dense_decode_attention(
-        _ptr(q), _ptr(K), _ptr(V), _ptr(off), _ptr(ln), _i32(B), ctypes.c_float(scale), _ptr(out),
-        _i32(_dtype_code(out)), _ptr(lse), _i32(S), _i32(Hq), _i32(Hkv), _i32(N), _i32(d), _i32(_dtype_code(q)),
-        _ptr(ws), wsb, _stream())
-    _check("saap_dense_decode_attention", st)
-    return out, lse
+def _built_on_first_use(name):
+    def call(*args, **kwargs):
+        return getattr(native(), name)(*args, **kwargs)
+
+    call.__name__ = call.__qualname__ = name
+    return call
+
+
+try:
+    from . import _native
+except ImportError:     # not built yet: the first call builds it, or says why it cannot be loaded
+    globals().update({_n: _built_on_first_use(_n) for _n in NATIVE})
+else:
+    globals().update({_n: getattr(_native, _n) for _n in NATIVE})

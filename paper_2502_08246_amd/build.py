@@ -1,4 +1,5 @@
-"""Builds paper_2502_08246_amd/libsaap.so from csrc/*.hip with hipcc for gfx950.
+"""Builds paper_2502_08246_amd/libsaap.so from csrc/*.hip with hipcc for gfx950, and the native call layer
+_native.so (csrc/native.cpp: host code, torch's C++ interface) beside it.
 
 Run as `python -m paper_2502_08246_amd.build`.  hipcc cross-compiles without a GPU.
 """
@@ -12,6 +13,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsaap.so")
+NATIVE = os.path.join(HERE, "_native.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -49,7 +51,28 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed")
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     subprocess.run(cmd, check=True)
+    build_native()
     return LIB
+
+
+def build_native() -> str:
+    """The Python module of the library's calls; links against libsaap.so in the same folder."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I", os.path.join(ROOT, "include")]
+    for path in [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    cmd += [os.path.join(HERE, "csrc", "native.cpp"), "-o", NATIVE]
+    for path in cpp_extension.library_paths():
+        cmd += ["-L", path]
+    cmd += ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-L", HERE, "-l:libsaap.so", "-Wl,-rpath,$ORIGIN"]
+    subprocess.run(cmd, check=True)
+    return NATIVE
 
 
 if __name__ == "__main__":

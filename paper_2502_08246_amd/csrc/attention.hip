@@ -1828,12 +1828,8 @@ LaunchPlan plan_launch(int n_units, long long est_keys_per_unit, long long max_k
 
 template <typename T, int G, bool LIST, int NT, bool MASKED = false, int SEL = 0>
 int32_t launch_nt(const AttnParams& p, const LaunchPlan& lp, hipStream_t stream) {
-  auto kern = attn_kernel<T, G, LIST, NT, MASKED, SEL>;
-  if (lp.lds > 48 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lp.lds) != hipSuccess)
-      return SAAP_HIP_ERROR;
-  }
+  constexpr auto kern = attn_kernel<T, G, LIST, NT, MASKED, SEL>;
+  if (!allow_lds<kern>(lp.lds)) return SAAP_HIP_ERROR;
   saap_trace_arm();
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.n_units * p.P)), dim3((unsigned)lp.threads), lp.lds, stream, p);
   return launch_status();
@@ -1972,10 +1968,8 @@ template <typename T>
 static int32_t launch_planned(const PlanParams& p, int G, unsigned grid, size_t lds, hipStream_t stream) {
 #define SAAP_CASE(GG)                                                                                     \
   case GG: {                                                                                              \
-    auto kern = attn_plan_kernel<T, GG, 512>;                                                             \
-    if (lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                      \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) \
-      return SAAP_HIP_ERROR;                                                                              \
+    constexpr auto kern = attn_plan_kernel<T, GG, 512>;                                                   \
+    if (!allow_lds<kern>(lds)) return SAAP_HIP_ERROR;                                                     \
     saap_trace_arm();                                                                                     \
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, p);                                      \
     return launch_status();                                                                               \
@@ -2370,7 +2364,6 @@ extern "C" int32_t saap_select_attend_fp8(const float* logits, const void* q, co
 namespace {
 static __device__ __align__(256) unsigned char scratch[SAAP_STATIC_SCRATCH_BYTES];
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices];   // per device: that device's copy of `scratch` (the array's name is no device address)
 

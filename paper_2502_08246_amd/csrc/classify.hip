@@ -22,6 +22,8 @@
 // straight from memory (correctness configuration, not tuned).
 #include "select_body.h"
 
+#include <type_traits>
+
 namespace saap {
 namespace {
 
@@ -450,21 +452,16 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
     if (lds < geo.lds) lds = geo.lds;
   }
   // the same slab width with and without the selection: the logits of both calls are then equal bit for bit
-  auto launch = [&](auto kernel) -> int32_t {
-    if (lds > 48 * 1024 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return SAAP_HIP_ERROR;
+  auto launch = [&](auto width, auto fused) -> int32_t {
+    constexpr auto kernel = mlp_out_bf16_kernel<decltype(width)::value, decltype(fused)::value>;
+    if (!allow_lds<kernel>(lds)) return SAAP_HIP_ERROR;
     hipLaunchKernelGGL(kernel, dim3(g2), dim3(kOutThreads), lds, hs, hbuf, static_cast<const bf16_t*>(W2), b2, scores, sh, f);
     return SAAP_OK;
   };
-  if (fs) {
-    if (slab_rows == 128) return launch(mlp_out_bf16_kernel<128, true>);
-    if (slab_rows == 64) return launch(mlp_out_bf16_kernel<64, true>);
-    return launch(mlp_out_bf16_kernel<32, true>);
-  }
-  if (slab_rows == 128) return launch(mlp_out_bf16_kernel<128, false>);
-  if (slab_rows == 64) return launch(mlp_out_bf16_kernel<64, false>);
-  return launch(mlp_out_bf16_kernel<32, false>);
+  auto launch_width = [&](auto width) { return fs ? launch(width, std::true_type{}) : launch(width, std::false_type{}); };
+  if (slab_rows == 128) return launch_width(std::integral_constant<int, 128>{});
+  if (slab_rows == 64) return launch_width(std::integral_constant<int, 64>{});
+  return launch_width(std::integral_constant<int, 32>{});
 }
 
 extern "C" int32_t saap_classify_queries(const void* xq, const void* W1, const float* b1, const void* W2,

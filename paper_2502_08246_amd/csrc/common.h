@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <atomic>
+
 #include "saap.h"
 
 namespace saap {
@@ -39,6 +41,24 @@ inline int env_int(const char* name, int dflt) {
 
 // Compute units of the current device; 256 (MI355X) when the query fails.
 int device_cus();
+
+constexpr int kMaxDevices = 64;
+// The current device's number, -1 if it cannot be had or is beyond the per-device tables.
+int current_device();
+
+// Lets `Kernel` take `lds` bytes of dynamic LDS.  The limit that was set is remembered per device, so that only the
+// first call of a size asks the runtime (about a microsecond of host time per launch otherwise).
+template <auto Kernel>
+inline bool allow_lds(size_t lds) {
+  static std::atomic<int> allowed[kMaxDevices];
+  if (lds <= 48 * 1024) return true;
+  const int dev = current_device();
+  if (dev >= 0 && allowed[dev].load(std::memory_order_relaxed) >= (int)lds) return true;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return false;
+  if (dev >= 0) allowed[dev].store((int)lds, std::memory_order_relaxed);
+  return true;
+}
 
 // Every entry point starts with begin_call(): an error that an earlier, unrelated HIP call of the process left
 // behind is dropped, so that launch_status() reports this call's launches only.

@@ -15,13 +15,21 @@ size_t mass_workspace_bytes(long long units, int G, int B);
 size_t mass_batch_workspace_bytes(long long units, long long R, int B);
 size_t train_workspace_bytes(long long Hw, long long R, int d, int hidden, int B);
 
+int current_device() {
+  int dev = -1;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices ? dev : -1;
+}
+
 int device_cus() {
-  // asked on every call: the caller may have switched devices since the last one
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-    return cus;
-  return 256;
+  // the device is asked for on every call (the caller may have switched), its size once
+  static std::atomic<int> known[kMaxDevices];
+  const int dev = current_device();
+  if (dev < 0) return 256;
+  int cus = known[dev].load(std::memory_order_relaxed);
+  if (cus > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  known[dev].store(cus, std::memory_order_relaxed);
+  return cus;
 }
 
 namespace {

@@ -127,15 +127,12 @@ static int32_t select_impl(const float* scores, bool logits, float* probs, int32
     const int cap = geo.cap;
     const size_t lds = geo.lds;
     po.lds_off = geo.plan_off;
-    const bool big_lds = lds > 48 * 1024;
     saap_trace_arm();
     const dim3 grid((unsigned)units), block((unsigned)threads);
 #define SAAP_SELECT_LAUNCH(E, L)                                                                             \
   do {                                                                                                       \
-    auto kern = select_radix_kernel<E, L>;                                                                   \
-    if (big_lds && hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                  \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)  \
-      return SAAP_HIP_ERROR;                                                                                 \
+    constexpr auto kern = select_radix_kernel<E, L>;                                                         \
+    if (!allow_lds<kern>(lds)) return SAAP_HIP_ERROR;                                                        \
     hipLaunchKernelGGL(kern, grid, block, lds, hs, scores, probs, selected, Hq, Hkv, B, nprobe, indep, n_sort, cap, po); \
   } while (0)
 #define SAAP_SELECT_CASE(E)                                                                                  \
@@ -159,11 +156,7 @@ static int32_t select_impl(const float* scores, bool logits, float* probs, int32
   if (threads < 64) threads = 64;
   if (threads > 1024) threads = 1024;
   const size_t lds = (size_t)n_pow2 * sizeof(unsigned long long) + (po.off ? (size_t)nprobe * sizeof(int) : 0);
-  if (lds > 48 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return SAAP_HIP_ERROR;
-  }
+  if (!allow_lds<select_kernel>(lds)) return SAAP_HIP_ERROR;
   hipLaunchKernelGGL(select_kernel, dim3((unsigned)units), dim3((unsigned)threads), lds, hs, scores, selected, Hq,
                      Hkv, B, nprobe, indep, n_pow2, po);
   return launch_status();

@@ -1,0 +1,62 @@
+"""The native call layer: arguments by position and by name, what it raises, and that outputs passed in come back as
+the objects they are."""
+import inspect
+import math
+
+import pytest
+import torch
+
+import paper_2502_08246_amd as saap
+from paper_2502_08246_amd import binding
+
+DEV = "cuda:0"
+
+
+def test_every_native_call_states_its_signature():
+    for name in binding.NATIVE:
+        assert len(inspect.signature(getattr(saap, name)).parameters) >= 3, name
+
+
+def test_arguments_are_checked_like_a_python_call():
+    x, c = torch.zeros(1, 1, 8, 128), torch.zeros(1, 4, 128)
+    with pytest.raises(TypeError):
+        saap.assign_keys(x)                                   # a mandatory argument is missing
+    with pytest.raises(TypeError):
+        saap.assign_keys(x, c, nothing=1)
+    with pytest.raises(TypeError):
+        saap.assign_keys(x, c, centroids=c)                   # given twice
+    with pytest.raises(TypeError):
+        saap.assign_keys(x, [1, 2])                           # not a tensor
+    with pytest.raises(ValueError):
+        saap.assign_keys(x[0], c)                             # a dimension short
+    with pytest.raises(ValueError):
+        saap.assign_keys(x, c[:, :, :64])
+    with pytest.raises(ValueError):
+        saap.assign_keys(x, c)                                # host memory
+    with pytest.raises(TypeError):
+        saap.sparse_decode_attention_fp8(*[x] * 8, 1.0)       # not an 8-bit cache
+
+
+@pytest.mark.gpu
+def test_names_positions_and_outputs_passed_in():
+    g = torch.Generator(device=DEV).manual_seed(1)
+    S, Hkv, G, N, B, nprobe = 2, 2, 4, 700, 16, 3
+    rand = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    x, q, cent = rand(S, Hkv, N, 128), rand(S, Hkv * G, 128), rand(Hkv, B, 128)
+    ids = saap.assign_keys(x, cent)
+    off, ln, _, Ks, Vs = saap.build_bucket_index(ids, x, x, B, slack=2)
+    logits = torch.randn(S, Hkv * G, B, generator=g, device=DEV)
+    sel = saap.select_buckets_from_logits(logits, nprobe=nprobe, Hkv=Hkv)
+    scale = 1 / math.sqrt(128)
+    want, want_lse = saap.sparse_decode_attention(q, Ks, Vs, off, ln, sel, scale)
+    out = torch.empty_like(q)
+    got = saap.sparse_decode_attention(scale=scale, selected=sel, ln=ln, off=off, Vs=Vs, Ks=Ks, q=q, out=out)
+    assert isinstance(got, tuple) and got[0] is out and got[0].dtype == torch.bfloat16
+    assert torch.equal(out, want.to(torch.bfloat16)) and torch.equal(got[1], want_lse)
+    half, _ = saap.sparse_decode_attention(q, Ks, Vs, off, ln, sel, scale, out_dtype=torch.bfloat16)
+    assert torch.equal(half, out)
+    with pytest.raises(ValueError):
+        saap.sparse_decode_attention(q.transpose(0, 1), Ks, Vs, off, ln, sel, scale)      # not contiguous
+    with pytest.raises(saap.SaapError) as e:
+        saap.sparse_decode_attention(q, Ks, Vs, off, ln, sel, scale, ws=torch.zeros(64, dtype=torch.uint8, device=DEV))
+    assert e.value.status == -3
