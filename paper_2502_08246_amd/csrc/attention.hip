@@ -766,8 +766,7 @@ __global__ void __launch_bounds__(NT) attn_kernel(AttnParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane & 15, grp = lane >> 4;
   SAAP_TRACE(0);
-  const int unit = blockIdx.x % p.n_units;
-  const int wg = blockIdx.x / p.n_units;
+  const int unit = blockIdx.x, wg = blockIdx.y;      // unit fastest: with a multiple of 8 units, one XCD per unit
 
   // unit -> kv unit and first query row
   int kvu, qrow0;
@@ -882,8 +881,8 @@ __global__ void __launch_bounds__(NT) attn_kernel(AttnParams p) {
     po.resident = p.resident;                       // the always-visited run, if any, closes the plan
     po.ps = 0;
     po.lds_off = p.sel_plan_off;
-    select_radix_body<SEL, true, false>(smem, unit, p.logits, nullptr, wg == 0 ? p.selected_out : nullptr, p.Hq,
-                                        p.Hkv, p.sel_B, p.nsel, 0, p.sel_n_sort, p.sel_cap, po);
+    select_radix_body<SEL, true, false>(smem, unit, p.logits, nullptr, wg == 0 ? p.selected_out : nullptr, G,
+                                        p.sel_B, p.nsel, 0, p.sel_n_sort, p.sel_cap, po);
     __syncthreads();
     T_total = tables[0];
   } else if (LIST) {
@@ -1831,7 +1830,7 @@ int32_t launch_nt(const AttnParams& p, const LaunchPlan& lp, hipStream_t stream)
   constexpr auto kern = attn_kernel<T, G, LIST, NT, MASKED, SEL>;
   if (!allow_lds<kern>(lp.lds)) return SAAP_HIP_ERROR;
   saap_trace_arm();
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.n_units * p.P)), dim3((unsigned)lp.threads), lp.lds, stream, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.n_units, (unsigned)p.P), dim3((unsigned)lp.threads), lp.lds, stream, p);
   return launch_status();
 }
 

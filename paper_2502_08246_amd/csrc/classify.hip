@@ -19,7 +19,7 @@
 // Every global load is a whole 128-byte line per 8 lanes, issued before the first LDS store so
 // that a workgroup's loads are all in flight together; matrix operands are read from LDS with a
 // padded row pitch (no bank conflicts).  fp32 weights use v_mfma_f32_16x16x4_f32 with operands
-// straight from memory (correctness configuration, not tuned).
+// straight from memory.
 #include "select_body.h"
 
 #include <type_traits>
@@ -31,15 +31,18 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
 
 struct MlpShape {
   int S, Hq, Hw, hidden, B;
-  int rows_per_set;   // S * Hq / Hw
+  int heads;          // query heads per weight set, Hq / Hw
+  float inv_heads;
+  int rows_per_set;   // S * heads
   int m_pad;          // rows_per_set rounded up to 16
 };
 
-// local row m of weight set w -> global query row (s*Hq + hq)
+// local row m of weight set w -> global query row (s*Hq + hq).  m / heads by a multiplication: (m + 1/2) / heads is at
+// least 1 / (2 heads) away from an integer and the product is off by less than that for m < 2^21 (an integer division
+// is some thirty dependent instructions, in front of the loads or the stores of a kernel of five microseconds).
 __device__ __forceinline__ int query_row(const MlpShape& sh, int w, int m) {
-  const int heads = sh.Hq / sh.Hw;
-  const int s = m / heads, hq = w * heads + m % heads;
-  return s * sh.Hq + hq;
+  const int s = (int)(((float)m + 0.5f) * sh.inv_heads);
+  return s * sh.Hq + w * sh.heads + (m - s * sh.heads);
 }
 
 // 16-byte global load.  The batches of loads below are kept ahead of the LDS stores that consume
@@ -48,30 +51,32 @@ __device__ __forceinline__ int query_row(const MlpShape& sh, int w, int m) {
 // volatile access is followed by a full wait.)
 __device__ __forceinline__ u32x4_t load16(const void* p) { return *reinterpret_cast<const u32x4_t*>(p); }
 
-// Decode a 1-D grid with the weight set fastest: workgroups are handed to the 8 XCDs round-robin,
+// Grids are (weight set, row tile, slab): workgroups are handed to the 8 XCDs round-robin with the weight set fastest,
 // so with Hw a multiple of 8 all workgroups of a weight set share one L2.
-__device__ __forceinline__ void decode_block(const MlpShape& sh, int& w, int& mt, int& slab) {
-  w = blockIdx.x % sh.Hw;
-  const int rest = blockIdx.x / sh.Hw;
-  const int m_tiles = sh.m_pad / 16;
-  mt = rest % m_tiles;
-  slab = rest / m_tiles;
-}
 
 constexpr int kPitchD = kD + 8;     // LDS row pitch (bf16 elements) of d-wide tiles
 
 // ---- bf16: hidden layer ------------------------------------------------------------------------
-// LINEAR: the same product without the ReLU, written straight to the score rows: the one-layer
-// model z = W x + b (sh.hidden is then the number of outputs).
-template <bool LINEAR>
+// What becomes of a hidden unit: HIDDEN_F32 relu as fp32 [weight set][row][hidden]; HIDDEN_PLANES relu as the three bf16
+// planes whose sum it is exactly, [weight set][row][3][hidden] (operands of mlp_out_rows_kernel: split once here and not
+// by every workgroup that reads them); HIDDEN_LINEAR no ReLU, written straight to the score rows: the one-layer model
+// z = W x + b (sh.hidden is then the number of outputs).
+enum { HIDDEN_F32, HIDDEN_PLANES, HIDDEN_LINEAR };
+// v == p[0] + p[1] + p[2] exactly, each the upper half of an fp32 pattern (8 significant bits)
+__device__ __forceinline__ void split_planes(float v, uint32_t (&p)[3]) {
+  p[0] = __float_as_uint(v) & 0xffff0000u;
+  const float r1 = v - __uint_as_float(p[0]);
+  p[1] = __float_as_uint(r1) & 0xffff0000u;
+  p[2] = __float_as_uint(r1 - __uint_as_float(p[1])) & 0xffff0000u;
+}
+template <int FORM>
 __global__ void __launch_bounds__(256)
 mlp_hidden_bf16_kernel(const bf16_t* __restrict__ xq, const bf16_t* __restrict__ W1, const float* __restrict__ b1,
-                       float* __restrict__ hbuf, MlpShape sh) {
+                       void* __restrict__ hout, MlpShape sh) {
   __shared__ __align__(16) bf16_t s_x[16 * kPitchD];
   __shared__ __align__(16) bf16_t s_w1[64 * kPitchD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int w, mt, slab;
-  decode_block(sh, w, mt, slab);
+  const int w = blockIdx.x, mt = blockIdx.y, slab = blockIdx.z;
   const int rc = lane & 15, kg = lane >> 4;
   SAAP_TRACE(0);
   // coalesced loads: the 16 query rows (one piece per thread) and 64 rows of W1 (four pieces)
@@ -107,8 +112,17 @@ mlp_hidden_bf16_kernel(const bf16_t* __restrict__ xq, const bf16_t* __restrict__
   for (int i = 0; i < 4; ++i) {
     const int row = mt * 16 + 4 * kg + i;
     if (row < sh.rows_per_set) {
-      if constexpr (LINEAR) hbuf[(size_t)query_row(sh, w, row) * sh.hidden + unit] = acc[i] + bv;
-      else hbuf[((size_t)w * sh.m_pad + row) * sh.hidden + unit] = fmaxf(acc[i] + bv, 0.f);
+      if constexpr (FORM == HIDDEN_LINEAR) {
+        static_cast<float*>(hout)[(size_t)query_row(sh, w, row) * sh.hidden + unit] = acc[i] + bv;
+      } else if constexpr (FORM == HIDDEN_F32) {
+        static_cast<float*>(hout)[((size_t)w * sh.m_pad + row) * sh.hidden + unit] = fmaxf(acc[i] + bv, 0.f);
+      } else {
+        uint32_t p[3];
+        split_planes(fmaxf(acc[i] + bv, 0.f), p);
+        bf16_t* dst = static_cast<bf16_t*>(hout) + ((size_t)w * sh.m_pad + row) * 3 * sh.hidden + unit;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) dst[(size_t)k * sh.hidden] = (bf16_t)(p[k] >> 16);
+      }
     }
   }
   SAAP_TRACE(2);
@@ -133,7 +147,7 @@ struct FusedSelect {
   unsigned* counters;     // one per weight set, a cache line apart, zero on entry and on exit
   float* probs;           // [Hq,B] or null
   int32_t* selected;      // [Hkv,nprobe]
-  int Hkv, nprobe, n_sort, cap, ept, expect;
+  int nprobe, n_sort, cap, ept, expect;
   PlanOut po;
 };
 
@@ -143,8 +157,7 @@ mlp_out_bf16_kernel(const float* __restrict__ hbuf, const bf16_t* __restrict__ W
                     float* __restrict__ scores, MlpShape sh, FusedSelect fs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int w, mt, slab;
-  decode_block(sh, w, mt, slab);
+  const int w = blockIdx.x, mt = blockIdx.y, slab = blockIdx.z;
   const int rc = lane & 15, kg = lane >> 4;
   constexpr int kTiles = SLAB / 16, KQ = 8 / kTiles;
   constexpr int kWLoads = SLAB * 64 / kOutThreads;      // 16-byte loads of weights per thread (chunk of 512)
@@ -215,12 +228,9 @@ mlp_out_bf16_kernel(const float* __restrict__ hbuf, const bf16_t* __restrict__ W
         uint32_t p0[4], p1[4], p2[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float hval = __uint_as_float(hv[i][j]);
-          p0[j] = __float_as_uint(hval) & 0xffff0000u;
-          const float r1 = hval - __uint_as_float(p0[j]);
-          p1[j] = __float_as_uint(r1) & 0xffff0000u;
-          const float r2 = r1 - __uint_as_float(p1[j]);
-          p2[j] = __float_as_uint(r2) & 0xffff0000u;
+          uint32_t pl[3];
+          split_planes(__uint_as_float(hv[i][j]), pl);
+          p0[j] = pl[0]; p1[j] = pl[1]; p2[j] = pl[2];
         }
         bf16_t* dst = s_h + hrow_i * pitch + hpc_i * 4;
         *reinterpret_cast<uint2*>(dst) = make_uint2((p0[0] >> 16) | p0[1], (p0[2] >> 16) | p0[3]);
@@ -303,14 +313,161 @@ mlp_out_bf16_kernel(const float* __restrict__ hbuf, const bf16_t* __restrict__ W
     if (!s_is_last) return;
     // weight set w = KV head w: its G rows of logits are complete
     switch (fs.ept) {
-      case 2: select_radix_body<2, true, true>(smem, w, scores, fs.probs, fs.selected, sh.Hq, fs.Hkv, sh.B, fs.nprobe, 0, fs.n_sort, fs.cap, fs.po); break;
-      case 4: select_radix_body<4, true, true>(smem, w, scores, fs.probs, fs.selected, sh.Hq, fs.Hkv, sh.B, fs.nprobe, 0, fs.n_sort, fs.cap, fs.po); break;
-      default: select_radix_body<8, true, true>(smem, w, scores, fs.probs, fs.selected, sh.Hq, fs.Hkv, sh.B, fs.nprobe, 0, fs.n_sort, fs.cap, fs.po); break;
+      case 2: select_radix_body<2, true, true>(smem, w, scores, fs.probs, fs.selected, sh.heads, sh.B, fs.nprobe, 0, fs.n_sort, fs.cap, fs.po); break;
+      case 4: select_radix_body<4, true, true>(smem, w, scores, fs.probs, fs.selected, sh.heads, sh.B, fs.nprobe, 0, fs.n_sort, fs.cap, fs.po); break;
+      default: select_radix_body<8, true, true>(smem, w, scores, fs.probs, fs.selected, sh.heads, sh.B, fs.nprobe, 0, fs.n_sort, fs.cap, fs.po); break;
     }
   }
 }
 
-// ---- fp32 (correctness configuration): operands straight from memory ------------------------------
+// ---- bf16: output layer, many rows per weight set ----------------------------------------------------
+// With 64 rows and more per weight set (batched decoding, a block of prompt tokens) the layer is a matrix product:
+// a workgroup of WM x WN waves owns a tile of 32 WM rows x 32 WN TN buckets and walks the hidden units in chunks of 64,
+// double buffered in LDS, the next two chunks' loads in flight (registers) under the products of the current one.  The
+// kernel above reads a slab of W2 again for every 16 rows, which is what bounded it: 512 rows per set, 1024 buckets,
+// 8 sets: 84 us, here 19; 128 rows per set: 20 us, here 9.  h enters as its three bf16 planes here too (products exact, fp32
+// accumulation); the two small planes share an accumulator, the large one has its own.
+constexpr int kManyRows = 64;                  // rows per weight set from which this kernel is the faster one (64 rows: the
+                                               // two layers 13.4 -> 11.1 us; 32 rows: the kernel above, 7.7)
+constexpr int kRowsChunk = 64;                 // hidden units per pass
+constexpr int kRowsPitch = kRowsChunk + 8;     // LDS row pitch in elements (144 bytes: conflict-free 16-byte reads)
+
+template <int WM, int WN, int TN>
+__global__ void __launch_bounds__(WM * WN * 64)
+mlp_out_rows_kernel(const bf16_t* __restrict__ planes, const bf16_t* __restrict__ W2, const float* __restrict__ b2,
+                    float* __restrict__ scores, MlpShape sh) {
+  typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+  constexpr int NT = WM * WN * 64, BM = 32 * WM, BN = 32 * WN * TN;
+  constexpr int kPieces = kRowsChunk / 8;                                          // 16-byte pieces of a row and chunk
+  constexpr int HL = 3 * BM * kPieces / NT, WL = BN * kPieces / NT;                // loads per thread and chunk
+  constexpr int kBuf = (3 * BM + BN) * kRowsPitch;                                 // elements of one LDS buffer
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t* s_all = reinterpret_cast<bf16_t*>(smem);     // [2][ 3 planes of h: [BM][pitch] | W2: [BN][pitch] ]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 31, half = lane >> 5;
+  const int w = blockIdx.x, m0 = blockIdx.y * BM, b0 = blockIdx.z * BN;
+  const bf16_t* hset = planes + (size_t)w * sh.m_pad * 3 * sh.hidden;
+  const bf16_t* wset = W2 + (size_t)w * sh.B * sh.hidden;
+  const int wm = wave / WN * 32, wn = wave % WN * (32 * TN);
+
+  struct Staged { u32x4_t h[HL], w[WL]; };
+  // rows and hidden units past the end repeat valid ones; stash clears the units of h, which clears their products
+  auto fetch = [&](Staged& g, int c0) {
+#pragma unroll
+    for (int i = 0; i < HL; ++i) {
+      const int q = tid + i * NT, r = q / kPieces, k = c0 + q % kPieces * 8;       // r = plane * BM + row
+      g.h[i] = load16(hset + ((size_t)min(m0 + r % BM, sh.rows_per_set - 1) * 3 + r / BM) * sh.hidden + min(k, sh.hidden - 8));
+    }
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int q = tid + i * NT, row = q / kPieces, k = c0 + q % kPieces * 8;
+      g.w[i] = load16(wset + (size_t)min(b0 + row, sh.B - 1) * sh.hidden + min(k, sh.hidden - 8));
+    }
+  };
+  auto stash = [&](const Staged& g, int buf, int c0) {
+    bf16_t* s_h = s_all + buf * kBuf;
+    bf16_t* s_w = s_h + 3 * BM * kRowsPitch;
+#pragma unroll
+    for (int i = 0; i < HL; ++i) {
+      const int q = tid + i * NT, pc = q % kPieces * 8;
+      const u32x4_t zero = {0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4_t*>(s_h + q / kPieces * kRowsPitch + pc) = c0 + pc < sh.hidden ? g.h[i] : zero;
+    }
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int q = tid + i * NT;
+      *reinterpret_cast<u32x4_t*>(s_w + q / kPieces * kRowsPitch + q % kPieces * 8) = g.w[i];
+    }
+  };
+
+  f32x16_t big[TN], small[TN];
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    big[t] = (f32x16_t){0};
+    small[t] = (f32x16_t){0};
+  }
+  auto compute = [&](int buf) {
+    const bf16_t* s_h = s_all + buf * kBuf + (wm + col) * kRowsPitch + half * 8;
+    const bf16_t* s_w = s_all + buf * kBuf + (3 * BM + wn + col) * kRowsPitch + half * 8;
+    auto lds16 = [](const bf16_t* ptr) { return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(ptr)); };
+#pragma unroll
+    for (int st = 0; st < kRowsChunk / 16; ++st) {
+      const bf16x8_t a0 = lds16(s_h + st * 16), a1 = lds16(s_h + BM * kRowsPitch + st * 16), a2 = lds16(s_h + 2 * BM * kRowsPitch + st * 16);
+#pragma unroll
+      for (int t = 0; t < TN; ++t) {
+        const bf16x8_t b = lds16(s_w + t * 32 * kRowsPitch + st * 16);
+        small[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b, small[t], 0, 0, 0);
+        big[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, big[t], 0, 0, 0);
+        small[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, small[t], 0, 0, 0);
+      }
+    }
+  };
+  // Two chunks of loads in flight: one covers a fraction of the memory latency only.  A buffer is written after the
+  // barrier behind its last reads.  Loads past the last chunk repeat it (unconditional: behind a branch the staging
+  // registers go to scratch).
+  const int n_chunks = (sh.hidden + kRowsChunk - 1) / kRowsChunk;
+  float bo[TN];                                // the lane's biases travel with the first operands
+#pragma unroll
+  for (int t = 0; t < TN; ++t) bo[t] = b2 ? b2[(size_t)w * sh.B + min(b0 + wn + t * 32 + col, sh.B - 1)] : 0.f;
+  auto chunk_at = [&](int c) { return min(c, n_chunks - 1) * kRowsChunk; };
+  Staged even, odd;
+  fetch(even, 0);
+  fetch(odd, chunk_at(1));
+  stash(even, 0, 0);
+  __syncthreads();
+  for (int c = 0; c < n_chunks; c += 2) {
+    fetch(even, chunk_at(c + 2));
+    compute(0);
+    stash(odd, 1, chunk_at(c + 1));
+    __syncthreads();
+    fetch(odd, chunk_at(c + 3));
+    if (c + 1 < n_chunks) compute(1);
+    stash(even, 0, chunk_at(c + 2));
+    __syncthreads();
+  }
+  // register r of this lane: row 8*(r/4) + 4*half + r%4 of the wave's 32, bucket `col` of each 32.  
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm + 8 * (r / 4) + 4 * half + (r % 4);
+    float* dst = scores + (size_t)query_row(sh, w, m) * sh.B + b0 + wn + col;
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+      if (m < sh.rows_per_set && b0 + wn + t * 32 + col < sh.B) dst[t * 32] = (big[t][r] + small[t][r]) + bo[t];
+  }
+}
+
+// ---- fp32: operands straight from memory ---------------------------------------------------------------
+// A lane reads 16 bytes of its row of either operand and feeds four matrix instructions from them: instruction j sums
+// features 4 kg + j of the 16, so that every load is a whole piece of a row and all loads of a wave's share are in
+// flight together (element by element, in a dependent loop, a 256 -> 64 layer took 16 us).
+__device__ __forceinline__ f32x4_t mfma_f32_rows(const float* a, const float* b, int k0, int k1, int kg, f32x4_t acc) {
+  constexpr int kDeep = 8;                              // pairs of loads in flight per lane
+  for (int k = k0; k < k1; k += 16 * kDeep) {
+    float4 av[kDeep], bv[kDeep];
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+      const int kk = min(k + 16 * u, k1 - 16) + 4 * kg;
+      av[u] = *reinterpret_cast<const float4*>(a + kk);
+      bv[u] = *reinterpret_cast<const float4*>(b + kk);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+      // past the end a zero operand; no branch, into which the loads would sink
+      const bool in = k + 16 * u < k1;
+      av[u].x = in ? av[u].x : 0.f;
+      av[u].y = in ? av[u].y : 0.f;
+      av[u].z = in ? av[u].z : 0.f;
+      av[u].w = in ? av[u].w : 0.f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].x, bv[u].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].y, bv[u].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].z, bv[u].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].w, bv[u].w, acc, 0, 0, 0);
+    }
+  }
+  return acc;
+}
+
 template <bool LINEAR>
 __global__ void __launch_bounds__(256)
 mlp_hidden_f32_kernel(const float* __restrict__ xq, const float* __restrict__ W1, const float* __restrict__ b1,
@@ -321,14 +478,10 @@ mlp_hidden_f32_kernel(const float* __restrict__ xq, const float* __restrict__ W1
   const int mt = blockIdx.y, w = blockIdx.z;
   const int rc = lane & 15, kg = lane >> 4;
   const int m = min(mt * 16 + rc, sh.rows_per_set - 1);
-  const float* xr = xq + (size_t)query_row(sh, w, m) * kD;
-  const float* wr = W1 + ((size_t)w * sh.hidden + utile * 16 + rc) * kD;
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-  for (int st = 0; st < kD / 4; ++st)
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[st * 4 + kg], wr[st * 4 + kg], acc, 0, 0, 0);
   const int unit = utile * 16 + rc;
   const float bv = b1 ? b1[(size_t)w * sh.hidden + unit] : 0.f;
+  const f32x4_t acc = mfma_f32_rows(xq + (size_t)query_row(sh, w, m) * kD, W1 + ((size_t)w * sh.hidden + unit) * kD, 0, kD, kg,
+                                    (f32x4_t){0.f, 0.f, 0.f, 0.f});
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = mt * 16 + 4 * kg + i;
@@ -340,21 +493,27 @@ mlp_hidden_f32_kernel(const float* __restrict__ xq, const float* __restrict__ W1
   }
 }
 
+// One workgroup per tile of 16 buckets: its four waves share the hidden units out in pieces of 16 and add their
+// products through LDS in wave order.
 __global__ void __launch_bounds__(256)
 mlp_out_f32_kernel(const float* __restrict__ hbuf, const float* __restrict__ W2, const float* __restrict__ b2,
                    float* __restrict__ scores, MlpShape sh) {
+  __shared__ f32x4_t s_part[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int btile = blockIdx.x * 4 + wave;           // tile of 16 buckets
-  if (btile * 16 >= sh.B) return;
-  const int mt = blockIdx.y, w = blockIdx.z;
+  const int btile = blockIdx.x, mt = blockIdx.y, w = blockIdx.z;
   const int rc = lane & 15, kg = lane >> 4;
-  const float* hp = hbuf + ((size_t)w * sh.m_pad + mt * 16 + rc) * sh.hidden;
-  const float* wr = W2 + ((size_t)w * sh.B + btile * 16 + rc) * sh.hidden;
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  for (int st = 0; st < sh.hidden / 4; ++st)
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(hp[st * 4 + kg], wr[st * 4 + kg], acc, 0, 0, 0);
   const int bucket = btile * 16 + rc;
   const float bv = b2 ? b2[(size_t)w * sh.B + bucket] : 0.f;
+  const int per = (sh.hidden / 16 + 3) / 4 * 16;       // hidden units per wave, a multiple of 16
+  const int k0 = min(wave * per, sh.hidden), k1 = min(k0 + per, sh.hidden);
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  if (k0 < k1)
+    acc = mfma_f32_rows(hbuf + ((size_t)w * sh.m_pad + mt * 16 + rc) * sh.hidden, W2 + ((size_t)w * sh.B + bucket) * sh.hidden, k0, k1,
+                        kg, acc);
+  s_part[wave][lane] = acc;
+  __syncthreads();
+  if (wave != 0) return;
+  acc = ((s_part[0][lane] + s_part[1][lane]) + s_part[2][lane]) + s_part[3][lane];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int m = mt * 16 + 4 * kg + i;
@@ -415,10 +574,10 @@ using namespace saap;
 
 // The two launches of the bf16 two-layer model; with `fs` the output kernel also selects (see FusedSelect).
 static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, const void* W2, const float* b2,
-                               float* scores, float* hbuf, const MlpShape& sh, const FusedSelect* fs, hipStream_t hs) {
+                               float* scores, void* hbuf, const MlpShape& sh, const FusedSelect* fs, hipStream_t hs) {
   const int hidden = sh.hidden, B = sh.B, Hw = sh.Hw;
   const int m_tiles = sh.m_pad / 16;
-  const unsigned g1 = (unsigned)((hidden + 63) / 64) * m_tiles * Hw;
+  const dim3 g1((unsigned)Hw, (unsigned)m_tiles, (unsigned)((hidden + 63) / 64));
   // 64 buckets per workgroup when 32 would give more than one workgroup per compute unit: every
   // workgroup reads its rows of the hidden activations (as many bytes as a 32-bucket slab of W2 for a
   // full 16-row tile), so fewer, wider workgroups move fewer bytes (batch 8: 11.5 -> 8.8 us)
@@ -433,8 +592,29 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
     if (wide && (long long)((B + 63) / 64) * m_tiles * Hw > (long long)device_cus() && lds128 <= 150 * 1024)
       slab_rows = 128;
   }
-  const unsigned g2 = (unsigned)((B + slab_rows - 1) / slab_rows) * m_tiles * Hw;
-  hipLaunchKernelGGL(mlp_hidden_bf16_kernel<false>, dim3(g1), dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
+  const dim3 g2((unsigned)Hw, (unsigned)m_tiles, (unsigned)((B + slab_rows - 1) / slab_rows));
+  if (!fs && sh.rows_per_set >= kManyRows) {
+    hipLaunchKernelGGL(mlp_hidden_bf16_kernel<HIDDEN_PLANES>, g1, dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
+                       static_cast<const bf16_t*>(W1), b1, hbuf, sh);
+    // 128 x 128 tiles once they fill the compute units, 64 x 64 before
+    auto tiles = [&](int bm, int bn) { return (long long)((sh.rows_per_set + bm - 1) / bm) * ((B + bn - 1) / bn) * Hw; };
+    auto launch_rows = [&](auto wm, auto wn, auto tn) -> int32_t {
+      constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TN = decltype(tn)::value;
+      constexpr auto kernel = mlp_out_rows_kernel<WM, WN, TN>;
+      constexpr size_t bytes = (size_t)2 * (3 * 32 * WM + 32 * WN * TN) * kRowsPitch * sizeof(bf16_t);
+      if (!allow_lds<kernel>(bytes)) return SAAP_HIP_ERROR;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)Hw, (unsigned)((sh.rows_per_set + 32 * WM - 1) / (32 * WM)),
+                                      (unsigned)((B + 32 * WN * TN - 1) / (32 * WN * TN))), dim3(WM * WN * 64), bytes, hs,
+                         static_cast<const bf16_t*>(hbuf), static_cast<const bf16_t*>(W2), b2, scores, sh);
+      return SAAP_OK;
+    };
+    typedef std::integral_constant<int, 1> one;
+    typedef std::integral_constant<int, 2> two;
+    typedef std::integral_constant<int, 4> four;
+    if (tiles(128, 128) >= device_cus()) return launch_rows(four{}, two{}, two{});
+    return launch_rows(two{}, two{}, one{});
+  }
+  hipLaunchKernelGGL(mlp_hidden_bf16_kernel<HIDDEN_F32>, g1, dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
                      static_cast<const bf16_t*>(W1), b1, hbuf, sh);
   const int chunk = hidden < kOutChunk ? hidden : kOutChunk;
   const int h_rows = sh.rows_per_set < 16 ? sh.rows_per_set : 16;
@@ -455,7 +635,8 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
   auto launch = [&](auto width, auto fused) -> int32_t {
     constexpr auto kernel = mlp_out_bf16_kernel<decltype(width)::value, decltype(fused)::value>;
     if (!allow_lds<kernel>(lds)) return SAAP_HIP_ERROR;
-    hipLaunchKernelGGL(kernel, dim3(g2), dim3(kOutThreads), lds, hs, hbuf, static_cast<const bf16_t*>(W2), b2, scores, sh, f);
+    hipLaunchKernelGGL(kernel, g2, dim3(kOutThreads), lds, hs, static_cast<const float*>(hbuf),
+                       static_cast<const bf16_t*>(W2), b2, scores, sh, f);
     return SAAP_OK;
   };
   auto launch_width = [&](auto width) { return fs ? launch(width, std::true_type{}) : launch(width, std::false_type{}); };
@@ -480,9 +661,11 @@ extern "C" int32_t saap_classify_queries(const void* xq, const void* W1, const f
   if (d != kD || hidden % 32 != 0 || B % 16 != 0 || B > SAAP_MAX_BUCKETS || hidden > 1536) return SAAP_UNSUPPORTED;
   MlpShape sh;
   sh.S = S; sh.Hq = Hq; sh.Hw = Hw; sh.hidden = linear ? B : hidden; sh.B = B;
-  sh.rows_per_set = S * (Hq / Hw);
+  sh.heads = Hq / Hw; sh.inv_heads = 1.0f / (float)sh.heads;
+  sh.rows_per_set = S * sh.heads;
   sh.m_pad = (sh.rows_per_set + 15) / 16 * 16;
-  const size_t need = (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * sh.m_pad * hidden * sizeof(float);
+  const size_t unit_bytes = dtype == SAAP_BF16 && sh.rows_per_set >= kManyRows ? 3 * sizeof(bf16_t) : sizeof(float);
+  const size_t need = (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * sh.m_pad * hidden * unit_bytes;
   if (ws_bytes < need) return SAAP_WORKSPACE_TOO_SMALL;
   const int m_tiles = sh.m_pad / 16;
   if (m_tiles > 65535 || Hw > 65535) return SAAP_UNSUPPORTED;
@@ -491,8 +674,8 @@ extern "C" int32_t saap_classify_queries(const void* xq, const void* W1, const f
   saap_trace_arm();
   if (linear) {
     if (dtype == SAAP_BF16) {
-      const unsigned g = (unsigned)((B + 63) / 64) * m_tiles * Hw;
-      hipLaunchKernelGGL(mlp_hidden_bf16_kernel<true>, dim3(g), dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
+      const dim3 g((unsigned)Hw, (unsigned)m_tiles, (unsigned)((B + 63) / 64));
+      hipLaunchKernelGGL(mlp_hidden_bf16_kernel<HIDDEN_LINEAR>, g, dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
                          static_cast<const bf16_t*>(W2), b2, scores, sh);
     } else {
       const dim3 g((unsigned)((B / 16 + 3) / 4), (unsigned)m_tiles, (unsigned)Hw);
@@ -504,7 +687,7 @@ extern "C" int32_t saap_classify_queries(const void* xq, const void* W1, const f
     if (st != SAAP_OK) return st;
   } else {
     const dim3 g1((unsigned)((hidden / 16 + 3) / 4), (unsigned)m_tiles, (unsigned)Hw);
-    const dim3 g2((unsigned)((B / 16 + 3) / 4), (unsigned)m_tiles, (unsigned)Hw);
+    const dim3 g2((unsigned)(B / 16), (unsigned)m_tiles, (unsigned)Hw);
     hipLaunchKernelGGL(mlp_hidden_f32_kernel<false>, g1, dim3(256), 0, hs, static_cast<const float*>(xq),
                        static_cast<const float*>(W1), b1, hbuf, sh);
     hipLaunchKernelGGL(mlp_out_f32_kernel, g2, dim3(256), 0, hs, hbuf, static_cast<const float*>(W2), b2, scores,
@@ -553,14 +736,15 @@ extern "C" int32_t saap_classify_select(const void* xq, const void* W1, const fl
   if (d != kD || hidden % 32 != 0 || B % 16 != 0 || B > SAAP_MAX_BUCKETS || hidden > 1536) return SAAP_UNSUPPORTED;
   MlpShape sh;
   sh.S = S; sh.Hq = Hq; sh.Hw = Hw; sh.hidden = hidden; sh.B = B;
-  sh.rows_per_set = S * (Hq / Hw);
+  sh.heads = Hq / Hw; sh.inv_heads = 1.0f / (float)sh.heads;
+  sh.rows_per_set = S * sh.heads;
   sh.m_pad = (sh.rows_per_set + 15) / 16 * 16;
   const size_t need = (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * sh.m_pad * hidden * sizeof(float);
   if (ws_bytes < need) return SAAP_WORKSPACE_TOO_SMALL;
   float* hbuf = reinterpret_cast<float*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
   FusedSelect fs{};
   fs.counters = reinterpret_cast<unsigned*>(ws);
-  fs.probs = probs; fs.selected = selected; fs.Hkv = Hkv; fs.nprobe = nprobe;
+  fs.probs = probs; fs.selected = selected; fs.nprobe = nprobe;
   fs.ept = B <= 2 * kOutThreads ? 2 : B <= 4 * kOutThreads ? 4 : 8;
   if (with_plan) {
     fs.po.off = off; fs.po.len = len; fs.po.plan = plan;

@@ -18,12 +18,11 @@ namespace saap {
 namespace {
 
 __global__ void __launch_bounds__(1024)
-select_kernel(const float* __restrict__ scores, int32_t* __restrict__ selected, int Hq, int Hkv, int B,
-              int nprobe, int independent, int n_pow2, PlanOut po) {
+select_kernel(const float* __restrict__ scores, int32_t* __restrict__ selected, int G, int B, int nprobe,
+              int independent, int n_pow2, PlanOut po) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);
   const int unit = blockIdx.x;
-  const int G = Hq / Hkv;
   const int heads = independent ? 1 : G;
   // first score row of the list: (s, hq) for independent lists, (s, h*G) for group lists
   const size_t row0 = independent ? (size_t)unit : (size_t)unit * G;
@@ -64,7 +63,7 @@ select_kernel(const float* __restrict__ scores, int32_t* __restrict__ selected, 
     int* ids = reinterpret_cast<int*>(keys + n_pow2);
     for (int j = threadIdx.x; j < nprobe; j += blockDim.x) ids[j] = (int)(0xFFFFFFFFu - (unsigned)(keys[j] & 0xFFFFFFFFull));
     __syncthreads();
-    const int kvu = independent ? (unit / Hq) * Hkv + (unit % Hq) / G : unit;
+    const int kvu = independent ? unit / G : unit;
     emit_plan(ids, po.len + (size_t)kvu * po.runs, po.off + (size_t)kvu * (po.runs + 1), nprobe, po.resident,
               po.plan + (size_t)unit * po.ps);
   }
@@ -75,10 +74,10 @@ select_kernel(const float* __restrict__ scores, int32_t* __restrict__ selected, 
 template <int EPT, bool LOGITS>
 __global__ void __launch_bounds__(1024)
 select_radix_kernel(const float* __restrict__ scores, float* __restrict__ probs, int32_t* __restrict__ selected,
-                    int Hq, int Hkv, int B, int nprobe, int independent, int n_sort, int cap, PlanOut po) {
+                    int G, int B, int nprobe, int independent, int n_sort, int cap, PlanOut po) {
   extern __shared__ __align__(16) unsigned char smem[];
-  select_radix_body<EPT, LOGITS, false>(smem, (int)blockIdx.x, scores, probs, selected, Hq, Hkv, B, nprobe, independent,
-                                        n_sort, cap, po);
+  select_radix_body<EPT, LOGITS, false>(smem, (int)blockIdx.x, scores, probs, selected, G, B, nprobe, independent, n_sort,
+                                        cap, po);
 }
 
 }  // namespace
@@ -133,7 +132,7 @@ static int32_t select_impl(const float* scores, bool logits, float* probs, int32
   do {                                                                                                       \
     constexpr auto kern = select_radix_kernel<E, L>;                                                         \
     if (!allow_lds<kern>(lds)) return SAAP_HIP_ERROR;                                                        \
-    hipLaunchKernelGGL(kern, grid, block, lds, hs, scores, probs, selected, Hq, Hkv, B, nprobe, indep, n_sort, cap, po); \
+    hipLaunchKernelGGL(kern, grid, block, lds, hs, scores, probs, selected, Hq / Hkv, B, nprobe, indep, n_sort, cap, po); \
   } while (0)
 #define SAAP_SELECT_CASE(E)                                                                                  \
   case E:                                                                                                    \
@@ -157,8 +156,8 @@ static int32_t select_impl(const float* scores, bool logits, float* probs, int32
   if (threads > 1024) threads = 1024;
   const size_t lds = (size_t)n_pow2 * sizeof(unsigned long long) + (po.off ? (size_t)nprobe * sizeof(int) : 0);
   if (!allow_lds<select_kernel>(lds)) return SAAP_HIP_ERROR;
-  hipLaunchKernelGGL(select_kernel, dim3((unsigned)units), dim3((unsigned)threads), lds, hs, scores, selected, Hq,
-                     Hkv, B, nprobe, indep, n_pow2, po);
+  hipLaunchKernelGGL(select_kernel, dim3((unsigned)units), dim3((unsigned)threads), lds, hs, scores, selected,
+                     Hq / Hkv, B, nprobe, indep, n_pow2, po);
   return launch_status();
 }
 

@@ -178,15 +178,13 @@ __device__ __forceinline__ void softmax_group_scores(const float* __restrict__ z
 // dynamic LDS, laid out as select_geometry() says.  Called by every thread of the workgroup.
 template <int EPT, bool LOGITS, bool COHERENT>
 __device__ __forceinline__ void select_radix_body(unsigned char* smem, int unit, const float* __restrict__ scores,
-                                                  float* __restrict__ probs, int32_t* __restrict__ selected, int Hq,
-                                                  int Hkv, int B, int nprobe, int independent, int n_sort, int cap,
-                                                  PlanOut po) {
+                                                  float* __restrict__ probs, int32_t* __restrict__ selected, int G,
+                                                  int B, int nprobe, int independent, int n_sort, int cap, PlanOut po) {
   unsigned long long* sortbuf = reinterpret_cast<unsigned long long*>(smem);   // [cap] candidates, cap >= n_sort
   unsigned* eqbits = reinterpret_cast<unsigned*>(sortbuf + cap);               // [B/32 + 1]
   __shared__ unsigned s_hist[2][256];
   __shared__ unsigned s_digit, s_krem, s_bin, s_cnt, s_neq, s_and, s_or;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = blockDim.x;
-  const int G = Hq / Hkv;
   const int heads = independent ? 1 : G;
   const size_t row0 = independent ? (size_t)unit : (size_t)unit * G;
   const float* sc = scores + row0 * B;
@@ -199,7 +197,7 @@ __device__ __forceinline__ void select_radix_body(unsigned char* smem, int unit,
   int* s_sel = s_off + po.runs;                                 // [nprobe]
   int lv[EPT + 1], ov[EPT + 1];
   if (po.off) {
-    const int kvu = independent ? (unit / Hq) * Hkv + (unit % Hq) / G : unit;
+    const int kvu = independent ? unit / G : unit;      // (sequence, head) -> (sequence, KV head): Hq = Hkv * G
     const int32_t* lenu = po.len + (size_t)kvu * po.runs;
     const int32_t* offu = po.off + (size_t)kvu * (po.runs + 1);
 #pragma unroll
@@ -441,13 +439,14 @@ __device__ __forceinline__ void select_radix_body(unsigned char* smem, int unit,
     // split over `parts` neighbouring lanes (a power of two, so they share a wave): each counts the larger
     // keys in its slice, the counts are added up over those lanes, and the first of them places the key.
     if (tid == 0) SAAP_TRACE_VALUE(6, n_cand);
-    int parts = 1;
-    while (parts < 64 && 2 * parts * n_cand <= nt) parts *= 2;
-    const int slice = (n_cand + parts - 1) / parts;
-    const int items = n_cand * parts;
+    int parts_log2 = 0;
+    while (parts_log2 < 6 && (n_cand << (parts_log2 + 1)) <= nt) ++parts_log2;
+    const int parts = 1 << parts_log2;
+    const int slice = (n_cand + parts - 1) >> parts_log2;
+    const int items = n_cand << parts_log2;
     for (int w0 = 0; w0 < items; w0 += nt) {             // uniform trip count: every lane takes part in the exchanges
       const int w = w0 + tid;
-      const int i = w / parts, part = w % parts;
+      const int i = w >> parts_log2, part = w & (parts - 1);
       const bool real = w < items;
       const int j0 = part * slice, j1 = real ? min(j0 + slice, n_cand) : j0;
       const unsigned long long mine = sortbuf[real ? i : 0];
