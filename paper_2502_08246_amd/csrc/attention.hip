@@ -1774,11 +1774,16 @@ struct LaunchPlan {
   size_t lds;
 };
 
-// Workgroups per unit for a launch shape: the device filled once, no more than the work gives.
-static long long plan_p(int n_units, long long est_keys_per_unit, int threads, int wgs_per_cu, int kb) {
+// Workgroups per unit for a launch shape: the device filled once, no more than the work gives.  The length of a list of
+// buckets is only expected, and a workgroup that finds a second batch of keys holds its unit up for 1.2 us (a batch's
+// memory latency), while one that finds none costs next to nothing: while the device is not full a list gets half as many
+// workgroups again as its expected keys make batches (512 keys per unit: 9.7 -> 8.5 us, 3072: 10.3 -> 9.5).  Up to one
+// and a half batches a single workgroup takes the unit, without partial results and their merge (128 keys: 8.0 -> 6.9 us).
+static long long plan_p(int n_units, long long est_keys_per_unit, int threads, int wgs_per_cu, int kb, bool exact) {
   const long long chunk = (long long)(threads / 16) * kb;   // keys per workgroup batch
   long long P = (long long)device_cus() * wgs_per_cu / n_units;
-  const long long by_work = (est_keys_per_unit + chunk - 1) / chunk;
+  long long by_work = (est_keys_per_unit + chunk - 1) / chunk;
+  if (!exact) by_work = 2 * est_keys_per_unit <= 3 * chunk ? 1 : (3 * est_keys_per_unit + 2 * chunk - 1) / (2 * chunk);
   if (P > by_work) P = by_work;
   if (P > kMaxP) P = kMaxP;
   return P < 1 ? 1 : P;
@@ -1792,8 +1797,8 @@ static long long plan_p(int n_units, long long est_keys_per_unit, int threads, i
 // first is better below that, so a launch with a selection always takes the first.
 static bool narrow_shape_pays(int n_units, long long est_keys_per_unit, int G, int key_bytes, int kb) {
   const double stream_us = (double)est_keys_per_unit * n_units * key_bytes / 6.0e6;   // at 6 TB/s
-  const long long p_wide = plan_p(n_units, est_keys_per_unit, 512, 1, kb);
-  const long long p_narrow = plan_p(n_units, est_keys_per_unit, 256, 2, kb);
+  const long long p_wide = plan_p(n_units, est_keys_per_unit, 512, 1, kb, true);
+  const long long p_narrow = plan_p(n_units, est_keys_per_unit, 256, 2, kb, true);
   const double merge_us = 0.02 * G * (double)(p_narrow > p_wide ? p_narrow - p_wide : 0) + 0.5;
   return 0.08 * stream_us > merge_us;
 }
@@ -1807,7 +1812,7 @@ LaunchPlan plan_launch(int n_units, long long est_keys_per_unit, long long max_k
   if (masked) threads = 512;
   const int wgs_per_cu = env_int("SAAP_ATTN_WGS_PER_CU", threads == 256 ? 2 : 1);
   const long long chunk = (long long)(threads / 16) * kb;   // keys per workgroup batch
-  long long P = plan_p(n_units, est_keys_per_unit, threads, wgs_per_cu, kb);
+  long long P = plan_p(n_units, est_keys_per_unit, threads, wgs_per_cu, kb, !has_selection);
   const int force_p = env_int("SAAP_ATTN_P", 0);
   if (force_p > 0 && force_p <= kMaxP) P = force_p;
   LaunchPlan lp;
