@@ -80,7 +80,8 @@ enum {
   SAAP_OP_QUERY_MODEL_LOSS_GRADS = 9,  /* shape: Hkv = weight sets, N = rows per set, d, hidden, B */
   SAAP_OP_BUCKET_ATTENTION_MASS_BATCH = 10,  /* shape: S, Hkv, N = queries per KV head, B */
   SAAP_OP_PLANNED_DECODE_ATTENTION = 11,     /* shape: S, Hq, Hkv, mode */
-  SAAP_OP_PREFILL_SPARSE_ATTENTION = 12      /* shape: S, Hq, Hkv, N = query tokens per sequence (Tq), nprobe */
+  SAAP_OP_PREFILL_SPARSE_ATTENTION = 12,     /* shape: S, Hq, Hkv, N = query tokens per sequence (Tq), nprobe */
+  SAAP_OP_UPDATE_CENTROIDS_FROM_IDS = 13     /* shape: S, Hkv, N, B */
 };
 
 #define SAAP_WS_HEADER_BYTES 65536u
@@ -171,6 +172,14 @@ int32_t saap_build_bucket_index(const int32_t* bucket_ids, const void* K, const 
                                 int32_t S, int32_t Hkv, int32_t N, int32_t Ncap, int32_t B,
                                 int32_t d, int32_t dtype, int32_t slack,
                                 void* ws, size_t ws_bytes, void* stream);
+
+/* The same, and the free slots of Ksorted and Vsorted are set to zero. */
+int32_t saap_build_bucket_index_zeroed(const int32_t* bucket_ids, const void* K, const void* V,
+                                       int32_t* off, int32_t* len, int32_t* idx,
+                                       void* Ksorted, void* Vsorted,
+                                       int32_t S, int32_t Hkv, int32_t N, int32_t Ncap, int32_t B,
+                                       int32_t d, int32_t dtype, int32_t slack,
+                                       void* ws, size_t ws_bytes, void* stream);
 
 /*
  * append_keys -- one decode step's new key per (sequence, KV head): assign it
@@ -399,6 +408,15 @@ int32_t saap_build_windowed_index(const int32_t* bucket_ids, const void* K, cons
                                   int32_t n_sink, int32_t n_recent,
                                   void* ws, size_t ws_bytes, void* stream);
 
+/* The same, and the free slots of Ksorted and Vsorted (empty resident slots too) are set to zero. */
+int32_t saap_build_windowed_index_zeroed(const int32_t* bucket_ids, const void* K, const void* V,
+                                         int32_t* off, int32_t* len, int32_t* idx,
+                                         void* Ksorted, void* Vsorted, int32_t* resident_ids,
+                                         int32_t S, int32_t Hkv, int32_t N, int32_t Ncap, int32_t B,
+                                         int32_t d, int32_t dtype, int32_t slack,
+                                         int32_t n_sink, int32_t n_recent,
+                                         void* ws, size_t ws_bytes, void* stream);
+
 /*
  * window_push -- one decode step's new key per (sequence, KV head) enters the resident
  * block; the key it displaces (position pos - n_recent) is appended to the first free slot
@@ -480,6 +498,18 @@ int32_t saap_update_centroids(const void* x_sorted, const int32_t* off, const in
                               const void* centroids_old, void* centroids_new,
                               int32_t S, int32_t Hkv, int32_t Ncap, int32_t B, int32_t d, int32_t dtype,
                               int32_t normalize, void* stream);
+
+/*
+ * update_centroids_from_ids -- the same centroids from the features as they are and their bucket ids, without a
+ * grouped copy of the features: saap_assign_keys and this call make one Lloyd iteration.
+ *   x [S,Hkv,N,d] dtype; bucket_ids [S,Hkv,N] int32 (ids outside [0,B) are left out)
+ * The sums run in the order of saap_update_centroids on saap_build_bucket_index's grouping: same bits.
+ * Workspace: SAAP_OP_UPDATE_CENTROIDS_FROM_IDS.
+ */
+int32_t saap_update_centroids_from_ids(const void* x, const int32_t* bucket_ids,
+                                       const void* centroids_old, void* centroids_new,
+                                       int32_t S, int32_t Hkv, int32_t N, int32_t B, int32_t d, int32_t dtype,
+                                       int32_t normalize, void* ws, size_t ws_bytes, void* stream);
 
 /*
  * bucket_attention_mass -- the share of a query's softmax attention that falls into each

@@ -22,7 +22,7 @@ PROBS, LOGITS = 0, 1
 OP_ASSIGN_KEYS, OP_BUILD_BUCKET_INDEX, OP_CLASSIFY_QUERIES, OP_SELECT_BUCKETS = 0, 1, 2, 3
 OP_SPARSE_DECODE_ATTENTION, OP_DENSE_DECODE_ATTENTION, OP_APPEND_KEYS, OP_WINDOW_PUSH = 4, 5, 6, 7
 OP_BUCKET_ATTENTION_MASS, OP_QUERY_MODEL_LOSS_GRADS, OP_BUCKET_ATTENTION_MASS_BATCH = 8, 9, 10
-OP_PLANNED_DECODE_ATTENTION, OP_PREFILL_SPARSE_ATTENTION = 11, 12
+OP_PLANNED_DECODE_ATTENTION, OP_PREFILL_SPARSE_ATTENTION, OP_UPDATE_CENTROIDS_FROM_IDS = 11, 12, 13
 WS_HEADER_BYTES = 65536
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -54,6 +54,8 @@ EXPORTS = (
     "saap_build_visit_plan", "saap_select_buckets_planned", "saap_planned_decode_attention",
     "saap_planned_decode_attention_fp8", "saap_visit_plan_bytes", "saap_sparse_decode_attention_noalloc",
     "saap_prefill_sparse_attention", "saap_classify_select", "saap_select_attend", "saap_select_attend_fp8", "saap_select_attend_windowed",
+    "saap_build_bucket_index_zeroed", "saap_build_windowed_index_zeroed",
+    "saap_update_centroids_from_ids",
 )
 
 
@@ -398,16 +400,27 @@ def update_centroids(x_sorted, off, ln, centroids_old, normalize=True, out=None)
     return new
 
 
+def update_centroids_from_ids(x, bucket_ids, centroids_old, normalize=True, out=None, ws=None):
+    """x [S,Hkv,N,d] and its bucket_ids int32 [S,Hkv,N] (assign_keys) -> new centroids [Hkv,B,d]."""
+    S, Hkv, N, d = x.shape
+    B = centroids_old.shape[1]
+    if bucket_ids.shape != (S, Hkv, N) or bucket_ids.dtype != torch.int32 or centroids_old.dtype != x.dtype:
+        raise ValueError("bucket_ids must be int32 [S,Hkv,N] and the centroids in the dtype of x")
+    new = out if out is not None else torch.empty_like(centroids_old)
+    ws, wsb = _ws(OP_UPDATE_CENTROIDS_FROM_IDS, x.device, ws, S=S, Hkv=Hkv, N=N, B=B)
+    st = load_library().saap_update_centroids_from_ids(
+        _ptr(x), _ptr(bucket_ids), _ptr(centroids_old), _ptr(new), _i32(S), _i32(Hkv), _i32(N), _i32(B), _i32(d),
+        _i32(_dtype_code(x)), _i32(1 if normalize else 0), _ptr(ws), wsb, _stream())
+    _check("saap_update_centroids_from_ids", st)
+    return new
+
+
 def lloyd_iterations(x, centroids, iters, normalize=True):
-    """`iters` iterations of (spherical) k-means on the device, composed of the library's calls: assign_keys,
-    build_bucket_index on the features (grouping) and update_centroids.  x [S,Hkv,N,d], centroids [Hkv,B,d]
-    (the initial ones; not modified) -> new centroids."""
-    B = centroids.shape[1]
+    """`iters` iterations of (spherical) k-means on the device, composed of the library's calls: assign_keys and
+    update_centroids_from_ids.  x [S,Hkv,N,d], centroids [Hkv,B,d] (the initial ones; not modified) -> new centroids."""
     c = centroids
     for _ in range(iters):
-        ids = assign_keys(x, c)
-        off, ln, _, xs, _ = build_bucket_index(ids, x, x, B, 0)
-        c = update_centroids(xs, off, ln, c, normalize)
+        c = update_centroids_from_ids(x, assign_keys(x, c), c, normalize)
     return c
 
 

@@ -65,6 +65,11 @@ inline bool allow_lds(size_t lds) {
 inline void begin_call() { (void)hipGetLastError(); }
 inline int32_t launch_status() { return hipGetLastError() == hipSuccess ? SAAP_OK : SAAP_HIP_ERROR; }
 
+size_t build_workspace_bytes(long long units, int N, int B);
+// The stable counting sort of an index build: off, len and idx from bucket ids (index.hip).
+void order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int32_t* idx, int32_t* res_ids, int32_t* slice_hist,
+                long long units, int N, int Ncap, int B, int slack, int W, int n_sink, int n_recent, hipStream_t hs);
+
 // ---- device side -------------------------------------------------------------------------
 
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }

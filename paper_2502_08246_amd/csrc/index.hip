@@ -7,10 +7,11 @@
 //   1. hist      every workgroup counts the bucket ids of its slice of positions
 //   2. colscan   per bucket, exclusive scan of the slice counts over slices -> len, slice bases
 //   3. offscan   per (sequence, head), exclusive scan of (len + slack) over buckets -> off
-//   4. scatter   one wavefront per slice walks its positions in order, 64 at a time; the rank of
-//                a position among equal ids inside the 64 comes from ballots, the running
-//                position of every bucket is kept in LDS -> idx
+//   4. scatter   one workgroup per slice; every wave walks its part of the slice in order, 64 positions at a
+//                time; the rank of a position among equal ids inside the 64 comes from ballots, the waves' and
+//                the buckets' running positions are kept in LDS -> idx
 //   5. permute   rows of K and V are copied to their slot, 16 bytes per lane, whole rows
+// A short context is one slice: order_small does steps 1 to 4 in one launch.
 //
 // With a resident block (attention sink + recent keys, Section 3 "Per-head attention span")
 // only the positions [lo, hi) go through steps 1-4; the resident positions are placed by
@@ -101,24 +102,30 @@ offscan_kernel(int32_t* __restrict__ len, int32_t* __restrict__ off, int B, int 
   }
 }
 
-// Resident keys of a unit: position -> slot of the resident run, ids kept for the later move.
+// Resident key j of a unit (j-th resident position in ascending order): its place in the resident run, its id kept
+// for the later move; slots that stay empty (context shorter than the run) are marked.
+__device__ __forceinline__ void place_resident(int j, const int32_t* __restrict__ ids, int32_t* __restrict__ idx,
+                                               int32_t* __restrict__ rid, int base, int N, int n_sink, int n_recent, int n_res) {
+  const int W = n_sink + n_recent;
+  if (j >= n_res) {              // slot r(p) = p while the block is not full: slots n_res.. are empty
+    rid[j] = -1;
+    idx[base + j] = -1;
+    return;
+  }
+  const int p = (N <= W || j < n_sink) ? j : N - n_recent + (j - n_sink);
+  const int r = p < n_sink ? p : n_sink + (p - n_sink) % n_recent;
+  idx[base + r] = p;
+  rid[r] = ids[p];
+}
+
 __global__ void __launch_bounds__(256)
 resident_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ off, int32_t* __restrict__ idx,
                 int32_t* __restrict__ res_ids, int N, int Ncap, int B, int n_sink, int n_recent, int n_res) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x, unit = blockIdx.y;
   const int W = n_sink + n_recent;
   if (j >= W) return;
-  int32_t* rid = res_ids + (size_t)unit * W;
-  if (j >= n_res) {              // slot r(p) = p while the block is not full: slots n_res.. are empty
-    rid[j] = -1;
-    return;
-  }
-  // j-th resident position in ascending order
-  const int p = (N <= W || j < n_sink) ? j : N - n_recent + (j - n_sink);
-  const int r = p < n_sink ? p : n_sink + (p - n_sink) % n_recent;
-  const int base = off[(size_t)unit * (B + 2) + B];
-  idx[(size_t)unit * Ncap + base + r] = p;
-  rid[r] = ids[(size_t)unit * N + p];
+  place_resident(j, ids + (size_t)unit * N, idx + (size_t)unit * Ncap, res_ids + (size_t)unit * W, off[(size_t)unit * (B + 2) + B], N,
+                 n_sink, n_recent, n_res);
 }
 
 __global__ void __launch_bounds__(256) fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
@@ -126,99 +133,210 @@ __global__ void __launch_bounds__(256) fill_i32_kernel(int32_t* p, size_t n, int
   if (i < n) p[i] = v;
 }
 
-// One wavefront per slice.  s_next[b] = slot of the next member of bucket b.
-__global__ void __launch_bounds__(64)
+// Counters of the waves of a workgroup, 16 bits per (wave, bucket), two buckets to a word.
+__device__ __forceinline__ void wave_count_add(unsigned* cnt, int b, unsigned n) { atomicAdd(&cnt[b >> 1], n << (16 * (b & 1))); }
+__device__ __forceinline__ unsigned wave_count(const unsigned* cnt, int b) { return (cnt[b >> 1] >> (16 * (b & 1))) & 0xffffu; }
+
+// The position in `b` (-1: none) of each of the wave's 64 lanes goes to its slot.  next[b]: first slot of bucket b of
+// this slice; mine: the wave's counters, holding what the waves before it (and its own earlier rounds) have placed.
+__device__ __forceinline__ void place_round(int b, int n, int id_bits, const int* next, unsigned* mine, int32_t* __restrict__ ix) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const bool ok = b >= 0;
+  unsigned long long eq = __ballot(ok);
+  for (int i = 0; i < id_bits; ++i) {
+    const bool bit = (b >> i) & 1;
+    const unsigned long long m = __ballot(bit);
+    eq &= bit ? m : ~m;
+  }
+  if (ok) {
+    const int rank = __popcll(eq & below);
+    ix[next[b] + (int)wave_count(mine, b) + rank] = n;
+    // one update per id, by the last of its lanes; lanes of two ids may share a word, hence an atomic
+    if ((eq & ~below) == (1ull << lane)) wave_count_add(mine, b, (unsigned)__popcll(eq));
+  }
+  // one wave: its LDS accesses execute in order, so the update is seen by the next 64 positions.  No barrier:
+  // a barrier also waits for the index store above, one memory round trip per 64 positions
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// One workgroup of four waves per slice of 2048 positions, 512 of them to a wave.  The waves count their parts first, so
+// that each knows what the others before it place: eight rounds one after the other, where one wave per slice had 32
+// (512 units x slices of the 128k workload: 22 -> 6 us; 4096: 115 -> 20 us).  The workgroup also marks the free slots of
+// every n_slices-th bucket.
+constexpr int kScatterThreads = 256, kScatterWaves = kScatterThreads / 64;
+__global__ void __launch_bounds__(kScatterThreads)
 scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slice_base,
                const int32_t* __restrict__ off, int32_t* __restrict__ idx, int N, int Ncap, int B,
-               int n_slices, int id_bits, int lo, int hi, int ostride) {
-  extern __shared__ int s_next[];
-  const int slice = blockIdx.x, unit = blockIdx.y, lane = threadIdx.x;
+               int n_slices, int id_bits, int lo, int hi, int ostride, int slack) {
+  extern __shared__ int s_next[];                        // [B] | counters [waves][words]
+  const int slice = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int words = (B + 1) / 2;
+  unsigned* s_cnt = reinterpret_cast<unsigned*>(s_next + B);
   const int32_t* base = slice_base + ((size_t)unit * n_slices + slice) * B;
   const int32_t* o = off + (size_t)unit * ostride;
-  // eight pairs of loads in flight per lane: one at a time the 2 * B / 64 dependent round trips took as long as
-  // the scatter itself
-  for (int b0 = 0; b0 < B; b0 += 64 * 8) {
-    int ov[8], bv[8];
+  int32_t* ix = idx + (size_t)unit * Ncap;
+  const int32_t* idu = ids + (size_t)unit * N;
+  constexpr int kRounds = kSlice / kScatterThreads;      // of 64 positions per wave
+  const int n0 = slice * kSlice + wave * (kSlice / kScatterWaves);
+  int mine[kRounds];                                     // the wave's ids, loaded up front
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int b = min(b0 + u * 64 + lane, B - 1);
-      ov[u] = o[b];
-      bv[u] = base[b];
-    }
+  for (int k = 0; k < kRounds; ++k) {
+    const int n = n0 + k * 64 + lane;
+    mine[k] = n >= lo && n < hi ? idu[n] : -1;           // hi <= N
+  }
+  for (int i = tid; i < kScatterWaves * words; i += kScatterThreads) s_cnt[i] = 0u;
+  for (int b = tid; b < B; b += kScatterThreads) s_next[b] = o[b] + base[b];
+  __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int b = b0 + u * 64 + lane;
-      if (b < B) s_next[b] = ov[u] + bv[u];
+  for (int k = 0; k < kRounds; ++k) {
+    if (mine[k] >= B) mine[k] = -1;
+    if (mine[k] >= 0) wave_count_add(s_cnt + wave * words, mine[k], 1u);
+  }
+  __syncthreads();
+  // exclusive prefix over the waves; at most 2048 per half word, no carry between the two
+  for (int i = tid; i < words; i += kScatterThreads) {
+    unsigned run = 0u;
+#pragma unroll
+    for (int w = 0; w < kScatterWaves; ++w) {
+      const unsigned c = s_cnt[w * words + i];
+      s_cnt[w * words + i] = run;
+      run += c;
     }
   }
   __syncthreads();
-  const int n0 = slice * kSlice, n1 = min(n0 + kSlice, N);
-  const int32_t* idu = ids + (size_t)unit * N;
-  int32_t* ix = idx + (size_t)unit * Ncap;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  int mine[kSlice / 64];       // the wave's ids, loaded up front
 #pragma unroll
-  for (int k = 0; k < kSlice / 64; ++k) {
-    const int n = n0 + k * 64 + lane;
-    mine[k] = n < n1 && n >= lo && n < hi ? idu[n] : -1;
-  }
-#pragma unroll
-  for (int k = 0; k < kSlice / 64; ++k) {
-    const int c = n0 + k * 64;
-    if (c >= n1) break;
-    const int n = c + lane;
-    const int b = mine[k];
-    const bool ok = b >= 0 && b < B;
-    unsigned long long eq = __ballot(ok);
-    for (int i = 0; i < id_bits; ++i) {
-      const bool bit = (b >> i) & 1;
-      const unsigned long long m = __ballot(bit);
-      eq &= bit ? m : ~m;
-    }
-    if (ok) {
-      const int rank = __popcll(eq & below);
-      const int cnt = __popcll(eq);
-      const int slot = s_next[b];
-      ix[slot + rank] = n;
-      if (rank == cnt - 1) s_next[b] = slot + cnt;
-    }
-    // one wave: its LDS accesses execute in order, so the update is seen by the next 64 positions.  No barrier:
-    // a barrier also waits for the index store above, one memory round trip per 64 positions
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  for (int k = 0; k < kRounds; ++k) place_round(mine[k], n0 + k * 64 + lane, id_bits, s_next, s_cnt + wave * words, ix);
+  for (int b = slice + wave * n_slices; slack > 0 && b < B; b += n_slices * kScatterWaves) {
+    const int end = o[b + 1];
+    for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
   }
 }
 
-// Copy rows into their slots: out[slot] = in[idx[slot]] for member slots.
-template <int CHUNKS /* 16-byte pieces per row */>
+// Steps 1 to 4 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
+// waves per unit, each wave counting and then placing its sixteenth of the positions.  Five launches of 2 to 3 us become
+// one (8 heads of 5003 keys: 26 -> 7 us).
+constexpr int kSmallKeys = 16384, kSmallBuckets = 2048, kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
+__global__ void __launch_bounds__(kSmallThreads)
+order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
+                   int32_t* __restrict__ res_ids, int N, int Ncap, int B, int id_bits, int lo, int hi, int slack, int W, int n_sink,
+                   int n_recent, int n_res) {
+  extern __shared__ int s_next[];                        // [B] | counters [waves][words]
+  __shared__ int s_wsum[kSmallWaves], s_end;
+  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int words = (B + 1) / 2;
+  unsigned* s_cnt = reinterpret_cast<unsigned*>(s_next + B);
+  unsigned* cnt = s_cnt + wave * words;
+  const int32_t* idu = ids + (size_t)unit * N;
+  int32_t* ix = idx + (size_t)unit * Ncap;
+  const int lstride = W >= 0 ? B + 1 : B;
+  int32_t* l = len + (size_t)unit * lstride;
+  int32_t* o = off + (size_t)unit * (lstride + 1);
+  const int per = ((hi - lo + kSmallWaves - 1) / kSmallWaves + 63) & ~63;      // positions per wave
+  const int n0 = lo + wave * per, n1 = min(n0 + per, hi);
+  constexpr int kDeep = 4;                               // rounds of ids in flight
+  auto load_ids = [&](int n, int (&v)[kDeep]) {
+#pragma unroll
+    for (int k = 0; k < kDeep; ++k) {
+      const int at = n + k * 64 + lane;
+      v[k] = idu[min(at, N - 1)];
+      if (at >= n1 || v[k] < 0 || v[k] >= B) v[k] = -1;
+    }
+  };
+  int v[kDeep];
+  load_ids(n0, v);                                       // in flight while the counters are cleared
+  for (int i = tid; i < kSmallWaves * words; i += kSmallThreads) s_cnt[i] = 0u;
+  __syncthreads();
+  for (int n = n0; n < n1; n += 64 * kDeep) {
+    if (n > n0) load_ids(n, v);
+#pragma unroll
+    for (int k = 0; k < kDeep; ++k)
+      if (v[k] >= 0) wave_count_add(cnt, v[k], 1u);
+  }
+  __syncthreads();
+  // exclusive prefix over the waves (at most 16384 per half word), totals, and the buckets' offsets
+  constexpr int kPairs = kSmallBuckets / 2 / kSmallThreads;                      // pairs of buckets per thread
+  static_assert(kPairs == 1, "one pair of buckets per thread");
+  unsigned tot = 0u;
+  if (tid < words)
+    for (int w = 0; w < kSmallWaves; ++w) {
+      const unsigned c = s_cnt[w * words + tid];
+      s_cnt[w * words + tid] = tot;
+      tot += c;
+    }
+  const int b0 = 2 * tid, len0 = (int)(tot & 0xffffu), len1 = (int)(tot >> 16);
+  const int mine = (b0 < B ? len0 + slack : 0) + (b0 + 1 < B ? len1 + slack : 0);
+  const int incl = (int)wave_prefix_sum((unsigned)mine);
+  if (lane == 63) s_wsum[wave] = incl;
+  __syncthreads();
+  int run = incl - mine;
+  for (int w = 0; w < wave; ++w) run += s_wsum[w];
+  if (tid == 0) o[0] = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int b = b0 + i;
+    if (b < B) {
+      s_next[b] = run;
+      l[b] = i ? len1 : len0;
+      run += (i ? len1 : len0) + slack;
+      o[b + 1] = run;
+      if (b == B - 1) {
+        s_end = run;
+        if (W >= 0) {
+          o[B + 1] = run + W;
+          l[B] = n_res;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (int n = n0; n < n1; n += 64 * kDeep) {
+    load_ids(n, v);
+#pragma unroll
+    for (int k = 0; k < kDeep; ++k)
+      if (n + k * 64 < n1) place_round(v[k], n + k * 64 + lane, id_bits, s_next, cnt, ix);
+  }
+  // free slots: the end of a bucket is the start of the next
+  const int all = s_end;
+  for (int b = wave; slack > 0 && b < B; b += kSmallWaves) {
+    const int end = b + 1 < B ? s_next[b + 1] : all;
+    for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
+  }
+  if (W > 0)
+    for (int j = tid; j < W; j += kSmallThreads) place_resident(j, idu, ix, res_ids + (size_t)unit * W, all, N, n_sink, n_recent, n_res);
+}
+
+// Copy rows into their slots: out[slot] = in[idx[slot]] for member slots.  ZERO: free slots are set to zero (here they
+// cost their own bytes once; a fill of the whole cache ahead of the copy writes every member slot twice).
+template <int CHUNKS /* 16-byte pieces per row */, bool ZERO>
 __global__ void __launch_bounds__(256)
 permute_kernel(const uint4* __restrict__ K, const uint4* __restrict__ V, const int32_t* __restrict__ idx,
-               uint4* __restrict__ Ks, uint4* __restrict__ Vs, int N, int Ncap, long long total_slots) {
+               uint4* __restrict__ Ks, uint4* __restrict__ Vs, int N, int Ncap) {
   constexpr int kRowsPerThread = 4;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int piece = (int)(t % CHUNKS);
-  const long long group = t / CHUNKS;               // handles slots group*4 .. group*4+3
+  const int unit = blockIdx.y, piece = threadIdx.x % CHUNKS;
+  const int first = (int)((blockIdx.x * 256u + threadIdx.x) / CHUNKS) * kRowsPerThread;
+  const int32_t* ix = idx + (size_t)unit * Ncap;
+  const uint4* Ku = K + (size_t)unit * N * CHUNKS + piece;
+  const uint4* Vu = V + (size_t)unit * N * CHUNKS + piece;
+  uint4* Ko = Ks + (size_t)unit * Ncap * CHUNKS + piece;
+  uint4* Vo = Vs + (size_t)unit * Ncap * CHUNKS + piece;
   int src[kRowsPerThread];
-  long long slot[kRowsPerThread];
 #pragma unroll
-  for (int r = 0; r < kRowsPerThread; ++r) {
-    slot[r] = group * kRowsPerThread + r;
-    src[r] = slot[r] < total_slots ? idx[slot[r]] : -1;
-  }
+  for (int r = 0; r < kRowsPerThread; ++r) src[r] = first + r < Ncap ? ix[first + r] : -1;
   uint4 kv[kRowsPerThread], vv[kRowsPerThread];
 #pragma unroll
   for (int r = 0; r < kRowsPerThread; ++r) {
+    kv[r] = vv[r] = make_uint4(0u, 0u, 0u, 0u);
     if (src[r] >= 0) {
-      const long long unit = slot[r] / Ncap;
-      const size_t in = ((size_t)unit * N + src[r]) * CHUNKS + piece;
-      kv[r] = stream_load16(K + in);
-      vv[r] = stream_load16(V + in);
+      kv[r] = stream_load16(Ku + (size_t)src[r] * CHUNKS);
+      vv[r] = stream_load16(Vu + (size_t)src[r] * CHUNKS);
     }
   }
 #pragma unroll
   for (int r = 0; r < kRowsPerThread; ++r) {
-    if (src[r] >= 0) {
-      stream_store16(Ks + (size_t)slot[r] * CHUNKS + piece, kv[r]);
-      stream_store16(Vs + (size_t)slot[r] * CHUNKS + piece, vv[r]);
+    if (src[r] >= 0 || (ZERO && first + r < Ncap)) {
+      stream_store16(Ko + (size_t)(first + r) * CHUNKS, kv[r]);
+      stream_store16(Vo + (size_t)(first + r) * CHUNKS, vv[r]);
     }
   }
 }
@@ -572,12 +690,53 @@ size_t build_workspace_bytes(long long units, int N, int B) {
 
 using namespace saap;
 
-// Shared body of the two build calls.  res_ids == nullptr: plain index (B runs); otherwise the
-// index with a resident run of W = n_sink + n_recent slots behind the B buckets.
+// off, len and idx of the index (steps 1 to 4).  W < 0: plain index (B runs); otherwise the index with a resident run of
+// W slots behind the B buckets and its ids in res_ids.  slice_hist: scratch of units * slices * B counters.
+void saap::order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int32_t* idx, int32_t* res_ids, int32_t* slice_hist,
+                      long long units, int N, int Ncap, int B, int slack, int W, int n_sink, int n_recent, hipStream_t hs) {
+  const bool windowed = W >= 0;
+  const int n_res = windowed ? (N < W ? N : W) : 0;
+  int id_bits = 1;
+  while ((1 << id_bits) < B) ++id_bits;
+  // positions [lo, hi) go into the buckets
+  const int lo = windowed ? (N <= W ? 0 : n_sink) : 0;
+  const int hi = windowed ? (N <= W ? 0 : N - n_recent) : N;
+  const size_t next_bytes = (size_t)B * sizeof(int), wave_bytes = (size_t)(B + 1) / 2 * sizeof(unsigned);
+  if (N <= kSmallKeys && B <= kSmallBuckets && allow_lds<order_small_kernel>(next_bytes + kSmallWaves * wave_bytes)) {
+    hipLaunchKernelGGL(order_small_kernel, dim3((unsigned)units), dim3(kSmallThreads), next_bytes + kSmallWaves * wave_bytes, hs,
+                       bucket_ids, len, off, idx, res_ids, N, Ncap, B, id_bits, lo, hi, slack, W, n_sink, n_recent, n_res);
+    return;
+  }
+  const int n_slices = (N + kSlice - 1) / kSlice, lstride = windowed ? B + 1 : B;
+  hipLaunchKernelGGL(hist_kernel, dim3(n_slices, (unsigned)units), dim3(256), next_bytes, hs, bucket_ids, slice_hist, N, B, n_slices,
+                     lo, hi);
+  hipLaunchKernelGGL(colscan_kernel, dim3((B + 255) / 256, (unsigned)units), dim3(256), 0, hs, slice_hist, len, B, n_slices, lstride);
+  hipLaunchKernelGGL(offscan_kernel, dim3((unsigned)units), dim3(1024), 0, hs, len, off, B, slack, W, n_res);
+  const size_t lds = next_bytes + kScatterWaves * wave_bytes;
+  (void)allow_lds<scatter_kernel>(lds);
+  hipLaunchKernelGGL(scatter_kernel, dim3(n_slices, (unsigned)units), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, off, idx,
+                     N, Ncap, B, n_slices, id_bits, lo, hi, lstride + 1, slack);
+  if (W > 0)
+    hipLaunchKernelGGL(resident_kernel, dim3((unsigned)((W + 255) / 256), (unsigned)units), dim3(256), 0, hs, bucket_ids, off, idx,
+                       res_ids, N, Ncap, B, n_sink, n_recent, n_res);
+}
+
+template <int CHUNKS>
+static void permute(const void* K, const void* V, const int32_t* idx, void* Ks, void* Vs, long long units, int N, int Ncap, bool zero,
+                    hipStream_t hs) {
+  const dim3 grid((unsigned)(((long long)(Ncap + 3) / 4 * CHUNKS + 255) / 256), (unsigned)units);
+  const auto *k = static_cast<const uint4*>(K), *v = static_cast<const uint4*>(V);
+  auto *ko = static_cast<uint4*>(Ks), *vo = static_cast<uint4*>(Vs);
+  if (zero) hipLaunchKernelGGL((permute_kernel<CHUNKS, true>), grid, dim3(256), 0, hs, k, v, idx, ko, vo, N, Ncap);
+  else hipLaunchKernelGGL((permute_kernel<CHUNKS, false>), grid, dim3(256), 0, hs, k, v, idx, ko, vo, N, Ncap);
+}
+
+// Shared body of the build calls.  res_ids == nullptr: plain index (B runs); otherwise the
+// index with a resident run of W = n_sink + n_recent slots behind the B buckets.  zero: free slots are set to zero.
 static int32_t build_index(const int32_t* bucket_ids, const void* K, const void* V, int32_t* off, int32_t* len,
                            int32_t* idx, void* Ksorted, void* Vsorted, int32_t* res_ids, int32_t S, int32_t Hkv,
                            int32_t N, int32_t Ncap, int32_t B, int32_t d, int32_t dtype, int32_t slack,
-                           int32_t n_sink, int32_t n_recent, void* ws, size_t ws_bytes, void* stream) {
+                           int32_t n_sink, int32_t n_recent, bool zero, void* ws, size_t ws_bytes, void* stream) {
   const bool windowed = res_ids != nullptr;
   if (!bucket_ids || !K || !V || !off || !len || !idx || !Ksorted || !Vsorted || !ws) return SAAP_INVALID_ARG;
   const void* ptrs[] = {bucket_ids, K, V, off, len, idx, Ksorted, Vsorted, ws, res_ids};
@@ -594,40 +753,10 @@ static int32_t build_index(const int32_t* bucket_ids, const void* K, const void*
   if (units > 65535) return SAAP_UNSUPPORTED;
   if (ws_bytes < build_workspace_bytes(units, N, B)) return SAAP_WORKSPACE_TOO_SMALL;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const int n_slices = (N + kSlice - 1) / kSlice;
   int32_t* slice_hist = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
-  int id_bits = 1;
-  while ((1 << id_bits) < B) ++id_bits;
-  // positions [lo, hi) go into the buckets
-  const int lo = windowed ? (N <= W ? 0 : n_sink) : 0;
-  const int hi = windowed ? (N <= W ? 0 : N - n_recent) : N;
-  const int lstride = windowed ? B + 1 : B;
-
-  hipLaunchKernelGGL(hist_kernel, dim3(n_slices, (unsigned)units), dim3(256), (size_t)B * sizeof(int), hs,
-                     bucket_ids, slice_hist, N, B, n_slices, lo, hi);
-  hipLaunchKernelGGL(colscan_kernel, dim3((B + 255) / 256, (unsigned)units), dim3(256), 0, hs, slice_hist, len,
-                     B, n_slices, lstride);
-  hipLaunchKernelGGL(offscan_kernel, dim3((unsigned)units), dim3(1024), 0, hs, len, off, B, slack,
-                     windowed ? (int)W : -1, (int)n_res);
-  const size_t n_idx = (size_t)units * Ncap;
-  hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n_idx + 255) / 256)), dim3(256), 0, hs, idx, n_idx, -1);
-  hipLaunchKernelGGL(scatter_kernel, dim3(n_slices, (unsigned)units), dim3(64), (size_t)B * sizeof(int), hs,
-                     bucket_ids, slice_hist, off, idx, N, Ncap, B, n_slices, id_bits, lo, hi, lstride + 1);
-  if (windowed && W > 0)
-    hipLaunchKernelGGL(resident_kernel, dim3((unsigned)((W + 255) / 256), (unsigned)units), dim3(256), 0, hs,
-                       bucket_ids, off, idx, res_ids, N, Ncap, B, n_sink, n_recent, (int)n_res);
-  const long long total_slots = units * Ncap;
-  if (dtype == SAAP_BF16) {
-    const long long threads = (total_slots + 3) / 4 * 16;
-    hipLaunchKernelGGL(permute_kernel<16>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, hs,
-                       static_cast<const uint4*>(K), static_cast<const uint4*>(V), idx,
-                       static_cast<uint4*>(Ksorted), static_cast<uint4*>(Vsorted), N, Ncap, total_slots);
-  } else {
-    const long long threads = (total_slots + 3) / 4 * 32;
-    hipLaunchKernelGGL(permute_kernel<32>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, hs,
-                       static_cast<const uint4*>(K), static_cast<const uint4*>(V), idx,
-                       static_cast<uint4*>(Ksorted), static_cast<uint4*>(Vsorted), N, Ncap, total_slots);
-  }
+  order_keys(bucket_ids, off, len, idx, res_ids, slice_hist, units, N, Ncap, B, slack, windowed ? (int)W : -1, n_sink, n_recent, hs);
+  if (dtype == SAAP_BF16) permute<16>(K, V, idx, Ksorted, Vsorted, units, N, Ncap, zero, hs);
+  else permute<32>(K, V, idx, Ksorted, Vsorted, units, N, Ncap, zero, hs);
   return launch_status();
 }
 
@@ -638,7 +767,17 @@ extern "C" int32_t saap_build_bucket_index(const int32_t* bucket_ids, const void
                                            size_t ws_bytes, void* stream) {
   begin_call();
   return build_index(bucket_ids, K, V, off, len, idx, Ksorted, Vsorted, nullptr, S, Hkv, N, Ncap, B, d, dtype, slack,
-                     0, 0, ws, ws_bytes, stream);
+                     0, 0, false, ws, ws_bytes, stream);
+}
+
+extern "C" int32_t saap_build_bucket_index_zeroed(const int32_t* bucket_ids, const void* K, const void* V,
+                                                  int32_t* off, int32_t* len, int32_t* idx, void* Ksorted,
+                                                  void* Vsorted, int32_t S, int32_t Hkv, int32_t N, int32_t Ncap,
+                                                  int32_t B, int32_t d, int32_t dtype, int32_t slack, void* ws,
+                                                  size_t ws_bytes, void* stream) {
+  begin_call();
+  return build_index(bucket_ids, K, V, off, len, idx, Ksorted, Vsorted, nullptr, S, Hkv, N, Ncap, B, d, dtype, slack,
+                     0, 0, true, ws, ws_bytes, stream);
 }
 
 extern "C" int32_t saap_build_windowed_index(const int32_t* bucket_ids, const void* K, const void* V,
@@ -650,7 +789,19 @@ extern "C" int32_t saap_build_windowed_index(const int32_t* bucket_ids, const vo
   begin_call();
   if (!resident_ids) return SAAP_INVALID_ARG;
   return build_index(bucket_ids, K, V, off, len, idx, Ksorted, Vsorted, resident_ids, S, Hkv, N, Ncap, B, d, dtype,
-                     slack, n_sink, n_recent, ws, ws_bytes, stream);
+                     slack, n_sink, n_recent, false, ws, ws_bytes, stream);
+}
+
+extern "C" int32_t saap_build_windowed_index_zeroed(const int32_t* bucket_ids, const void* K, const void* V,
+                                                    int32_t* off, int32_t* len, int32_t* idx, void* Ksorted,
+                                                    void* Vsorted, int32_t* resident_ids, int32_t S, int32_t Hkv,
+                                                    int32_t N, int32_t Ncap, int32_t B, int32_t d, int32_t dtype,
+                                                    int32_t slack, int32_t n_sink, int32_t n_recent, void* ws,
+                                                    size_t ws_bytes, void* stream) {
+  begin_call();
+  if (!resident_ids) return SAAP_INVALID_ARG;
+  return build_index(bucket_ids, K, V, off, len, idx, Ksorted, Vsorted, resident_ids, S, Hkv, N, Ncap, B, d, dtype,
+                     slack, n_sink, n_recent, true, ws, ws_bytes, stream);
 }
 
 extern "C" int32_t saap_window_push(const void* x_new, const void* k_new, const void* v_new,

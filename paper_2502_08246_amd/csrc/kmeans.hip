@@ -13,9 +13,10 @@
 namespace saap {
 namespace {
 
-template <typename T>
+// idx: null (x grouped by bucket) or [S,Hkv,Ncap], the row of each slot.
+template <typename T, bool GATHER>
 __global__ void __launch_bounds__(256)
-centroid_update_kernel(const T* __restrict__ x_sorted, const int32_t* __restrict__ off, const int32_t* __restrict__ len,
+centroid_update_kernel(const T* __restrict__ x, const int32_t* __restrict__ idx, const int32_t* __restrict__ off, const int32_t* __restrict__ len,
                        const T* __restrict__ cent_old, T* __restrict__ cent_new, int S, int Hkv, int Ncap, int B,
                        int normalize) {
   __shared__ float s_part[16][kD];
@@ -30,14 +31,27 @@ centroid_update_kernel(const T* __restrict__ x_sorted, const int32_t* __restrict
     const size_t unit = (size_t)s * Hkv + h;
     const int first = off[unit * (B + 1) + b], n = len[unit * B + b];
     count += n;
-    const T* rows = x_sorted + (unit * Ncap + first) * kD + sub * 8;
-    for (int r = grp; r < n; r += 16) {
-      Vec8<T> v;
-      v.load(rows + (size_t)r * kD);
-      float f[8];
-      v.to_float(f);
+    const T* rows = x + (GATHER ? unit * Ncap : unit * Ncap + first) * kD + sub * 8;
+    const int32_t* ix = GATHER ? idx + unit * Ncap + first : nullptr;
+    constexpr int kDeep = 4;                             // rows of a 16-lane group in flight
+    for (int r = grp; r < n; r += 16 * kDeep) {
+      int at[kDeep];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += f[e];
+      for (int u = 0; u < kDeep; ++u) {
+        at[u] = min(r + 16 * u, n - 1);
+        if constexpr (GATHER) at[u] = ix[at[u]];
+      }
+      Vec8<T> v[kDeep];
+#pragma unroll
+      for (int u = 0; u < kDeep; ++u) v[u].load(rows + (size_t)at[u] * kD);
+#pragma unroll
+      for (int u = 0; u < kDeep; ++u) {
+        float f[8];
+        v[u].to_float(f);
+        const bool in = r + 16 * u < n;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += in ? f[e] : 0.f;
+      }
     }
   }
 #pragma unroll
@@ -70,30 +84,77 @@ centroid_update_kernel(const T* __restrict__ x_sorted, const int32_t* __restrict
   }
 }
 
+template <typename T, bool GATHER>
+void launch_update(const void* x, const int32_t* idx, const int32_t* off, const int32_t* len, const void* cent_old, void* cent_new,
+                   int S, int Hkv, int Ncap, int B, int normalize, hipStream_t hs) {
+  hipLaunchKernelGGL((centroid_update_kernel<T, GATHER>), dim3((unsigned)B, (unsigned)Hkv), dim3(256), 0, hs, static_cast<const T*>(x),
+                     idx, off, len, static_cast<const T*>(cent_old), static_cast<T*>(cent_new), S, Hkv, Ncap, B, normalize);
+}
+
+size_t align16(size_t n) { return (n + 15) & ~(size_t)15; }
+
 }  // namespace
+
+// header | the slices' counters of the sort | off [units,B+1] | len [units,B] | idx [units,N]
+size_t update_from_ids_workspace_bytes(long long units, int N, int B) {
+  return align16(build_workspace_bytes(units, N, B)) + align16((size_t)units * (B + 1) * 4) + align16((size_t)units * B * 4) +
+         (size_t)units * N * 4;
+}
+
 }  // namespace saap
 
 using namespace saap;
+
+static int32_t check_update(const void* x, const void* cent_old, const void* cent_new, int32_t S, int32_t Hkv, int32_t N, int32_t B,
+                            int32_t d, int32_t dtype) {
+  if (!x || !cent_old || !cent_new) return SAAP_INVALID_ARG;
+  if (!aligned16(x) || !aligned16(cent_old) || !aligned16(cent_new)) return SAAP_INVALID_ARG;
+  if (S <= 0 || Hkv <= 0 || N <= 0 || B <= 0) return SAAP_INVALID_ARG;
+  if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
+  if (d != kD || B > SAAP_MAX_BUCKETS || Hkv > 65535) return SAAP_UNSUPPORTED;
+  return SAAP_OK;
+}
 
 extern "C" int32_t saap_update_centroids(const void* x_sorted, const int32_t* off, const int32_t* len,
                                          const void* centroids_old, void* centroids_new, int32_t S, int32_t Hkv,
                                          int32_t Ncap, int32_t B, int32_t d, int32_t dtype, int32_t normalize,
                                          void* stream) {
   begin_call();
-  if (!x_sorted || !off || !len || !centroids_old || !centroids_new) return SAAP_INVALID_ARG;
-  if (!aligned16(x_sorted) || !aligned16(centroids_old) || !aligned16(centroids_new)) return SAAP_INVALID_ARG;
-  if (S <= 0 || Hkv <= 0 || Ncap <= 0 || B <= 0) return SAAP_INVALID_ARG;
-  if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
-  if (d != kD || B > SAAP_MAX_BUCKETS || Hkv > 65535) return SAAP_UNSUPPORTED;
+  if (!off || !len) return SAAP_INVALID_ARG;
+  const int32_t st = check_update(x_sorted, centroids_old, centroids_new, S, Hkv, Ncap, B, d, dtype);
+  if (st != SAAP_OK) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const dim3 grid((unsigned)B, (unsigned)Hkv);
   if (dtype == SAAP_BF16)
-    hipLaunchKernelGGL(centroid_update_kernel<bf16_t>, grid, dim3(256), 0, hs, static_cast<const bf16_t*>(x_sorted),
-                       off, len, static_cast<const bf16_t*>(centroids_old), static_cast<bf16_t*>(centroids_new), S,
-                       Hkv, Ncap, B, normalize);
+    launch_update<bf16_t, false>(x_sorted, nullptr, off, len, centroids_old, centroids_new, S, Hkv, Ncap, B, normalize, hs);
   else
-    hipLaunchKernelGGL(centroid_update_kernel<float>, grid, dim3(256), 0, hs, static_cast<const float*>(x_sorted),
-                       off, len, static_cast<const float*>(centroids_old), static_cast<float*>(centroids_new), S, Hkv,
-                       Ncap, B, normalize);
+    launch_update<float, false>(x_sorted, nullptr, off, len, centroids_old, centroids_new, S, Hkv, Ncap, B, normalize, hs);
+  return launch_status();
+}
+
+extern "C" int32_t saap_update_centroids_from_ids(const void* x, const int32_t* bucket_ids, const void* centroids_old,
+                                                  void* centroids_new, int32_t S, int32_t Hkv, int32_t N, int32_t B,
+                                                  int32_t d, int32_t dtype, int32_t normalize, void* ws, size_t ws_bytes,
+                                                  void* stream) {
+  begin_call();
+  if (!bucket_ids || !ws || !aligned16(ws)) return SAAP_INVALID_ARG;
+  const int32_t st = check_update(x, centroids_old, centroids_new, S, Hkv, N, B, d, dtype);
+  if (st != SAAP_OK) return st;
+  const long long units = (long long)S * Hkv;
+  if (units > 65535) return SAAP_UNSUPPORTED;
+  if (ws_bytes < update_from_ids_workspace_bytes(units, N, B)) return SAAP_WORKSPACE_TOO_SMALL;
+  hipStream_t hs = static_cast<hipStream_t>(stream);
+  char* p = static_cast<char*>(ws);
+  int32_t* slice_hist = reinterpret_cast<int32_t*>(p + SAAP_WS_HEADER_BYTES);
+  p += align16(build_workspace_bytes(units, N, B));
+  int32_t* off = reinterpret_cast<int32_t*>(p);
+  p += align16((size_t)units * (B + 1) * 4);
+  int32_t* len = reinterpret_cast<int32_t*>(p);
+  p += align16((size_t)units * B * 4);
+  int32_t* idx = reinterpret_cast<int32_t*>(p);
+  order_keys(bucket_ids, off, len, idx, nullptr, slice_hist, units, N, N, B, 0, -1, 0, 0, hs);
+  if (dtype == SAAP_BF16)
+    launch_update<bf16_t, true>(x, idx, off, len, centroids_old, centroids_new, S, Hkv, N, B, normalize, hs);
+  else
+    launch_update<float, true>(x, idx, off, len, centroids_old, centroids_new, S, Hkv, N, B, normalize, hs);
   return launch_status();
 }

@@ -13,6 +13,7 @@ size_t push_workspace_bytes(long long units, int B);
 size_t classify_workspace_bytes(long long rows, int hidden);
 size_t mass_workspace_bytes(long long units, int G, int B);
 size_t mass_batch_workspace_bytes(long long units, long long R, int B);
+size_t update_from_ids_workspace_bytes(long long units, int N, int B);
 size_t train_workspace_bytes(long long Hw, long long R, int d, int hidden, int B);
 
 int current_device() {
@@ -139,6 +140,9 @@ extern "C" size_t saap_workspace_bytes(int32_t op, const saap_shape* sh) {
     case SAAP_OP_BUILD_BUCKET_INDEX:
       if (S <= 0 || Hkv <= 0 || sh->N <= 0 || sh->B <= 0) return 0;
       return build_workspace_bytes(S * Hkv, sh->N, sh->B);
+    case SAAP_OP_UPDATE_CENTROIDS_FROM_IDS:
+      if (S <= 0 || Hkv <= 0 || sh->N <= 0 || sh->B <= 0) return 0;
+      return update_from_ids_workspace_bytes(S * Hkv, sh->N, sh->B);
     case SAAP_OP_CLASSIFY_QUERIES:
       if (S <= 0 || Hq <= 0 || sh->hidden < 0) return 0;
       return classify_workspace_bytes(S * Hq, sh->hidden);

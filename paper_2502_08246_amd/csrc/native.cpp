@@ -303,10 +303,7 @@ SAAP_FUNCTION(build_bucket_index) {
   const int32_t S = size(K, 0), Hkv = size(K, 1), N = size(K, 2), d = size(K, 3);
   const int32_t B = a.integer(3), slack = a.integer(4, 0), Ncap = N + B * slack, dt = dtype_code(K);
   Out off(a, -1, {S, Hkv, B + 1}, at::kInt, K), len(a, -1, {S, Hkv, B}, at::kInt, K), idx(a, -1, {S, Hkv, Ncap}, at::kInt, K);
-  auto rows = [&] {
-    return slack > 0 ? at::zeros({S, Hkv, Ncap, d}, K.options()) : at::empty({S, Hkv, Ncap, d}, K.options());
-  };
-  Out Ks(rows()), Vs(rows());
+  Out Ks(a, -1, {S, Hkv, Ncap, d}, K.scalar_type(), K), Vs(a, -1, {S, Hkv, Ncap, d}, K.scalar_type(), K);
   saap_shape sh = shape_of(S, 0, Hkv);
   sh.N = N; sh.B = B;
   const Ws ws(a, 5, K, SAAP_OP_BUILD_BUCKET_INDEX, sh);
@@ -315,7 +312,7 @@ SAAP_FUNCTION(build_bucket_index) {
   int32_t *po = ptr_as<int32_t>(off.t), *pl = ptr_as<int32_t>(len.t), *px = ptr_as<int32_t>(idx.t);
   void* st = stream();
   call("saap_build_bucket_index", [&] {
-    return saap_build_bucket_index(pi, pk, pv, po, pl, px, pks, pvs, S, Hkv, N, Ncap, B, d, dt, slack, ws.p, ws.bytes, st);
+    return saap_build_bucket_index_zeroed(pi, pk, pv, po, pl, px, pks, pvs, S, Hkv, N, Ncap, B, d, dt, slack, ws.p, ws.bytes, st);
   });
   return tuple_of({&off, &len, &idx, &Ks, &Vs});
   SAAP_END
@@ -329,7 +326,7 @@ SAAP_FUNCTION(build_windowed_index) {
   const int32_t B = a.integer(3), slack = a.integer(4), n_sink = a.integer(5), n_recent = a.integer(6), dt = dtype_code(K);
   const int32_t W = n_sink + n_recent, Ncap = std::max(N - W, 0) + B * slack + W;
   Out off(a, -1, {S, Hkv, B + 2}, at::kInt, K), len(a, -1, {S, Hkv, B + 1}, at::kInt, K), idx(a, -1, {S, Hkv, Ncap}, at::kInt, K);
-  Out Ks(at::zeros({S, Hkv, Ncap, d}, K.options())), Vs(at::zeros({S, Hkv, Ncap, d}, K.options()));
+  Out Ks(a, -1, {S, Hkv, Ncap, d}, K.scalar_type(), K), Vs(a, -1, {S, Hkv, Ncap, d}, K.scalar_type(), K);
   // W may be 0: an address for the call all the same, and an empty tensor for the caller
   Tensor res = at::empty({S, Hkv, std::max(W, 1)}, K.options().dtype(at::kInt));
   int32_t* pr = ptr_as<int32_t>(res);
@@ -341,7 +338,7 @@ SAAP_FUNCTION(build_windowed_index) {
   int32_t *po = ptr_as<int32_t>(off.t), *pl = ptr_as<int32_t>(len.t), *px = ptr_as<int32_t>(idx.t);
   void* st = stream();
   call("saap_build_windowed_index", [&] {
-    return saap_build_windowed_index(pi, pk, pv, po, pl, px, pks, pvs, pr, S, Hkv, N, Ncap, B, d, dt, slack, n_sink,
+    return saap_build_windowed_index_zeroed(pi, pk, pv, po, pl, px, pks, pvs, pr, S, Hkv, N, Ncap, B, d, dt, slack, n_sink,
                                      n_recent, ws.p, ws.bytes, st);
   });
   Out res_out(W > 0 ? res : res.slice(2, 0, 0));
