@@ -10,16 +10,20 @@
 // the second on each tensor.  All arithmetic is fp32, every sum is taken by one thread or one
 // workgroup in a fixed order (no atomics), so a step is reproducible bit for bit.
 //
-// The five matrix products run on the matrix cores (v_mfma_f32_32x32x2_f32): a workgroup of four
-// waves owns a 64x64 tile of the result, operands are staged through LDS in k-slices of 16 by
-// loaders that read global memory along its contiguous dimension whichever operand is
-// transposed, bounds are checked on every dimension (R, B, hidden are free).
+// The five matrix products run on the matrix cores (v_mfma_f32_32x32x2_f32), bound by their fp32 rate (154 TFLOP/s in a
+// large product on this card): a workgroup of four waves owns a 64x64 tile of the result, operands are staged
+// through LDS by loaders that read global memory 16 bytes at a time along its contiguous dimension whichever operand is
+// transposed, double buffered with the next two slices' loads in flight.  Bounds are checked on every dimension (R, B,
+// hidden are free; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
+// column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
+// 8 weight sets, 1000 rows, 128 -> 512 -> 1024, the five products and two sums: 710 us with element loads, every slice's
+// loads waited for and the sums in launches of their own, 315 us now (100 of the 154 TFLOP/s).
 #include "common.h"
 
 namespace saap {
 namespace {
 
-constexpr int kTile = 64, kSlice = 16, kGemmThreads = 256;
+constexpr int kTile = 64, kSlice = 32, kPitch = kTile + 4, kGemmThreads = 256;
 
 enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_MASK = 3 };
 
@@ -31,51 +35,143 @@ struct GemmArgs {
   const float* aux;    // [M,N] (EPI_MASK: C = aux > 0 ? acc : 0)
   int M, N, K;
   long long sA, sB, sC, sBias, sAux;   // strides between the weight sets (blockIdx.z), in elements
+  float* colsum;       // [M] per weight set or null: sums of A' over k (TA only), strides sColsum
+  long long sColsum;
 };
 
-// C = A' B' for one 64x64 tile; A' is M x K, B' is K x N.
-template <bool TA, bool TB, int EPI>
+// One thread's share of a 64 x 32 slice of an operand, four elements a piece.  KC: the operand's contiguous dimension is
+// k (rows of length K), else it is the tile's dimension.
+template <bool KC, bool VEC>
+struct SliceLoader {
+  static constexpr int kPieces = kTile * kSlice / 4 / kGemmThreads;
+  float4 r[kPieces];
+  // piece i of this thread: element (row t, first of four k) or (first of four rows t, k) of the slice
+  static __device__ __forceinline__ void place(int i, int& t, int& k) {
+    const int q = threadIdx.x + i * kGemmThreads;
+    if constexpr (KC) { k = q % (kSlice / 4) * 4; t = q / (kSlice / 4); } else { t = q % (kTile / 4) * 4; k = q / (kTile / 4); }
+  }
+  // Loads at valid addresses whatever the slice; stash() clears what lies outside.  (Cleared here, the values would be
+  // waited for here.)
+  __device__ __forceinline__ void fetch(const float* X, int t0, int k0, int n_t, int K) {
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      int t, k;
+      place(i, t, k);
+      const int ld = KC ? K : n_t;                        // row length
+      const int row = min(KC ? t0 + t : k0 + k, (KC ? n_t : K) - 1), at = KC ? k0 + k : t0 + t;
+      if constexpr (VEC) {                                // ld is a multiple of 4: a piece is inside a row or outside
+        r[i] = *reinterpret_cast<const float4*>(X + (size_t)row * ld + min(at, ld - 4));
+      } else {
+        const float* x = X + (size_t)row * ld;
+        r[i] = make_float4(x[min(at, ld - 1)], x[min(at + 1, ld - 1)], x[min(at + 2, ld - 1)], x[min(at + 3, ld - 1)]);
+      }
+    }
+  }
+  // s: [kSlice][kPitch]; the values are left as they were stored
+  __device__ __forceinline__ void stash(float* s, int t0, int k0, int n_t, int K) {
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      int t, k;
+      place(i, t, k);
+      const int ld = KC ? K : n_t, at = KC ? k0 + k : t0 + t;
+      const bool in = KC ? t0 + t < n_t : k0 + k < K;
+      r[i].x = in && at < ld ? r[i].x : 0.f;
+      r[i].y = in && at + 1 < ld ? r[i].y : 0.f;
+      r[i].z = in && at + 2 < ld ? r[i].z : 0.f;
+      r[i].w = in && at + 3 < ld ? r[i].w : 0.f;
+      if constexpr (KC) {
+        s[k * kPitch + t] = r[i].x;
+        s[(k + 1) * kPitch + t] = r[i].y;
+        s[(k + 2) * kPitch + t] = r[i].z;
+        s[(k + 3) * kPitch + t] = r[i].w;
+      } else {
+        *reinterpret_cast<float4*>(s + k * kPitch + t) = r[i];
+      }
+    }
+  }
+};
+
+// C = A' B' for one 64x64 tile; A' is M x K, B' is K x N.  A wave owns a quarter of the tile, a matrix tile of 32.
+template <bool TA, bool TB, int EPI, bool VEC>
 __global__ void __launch_bounds__(kGemmThreads)
 gemm_kernel(GemmArgs g) {
-  __shared__ float s_a[kSlice][kTile + 1];   // [k][m]
-  __shared__ float s_b[kSlice][kTile + 1];   // [k][n]
   typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+  typedef SliceLoader<!TA, VEC> LoadA;
+  typedef SliceLoader<TB, VEC> LoadB;
+  constexpr int kOperand = kSlice * kPitch;
+  __shared__ __align__(16) float s_ab[2][2 * kOperand];          // [buffer][A slice | B slice], each [k][row]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
   const float* A = g.A + (size_t)blockIdx.z * g.sA;
   const float* B = g.B + (size_t)blockIdx.z * g.sB;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;     // this wave's 32x32 corner of the tile
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int col = lane & 31, half = lane >> 5;
+  const bool sums = TA && g.colsum != nullptr && blockIdx.x == 0;
+  float4 csum = make_float4(0.f, 0.f, 0.f, 0.f);                // of the thread's four columns of A (TA: they are always the same)
   f32x16_t acc = {0};
-  for (int k0 = 0; k0 < g.K; k0 += kSlice) {
-    // 64 x 16 elements per operand, four per thread, read along the contiguous dimension
+
+  struct Staged { LoadA a; LoadB b; };
+  auto fetch = [&](Staged& st, int k0) {
+    st.a.fetch(A, m0, k0, g.M, g.K);
+    st.b.fetch(B, n0, k0, g.N, g.K);
+  };
+  auto stash = [&](Staged& st, int buf, int k0) {
+    st.a.stash(s_ab[buf], m0, k0, g.M, g.K);
+    st.b.stash(s_ab[buf] + kOperand, n0, k0, g.N, g.K);
+    if (TA && sums) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * kGemmThreads;
-      int m, k;
-      if (TA) { m = e % kTile; k = e / kTile; } else { k = e % kSlice; m = e / kSlice; }
-      const bool ok = m0 + m < g.M && k0 + k < g.K;
-      s_a[k][m] = ok ? (TA ? A[(size_t)(k0 + k) * g.M + m0 + m] : A[(size_t)(m0 + m) * g.K + k0 + k]) : 0.f;
-      int n, kb;
-      if (TB) { kb = e % kSlice; n = e / kSlice; } else { n = e % kTile; kb = e / kTile; }
-      const bool okb = n0 + n < g.N && k0 + kb < g.K;
-      s_b[kb][n] = okb ? (TB ? B[(size_t)(n0 + n) * g.K + k0 + kb] : B[(size_t)(k0 + kb) * g.N + n0 + n]) : 0.f;
+      for (int i = 0; i < LoadA::kPieces; ++i) {
+        csum.x += st.a.r[i].x; csum.y += st.a.r[i].y; csum.z += st.a.r[i].z; csum.w += st.a.r[i].w;
+      }
     }
-    __syncthreads();
+  };
+  auto compute = [&](int buf) {
+    const float* sa = s_ab[buf] + half * kPitch + wm + col;
+    const float* sb = s_ab[buf] + kOperand + half * kPitch + wn + col;
 #pragma unroll
-    for (int k = 0; k < kSlice; k += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_a[k + half][wm + col], s_b[k + half][wn + col], acc, 0, 0, 0);
+    for (int k = 0; k < kSlice; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sa[k * kPitch], sb[k * kPitch], acc, 0, 0, 0);
+  };
+  const int n_slices = (g.K + kSlice - 1) / kSlice;
+  Staged even, odd;
+  fetch(even, 0);
+  fetch(odd, kSlice);
+  stash(even, 0, 0);
+  __syncthreads();
+  for (int c = 0; c < n_slices; c += 2) {
+    fetch(even, (c + 2) * kSlice);
+    compute(0);
+    stash(odd, 1, (c + 1) * kSlice);
     __syncthreads();
+    fetch(odd, (c + 3) * kSlice);
+    if (c + 1 < n_slices) compute(1);
+    stash(even, 0, (c + 2) * kSlice);
+    __syncthreads();
+  }
+  if (TA && sums) {
+    // the threads that loaded the same columns add up in a fixed order
+    constexpr int kGroups = kGemmThreads / (kTile / 4);
+    float* s = s_ab[0];                                           // [kGroups][kTile]
+    *reinterpret_cast<float4*>(s + tid / (kTile / 4) * kTile + tid % (kTile / 4) * 4) = csum;
+    __syncthreads();
+    if (tid < kTile && m0 + tid < g.M) {
+      float t = 0.f;
+#pragma unroll
+      for (int i = 0; i < kGroups; ++i) t += s[i * kTile + tid];
+      g.colsum[(size_t)blockIdx.z * g.sColsum + m0 + tid] = t;
+    }
   }
   // register r of this lane: row 8*(r/4) + 4*half + r%4, column `col` of the wave's corner
   float* C = g.C + (size_t)blockIdx.z * g.sC;
   const int n = n0 + wn + col;
+  if (n >= g.N) return;
+  float bias = 0.f;
+  if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) bias = g.bias[(size_t)blockIdx.z * g.sBias + n];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + wm + 8 * (r / 4) + 4 * half + (r % 4);
-    if (m < g.M && n < g.N) {
+    if (m < g.M) {
       float v = acc[r];
-      if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) v += g.bias[(size_t)blockIdx.z * g.sBias + n];
+      if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) v += bias;
       if (EPI == EPI_BIAS_RELU) v = fmaxf(v, 0.f);
       if (EPI == EPI_MASK) v = g.aux[(size_t)blockIdx.z * g.sAux + (size_t)m * g.N + n] > 0.f ? v : 0.f;
       C[(size_t)m * g.N + n] = v;
@@ -85,8 +181,13 @@ gemm_kernel(GemmArgs g) {
 
 template <bool TA, bool TB, int EPI>
 void gemm(const GemmArgs& g, int Hw, hipStream_t hs) {
+  // 16-byte loads need rows of both operands that start on 16 bytes
+  auto rows_aligned = [](const float* p, int ld, long long stride) { return aligned16(p) && ld % 4 == 0 && stride % 4 == 0; };
+  const bool vec = rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB);
+  // (128x128 tiles measured no faster: their fewer workgroups leave the start and the stores of a product uncovered)
   const dim3 grid((unsigned)((g.N + kTile - 1) / kTile), (unsigned)((g.M + kTile - 1) / kTile), (unsigned)Hw);
-  hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI>), grid, dim3(kGemmThreads), 0, hs, g);
+  if (vec) hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, true>), grid, dim3(kGemmThreads), 0, hs, g);
+  else hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, false>), grid, dim3(kGemmThreads), 0, hs, g);
 }
 
 __global__ void widen_kernel(const bf16_t* __restrict__ x, float* __restrict__ y, size_t n) {
@@ -167,24 +268,8 @@ __device__ __forceinline__ float slice_sum(float v, float (*s_part)[kBnCols], in
   return t;
 }
 
-// out[n] = sum over the rows of X [rows, n_cols]
-__global__ void __launch_bounds__(kBnThreads)
-colsum_kernel(const float* __restrict__ X, float* __restrict__ out, int rows, int n_cols, long long sX, long long sOut) {
-  __shared__ float s_part[kBnSlices][kBnCols];
-  const int col = threadIdx.x % kBnCols, slice = threadIdx.x / kBnCols;
-  const int c = blockIdx.x * kBnCols + col;
-  const bool live = c < n_cols;
-  const int per = (rows + kBnSlices - 1) / kBnSlices, r0 = slice * per, r1 = min(r0 + per, rows);
-  const float* x = X + (size_t)blockIdx.y * sX + (live ? c : 0);
-  float v = 0.f;
-  if (live)
-    for (int r = r0; r < r1; ++r) v += x[(size_t)r * n_cols];
-  v = slice_sum(v, s_part, col, slice);
-  if (live && slice == 0) out[(size_t)blockIdx.y * sOut + c] = v;
-}
-
 // Batch normalisation of the hidden pre-activations a [rows, n_cols] (Section 6.1 names the layer).
-// Columns and rows are dealt as in colsum_kernel.  The batch mean, then the variance about it (divisor rows).
+// Columns and rows are dealt as above.  The batch mean, then the variance about it (divisor rows).
 // stats [4, n_cols] per weight set: mean, 1/sqrt(var + eps), and room for the two backward sums.
 // Running statistics (optional) follow run = (1 - momentum) run + momentum batch, the variance with
 // divisor rows - 1.
@@ -360,26 +445,23 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
   const dim3 per_elem((unsigned)(((size_t)R * hidden + 255) / 256), (unsigned)Hw);
   if (!bn) {
     // h = relu(x W1^T + b1)
-    gemm<false, true, EPI_BIAS_RELU>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0}, Hw, hs);
+    gemm<false, true, EPI_BIAS_RELU>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0}, Hw, hs);
   } else {
     // a = x W1^T + b1;  h = relu(gamma * normalised(a) + beta)
-    gemm<false, true, EPI_BIAS>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0}, Hw, hs);
+    gemm<false, true, EPI_BIAS>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0}, Hw, hs);
     hipLaunchKernelGGL(bn_stats_kernel, per_col, dim3(kBnThreads), 0, hs, pre, stats, bn->running_mean, bn->running_var, R, hidden,
                        bn->eps, bn->momentum);
     hipLaunchKernelGGL(bn_relu_kernel, per_elem, dim3(256), 0, hs, pre, stats, bn->gamma, bn->beta, h, R, hidden);
   }
   // z = h W2^T + b2
-  gemm<false, true, EPI_BIAS>({h, params->W2, z, params->b2, nullptr, R, B, hidden, sh, sW2, sz, B, 0}, Hw, hs);
+  gemm<false, true, EPI_BIAS>({h, params->W2, z, params->b2, nullptr, R, B, hidden, sh, sW2, sz, B, 0, nullptr, 0}, Hw, hs);
   // row losses; z becomes dL/dz
   hipLaunchKernelGGL(softmax_kl_kernel, dim3((unsigned)R, (unsigned)Hw), dim3(256), 0, hs, z, target, loss_rows, R, B);
   hipLaunchKernelGGL(loss_mean_kernel, dim3((unsigned)Hw), dim3(256), 0, hs, loss_rows, loss, R);
   // dW2 = dz^T h, db2 = column sums of dz
-  gemm<true, false, EPI_NONE>({z, h, grads->W2, nullptr, nullptr, B, hidden, R, sz, sh, sW2, 0, 0}, Hw, hs);
-  hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((B + kBnCols - 1) / kBnCols), (unsigned)Hw), dim3(kBnThreads), 0, hs, z,
-                     grads->b2, R, B,
-                     sz, (long long)B);
+  gemm<true, false, EPI_NONE>({z, h, grads->W2, nullptr, nullptr, B, hidden, R, sz, sh, sW2, 0, 0, grads->b2, B}, Hw, hs);
   // da = (dz W2) where h > 0
-  gemm<false, false, EPI_MASK>({z, params->W2, da, nullptr, h, R, hidden, B, sz, sW2, sh, 0, sh}, Hw, hs);
+  gemm<false, false, EPI_MASK>({z, params->W2, da, nullptr, h, R, hidden, B, sz, sW2, sh, 0, sh, nullptr, 0}, Hw, hs);
   if (bn) {
     // through the normalisation: da holds dL/dy on entry and dL/da on exit
     hipLaunchKernelGGL(bn_backward_sums_kernel, per_col, dim3(kBnThreads), 0, hs, pre, da, stats, bn->grad_gamma, bn->grad_beta, R,
@@ -387,8 +469,7 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
     hipLaunchKernelGGL(bn_backward_kernel, per_elem, dim3(256), 0, hs, pre, da, stats, bn->gamma, R, hidden);
   }
   // dW1 = da^T x, db1 = column sums of da
-  gemm<true, false, EPI_NONE>({da, xin, grads->W1, nullptr, nullptr, hidden, d, R, sh, sx, sW1, 0, 0}, Hw, hs);
-  hipLaunchKernelGGL(colsum_kernel, per_col, dim3(kBnThreads), 0, hs, da, grads->b1, R, hidden, sh, (long long)hidden);
+  gemm<true, false, EPI_NONE>({da, xin, grads->W1, nullptr, nullptr, hidden, d, R, sh, sx, sW1, 0, 0, grads->b1, hidden}, Hw, hs);
   return launch_status();
 }
 
