@@ -115,129 +115,224 @@ void launch_mass(const void* q, const void* K, const int32_t* off, const int32_t
 }
 
 // ---- many queries per KV head (a training batch): scores on the matrix cores -----------------------
-// 128 queries per workgroup sit in registers as the B operand of v_mfma_f32_32x32x16_bf16 (32 per
-// wave, one lane per query and half of the key rows); the keys of a bucket stream through LDS in
-// tiles of 32 as the A operand (padded rows, whole-row loads), so that one lane sees 16 scores of
-// its query per tile and keeps the bucket's running maximum and sum for it.  A workgroup takes
-// every n_slices-th bucket.  part[(unit*B + b)*R + q] = (m, s).
+// 32 QT queries per wave sit in registers as the B operand of v_mfma_f32_32x32x16_bf16 (one lane per query and half of
+// the key rows); the keys of a bucket stream through LDS in tiles of 32 as the A operand (padded rows, whole-row loads,
+// double buffered, two tiles of loads in flight), so that one lane sees 16 scores of its query per tile and keeps the
+// bucket's running maximum and sum for it.  A workgroup takes every n_slices-th bucket.  part[(unit*B + b)*R + q] = (m, s).
+// Per tile and 32 queries a wave issues 8 matrix instructions (256 cycles) and about 50 vector instructions, 16 of them
+// exponentials at a fraction of the rate: the vector pipe bounds it, three workgroups per compute unit overlap the pipes.  8 heads, 1000 queries, 131072 keys: 486 us with one key tile waited for at a time, 350 us now.
 constexpr int kMassPitch = 136;      // bf16 elements per LDS row (272 bytes: conflict-free b128 reads)
-constexpr int kMassQueries = 128;    // queries per workgroup
+constexpr int kMassTile = 32;        // keys per tile
+constexpr int kMassBuckets = 512;    // buckets per workgroup at most
 
-__global__ void __launch_bounds__(256)
+// NEG: the score scale is negative, the largest score is the smallest product.
+template <int QT, bool NEG>
+__global__ void __launch_bounds__(256, 2)
 mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, const int32_t* __restrict__ off,
                  const int32_t* __restrict__ len, float2* __restrict__ part, long long rows, int B, int R,
                  float scale_log2) {
   typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-  __shared__ __align__(16) bf16_t s_k[32 * kMassPitch];
+  __shared__ __align__(16) bf16_t s_k[2][kMassTile * kMassPitch];
+  __shared__ int4 s_list[kMassBuckets];               // bucket, first row, length
+  __shared__ int s_live, s_tiles;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   const int unit = blockIdx.z;
-  const int qi = blockIdx.y * kMassQueries + wave * 32 + col;
-  // B operand: lane holds features 16*step + 8*half .. +7 of query `col` (idle columns repeat the last query)
-  bf16x8_t xb[8];
-  {
-    const bf16_t* qr = q + ((size_t)unit * R + min(qi, R - 1)) * kD + half * 8;
+  const int q0 = (blockIdx.y * 4 + wave) * 32 * QT + col;
+  // B operand: lane holds features 16*step + 8*half .. +7 of query `col` of each tile (idle columns repeat the last query)
+  bf16x8_t xb[QT][8];
 #pragma unroll
-    for (int st = 0; st < 8; ++st) xb[st] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qr + st * 16));
+  for (int i = 0; i < QT; ++i) {
+    const bf16_t* qr = q + ((size_t)unit * R + min(q0 + 32 * i, R - 1)) * kD + half * 8;
+#pragma unroll
+    for (int st = 0; st < 8; ++st) xb[i][st] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qr + st * 16));
   }
   const bf16_t* Ku = K + (size_t)unit * rows * kD;
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    const int first = off[(size_t)unit * (B + 1) + b], n = len[(size_t)unit * B + b];
-    float m = kNegBig, s = 0.f;
-    for (int t0 = 0; t0 < n; t0 += 32) {
-      __syncthreads();                                   // the previous tile has been read
-      // 32 rows x 16 pieces of 16 bytes, two per thread; rows past the bucket repeat its last key
-      uint4 piece[2];
+  // The workgroup's buckets (every gridDim.x-th) that hold keys, in LDS, so that walking on to the next one is no trip to
+  // memory; their order does not matter.  The pairs of a bucket without keys are written here.
+  auto pair_of = [&](int b, int i) { return part + ((size_t)unit * B + b) * R + q0 + 32 * i; };
+  if (tid == 0) s_live = s_tiles = 0;
+  __syncthreads();
+  for (int b = blockIdx.x + tid * gridDim.x; b < B; b += 256 * gridDim.x) {      // at most kMassBuckets: checked on the host
+    const int n = len[(size_t)unit * B + b], first = off[(size_t)unit * (B + 1) + b];
+    if (n > 0) {
+      s_list[atomicAdd(&s_live, 1)] = make_int4(b, first, n, 0);
+      atomicAdd(&s_tiles, (n + kMassTile - 1) / kMassTile);
+    }
+  }
+  for (int b = blockIdx.x; b < B; b += gridDim.x)
+    if (half == 0 && len[(size_t)unit * B + b] <= 0)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int pi = tid + 256 * i, r = pi >> 4, pc = pi & 15;
-        piece[i] = *reinterpret_cast<const uint4*>(Ku + (size_t)(first + min(t0 + r, n - 1)) * kD + pc * 8);
-      }
+      for (int i = 0; i < QT; ++i)
+        if (q0 + 32 * i < R) *pair_of(b, i) = make_float2(kNegBig, 0.f);
+  __syncthreads();
+  const int n_live = __builtin_amdgcn_readfirstlane(s_live), n_tiles = __builtin_amdgcn_readfirstlane(s_tiles);
+  if (n_tiles == 0) return;
+  // Tiles of 32 keys, bucket by bucket; the walk is the same in all waves (scalar registers) and, past the end, comes back
+  // to the last bucket (valid loads that nobody uses).
+  struct Tile { int j, b, first, n, t0; };
+  auto enter = [&](int j) {
+    const int4 e = s_list[j];
+    return Tile{j, __builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y), __builtin_amdgcn_readfirstlane(e.z), 0};
+  };
+  auto after = [&](const Tile& t) {
+    const bool same = t.t0 + kMassTile < t.n;
+    Tile r = enter(same ? t.j : min(t.j + 1, n_live - 1));
+    r.t0 = same ? t.t0 + kMassTile : 0;
+    return r;
+  };
+
+  struct Staged { u32x4_t p[2]; };        // native vectors: a uint4 here ends up in scratch memory
+  // 32 rows x 16 pieces of 16 bytes, two per thread; rows past the bucket repeat its last key
+  auto fetch = [&](Staged& g, const Tile& t) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int pi = tid + 256 * i, r = pi >> 4, pc = pi & 15;
-        *reinterpret_cast<uint4*>(&s_k[r * kMassPitch + pc * 8]) = piece[i];
-      }
-      __syncthreads();
-      f32x16_t acc = {0};
+    for (int i = 0; i < 2; ++i) {
+      const int pi = tid + 256 * i, r = pi >> 4, pc = pi & 15;
+      g.p[i] = *reinterpret_cast<const u32x4_t*>(Ku + (size_t)(t.first + min(t.t0 + r, t.n - 1)) * kD + pc * 8);
+    }
+  };
+  auto stash = [&](const Staged& g, int buf) {
 #pragma unroll
-      for (int st = 0; st < 8; ++st) {
-        const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(&s_k[col * kMassPitch + st * 16 + half * 8]));
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[st], acc, 0, 0, 0);
-      }
-      // register r of this lane: key t0 + 8*(r/4) + 4*half + r%4 against query `col`
-      float t[16], bm = -INFINITY;
+    for (int i = 0; i < 2; ++i) {
+      const int pi = tid + 256 * i, r = pi >> 4, pc = pi & 15;
+      *reinterpret_cast<u32x4_t*>(&s_k[buf][r * kMassPitch + pc * 8]) = g.p[i];
+    }
+  };
+  // Sums are kept relative to a reference m (base-2 logits) that stays over the buckets and moves only when a tile's sum
+  // says that scores lie far above it, so that no maximum is taken over a tile's scores: within 2^64 above the
+  // reference a sum loses nothing, and a key so far below it that its weight vanishes is as far below the largest key.
+  constexpr float kFarAbove = 1.8446744e19f;             // 2^64
+  float m[QT], s[QT];
+#pragma unroll
+  for (int i = 0; i < QT; ++i) {
+    m[i] = kNegBig;
+    s[i] = 0.f;
+  }
+  auto compute = [&](int buf, const Tile& t) {
+    f32x16_t acc[QT];
+#pragma unroll
+    for (int i = 0; i < QT; ++i) acc[i] = (f32x16_t){0};
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(&s_k[buf][col * kMassPitch + st * 16 + half * 8]));
+#pragma unroll
+      for (int i = 0; i < QT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[i][st], acc[i], 0, 0, 0);
+    }
+    // register r of this lane: key t0 + 8*(r/4) + 4*half + r%4 against query `col`
+    if (t.t0 + kMassTile > t.n) {                        // the bucket's last tile: rows past its end do not count
+#pragma unroll
+      for (int i = 0; i < QT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (t.t0 + 8 * (r / 4) + 4 * half + (r % 4) >= t.n) acc[i][r] = NEG ? INFINITY : -INFINITY;
+    }
+    auto weights = [&](const f32x16_t& c, float ref) {
+      float add[4];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int key = t0 + 8 * (r / 4) + 4 * half + (r % 4);
-        t[r] = key < n ? acc[r] * scale_log2 : -INFINITY;
-        bm = fmaxf(bm, t[r]);
+        const float w = fast_exp2(fmaf(c[r], scale_log2, -ref));
+        add[r % 4] = r < 4 ? w : add[r % 4] + w;
       }
-      const float mn = fmaxf(m, bm);                     // may stay at the stand-in when this half holds no real key
-      float add = 0.f;
+      return (add[0] + add[1]) + (add[2] + add[3]);
+    };
 #pragma unroll
-      for (int r = 0; r < 16; ++r) add += fast_exp2(t[r] - mn);
-      s = s * fast_exp2(m - mn) + add;
-      m = mn;
+    for (int i = 0; i < QT; ++i) {
+      float add = weights(acc[i], m[i]);
+      if (__builtin_expect(__ballot(!(add < kFarAbove)) != 0ull, 0)) {      // the first tile, and rarely after it
+        float best = acc[i][0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) best = NEG ? fminf(best, acc[i][r]) : fmaxf(best, acc[i][r]);
+        const float mn = fmaxf(m[i], best * scale_log2);   // stays where this half holds no key above it
+        add = weights(acc[i], mn);
+        s[i] *= fast_exp2(m[i] - mn);
+        m[i] = mn;
+      }
+      s[i] += add;
     }
-    // lanes l and l+32 hold the same query
-    const float mo = __shfl_xor(m, 32), so = __shfl_xor(s, 32);
-    const float M = fmaxf(m, mo);
-    const float S = s * fast_exp2(m - M) + so * fast_exp2(mo - M);
-    if (half == 0 && qi < R) part[((size_t)unit * B + b) * R + qi] = make_float2(M, S);
+    if (t.t0 + kMassTile >= t.n) {                       // the bucket is complete; lanes l and l+32 hold the same query
+#pragma unroll
+      for (int i = 0; i < QT; ++i) {
+        const float mo = __shfl_xor(m[i], 32), so = __shfl_xor(s[i], 32);
+        const float M = fmaxf(m[i], mo);
+        const float S = s[i] * fast_exp2(m[i] - M) + so * fast_exp2(mo - M);
+        if (half == 0 && q0 + 32 * i < R) *pair_of(t.b, i) = make_float2(M, S);
+        s[i] = 0.f;
+      }
+    }
+  };
+  // straight-line loads and stores (no early exit between them): behind branches the staging registers go to scratch
+  Tile t0 = enter(0), t1 = after(t0);
+  Staged even, odd;
+  fetch(even, t0);
+  fetch(odd, t1);
+  stash(even, 0);
+  __syncthreads();
+  for (int c = 0; c < n_tiles; c += 2) {
+    const Tile t2 = after(t1);
+    fetch(even, t2);
+    compute(0, t0);
+    stash(odd, 1);
+    __syncthreads();
+    const Tile t3 = after(t2);
+    fetch(odd, t3);
+    if (c + 1 < n_tiles) compute(1, t1);
+    stash(even, 0);
+    __syncthreads();
+    t0 = t2;
+    t1 = t3;
   }
 }
 
-// mass[(unit*R + q)*B + b] = s_b 2^(m_b - M) / L for 32 queries per workgroup: thread (query, bucket group).
+// mass[(unit*R + q)*B + b] = s_b 2^(m_b - M) / L for 32 queries per workgroup: thread (query, bucket group).  Two passes
+// over the pairs, eight loads in flight per thread: maximum and sum in one (the sum rescaled when the maximum moves), then
+// the masses, in tiles of 32 queries x 64 buckets through LDS so that the rows of `mass` are written in whole lines
+// (three passes, one load at a time: 130 us for 8 x 1000 queries and 1024 buckets, 32 us now).
 __global__ void __launch_bounds__(256)
 mass_normalise_batch_kernel(const float2* __restrict__ part, float* __restrict__ mass, float* __restrict__ lse, int B,
                             int R) {
-  __shared__ float s_red[8][32];
-  __shared__ float s_tile[32][33];
+  constexpr int kDeep = 8;
+  __shared__ float s_m[8][32], s_l[8][32];
+  __shared__ float s_tile[32][65];
   const int tid = threadIdx.x, ql = tid & 31, bg = tid >> 5;
   const int unit = blockIdx.y, q0 = blockIdx.x * 32;
   const int qi = min(q0 + ql, R - 1);
   const float2* pu = part + (size_t)unit * B * R + qi;
-  float M = kNegBig;
-  for (int b = bg; b < B; b += 8) M = fmaxf(M, pu[(size_t)b * R].x);
-  s_red[bg][ql] = M;
+  float M = kNegBig, L = 0.f;
+  for (int b0 = bg; b0 < B; b0 += 8 * kDeep) {
+    float2 p[kDeep];
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) p[u] = pu[(size_t)min(b0 + 8 * u, B - 1) * R];
+    float bm = M;
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) bm = fmaxf(bm, p[u].x);
+    L *= fast_exp2(M - bm);
+    M = bm;
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u)
+      if (b0 + 8 * u < B) L = fmaf(p[u].y, fast_exp2(p[u].x - M), L);
+  }
+  s_m[bg][ql] = M;
+  s_l[bg][ql] = L;
   __syncthreads();
 #pragma unroll
-  for (int g = 0; g < 8; ++g) M = fmaxf(M, s_red[g][ql]);
-  __syncthreads();
-  float L = 0.f;
-  for (int b = bg; b < B; b += 8) {
-    const float2 p = pu[(size_t)b * R];
-    L = fmaf(p.y, fast_exp2(p.x - M), L);
-  }
-  s_red[bg][ql] = L;
-  __syncthreads();
+  for (int g = 0; g < 8; ++g) M = fmaxf(M, s_m[g][ql]);
   L = 0.f;
 #pragma unroll
-  for (int g = 0; g < 8; ++g) L += s_red[g][ql];           // fixed order
+  for (int g = 0; g < 8; ++g) L = fmaf(s_l[g][ql], fast_exp2(s_m[g][ql] - M), L);      // fixed order
   const float inv = L > 0.f ? 1.0f / L : 0.f;
   if (bg == 0 && q0 + ql < R && lse) lse[(size_t)unit * R + q0 + ql] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
-  // tiles of 32 queries x 32 buckets go through LDS so that the rows of `mass` are written in whole lines
-  for (int bt = 0; bt < B; bt += 32) {
+  for (int bt = 0; bt < B; bt += 8 * kDeep) {
+    float2 p[kDeep];
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) p[u] = pu[(size_t)min(bt + bg + 8 * u, B - 1) * R];
+    __syncthreads();                                     // the tile before has been written out
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) s_tile[ql][bg + 8 * u] = p[u].y * fast_exp2(p[u].x - M) * inv;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int bb = bg * 4 + i, b = bt + bb;
-      float v = 0.f;
-      if (b < B) {
-        const float2 p = pu[(size_t)b * R];
-        v = p.y * fast_exp2(p.x - M) * inv;
-      }
-      s_tile[ql][bb] = v;
-    }
-    __syncthreads();
-    const int row = tid >> 3, seg = tid & 7;
-    if (q0 + row < R) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int b = bt + seg * 4 + i;
-        if (b < B) mass[((size_t)unit * R + q0 + row) * B + b] = s_tile[row][seg * 4 + i];
-      }
+    for (int i = 0; i < 8; ++i) {
+      const int row = (tid >> 6) + 4 * i, b = bt + (tid & 63);
+      if (q0 + row < R && b < B) mass[((size_t)unit * R + q0 + row) * B + b] = s_tile[row][tid & 63];
     }
   }
 }
@@ -306,18 +401,25 @@ extern "C" int32_t saap_bucket_attention_mass_batch(const void* q, const void* K
   if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
   if (d != kD || dtype != SAAP_BF16) return SAAP_UNSUPPORTED;
   const long long units = (long long)S * Hkv;
-  if (units > 65535 || (R + kMassQueries - 1) / kMassQueries > 65535) return SAAP_UNSUPPORTED;
+  if (units > 65535 || (R + 127) / 128 > 65535) return SAAP_UNSUPPORTED;
   if (ws_bytes < mass_batch_workspace_bytes(units, R, B)) return SAAP_WORKSPACE_TOO_SMALL;
   float2* part = reinterpret_cast<float2*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const int qblocks = (R + kMassQueries - 1) / kMassQueries;
-  // bucket slices: enough workgroups to fill the chip a few times, never more than buckets
-  long long slices = ((long long)device_cus() * 4 + units * qblocks - 1) / (units * qblocks);
+  // 256 queries per workgroup (two tiles per wave share the key operand's LDS reads) unless 128 leave fewer idle
+  const int qt = (R + 255) / 256 * 256 <= (R + 127) / 128 * 128 ? 2 : 1;
+  const int qblocks = (R + 128 * qt - 1) / (128 * qt);
+  // bucket slices: enough workgroups to fill the chip a few times (buckets differ in size), never more than buckets
+  long long slices = ((long long)device_cus() * 8 + units * qblocks - 1) / (units * qblocks);
   if (slices > B) slices = B;
   if (slices < 1) slices = 1;
-  hipLaunchKernelGGL(mass_mfma_kernel, dim3((unsigned)slices, (unsigned)qblocks, (unsigned)units), dim3(256), 0, hs,
-                     static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(Ksorted), off, len, part, (long long)Ncap,
-                     B, R, scale * kLog2e);
+  if (slices < (B + kMassBuckets - 1) / kMassBuckets) slices = (B + kMassBuckets - 1) / kMassBuckets;
+  const float scale_log2 = scale * kLog2e;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)slices, (unsigned)qblocks, (unsigned)units), dim3(256), 0, hs, static_cast<const bf16_t*>(q),
+                       static_cast<const bf16_t*>(Ksorted), off, len, part, (long long)Ncap, B, R, scale_log2);
+  };
+  if (scale_log2 < 0.f) qt == 2 ? launch(mass_mfma_kernel<2, true>) : launch(mass_mfma_kernel<1, true>);
+  else qt == 2 ? launch(mass_mfma_kernel<2, false>) : launch(mass_mfma_kernel<1, false>);
   hipLaunchKernelGGL(mass_normalise_batch_kernel, dim3((unsigned)((R + 31) / 32), (unsigned)units), dim3(256), 0, hs, part,
                      mass, lse, B, R);
   return launch_status();

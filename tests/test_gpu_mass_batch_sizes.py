@@ -1,0 +1,50 @@
+"""bucket_attention_mass_batch at the edges of its query tiles and key tiles, with empty buckets, with a negative score
+scale and with scores so far apart that the reference of the running sums has to move, against float64 numpy."""
+import numpy as np
+import pytest
+import torch
+
+from synth import gen
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def saap():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible: the -m gpu tests need a real device")
+    import paper_2502_08246_amd as lib
+    lib.load_library()
+    return lib
+
+
+@pytest.mark.parametrize("R,lens,scale,spread", [
+    (1, [1], 0.09, 1.0), (31, [0, 1, 31, 32, 33, 0, 65, 2], 0.09, 1.0), (128, [64] * 5, 0.09, 1.0), (129, [3, 0, 40] * 30, 0.09, 1.0),
+    (256, [33, 95, 1, 0], -0.09, 1.0), (300, [10, 200, 31], 0.09, 40.0), (257, [70, 0, 5, 64, 90], -0.09, 40.0),
+    (40, [1, 0, 2] * 400, 0.09, 1.0), (130, [0, 0, 0], 0.09, 1.0)])
+def test_mass(saap, R, lens, scale, spread):
+    Hkv, B, N = 2, len(lens), max(sum(lens), 1)
+    g = torch.Generator(device=DEV).manual_seed(R)
+    q = torch.randn(1, Hkv, R, 128, generator=g, device=DEV).to(torch.bfloat16)
+    # later keys reach far above earlier ones when `spread` is large (score range of some hundred bits)
+    grow = torch.linspace(1.0, spread, N, device=DEV).view(1, 1, N, 1)
+    K = (grow * torch.randn(1, Hkv, N, 128, generator=g, device=DEV)).to(torch.bfloat16)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device=DEV).view(1, 1, B + 1).repeat(1, Hkv, 1).contiguous()
+    ln = torch.tensor(lens, dtype=torch.int32, device=DEV).view(1, 1, B).repeat(1, Hkv, 1).contiguous()
+    mass, lse = saap.bucket_attention_mass_batch(q, K, off, ln, scale)
+    mass, lse = mass.cpu().numpy(), lse.cpu().numpy()
+    hq, hK = gen.to_host_f32(q).astype(np.float64), gen.to_host_f32(K).astype(np.float64)
+    for h in range(Hkv):
+        if sum(lens) == 0:
+            assert not mass[0, h].any() and np.isneginf(lse[0, h]).all()
+            continue
+        t = scale * hq[0, h] @ hK[0, h].T
+        top = t.max(-1, keepdims=True)
+        w = np.exp(t - top)
+        want = np.stack([w[:, a:a + n].sum(-1) for a, n in zip(np.cumsum([0] + list(lens))[:-1], lens)], -1)
+        total = w.sum(-1, keepdims=True)
+        # an fp32 score of magnitude s is off by about 2^-24 sqrt(128) s, which the exponential turns into a relative error
+        tol = 1e-5 * max(1.0, np.abs(t).max())
+        np.testing.assert_allclose(mass[0, h], want / total, rtol=tol, atol=1e-7)
+        np.testing.assert_allclose(lse[0, h], (top + np.log(total))[:, 0], rtol=1e-5, atol=1e-4)
