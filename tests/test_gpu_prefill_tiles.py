@@ -1,0 +1,37 @@
+"""Prefill-time sparse attention where its key and query tiles end: groups of 1 to 8 heads, blocks that do not fill a tile of
+query rows, buckets of less than a key tile and of many, tokens that list the same buckets and tokens that list none."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from test_gpu_prefill import DEV, SCALE, assert_close, h, setup
+from test_gpu_prefill import saap  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,Nt,B,Tq,nprobe,n_sink,n_recent,pos0,same", [
+    (1, 2, 2, 700, 16, 33, 3, 1, 40, (600,), False),             # one head per group: 32 tokens a tile, and one more
+    (2, 4, 2, 900, 64, 17, 9, 0, 33, (0, 883), False),           # buckets below a key tile; a block that opens its prompt
+    (1, 8, 2, 5000, 4, 35, 2, 3, 129, (4965,), False),            # buckets long enough to be shared out over waves
+    (1, 8, 1, 5000, 8, 67, 3, 2, 64, (3000,), True),             # every token lists the same buckets; keys beyond the block
+    (4, 16, 2, 1300, 40, 8, 40, 1, 1, (1292, 0, 7, 640), False), # as few tokens as come here, every bucket
+    (3, 4, 1, 600, 8, 130, 1, 600, 0, (0, 100, 470), False),     # a sink as large as the cache
+    (1, 4, 4, 2500, 300, 65, 250, 0, 500, (2000,), False),       # hundreds of lists per token
+])
+def test_prefill_tiles(saap, S, Hq, Hkv, Nt, B, Tq, nprobe, n_sink, n_recent, pos0, same):  # noqa: F811
+    cache, ids, (off, ln, idx, Ks, Vs), q = setup(saap, "bf16", S, Hq, Hkv, Nt, B, Tq, 5 + Tq, slack=2)
+    rng = np.random.default_rng(Tq + nprobe)
+    sel = np.stack([rng.permutation(B)[:nprobe] for _ in range(S * Hkv * Tq)]).reshape(S, Hkv, Tq, nprobe).astype(np.int32)
+    if same:
+        sel[:] = sel[:, :, :1]
+    p0 = np.array(pos0, dtype=np.int32)
+    args = (cache["K"], cache["V"], Ks, Vs, off, ln, idx, torch.from_numpy(sel).to(DEV), torch.from_numpy(p0).to(DEV), n_sink, n_recent)
+    out, lse = saap.prefill_sparse_attention(q, *args, SCALE)
+    again, _ = saap.prefill_sparse_attention(q, *args, SCALE)
+    torch.cuda.synchronize()
+    ro, rl = ref.prefill_sparse_attention(h(q), h(cache["K"]), h(cache["V"]), ids.cpu().numpy(), sel, p0, n_sink, n_recent, SCALE, B)
+    assert_close(out.cpu().numpy(), ro, "bf16", "out")
+    assert_close(lse.cpu().numpy(), rl, "bf16", "lse")
+    assert torch.equal(out, again)                               # whatever order the work is taken in
