@@ -162,15 +162,16 @@ __device__ __forceinline__ void place_round(int b, int n, int id_bits, const int
 
 // One workgroup of four waves per slice of 2048 positions, 512 of them to a wave.  The waves count their parts first, so
 // that each knows what the others before it place: eight rounds one after the other, where one wave per slice had 32
-// (512 units x slices of the 128k workload: 22 -> 6 us; 4096: 115 -> 20 us).  The workgroup also marks the free slots of
-// every n_slices-th bucket.
+// (8 units of 65536 positions: 22 -> 9.6 us).  The unit is the fastest grid dimension: with a multiple of 8 units all slices
+// of one share an L2, where the 4-byte stores of many slices to a line of idx meet (64 units of 131072 positions: 105 -> 58 us;
+// 8 of 65536: 9.6 -> 7.9).  The workgroup also marks the free slots of every n_slices-th bucket.
 constexpr int kScatterThreads = 256, kScatterWaves = kScatterThreads / 64;
 __global__ void __launch_bounds__(kScatterThreads)
 scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slice_base,
                const int32_t* __restrict__ off, int32_t* __restrict__ idx, int N, int Ncap, int B,
                int n_slices, int id_bits, int lo, int hi, int ostride, int slack) {
   extern __shared__ int s_next[];                        // [B] | counters [waves][words]
-  const int slice = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int unit = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int words = (B + 1) / 2;
   unsigned* s_cnt = reinterpret_cast<unsigned*>(s_next + B);
   const int32_t* base = slice_base + ((size_t)unit * n_slices + slice) * B;
@@ -215,7 +216,7 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
 
 // Steps 1 to 4 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
 // waves per unit, each wave counting and then placing its sixteenth of the positions.  Five launches of 2 to 3 us become
-// one (8 heads of 5003 keys: 26 -> 7 us).
+// one (8 heads of 5003 keys: 26 -> 10 us).
 constexpr int kSmallKeys = 16384, kSmallBuckets = 2048, kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
 __global__ void __launch_bounds__(kSmallThreads)
 order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
@@ -714,7 +715,7 @@ void saap::order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int
   hipLaunchKernelGGL(offscan_kernel, dim3((unsigned)units), dim3(1024), 0, hs, len, off, B, slack, W, n_res);
   const size_t lds = next_bytes + kScatterWaves * wave_bytes;
   (void)allow_lds<scatter_kernel>(lds);
-  hipLaunchKernelGGL(scatter_kernel, dim3(n_slices, (unsigned)units), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, off, idx,
+  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)units, n_slices), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, off, idx,
                      N, Ncap, B, n_slices, id_bits, lo, hi, lstride + 1, slack);
   if (W > 0)
     hipLaunchKernelGGL(resident_kernel, dim3((unsigned)((W + 255) / 256), (unsigned)units), dim3(256), 0, hs, bucket_ids, off, idx,
