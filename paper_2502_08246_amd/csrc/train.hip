@@ -11,19 +11,22 @@
 // workgroup in a fixed order (no atomics), so a step is reproducible bit for bit.
 //
 // The five matrix products run on the matrix cores (v_mfma_f32_32x32x2_f32), bound by their fp32 rate (154 TFLOP/s in a
-// large product on this card): a workgroup of four waves owns a 64x64 tile of the result, operands are staged
-// through LDS by loaders that read global memory 16 bytes at a time along its contiguous dimension whichever operand is
-// transposed, double buffered with the next two slices' loads in flight.  Bounds are checked on every dimension (R, B,
-// hidden are free; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
-// column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
+// large product on this card).  fp32 matrix instructions take the vector units' time, so that every vector instruction per
+// slice costs them: operands are loaded 16 bytes at a time along their contiguous dimension, whichever operand is transposed,
+// at offsets made once, and read back from LDS four values of k at a time, double buffered with the next two slices' loads in
+// flight.  Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias
+// gradients are the column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as
+// they load it.
 // 8 weight sets, 1000 rows, 128 -> 512 -> 1024, the five products and two sums: 710 us with element loads, every slice's
-// loads waited for and the sums in launches of their own, 315 us now (100 of the 154 TFLOP/s).
+// loads waited for and the sums in launches of their own; 315 us with 64x64 tiles and address arithmetic in every slice; 281 us
+// now (107 of the 154 TFLOP/s).  What is left is the start and the stores of a product, 13 us each of 88, which nothing covers:
+// all tiles of a product run at once.
 #include "common.h"
 
 namespace saap {
 namespace {
 
-constexpr int kTile = 64, kSlice = 32, kPitch = kTile + 4, kGemmThreads = 256;
+constexpr int kGemmThreads = 256;
 
 enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_MASK = 3 };
 
@@ -34,90 +37,143 @@ struct GemmArgs {
   const float* bias;   // [N]   (EPI_BIAS, EPI_BIAS_RELU)
   const float* aux;    // [M,N] (EPI_MASK: C = aux > 0 ? acc : 0)
   int M, N, K;
-  long long sA, sB, sC, sBias, sAux;   // strides between the weight sets (blockIdx.z), in elements
+  long long sA, sB, sC, sBias, sAux;   // strides between the weight sets (blockIdx.x), in elements
   float* colsum;       // [M] per weight set or null: sums of A' over k (TA only), strides sColsum
   long long sColsum;
 };
 
-// One thread's share of a 64 x 32 slice of an operand, four elements a piece.  KC: the operand's contiguous dimension is
-// k (rows of length K), else it is the tile's dimension.
-template <bool KC, bool VEC>
+// One thread's share of a slice of an operand, R rows by SL values of k, four elements a piece, on its way to LDS.  KC: the
+// operand's contiguous dimension is k, LDS holds [row][k] and a lane reads four k at a time; else it is the row dimension, LDS
+// holds [k][row].  Either way product (g, j) of a slice sums k = 8 g + 4 (lane / 32) + j.  The pitches make both reads free of
+// bank conflicts.  VEC: rows start on 16 bytes and are whole pieces long.
+template <bool KC, bool VEC, int R, int SL>
 struct SliceLoader {
-  static constexpr int kPieces = kTile * kSlice / 4 / kGemmThreads;
+  static constexpr int kPieces = R * SL / 4 / kGemmThreads, kPitch = KC ? SL + 4 : R + 8, kFloats = KC ? R * (SL + 4) : SL * (R + 8);
   float4 r[kPieces];
   // piece i of this thread: element (row t, first of four k) or (first of four rows t, k) of the slice
   static __device__ __forceinline__ void place(int i, int& t, int& k) {
     const int q = threadIdx.x + i * kGemmThreads;
-    if constexpr (KC) { k = q % (kSlice / 4) * 4; t = q / (kSlice / 4); } else { t = q % (kTile / 4) * 4; k = q / (kTile / 4); }
+    if constexpr (KC) { k = q % (SL / 4) * 4; t = q / (SL / 4); } else { t = q % (R / 4) * 4; k = q / (R / 4); }
   }
-  // Loads at valid addresses whatever the slice; stash() clears what lies outside.  (Cleared here, the values would be
-  // waited for here.)
-  __device__ __forceinline__ void fetch(const float* X, int t0, int k0, int n_t, int K) {
+  // Byte offsets of the pieces from the slice's first value (Offsets): all that a lane adds to an address that the whole workgroup shares.
+  // (fp32 matrix products and ordinary vector instructions take the same units by turns: address arithmetic per slice cost a
+  // fifth of the products' time.)  Rows past the end repeat the last one and are not stored.
+  struct Offsets { unsigned at[VEC ? kPieces : 4 * kPieces]; };
+  static __device__ __forceinline__ Offsets offsets(int t0, int n_t, int K) {
+    Offsets o;
 #pragma unroll
     for (int i = 0; i < kPieces; ++i) {
       int t, k;
       place(i, t, k);
-      const int ld = KC ? K : n_t;                        // row length
-      const int row = min(KC ? t0 + t : k0 + k, (KC ? n_t : K) - 1), at = KC ? k0 + k : t0 + t;
       if constexpr (VEC) {                                // ld is a multiple of 4: a piece is inside a row or outside
-        r[i] = *reinterpret_cast<const float4*>(X + (size_t)row * ld + min(at, ld - 4));
+        o.at[i] = 4u * (unsigned)(KC ? min(t0 + t, n_t - 1) * K + k : k * n_t + min(t0 + t, n_t - 4));
       } else {
-        const float* x = X + (size_t)row * ld;
-        r[i] = make_float4(x[min(at, ld - 1)], x[min(at + 1, ld - 1)], x[min(at + 2, ld - 1)], x[min(at + 3, ld - 1)]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o.at[4 * i + e] = 4u * (unsigned)(KC ? min(t0 + t, n_t - 1) * K + k + e : k * n_t + min(t0 + t + e, n_t - 1));
+      }
+    }
+    return o;
+  }
+  // The slice from k0 on; where it would reach past the end of k, the last SL values instead, of which stash() clears those
+  // before k0.  (Cleared here, they would be waited for here.)
+  __device__ __forceinline__ void fetch(const float* X, const Offsets& o, int k0, int n_t, int K) {
+    const char* x = reinterpret_cast<const char*>(X + (size_t)min(k0, K - SL) * (KC ? 1 : n_t));
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      if constexpr (VEC) {
+        r[i] = *reinterpret_cast<const float4*>(x + o.at[i]);
+      } else {
+        r[i].x = *reinterpret_cast<const float*>(x + o.at[4 * i]);
+        r[i].y = *reinterpret_cast<const float*>(x + o.at[4 * i + 1]);
+        r[i].z = *reinterpret_cast<const float*>(x + o.at[4 * i + 2]);
+        r[i].w = *reinterpret_cast<const float*>(x + o.at[4 * i + 3]);
       }
     }
   }
-  // s: [kSlice][kPitch]; the values are left as they were stored
-  __device__ __forceinline__ void stash(float* s, int t0, int k0, int n_t, int K) {
+  __device__ __forceinline__ void stash(float* s, int k0, int K) {
+    const int before = k0 - min(k0, K - SL);              // values of the slice that belong to the one before it
 #pragma unroll
     for (int i = 0; i < kPieces; ++i) {
       int t, k;
       place(i, t, k);
-      const int ld = KC ? K : n_t, at = KC ? k0 + k : t0 + t;
-      const bool in = KC ? t0 + t < n_t : k0 + k < K;
-      r[i].x = in && at < ld ? r[i].x : 0.f;
-      r[i].y = in && at + 1 < ld ? r[i].y : 0.f;
-      r[i].z = in && at + 2 < ld ? r[i].z : 0.f;
-      r[i].w = in && at + 3 < ld ? r[i].w : 0.f;
-      if constexpr (KC) {
-        s[k * kPitch + t] = r[i].x;
-        s[(k + 1) * kPitch + t] = r[i].y;
-        s[(k + 2) * kPitch + t] = r[i].z;
-        s[(k + 3) * kPitch + t] = r[i].w;
-      } else {
-        *reinterpret_cast<float4*>(s + k * kPitch + t) = r[i];
+      if (before > 0) {
+        r[i].x = k >= before ? r[i].x : 0.f;
+        r[i].y = k + (KC ? 1 : 0) >= before ? r[i].y : 0.f;
+        r[i].z = k + (KC ? 2 : 0) >= before ? r[i].z : 0.f;
+        r[i].w = k + (KC ? 3 : 0) >= before ? r[i].w : 0.f;
       }
+      *reinterpret_cast<float4*>(s + (KC ? t * kPitch + k : k * kPitch + t)) = r[i];
+    }
+  }
+  // the lane's four values of k of group g, of row `row`
+  static __device__ __forceinline__ float4 read(const float* s, int row, int g, int half) {
+    const int k = 8 * g + 4 * half;
+    if constexpr (KC) {
+      return *reinterpret_cast<const float4*>(s + row * kPitch + k);
+    } else {
+      const float* x = s + k * kPitch + row;
+      return make_float4(x[0], x[kPitch], x[2 * kPitch], x[3 * kPitch]);
     }
   }
 };
 
-// C = A' B' for one 64x64 tile; A' is M x K, B' is K x N.  A wave owns a quarter of the tile, a matrix tile of 32.
-template <bool TA, bool TB, int EPI, bool VEC>
-__global__ void __launch_bounds__(kGemmThreads)
-gemm_kernel(GemmArgs g) {
-  typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-  typedef SliceLoader<!TA, VEC> LoadA;
-  typedef SliceLoader<TB, VEC> LoadB;
-  constexpr int kOperand = kSlice * kPitch;
-  __shared__ __align__(16) float s_ab[2][2 * kOperand];          // [buffer][A slice | B slice], each [k][row]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
-  const float* A = g.A + (size_t)blockIdx.z * g.sA;
-  const float* B = g.B + (size_t)blockIdx.z * g.sB;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const int col = lane & 31, half = lane >> 5;
-  const bool sums = TA && g.colsum != nullptr && blockIdx.x == 0;
-  float4 csum = make_float4(0.f, 0.f, 0.f, 0.f);                // of the thread's four columns of A (TA: they are always the same)
-  f32x16_t acc = {0};
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
+// Registers r of a lane hold rows m0 + 8*(r/4) + 4*half + r%4 of column n.
+template <int EPI, int REGS, typename V>
+__device__ __forceinline__ void store_tile(const GemmArgs& g, int w, int m0, int n, int half, const V& acc) {
+  if (n >= g.N) return;
+  float bias = 0.f;
+  if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) bias = g.bias[(size_t)w * g.sBias + n];
+  auto row = [&](int r) { return m0 + 8 * (r / 4) + 4 * half + (r % 4); };
+  float aux[REGS];
+  if (EPI == EPI_MASK) {
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) aux[r] = g.aux[(size_t)w * g.sAux + (size_t)min(row(r), g.M - 1) * g.N + n];
+  }
+  float* C = g.C + (size_t)w * g.sC + n;
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    float v = acc[r];
+    if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) v += bias;
+    if (EPI == EPI_BIAS_RELU) v = fmaxf(v, 0.f);
+    if (EPI == EPI_MASK) v = aux[r] > 0.f ? v : 0.f;
+    if (row(r) < g.M) C[(size_t)row(r) * g.N] = v;
+  }
+}
+
+// C = A' B'; A' is M x K, B' is K x N.  A workgroup of two by two waves owns a tile of 64 TM x 64, a wave TM matrix tiles of 32.
+template <bool TA, bool TB, int EPI, bool VEC, int TM, int SL>
+__global__ void __launch_bounds__(kGemmThreads, 4)
+gemm_kernel(GemmArgs g) {
+  constexpr int BM = 64 * TM, BN = 64;
+  typedef SliceLoader<!TA, VEC, BM, SL> LoadA;
+  typedef SliceLoader<TB, VEC, BN, SL> LoadB;
+  __shared__ __align__(16) float s_ab[2][LoadA::kFloats + LoadB::kFloats];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
+  const float* A = g.A + (size_t)w * g.sA;
+  const float* B = g.B + (size_t)w * g.sB;
+  const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32;
+  const int col = lane & 31, half = lane >> 5;
+  const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
+  float4 csum = make_float4(0.f, 0.f, 0.f, 0.f);                // of the thread's four columns of A (TA: they are always the same)
+  f32x16_t acc[TM];
+#pragma unroll
+  for (int a = 0; a < TM; ++a) acc[a] = (f32x16_t){0};
+
+  const typename LoadA::Offsets oa = LoadA::offsets(m0, g.M, g.K);
+  const typename LoadB::Offsets ob = LoadB::offsets(n0, g.N, g.K);
   struct Staged { LoadA a; LoadB b; };
   auto fetch = [&](Staged& st, int k0) {
-    st.a.fetch(A, m0, k0, g.M, g.K);
-    st.b.fetch(B, n0, k0, g.N, g.K);
+    st.a.fetch(A, oa, k0, g.M, g.K);
+    st.b.fetch(B, ob, k0, g.N, g.K);
+    __builtin_amdgcn_sched_barrier(0);                          // left alone the compiler moves the loads behind the products
   };
   auto stash = [&](Staged& st, int buf, int k0) {
-    st.a.stash(s_ab[buf], m0, k0, g.M, g.K);
-    st.b.stash(s_ab[buf] + kOperand, n0, k0, g.N, g.K);
+    st.a.stash(s_ab[buf], k0, g.K);
+    st.b.stash(s_ab[buf] + LoadA::kFloats, k0, g.K);
     if (TA && sums) {
 #pragma unroll
       for (int i = 0; i < LoadA::kPieces; ++i) {
@@ -126,68 +182,168 @@ gemm_kernel(GemmArgs g) {
     }
   };
   auto compute = [&](int buf) {
-    const float* sa = s_ab[buf] + half * kPitch + wm + col;
-    const float* sb = s_ab[buf] + kOperand + half * kPitch + wn + col;
+    const float* sa = s_ab[buf];
+    const float* sb = s_ab[buf] + LoadA::kFloats;
 #pragma unroll
-    for (int k = 0; k < kSlice; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sa[k * kPitch], sb[k * kPitch], acc, 0, 0, 0);
+    for (int q = 0; q < SL / 8; ++q) {
+      const float4 b = LoadB::read(sb, wn + col, q, half);
+      float4 a[TM];
+#pragma unroll
+      for (int t = 0; t < TM; ++t) a[t] = LoadA::read(sa, wm + 32 * t + col, q, half);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t].x, b.x, acc[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t].y, b.y, acc[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t].z, b.z, acc[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t].w, b.w, acc[t], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  const int n_slices = (g.K + kSlice - 1) / kSlice;
+  const int n_slices = (g.K + SL - 1) / SL;
   Staged even, odd;
   fetch(even, 0);
-  fetch(odd, kSlice);
+  fetch(odd, SL);
   stash(even, 0, 0);
   __syncthreads();
   for (int c = 0; c < n_slices; c += 2) {
-    fetch(even, (c + 2) * kSlice);
+    fetch(even, (c + 2) * SL);
     compute(0);
-    stash(odd, 1, (c + 1) * kSlice);
+    stash(odd, 1, (c + 1) * SL);
     __syncthreads();
-    fetch(odd, (c + 3) * kSlice);
+    fetch(odd, (c + 3) * SL);
     if (c + 1 < n_slices) compute(1);
-    stash(even, 0, (c + 2) * kSlice);
+    stash(even, 0, (c + 2) * SL);
     __syncthreads();
   }
   if (TA && sums) {
     // the threads that loaded the same columns add up in a fixed order
-    constexpr int kGroups = kGemmThreads / (kTile / 4);
-    float* s = s_ab[0];                                           // [kGroups][kTile]
-    *reinterpret_cast<float4*>(s + tid / (kTile / 4) * kTile + tid % (kTile / 4) * 4) = csum;
+    constexpr int kGroups = kGemmThreads / (BM / 4);
+    float* s = s_ab[0];                                           // [kGroups][BM]
+    *reinterpret_cast<float4*>(s + tid / (BM / 4) * BM + tid % (BM / 4) * 4) = csum;
     __syncthreads();
-    if (tid < kTile && m0 + tid < g.M) {
+    if (tid < BM && m0 + tid < g.M) {
       float t = 0.f;
 #pragma unroll
-      for (int i = 0; i < kGroups; ++i) t += s[i * kTile + tid];
-      g.colsum[(size_t)blockIdx.z * g.sColsum + m0 + tid] = t;
+      for (int i = 0; i < kGroups; ++i) t += s[i * BM + tid];
+      g.colsum[(size_t)w * g.sColsum + m0 + tid] = t;
     }
   }
-  // register r of this lane: row 8*(r/4) + 4*half + r%4, column `col` of the wave's corner
-  float* C = g.C + (size_t)blockIdx.z * g.sC;
-  const int n = n0 + wn + col;
-  if (n >= g.N) return;
-  float bias = 0.f;
-  if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) bias = g.bias[(size_t)blockIdx.z * g.sBias + n];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = m0 + wm + 8 * (r / 4) + 4 * half + (r % 4);
-    if (m < g.M) {
-      float v = acc[r];
-      if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) v += bias;
-      if (EPI == EPI_BIAS_RELU) v = fmaxf(v, 0.f);
-      if (EPI == EPI_MASK) v = g.aux[(size_t)blockIdx.z * g.sAux + (size_t)m * g.N + n] > 0.f ? v : 0.f;
-      C[(size_t)m * g.N + n] = v;
+  for (int t = 0; t < TM; ++t) store_tile<EPI, 16>(g, w, m0 + wm + 32 * t, n0 + wn + col, half, acc[t]);
+}
+
+// The same for results of few tiles: a workgroup owns one matrix tile, its four waves a quarter of the k each, operands straight
+// from memory (a lane loads what the matrix cores take from it), the next slice's loads in flight.  8 sets of 512 x 128 over
+// 1000 rows: 27 us in the kernel above, here 18.
+template <bool KC, bool VEC>
+struct DirectOperand {
+  float r[4][4];                                         // [g][j]: k = k0 + 8 g + 4 (lane / 32) + j
+  __device__ __forceinline__ void fetch(const float* X, int t0, int k0, int n_t, int K) {
+    const int lane = threadIdx.x & 63, half = lane >> 5, t = min(t0 + (lane & 31), n_t - 1);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int k = k0 + 8 * g + 4 * half;
+      if constexpr (KC && VEC) {
+        const float4 v = *reinterpret_cast<const float4*>(X + (size_t)t * K + min(k, K - 4));
+        r[g][0] = v.x; r[g][1] = v.y; r[g][2] = v.z; r[g][3] = v.w;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[g][j] = KC ? X[(size_t)t * K + min(k + j, K - 1)] : X[(size_t)min(k + j, K - 1) * n_t + t];
+      }
     }
   }
+  __device__ __forceinline__ void clear(int k0, int K) {
+    const int half = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[g][j] = k0 + 8 * g + 4 * half + j < K ? r[g][j] : 0.f;
+  }
+};
+
+template <bool TA, bool TB, int EPI, bool VEC>
+__global__ void __launch_bounds__(kGemmThreads, VEC ? 4 : 2)
+gemm_split_kernel(GemmArgs g) {
+  constexpr int kSlice = 32, kStep = 4 * kSlice;
+  __shared__ float4 s_red[4 * 4 * 64];                   // [wave][four registers][lane]
+  __shared__ float s_sum[4 * 32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
+  const int w = blockIdx.x, n0 = blockIdx.y * 32, m0 = blockIdx.z * 32;
+  const float* A = g.A + (size_t)w * g.sA;
+  const float* B = g.B + (size_t)w * g.sB;
+  const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
+  float csum = 0.f;                                      // of the lane's column of A, this half's k
+  f32x16_t acc = {0};
+  struct Staged { DirectOperand<!TA, VEC> a; DirectOperand<TB, VEC> b; };
+  auto fetch = [&](Staged& st, int k0) {
+    st.a.fetch(A, m0, k0, g.M, g.K);
+    st.b.fetch(B, n0, k0, g.N, g.K);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto compute = [&](Staged& st, int k0) {
+    if (k0 + kSlice > g.K) {
+      st.a.clear(k0, g.K);
+      st.b.clear(k0, g.K);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(st.a.r[q][j], st.b.r[q][j], acc, 0, 0, 0);
+        if (TA && sums) csum += st.a.r[q][j];
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  Staged even, odd;
+  fetch(even, wave * kSlice);
+  for (int k0 = wave * kSlice; k0 < g.K; k0 += 2 * kStep) {
+    fetch(odd, k0 + kStep);                              // past the end: the last values again, not used
+    compute(even, k0);
+    fetch(even, k0 + 2 * kStep);
+    if (k0 + kStep < g.K) compute(odd, k0 + kStep);
+  }
+  // wave i adds up registers 4 i .. 4 i + 3 of the four
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s_red[(wave * 4 + i) * 64 + lane] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+  csum += __shfl_xor(csum, 32);
+  if (half == 0) s_sum[wave * 32 + col] = csum;
+  __syncthreads();
+  float4 t = s_red[wave * 64 + lane];
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    const float4 v = s_red[(i * 4 + wave) * 64 + lane];
+    t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+  }
+  const f32x4_t part = {t.x, t.y, t.z, t.w};
+  store_tile<EPI, 4>(g, w, m0 + 8 * wave, n0 + col, half, part);
+  if (sums && threadIdx.x < 32 && m0 + col < g.M)
+    g.colsum[(size_t)w * g.sColsum + m0 + col] = (s_sum[col] + s_sum[32 + col]) + (s_sum[64 + col] + s_sum[96 + col]);
+}
+
+// 128 x 64 tiles where they give every compute unit the four workgroups it has room for, or else 64 x 64 (with slices twice as
+// long for the same LDS): a product is then one round of workgroups.  Below a workgroup per compute unit a tile's k is shared
+// out over four waves, and so it is where k is shorter than a slice or an operand too large for offsets of 32 bits.
+template <bool TA, bool TB, int EPI, bool VEC>
+void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
+  auto grid = [&](int bm, int bn) { return dim3((unsigned)Hw, (unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + bm - 1) / bm)); };
+  auto count = [&](int bm, int bn) { const dim3 d = grid(bm, bn); return (long long)d.x * d.y * d.z; };
+  const bool tiled = g.K >= 32 && (long long)g.M * g.K < (1ll << 29) && (long long)g.N * g.K < (1ll << 29);
+  if (tiled && count(128, 64) >= 4LL * device_cus())
+    hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 2, 16>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
+  else if (tiled && count(64, 64) >= device_cus())
+    hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 1, 32>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
+  else
+    hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC>), grid(32, 32), dim3(kGemmThreads), 0, hs, g);
 }
 
 template <bool TA, bool TB, int EPI>
 void gemm(const GemmArgs& g, int Hw, hipStream_t hs) {
   // 16-byte loads need rows of both operands that start on 16 bytes
   auto rows_aligned = [](const float* p, int ld, long long stride) { return aligned16(p) && ld % 4 == 0 && stride % 4 == 0; };
-  const bool vec = rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB);
-  // (128x128 tiles measured no faster: their fewer workgroups leave the start and the stores of a product uncovered)
-  const dim3 grid((unsigned)((g.N + kTile - 1) / kTile), (unsigned)((g.M + kTile - 1) / kTile), (unsigned)Hw);
-  if (vec) hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, true>), grid, dim3(kGemmThreads), 0, hs, g);
-  else hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, false>), grid, dim3(kGemmThreads), 0, hs, g);
+  if (rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB)) gemm_sized<TA, TB, EPI, true>(g, Hw, hs);
+  else gemm_sized<TA, TB, EPI, false>(g, Hw, hs);
 }
 
 __global__ void widen_kernel(const bf16_t* __restrict__ x, float* __restrict__ y, size_t n) {

@@ -1,0 +1,32 @@
+"""Loss and gradients of the query model where its matrix products take their large tiles: rows that start on 16 bytes and rows
+that do not, reductions that end inside a slice, operands on either side."""
+import pytest
+import torch
+
+from test_gpu_train import DEV, problem, to_dev
+from test_gpu_train import saap  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hw,R,d,hidden,B", [
+    (16, 900, 40, 132, 520), (16, 900, 40, 131, 521), (16, 60, 64, 452, 1030), (16, 60, 64, 450, 1032), (8, 1000, 128, 512, 1024),
+])
+def test_large_products(saap, Hw, R, d, hidden, B):  # noqa: F811
+    x, T, params = problem(5, Hw, R, d, hidden, B, torch.float32)
+    x, T, params = x.to(DEV), T.to(DEV), to_dev(params)
+    loss, grads = saap.query_model_loss_grads(x, T, params)
+    again = saap.query_model_loss_grads(x, T, params)[1]
+    ps = [p.double().requires_grad_() for p in params]
+    want = []
+    for w in range(Hw):
+        z = torch.relu(x[w].double() @ ps[0][w].T + ps[1][w]) @ ps[2][w].T + ps[3][w]
+        t = T[w].double()
+        want.append(torch.where(t > 0, t * (t.clamp_min(1e-300).log() - torch.log_softmax(z, -1)), 0 * z).sum(-1).mean())
+    want = torch.stack(want)
+    want.sum().backward()
+    torch.testing.assert_close(loss.double(), want.detach(), rtol=1e-5, atol=0.0)
+    for name, got, p, rep in zip(("dW1", "db1", "dW2", "db2"), grads, ps, again):
+        err = (got.double() - p.grad).norm(dim=tuple(range(1, got.dim()))) / p.grad.norm(dim=tuple(range(1, got.dim())))
+        assert err.max() < 3e-6, (name, err)
+        assert torch.equal(got, rep), name
