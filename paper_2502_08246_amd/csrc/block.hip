@@ -510,13 +510,13 @@ block_merge_kernel(BlockParams p) {
     float M = kNegBig;
     for (int i = lane; i < p.slots; i += 64) {
       const float2 v = ml[(size_t)i * G + g];
-      if (v.y > 0.f) M = fmaxf(M, v.x);
+      if (v.y != 0.f) M = fmaxf(M, v.x);
     }
     M = wave_max(M);
     float L = 0.f;
     for (int i = lane; i < p.slots; i += 64) {
       const float2 v = ml[(size_t)i * G + g];
-      const float wt = v.y > 0.f ? fast_exp2(v.x - M) : 0.f;
+      const float wt = v.y != 0.f ? fast_exp2(v.x - M) : 0.f;   // a sum that is no number is passed on
       s_w[i * G + g] = wt;
       L = fmaf(wt, v.y, L);
     }
@@ -557,7 +557,7 @@ block_merge_kernel(BlockParams p) {
     const float4 v = s_acc[i * kCols + tid];
     acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
-  const float L = s_L[g], inv = L > 0.f ? 1.0f / L : 0.f;
+  const float L = s_L[g], inv = L > 0.f ? 1.0f / L : 0.f * L;            // no keys: zeros; a score that is no number: no numbers
   const size_t qrow = (size_t)unit * G + g;              // units are (sequence, token, KV head)
   const int e0 = colx % (kD / 4) * 4;
   if (p.out_bf16) {

@@ -35,3 +35,32 @@ def test_prefill_tiles(saap, S, Hq, Hkv, Nt, B, Tq, nprobe, n_sink, n_recent, po
     assert_close(out.cpu().numpy(), ro, "bf16", "out")
     assert_close(lse.cpu().numpy(), rl, "bf16", "lse")
     assert torch.equal(out, again)                               # whatever order the work is taken in
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_scores_that_are_no_numbers(saap, bad):  # noqa: F811
+    """A key or a query that is not finite: the block gives what its tokens give four at a time (too few for shared tiles)."""
+    S, Hq, Hkv, Nt, B, Tq, nprobe, p0 = 1, 8, 2, 1500, 24, 40, 6, 1400
+    cache, ids, _, q = setup(saap, "bf16", S, Hq, Hkv, Nt, B, Tq, 11)
+    K = cache["K"].clone()
+    K[0, 0, 700], K[0, 1, p0 + 20] = bad, bad                    # a bucket's member; a key the block's second half sees
+    off, ln, idx, Ks, Vs = saap.build_bucket_index(ids, K, cache["V"], B, 0)
+    q = q.clone()
+    q[0, 9, 5] = bad
+    rng = np.random.default_rng(3)
+    sel = np.stack([rng.permutation(B)[:nprobe] for _ in range(Hkv * Tq)]).reshape(S, Hkv, Tq, nprobe).astype(np.int32)
+    sel = torch.from_numpy(sel).to(DEV)
+
+    def attend(t0, t1):
+        return saap.prefill_sparse_attention(q[:, t0:t1].contiguous(), K, cache["V"], Ks, Vs, off, ln, idx,
+                                             sel[:, :, t0:t1].contiguous(), torch.tensor([p0 + t0], dtype=torch.int32, device=DEV),
+                                             1, 64, SCALE)
+    out, lse = attend(0, Tq)
+    parts = [attend(t, t + 4) for t in range(0, Tq, 4)]
+    want, want_lse = torch.cat([p[0] for p in parts], 1), torch.cat([p[1] for p in parts], 1)
+    none = torch.isinf(want_lse)
+    assert 0 < none.sum() < none.numel()
+    assert torch.equal(torch.isinf(lse), none)
+    assert torch.isnan(out[none]).all()
+    assert_close(out[~none].cpu().numpy(), want[~none].cpu().numpy(), "bf16", "out")
+    assert_close(lse[~none].cpu().numpy(), want_lse[~none].cpu().numpy(), "bf16", "lse")
