@@ -21,6 +21,8 @@
 // loads waited for and the sums in launches of their own; 315 us with 64x64 tiles and address arithmetic in every slice; 281 us
 // now (107 of the 154 TFLOP/s).  What is left is the start and the stores of a product, 13 us each of 88, which nothing covers:
 // all tiles of a product run at once.
+#include <algorithm>
+
 #include "common.h"
 
 namespace saap {
@@ -40,6 +42,7 @@ struct GemmArgs {
   long long sA, sB, sC, sBias, sAux;   // strides between the weight sets (blockIdx.x), in elements
   float* colsum;       // [M] per weight set or null: sums of A' over k (TA only), strides sColsum
   long long sColsum;
+  int m_first, n_first;                // gemm_split_kernel: where the launch's first tile starts
 };
 
 // One thread's share of a slice of an operand, R rows by SL values of k, four elements a piece, on its way to LDS.  KC: the
@@ -270,10 +273,10 @@ gemm_split_kernel(GemmArgs g) {
   __shared__ float4 s_red[4 * 4 * 64];                   // [wave][four registers][lane]
   __shared__ float s_sum[4 * 32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
-  const int w = blockIdx.x, n0 = blockIdx.y * 32, m0 = blockIdx.z * 32;
+  const int w = blockIdx.x, n0 = g.n_first + (int)blockIdx.y * 32, m0 = g.m_first + (int)blockIdx.z * 32;
   const float* A = g.A + (size_t)w * g.sA;
   const float* B = g.B + (size_t)w * g.sB;
-  const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
+  const bool sums = TA && g.colsum != nullptr && n0 == 0;
   float csum = 0.f;                                      // of the lane's column of A, this half's k
   f32x16_t acc = {0};
   struct Staged { DirectOperand<!TA, VEC> a; DirectOperand<TB, VEC> b; };
@@ -324,18 +327,28 @@ gemm_split_kernel(GemmArgs g) {
 
 // 128 x 64 tiles where they give every compute unit the four workgroups it has room for, or else 64 x 64 (with slices twice as
 // long for the same LDS): a product is then one round of workgroups.  Below a workgroup per compute unit a tile's k is shared
-// out over four waves, and so it is where k is shorter than a slice or an operand too large for offsets of 32 bits.
+// out over four waves, and so it is where k is shorter than a slice or an operand too large for offsets of 32 bits; that one
+// takes several launches where a grid dimension has no room for its smaller tiles.
+constexpr long long kMostTiles = 65535;
 template <bool TA, bool TB, int EPI, bool VEC>
 void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
   auto grid = [&](int bm, int bn) { return dim3((unsigned)Hw, (unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + bm - 1) / bm)); };
   auto count = [&](int bm, int bn) { const dim3 d = grid(bm, bn); return (long long)d.x * d.y * d.z; };
-  const bool tiled = g.K >= 32 && (long long)g.M * g.K < (1ll << 29) && (long long)g.N * g.K < (1ll << 29);
+  const bool tiled = g.K >= 32 && (long long)g.M * g.K < (1ll << 29) && (long long)g.N * g.K < (1ll << 29) && g.N <= kMostTiles * 64;
   if (tiled && count(128, 64) >= 4LL * device_cus())
     hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 2, 16>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
   else if (tiled && count(64, 64) >= device_cus())
     hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 1, 32>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
   else
-    hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC>), grid(32, 32), dim3(kGemmThreads), 0, hs, g);
+    for (long long m = 0; m < g.M; m += kMostTiles * 32)
+      for (long long n = 0; n < g.N; n += kMostTiles * 32) {
+        GemmArgs part = g;
+        part.m_first = (int)m;
+        part.n_first = (int)n;
+        auto tiles = [](long long left) { return (unsigned)std::min((left + 31) / 32, kMostTiles); };
+        hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC>), dim3((unsigned)Hw, tiles(g.N - n), tiles(g.M - m)), dim3(kGemmThreads), 0,
+                           hs, part);
+      }
 }
 
 template <bool TA, bool TB, int EPI>
@@ -601,23 +614,23 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
   const dim3 per_elem((unsigned)(((size_t)R * hidden + 255) / 256), (unsigned)Hw);
   if (!bn) {
     // h = relu(x W1^T + b1)
-    gemm<false, true, EPI_BIAS_RELU>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0}, Hw, hs);
+    gemm<false, true, EPI_BIAS_RELU>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
   } else {
     // a = x W1^T + b1;  h = relu(gamma * normalised(a) + beta)
-    gemm<false, true, EPI_BIAS>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0}, Hw, hs);
+    gemm<false, true, EPI_BIAS>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
     hipLaunchKernelGGL(bn_stats_kernel, per_col, dim3(kBnThreads), 0, hs, pre, stats, bn->running_mean, bn->running_var, R, hidden,
                        bn->eps, bn->momentum);
     hipLaunchKernelGGL(bn_relu_kernel, per_elem, dim3(256), 0, hs, pre, stats, bn->gamma, bn->beta, h, R, hidden);
   }
   // z = h W2^T + b2
-  gemm<false, true, EPI_BIAS>({h, params->W2, z, params->b2, nullptr, R, B, hidden, sh, sW2, sz, B, 0, nullptr, 0}, Hw, hs);
+  gemm<false, true, EPI_BIAS>({h, params->W2, z, params->b2, nullptr, R, B, hidden, sh, sW2, sz, B, 0, nullptr, 0, 0, 0}, Hw, hs);
   // row losses; z becomes dL/dz
   hipLaunchKernelGGL(softmax_kl_kernel, dim3((unsigned)R, (unsigned)Hw), dim3(256), 0, hs, z, target, loss_rows, R, B);
   hipLaunchKernelGGL(loss_mean_kernel, dim3((unsigned)Hw), dim3(256), 0, hs, loss_rows, loss, R);
   // dW2 = dz^T h, db2 = column sums of dz
-  gemm<true, false, EPI_NONE>({z, h, grads->W2, nullptr, nullptr, B, hidden, R, sz, sh, sW2, 0, 0, grads->b2, B}, Hw, hs);
+  gemm<true, false, EPI_NONE>({z, h, grads->W2, nullptr, nullptr, B, hidden, R, sz, sh, sW2, 0, 0, grads->b2, B, 0, 0}, Hw, hs);
   // da = (dz W2) where h > 0
-  gemm<false, false, EPI_MASK>({z, params->W2, da, nullptr, h, R, hidden, B, sz, sW2, sh, 0, sh, nullptr, 0}, Hw, hs);
+  gemm<false, false, EPI_MASK>({z, params->W2, da, nullptr, h, R, hidden, B, sz, sW2, sh, 0, sh, nullptr, 0, 0, 0}, Hw, hs);
   if (bn) {
     // through the normalisation: da holds dL/dy on entry and dL/da on exit
     hipLaunchKernelGGL(bn_backward_sums_kernel, per_col, dim3(kBnThreads), 0, hs, pre, da, stats, bn->grad_gamma, bn->grad_beta, R,
@@ -625,7 +638,7 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
     hipLaunchKernelGGL(bn_backward_kernel, per_elem, dim3(256), 0, hs, pre, da, stats, bn->gamma, R, hidden);
   }
   // dW1 = da^T x, db1 = column sums of da
-  gemm<true, false, EPI_NONE>({da, xin, grads->W1, nullptr, nullptr, hidden, d, R, sh, sx, sW1, 0, 0, grads->b1, hidden}, Hw, hs);
+  gemm<true, false, EPI_NONE>({da, xin, grads->W1, nullptr, nullptr, hidden, d, R, sh, sx, sW1, 0, 0, grads->b1, hidden, 0, 0}, Hw, hs);
   return launch_status();
 }
 

@@ -30,3 +30,22 @@ def test_large_products(saap, Hw, R, d, hidden, B):  # noqa: F811
         err = (got.double() - p.grad).norm(dim=tuple(range(1, got.dim()))) / p.grad.norm(dim=tuple(range(1, got.dim())))
         assert err.max() < 3e-6, (name, err)
         assert torch.equal(got, rep), name
+
+
+def test_more_rows_than_one_launch_of_small_tiles(saap):  # noqa: F811
+    """65535 tiles of 32 rows and 41 rows more, reductions too short for the large tiles.  Only the last 50 rows have a target,
+    so that the gradients are sums over those (fp32 sums of 50 terms: 50 * 2^-24 = 3e-6 relative; 1e-5 with the logits' own)."""
+    R, live, (d, hidden, B) = 65535 * 32 + 41, 50, (4, 8, 8)
+    x, T, params = problem(7, 1, live, d, hidden, B, torch.float32)
+    params = to_dev(params)
+    X, target = torch.zeros(1, R, d, device=DEV), torch.zeros(1, R, B, device=DEV)
+    X[:, -live:], target[:, -live:] = x.to(DEV), T.to(DEV)
+    loss, grads = saap.query_model_loss_grads(X, target, params)
+    ps = [p.double().requires_grad_() for p in params]
+    z = torch.relu(X[0, -live:].double() @ ps[0][0].T + ps[1][0]) @ ps[2][0].T + ps[3][0]
+    t = target[0, -live:].double()
+    want = torch.where(t > 0, t * (t.clamp_min(1e-300).log() - torch.log_softmax(z, -1)), 0 * z).sum() / R
+    want.backward()
+    torch.testing.assert_close(loss[0].double(), want.detach(), rtol=1e-5, atol=0.0)
+    for name, got, p in zip(("dW1", "db1", "dW2", "db2"), grads, ps):
+        assert (got.double() - p.grad).norm() <= 1e-5 * p.grad.norm(), name
