@@ -384,29 +384,54 @@ __device__ __forceinline__ float block_max(float v, float* s_red) {
 
 // One workgroup per row: logits z -> the row's loss and, in place, the gradient with respect to
 // the logits: ((sum_b T) * softmax(z) - T) / R.
+// PER > 0: rows of at most 256 PER buckets, read once, all loads in flight together (8 x 1000 rows of 1024: 29 us with three
+// passes over a row, and 8 us less in a training iteration now; its 98 MB take 21 at the rate of a copy).  PER = 0: rows of any
+// length, three passes.
+template <int PER>
 __global__ void __launch_bounds__(256)
 softmax_kl_kernel(float* __restrict__ z, const float* __restrict__ T, float* __restrict__ loss_rows, int R, int B) {
   __shared__ float s_red[4];
   const size_t row = (size_t)blockIdx.y * R + blockIdx.x;
   float* zr = z + row * B;
   const float* tr = T + row * B;
-  float mx = -INFINITY, tsum = 0.f;
-  for (int b = threadIdx.x; b < B; b += 256) {
-    mx = fmaxf(mx, zr[b]);
-    tsum += tr[b];
+  float zv[PER > 0 ? PER : 1], tv[PER > 0 ? PER : 1];
+  if constexpr (PER > 0) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int b = min((int)threadIdx.x + 256 * i, B - 1);
+      zv[i] = zr[b];
+      tv[i] = tr[b];
+    }
   }
+  // f(b, z, t) for the thread's buckets, in ascending order
+  auto each = [&](auto f) {
+    if constexpr (PER > 0) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int b = threadIdx.x + 256 * i;
+        if (b < B) f(b, zv[i], tv[i]);
+      }
+    } else {
+      for (int b = threadIdx.x; b < B; b += 256) f(b, zr[b], tr[b]);
+    }
+  };
+  float mx = -INFINITY, tsum = 0.f;
+  each([&](int, float zb, float t) {
+    mx = fmaxf(mx, zb);
+    tsum += t;
+  });
   mx = block_max(mx, s_red);
   tsum = block_sum(tsum, s_red);
   float se = 0.f;
-  for (int b = threadIdx.x; b < B; b += 256) se += __expf(zr[b] - mx);
+  each([&](int, float zb, float) { se += __expf(zb - mx); });
   se = block_sum(se, s_red);
   const float lse = mx + __logf(se), inv_r = 1.0f / (float)R;
   float l = 0.f;
-  for (int b = threadIdx.x; b < B; b += 256) {
-    const float t = tr[b], logp = zr[b] - lse;
+  each([&](int b, float zb, float t) {
+    const float logp = zb - lse;
     if (t > 0.f) l += t * (__logf(t) - logp);
     zr[b] = (tsum * __expf(logp) - t) * inv_r;
-  }
+  });
   l = block_sum(l, s_red);
   if (threadIdx.x == 0) loss_rows[row] = l;
 }
@@ -625,7 +650,8 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
   // z = h W2^T + b2
   gemm<false, true, EPI_BIAS>({h, params->W2, z, params->b2, nullptr, R, B, hidden, sh, sW2, sz, B, 0, nullptr, 0, 0, 0}, Hw, hs);
   // row losses; z becomes dL/dz
-  hipLaunchKernelGGL(softmax_kl_kernel, dim3((unsigned)R, (unsigned)Hw), dim3(256), 0, hs, z, target, loss_rows, R, B);
+  auto softmax_kl = B <= 1024 ? softmax_kl_kernel<4> : B <= 2048 ? softmax_kl_kernel<8> : softmax_kl_kernel<0>;
+  hipLaunchKernelGGL(softmax_kl, dim3((unsigned)R, (unsigned)Hw), dim3(256), 0, hs, z, target, loss_rows, R, B);
   hipLaunchKernelGGL(loss_mean_kernel, dim3((unsigned)Hw), dim3(256), 0, hs, loss_rows, loss, R);
   // dW2 = dz^T h, db2 = column sums of dz
   gemm<true, false, EPI_NONE>({z, h, grads->W2, nullptr, nullptr, B, hidden, R, sz, sh, sW2, 0, 0, grads->b2, B, 0, 0}, Hw, hs);

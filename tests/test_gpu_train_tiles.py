@@ -49,3 +49,24 @@ def test_more_rows_than_one_launch_of_small_tiles(saap):  # noqa: F811
     torch.testing.assert_close(loss[0].double(), want.detach(), rtol=1e-5, atol=0.0)
     for name, got, p in zip(("dW1", "db1", "dW2", "db2"), grads, ps):
         assert (got.double() - p.grad).norm() <= 1e-5 * p.grad.norm(), name
+
+
+@pytest.mark.parametrize("B", [1, 255, 257, 1023, 1025, 2047, 2048, 2049])
+def test_rows_held_and_rows_read_again(saap, B):  # noqa: F811
+    """Row lengths around what a workgroup holds; fp32 sums of up to 2049 terms in trees of at most 16 + 8 additions, hardware
+    exponentials and logarithms of 2^-21 or so on arguments around 10: 1e-5."""
+    R, d, hidden = 37, 24, 16
+    x, T, params = problem(B, 2, R, d, hidden, B, torch.float32)
+    T = T.nan_to_num(0.0) if B > 1 else torch.ones_like(T) * (torch.arange(R)[None, :, None] % 2)
+    x, T, params = x.to(DEV), T.to(DEV), to_dev(params)
+    loss, grads = saap.query_model_loss_grads(x, T, params)
+    ps = [p.double().requires_grad_() for p in params]
+    want = []
+    for w in range(2):
+        z = torch.relu(x[w].double() @ ps[0][w].T + ps[1][w]) @ ps[2][w].T + ps[3][w]
+        t = T[w].double()
+        want.append(torch.where(t > 0, t * (t.clamp_min(1e-300).log() - torch.log_softmax(z, -1)), 0 * z).sum(-1).mean())
+    torch.stack(want).sum().backward()
+    torch.testing.assert_close(loss.double(), torch.stack(want).detach(), rtol=1e-5, atol=1e-6)
+    for name, got, p in zip(("dW1", "db1", "dW2", "db2"), grads, ps):
+        assert (got.double() - p.grad).norm() <= 1e-5 * p.grad.norm() + 1e-6, name
