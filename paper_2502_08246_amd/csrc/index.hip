@@ -164,7 +164,8 @@ __device__ __forceinline__ void place_round(int b, int n, int id_bits, const int
 // that each knows what the others before it place: eight rounds one after the other, where one wave per slice had 32
 // (8 units of 65536 positions: 22 -> 9.6 us).  The unit is the fastest grid dimension: with a multiple of 8 units all slices
 // of one share an L2, where the 4-byte stores of many slices to a line of idx meet (64 units of 131072 positions: 105 -> 58 us;
-// 8 of 65536: 9.6 -> 7.9).  The workgroup also marks the free slots of every n_slices-th bucket.
+// 8 of 65536: 9.6 -> 7.9).  The workgroup also marks the free slots of every n_slices-th bucket and its share of those
+// behind the last run: every entry of idx is written, and the row copy reads them all.
 constexpr int kScatterThreads = 256, kScatterWaves = kScatterThreads / 64;
 __global__ void __launch_bounds__(kScatterThreads)
 scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slice_base,
@@ -212,6 +213,8 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
     const int end = o[b + 1];
     for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
   }
+  // keys with ids outside [0,B) are dropped: as many slots stay empty behind the last run
+  for (int j = o[ostride - 1] + slice * kScatterThreads + tid; j < Ncap; j += n_slices * kScatterThreads) ix[j] = -1;
 }
 
 // Steps 1 to 4 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
@@ -303,12 +306,13 @@ order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, i
     const int end = b + 1 < B ? s_next[b + 1] : all;
     for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
   }
+  for (int j = all + max(W, 0) + tid; j < Ncap; j += kSmallThreads) ix[j] = -1;       // behind the last run: dropped keys
   if (W > 0)
     for (int j = tid; j < W; j += kSmallThreads) place_resident(j, idu, ix, res_ids + (size_t)unit * W, all, N, n_sink, n_recent, n_res);
 }
 
-// Copy rows into their slots: out[slot] = in[idx[slot]] for member slots.  ZERO: free slots are set to zero (here they
-// cost their own bytes once; a fill of the whole cache ahead of the copy writes every member slot twice).
+// Copy rows into their slots: out[slot] = in[idx[slot]] for member slots (0 <= idx[slot] < N).  ZERO: free slots are set
+// to zero (here they cost their own bytes once; a fill of the whole cache ahead of the copy writes every member slot twice).
 template <int CHUNKS /* 16-byte pieces per row */, bool ZERO>
 __global__ void __launch_bounds__(256)
 permute_kernel(const uint4* __restrict__ K, const uint4* __restrict__ V, const int32_t* __restrict__ idx,
@@ -328,14 +332,14 @@ permute_kernel(const uint4* __restrict__ K, const uint4* __restrict__ V, const i
 #pragma unroll
   for (int r = 0; r < kRowsPerThread; ++r) {
     kv[r] = vv[r] = make_uint4(0u, 0u, 0u, 0u);
-    if (src[r] >= 0) {
+    if ((unsigned)src[r] < (unsigned)N) {
       kv[r] = stream_load16(Ku + (size_t)src[r] * CHUNKS);
       vv[r] = stream_load16(Vu + (size_t)src[r] * CHUNKS);
     }
   }
 #pragma unroll
   for (int r = 0; r < kRowsPerThread; ++r) {
-    if (src[r] >= 0 || (ZERO && first + r < Ncap)) {
+    if ((unsigned)src[r] < (unsigned)N || (ZERO && first + r < Ncap)) {
       stream_store16(Ko + (size_t)(first + r) * CHUNKS, kv[r]);
       stream_store16(Vo + (size_t)(first + r) * CHUNKS, vv[r]);
     }
