@@ -145,18 +145,21 @@ def native():
     return _native
 
 
-def workspace(nbytes: int, device) -> torch.Tensor:
-    """The shared workspace buffer of the device, at least nbytes long.
+def workspace(nbytes: int, device, asked_for: bool = True) -> torch.Tensor:
+    """The shared workspace buffer of the device's current stream, at least nbytes long.
 
-    It is zero-filled when it is made, which is what the header of arrival counters needs, and replaced by a larger one
-    on demand.  A HIP graph that captured a call holds the RAW ADDRESS of the buffer it was given, so a buffer that has
-    been handed out is never freed: a graph captured earlier still replays into memory that belongs to the workspace.
+    Every stream has its own, zero-filled when it is made (which is what the header of arrival counters needs) and
+    replaced by a larger one on demand: calls on different streams may run at the same time and never meet in one.  Pass
+    it to calls on the stream it was asked for on.  One that a program has asked for is never freed.  A HIP graph holds the RAW ADDRESS of the buffer that its calls were
+    given: a capture takes over the buffer that the eager calls before it have made, all graphs of a device share that
+    one (replay them one after the other, or capture with ws=), no eager call uses it again and it is never freed.
     Growing while the current stream is capturing is refused (allocating there would also break the capture): run the
     call once eagerly first, or pass ws= explicitly."""
     device = torch.device(device)
     if device.type != "cuda":
         raise ValueError("SAAP workspaces live in GPU memory; there is no CPU path")
-    return native().workspace(int(nbytes), torch.cuda.current_device() if device.index is None else device.index)
+    return native().workspace(int(nbytes), torch.cuda.current_device() if device.index is None else device.index,
+                              asked_for)
 
 
 def _ws(op, device, ws, **shape):
@@ -164,7 +167,7 @@ def _ws(op, device, ws, **shape):
     if need == 0:
         raise SaapError("saap_workspace_bytes", -1)
     if ws is None:
-        ws = workspace(need, device)
+        ws = workspace(need, device, asked_for=False)
     return ws, ctypes.c_size_t(ws.numel())
 
 

@@ -5,7 +5,7 @@
 // took 44 us for 28 us of kernels.  Here a call costs a couple of microseconds on top of its kernel launches.
 //
 // Marshalling only: shapes are read off the tensors, outputs are allocated unless the caller passes them, the
-// workspace is the shared one of the device unless the caller passes one, pointers and the current stream go to the
+// workspace is the shared one of the current stream unless the caller passes one, pointers and the current stream go to the
 // C call, a status other than SAAP_OK is raised as SaapError.  The interpreter lock is released around the C call.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -21,6 +21,7 @@
 
 #include <initializer_list>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "saap.h"
@@ -197,53 +198,114 @@ PyObject* tuple_of(std::initializer_list<const Out*> outs) {
 }
 
 // ---- workspaces --------------------------------------------------------------------------------------
-// One shared buffer per device, zero-filled when it is made (the arrival counters in its header start at zero) and
-// replaced by a larger one on demand.  A HIP graph that captured a call holds the raw address it was given, so a
-// buffer that has been handed out is never freed; growing while the stream captures is refused.  Guarded by the
-// interpreter lock.
+// The shared buffers: one per device and stream, so that calls on two streams, which may run at the same time, never meet
+// in one.  A buffer is made, zero-filled (the arrival counters in its header start at zero) and used in the order of its
+// stream; one that has become too small is dropped, and the allocator hands its memory out again in that order (unless
+// the program has asked for the buffer itself and may have its address: that one is never freed).
+//
+// A HIP graph holds the raw address of the buffer that its calls were given, and is replayed on any stream: the first
+// captured call takes the buffer of the calls before it away from their stream (which makes a new one when it needs it),
+// later captures use it too, and it is never freed.  Making or growing a buffer while the stream captures is refused.
+// Guarded by the interpreter lock.
+struct StreamBuffer {
+  c10::DeviceIndex device;
+  hipStream_t stream;
+  Tensor buf;
+  std::thread::id thread = {};                // that used it last
+  uint64_t used = 0;                          // and when, counted in calls
+  bool asked_for = false;                     // by the program
+};
+constexpr size_t kMaxStreamBuffers = 64;      // streams may come and go: the one made first is dropped
 struct Workspaces {
-  std::vector<Tensor> current, retired;
+  std::vector<StreamBuffer> streams;
+  std::vector<StreamBuffer> captured;         // one per device (no stream of its own)
+  std::vector<Tensor> retired;                // replaced ones that a graph or the program may hold
+  uint64_t calls = 0;
 };
 Workspaces& workspaces() {
   static Workspaces* w = new Workspaces;      // not destroyed: the device may be gone by then
   return *w;
 }
-bool capturing() {
-  PyObject* mod = PyImport_ImportModule("torch.cuda");
-  PyObject* r = mod ? PyObject_CallMethod(mod, "is_current_stream_capturing", nullptr) : nullptr;
-  Py_XDECREF(mod);
-  if (!r) throw python_error();
-  const bool yes = PyObject_IsTrue(r) == 1;
-  Py_DECREF(r);
-  return yes;
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return status != hipStreamCaptureStatusNone;
 }
-const Tensor& shared_workspace(size_t bytes, at::Device device) {
-  Workspaces& w = workspaces();
-  const size_t at_dev = device.index() < 0 ? 0 : (size_t)device.index();
-  if (w.current.size() <= at_dev) w.current.resize(at_dev + 1);
-  Tensor& buf = w.current[at_dev];
-  if (!buf.defined() || (size_t)buf.numel() < bytes) {
-    if (capturing()) {
-      PyErr_SetString(PyExc_RuntimeError,
-                      "the shared SAAP workspace would have to grow during stream capture: call the operation once "
-                      "eagerly before capturing, or pass ws=");
-      throw python_error();
-    }
-    if (buf.defined()) w.retired.push_back(buf);
-    buf = at::zeros({(int64_t)std::max<size_t>(bytes, SAAP_WS_HEADER_BYTES)},
-                    at::TensorOptions().dtype(at::kByte).device(device));
+bool holds(const Tensor& buf, size_t bytes) { return buf.defined() && (size_t)buf.numel() >= bytes; }
+
+Tensor captured_workspace(Workspaces& w, size_t bytes, c10::DeviceIndex device) {
+  StreamBuffer* slot = nullptr;
+  for (auto& c : w.captured)
+    if (c.device == device) slot = &c;
+  if (slot && holds(slot->buf, bytes)) return slot->buf;
+  // the one that this thread's calls used last (the warm-up's, on whichever stream), or else another thread's
+  const StreamBuffer* from = nullptr;
+  const auto me = std::this_thread::get_id();
+  for (const auto& b : w.streams)
+    if (b.device == device && holds(b.buf, bytes) &&
+        (!from || (b.thread == me) > (from->thread == me) || ((b.thread == me) == (from->thread == me) && b.used > from->used)))
+      from = &b;
+  if (!from) {
+    PyErr_SetString(PyExc_RuntimeError,
+                    "the shared SAAP workspace would have to grow during stream capture: call the operation once "
+                    "eagerly before capturing, or pass ws=");
+    throw python_error();
+  }
+  const Tensor buf = from->buf;
+  w.streams.erase(w.streams.begin() + (from - w.streams.data()));
+  if (slot) {
+    w.retired.push_back(slot->buf);
+    slot->buf = buf;
+  } else {
+    w.captured.push_back({device, nullptr, buf});
   }
   return buf;
 }
+Tensor shared_workspace(size_t bytes, at::Device device, bool asked_for = false) {
+  Workspaces& w = workspaces();
+  auto drop = [&](StreamBuffer& b) {
+    if (b.asked_for) w.retired.push_back(b.buf);
+    b.asked_for = false;
+  };
+  const c10::DeviceIndex dev = device.index() < 0 ? 0 : device.index();
+  const hipStream_t stream = c10::hip::getCurrentHIPStream(dev).stream();
+  if (capturing(stream)) return captured_workspace(w, bytes, dev);
+  size_t at = 0;
+  while (at < w.streams.size() && (w.streams[at].device != dev || w.streams[at].stream != stream)) ++at;
+  if (at == w.streams.size() || !holds(w.streams[at].buf, bytes)) {
+    const Tensor buf = at::zeros({(int64_t)std::max<size_t>(bytes, SAAP_WS_HEADER_BYTES)},
+                                 at::TensorOptions().dtype(at::kByte).device(at::kCUDA, dev));
+    if (at == w.streams.size()) {
+      if (w.streams.size() >= kMaxStreamBuffers) {
+        drop(w.streams.front());
+        w.streams.erase(w.streams.begin());
+      }
+      w.streams.push_back({dev, stream, buf});
+      at = w.streams.size() - 1;
+    } else {
+      drop(w.streams[at]);
+      w.streams[at].buf = buf;
+    }
+  }
+  StreamBuffer& b = w.streams[at];
+  b.asked_for |= asked_for;
+  b.thread = std::this_thread::get_id();
+  b.used = ++w.calls;
+  return b.buf;
+}
 struct Ws {
+  Tensor keep;          // another thread may replace the shared buffer while this call is being enqueued
   void* p;
   size_t bytes;
   Ws(const Args& a, int i, const Tensor& like, size_t need) {
     if (need == 0) raise_saap("saap_workspace_bytes", SAAP_INVALID_ARG);
     if (!a.has(i) && !like.is_cuda()) raise_value("SAAP tensors must live in GPU memory; there is no CPU path");
-    const Tensor& t = a.has(i) ? a.tensor(i) : shared_workspace(need, like.device());
-    p = ptr(t);
-    bytes = (size_t)t.numel();
+    keep = a.has(i) ? a.tensor(i) : shared_workspace(need, like.device());
+    p = ptr(keep);
+    bytes = (size_t)keep.numel();
   }
   Ws(const Args& a, int i, const Tensor& like, int32_t op, const saap_shape& sh)
       : Ws(a, i, like, saap_workspace_bytes(op, &sh)) {}
@@ -910,10 +972,11 @@ SAAP_FUNCTION(adam_update) {
 
 // ---- module ------------------------------------------------------------------------------------------
 SAAP_FUNCTION(workspace) {
-  SAAP_BEGIN(2, "nbytes", "device_index")
+  SAAP_BEGIN(2, "nbytes", "device_index", "asked_for")
   const int64_t n = a.has(0) ? (int64_t)PyLong_AsLongLong(a.v[0]) : 0;
   if (n == -1 && PyErr_Occurred()) throw python_error();
-  return THPVariable_Wrap(shared_workspace((size_t)std::max<int64_t>(n, 0), at::Device(at::kCUDA, (int8_t)a.integer(1))));
+  return THPVariable_Wrap(
+      shared_workspace((size_t)std::max<int64_t>(n, 0), at::Device(at::kCUDA, (int8_t)a.integer(1)), a.truth(2, true)));
   SAAP_END
 }
 
@@ -1023,8 +1086,9 @@ PyMethodDef methods[] = {
                 "adam_update(param, grad, m, v, step, lr, beta1=0.9, beta2=0.999, eps=1e-8)\n--\n\n"
                 "One Adam step on one fp32 tensor, in place (param, m, v)."),
     SAAP_METHOD(workspace,
-                "workspace(nbytes, device_index)\n--\n\n"
-                "The shared workspace buffer of the device, at least nbytes long."),
+                "workspace(nbytes, device_index, asked_for=True)\n--\n\n"
+                "The shared workspace buffer of the device's current stream, at least nbytes long; asked_for: by the\n"
+                "program, which may keep its address."),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "The library's calls on torch tensors.", -1, methods,

@@ -60,3 +60,63 @@ def test_names_positions_and_outputs_passed_in():
     with pytest.raises(saap.SaapError) as e:
         saap.sparse_decode_attention(q, Ks, Vs, off, ln, sel, scale, ws=torch.zeros(64, dtype=torch.uint8, device=DEV))
     assert e.value.status == -3
+
+
+@pytest.mark.gpu
+def test_every_stream_has_its_own_workspace_and_graphs_have_theirs():
+    """The default workspace: one per stream, a zeroed header each, kept while it is large enough; a capture takes the
+    one that the calls before it used, which no later eager call gets."""
+    here = saap.workspace(1 << 20, DEV)
+    assert saap.workspace(0, DEV).data_ptr() == here.data_ptr()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        there = saap.workspace(0, DEV)
+        assert there.data_ptr() == saap.workspace(0, DEV).data_ptr() != here.data_ptr()
+        assert not there[:saap.binding.WS_HEADER_BYTES].any()
+    g = torch.Generator(device=DEV).manual_seed(2)
+    logits = torch.randn(2, 8, 64, generator=g, device=DEV)
+    want = saap.select_buckets_from_logits(logits, 2, 5)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = saap.select_buckets_from_logits(logits, 2, 5)
+        inside = saap.workspace(0, DEV).data_ptr()
+        with pytest.raises(RuntimeError):
+            saap.workspace(1 << 40, DEV)                       # a capture cannot make one
+    assert inside == here.data_ptr()
+    after = saap.workspace(0, DEV).data_ptr()
+    assert after not in (inside, there.data_ptr())
+    with torch.cuda.stream(side):
+        assert saap.workspace(0, DEV).data_ptr() == there.data_ptr()
+    for _ in range(3):
+        got.zero_()
+        graph.replay()
+        assert torch.equal(got, want)
+        assert torch.equal(saap.select_buckets_from_logits(logits, 2, 5), want)
+
+
+@pytest.mark.gpu
+def test_two_streams_at_once_give_what_one_gives():
+    """Several launches and counters per call: two streams that enqueue them by turns, with the default workspace."""
+    S, Hq, Hkv, N, B, Tq, nprobe, scale = 1, 8, 8, 6000, 48, 64, 6, 1 / math.sqrt(128)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    rand = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    K, V = rand(S, Hkv, N, 128), rand(S, Hkv, N, 128)
+    ids = torch.randint(0, B, (S, Hkv, N), generator=g, device=DEV, dtype=torch.int32)
+    off, ln, idx, Ks, Vs = saap.build_bucket_index(ids, K, V, B)
+    pos0 = torch.tensor([N - Tq], dtype=torch.int32, device=DEV)
+    jobs = []
+    for _ in range(2):
+        sel = torch.rand(S, Hkv, Tq, B, generator=g, device=DEV).topk(nprobe, dim=-1).indices.to(torch.int32).contiguous()
+        jobs.append((rand(S, Tq, Hq, 128), K, V, Ks, Vs, off, ln, idx, sel, pos0, 1, 200, scale))
+    want = [saap.prefill_sparse_attention(*j) for j in jobs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in jobs]
+    got = [[], []]
+    for _ in range(20):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got[i].append(saap.prefill_sparse_attention(*jobs[i]))
+    torch.cuda.synchronize()
+    for w, results in zip(want, got):
+        for r in results:
+            assert torch.equal(r[0], w[0]) and torch.equal(r[1], w[1])
