@@ -34,7 +34,8 @@
  *     that uses the buffer (saap_workspace_reset does that) and every call
  *     leaves them zero again when its kernels have finished.  The rest is
  *     scratch without meaning between calls.  Two calls that run
- *     concurrently must not share a workspace.
+ *     concurrently must not share a workspace (the launches of a call are
+ *     enqueued together, so threads that share a stream may share one).
  */
 #ifndef SAAP_H
 #define SAAP_H

@@ -1958,7 +1958,7 @@ extern "C" size_t saap_visit_plan_bytes(int32_t S, int32_t Hq, int32_t Hkv, int3
 extern "C" int32_t saap_build_visit_plan(const int32_t* selected, const int32_t* off, const int32_t* len,
                                          int32_t nprobe, int32_t mode, int32_t resident_run, int32_t* plan,
                                          int32_t S, int32_t Hq, int32_t Hkv, int32_t runs, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!off || !len || !plan || !aligned16(plan) || (nprobe > 0 && !selected)) return SAAP_INVALID_ARG;
   if (S <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0 || runs <= 0) return SAAP_INVALID_ARG;
   if (mode != SAAP_GROUP_SUM && mode != SAAP_INDEPENDENT) return SAAP_INVALID_ARG;
@@ -2055,7 +2055,7 @@ extern "C" int32_t saap_planned_decode_attention(const void* q, const void* Ksor
                                                  void* out, int32_t out_dtype, float* lse, int32_t S, int32_t Hq,
                                                  int32_t Hkv, int32_t Ncap, int32_t d, int32_t dtype, void* ws,
                                                  size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
   return planned_attention(q, Ksorted, Vsorted, nullptr, nullptr, plan, nruns, mode, scale, out, out_dtype, lse, S, Hq,
                            Hkv, Ncap, d, dtype, ws, ws_bytes, stream);
@@ -2066,7 +2066,7 @@ extern "C" int32_t saap_planned_decode_attention_fp8(const void* q, const uint8_
                                                      int32_t nruns, int32_t mode, float scale, void* out,
                                                      int32_t out_dtype, float* lse, int32_t S, int32_t Hq, int32_t Hkv,
                                                      int32_t Ncap, int32_t d, void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!kscale || !vscale) return SAAP_INVALID_ARG;
   return planned_attention(q, K8, V8, kscale, vscale, plan, nruns, mode, scale, out, out_dtype, lse, S, Hq, Hkv, Ncap,
                            d, kDtypeFp8, ws, ws_bytes, stream);
@@ -2131,7 +2131,7 @@ extern "C" int32_t saap_sparse_decode_attention(const void* q, const void* Ksort
                                                 int32_t S, int32_t Hq, int32_t Hkv, int32_t Ncap, int32_t B,
                                                 int32_t d, int32_t dtype, void* ws, size_t ws_bytes,
                                                 void* stream) {
-  begin_call();
+  const Call call(stream);
   return sparse_attention(q, Ksorted, Vsorted, nullptr, nullptr, off, len, selected, nprobe, mode, -1, scale, out,
                           out_dtype, lse, S, Hq, Hkv, Ncap, B, d, dtype, ws, ws_bytes, stream);
 }
@@ -2143,7 +2143,7 @@ extern "C" int32_t saap_windowed_decode_attention(const void* q, const void* Kso
                                                   int32_t out_dtype, float* lse, int32_t S, int32_t Hq,
                                                   int32_t Hkv, int32_t Ncap, int32_t runs, int32_t d,
                                                   int32_t dtype, void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   return sparse_attention(q, Ksorted, Vsorted, nullptr, nullptr, off, len, selected, nprobe, mode, resident_run, scale,
                           out, out_dtype, lse, S, Hq, Hkv, Ncap, runs, d, dtype, ws, ws_bytes, stream);
 }
@@ -2187,7 +2187,7 @@ extern "C" int32_t saap_dense_decode_attention(const void* q, const void* K, con
                                                float scale, void* out, int32_t out_dtype, float* lse,
                                                int32_t S, int32_t Hq, int32_t Hkv, int32_t N, int32_t d,
                                                int32_t dtype, void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
   return dense_attention(q, K, V, nullptr, nullptr, off, len, B, scale, out, out_dtype, lse, S, Hq, Hkv, N, d, dtype,
                          ws, ws_bytes, stream);
@@ -2200,7 +2200,7 @@ extern "C" int32_t saap_sparse_decode_attention_fp8(const void* q, const uint8_t
                                                     float scale, void* out, int32_t out_dtype, float* lse,
                                                     int32_t S, int32_t Hq, int32_t Hkv, int32_t Ncap, int32_t B,
                                                     int32_t d, void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!kscale || !vscale) return SAAP_INVALID_ARG;
   return sparse_attention(q, K8, V8, kscale, vscale, off, len, selected, nprobe, mode, -1, scale, out, out_dtype, lse,
                           S, Hq, Hkv, Ncap, B, d, kDtypeFp8, ws, ws_bytes, stream);
@@ -2214,7 +2214,7 @@ extern "C" int32_t saap_windowed_decode_attention_fp8(const void* q, const uint8
                                                       int32_t out_dtype, float* lse, int32_t S, int32_t Hq,
                                                       int32_t Hkv, int32_t Ncap, int32_t runs, int32_t d, void* ws,
                                                       size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!kscale || !vscale) return SAAP_INVALID_ARG;
   return sparse_attention(q, K8, V8, kscale, vscale, off, len, selected, nprobe, mode, resident_run, scale, out,
                           out_dtype, lse, S, Hq, Hkv, Ncap, runs, d, kDtypeFp8, ws, ws_bytes, stream);
@@ -2226,7 +2226,7 @@ extern "C" int32_t saap_dense_decode_attention_fp8(const void* q, const uint8_t*
                                                    float scale, void* out, int32_t out_dtype, float* lse,
                                                    int32_t S, int32_t Hq, int32_t Hkv, int32_t N, int32_t d,
                                                    void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!kscale || !vscale) return SAAP_INVALID_ARG;
   return dense_attention(q, K8, V8, kscale, vscale, off, len, B, scale, out, out_dtype, lse, S, Hq, Hkv, N, d,
                          kDtypeFp8, ws, ws_bytes, stream);
@@ -2338,7 +2338,7 @@ extern "C" int32_t saap_select_attend(const float* logits, const void* q, const 
                                       int32_t* selected, void* out, int32_t out_dtype, float* lse, int32_t S,
                                       int32_t Hq, int32_t Hkv, int32_t Ncap, int32_t B, int32_t d, int32_t dtype,
                                       void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (dtype != SAAP_BF16 && dtype != SAAP_F32) return SAAP_UNSUPPORTED;
   return select_attend(logits, q, Ksorted, Vsorted, nullptr, nullptr, off, len, nprobe, -1, scale, selected, out, out_dtype,
                        lse, S, Hq, Hkv, Ncap, B, d, dtype, ws, ws_bytes, stream);
@@ -2350,7 +2350,7 @@ extern "C" int32_t saap_select_attend_windowed(const float* logits, const void* 
                                                void* out, int32_t out_dtype, float* lse, int32_t S, int32_t Hq,
                                                int32_t Hkv, int32_t Ncap, int32_t B, int32_t d, int32_t dtype, void* ws,
                                                size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (dtype != SAAP_BF16 && dtype != SAAP_F32) return SAAP_UNSUPPORTED;
   return select_attend(logits, q, Ksorted, Vsorted, nullptr, nullptr, off, len, nprobe, resident_run, scale, selected, out,
                        out_dtype, lse, S, Hq, Hkv, Ncap, B, d, dtype, ws, ws_bytes, stream);
@@ -2362,7 +2362,7 @@ extern "C" int32_t saap_select_attend_fp8(const float* logits, const void* q, co
                                           void* out, int32_t out_dtype, float* lse, int32_t S, int32_t Hq,
                                           int32_t Hkv, int32_t Ncap, int32_t B, int32_t d, void* ws, size_t ws_bytes,
                                           void* stream) {
-  begin_call();
+  const Call call(stream);
   return select_attend(logits, q, K8, V8, kscale, vscale, off, len, nprobe, -1, scale, selected, out, out_dtype, lse, S, Hq,
                        Hkv, Ncap, B, d, kDtypeFp8, ws, ws_bytes, stream);
 }
@@ -2397,7 +2397,7 @@ extern "C" int32_t saap_sparse_decode_attention_noalloc(const void* q, const voi
                                                         float scale, void* out, int32_t out_dtype, float* lse,
                                                         int32_t S, int32_t Hq, int32_t Hkv, int32_t Ncap, int32_t B,
                                                         int32_t d, int32_t dtype, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
   // every argument is checked before the device is touched (the scratch is the one pointer that is not the caller's)
   int32_t st = check_common(q, Ksorted, Vsorted, out, S, Hq, Hkv, d, dtype, out_dtype, /*ws=*/q);
@@ -2438,7 +2438,7 @@ extern "C" int32_t saap_prefill_sparse_attention(const void* q, const void* K, c
                                                  void* out, int32_t out_dtype, float* lse, int32_t S, int32_t Hq,
                                                  int32_t Hkv, int32_t Tq, int32_t Nt, int32_t Ncap, int32_t B,
                                                  int32_t d, int32_t dtype, void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (dtype != SAAP_F32 && dtype != SAAP_BF16) return SAAP_INVALID_ARG;
   int32_t st = check_common(q, Ksorted, Vsorted, out, S, Hq, Hkv, d, dtype, out_dtype, ws);
   if (st != SAAP_OK) return st;

@@ -8,6 +8,7 @@
 
 #include <atomic>
 
+#include "host_sync.h"
 #include "saap.h"
 
 namespace saap {
@@ -60,9 +61,13 @@ inline bool allow_lds(size_t lds) {
   return true;
 }
 
-// Every entry point starts with begin_call(): an error that an earlier, unrelated HIP call of the process left
-// behind is dropped, so that launch_status() reports this call's launches only.
-inline void begin_call() { (void)hipGetLastError(); }
+// Every entry point starts with `const Call call(stream)`: its launches are enqueued without another thread's between them
+// on that stream, and an error that an earlier, unrelated HIP call of the process left behind is dropped, so that
+// launch_status() reports this call's launches only.
+class Call : InOrder {
+ public:
+  explicit Call(const void* stream) : InOrder(stream) { (void)hipGetLastError(); }
+};
 inline int32_t launch_status() { return hipGetLastError() == hipSuccess ? SAAP_OK : SAAP_HIP_ERROR; }
 
 size_t build_workspace_bytes(long long units, int N, int B);

@@ -119,7 +119,7 @@ extern "C" int32_t saap_update_centroids(const void* x_sorted, const int32_t* of
                                          const void* centroids_old, void* centroids_new, int32_t S, int32_t Hkv,
                                          int32_t Ncap, int32_t B, int32_t d, int32_t dtype, int32_t normalize,
                                          void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!off || !len) return SAAP_INVALID_ARG;
   const int32_t st = check_update(x_sorted, centroids_old, centroids_new, S, Hkv, Ncap, B, d, dtype);
   if (st != SAAP_OK) return st;
@@ -135,7 +135,7 @@ extern "C" int32_t saap_update_centroids_from_ids(const void* x, const int32_t* 
                                                   void* centroids_new, int32_t S, int32_t Hkv, int32_t N, int32_t B,
                                                   int32_t d, int32_t dtype, int32_t normalize, void* ws, size_t ws_bytes,
                                                   void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!bucket_ids || !ws || !aligned16(ws)) return SAAP_INVALID_ARG;
   const int32_t st = check_update(x, centroids_old, centroids_new, S, Hkv, N, B, d, dtype);
   if (st != SAAP_OK) return st;

@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(256) mfma_rate_kernel(const uint4* __restrict_
 using namespace saap;
 
 extern "C" int32_t saap_stream_read_probe(const void* src, size_t bytes, void* sink, size_t sink_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!src || !sink || !aligned16(src) || !aligned16(sink) || bytes < 16) return SAAP_INVALID_ARG;
   // one workgroup of eight waves per compute unit: the shape that read fastest in a sweep of 128-512 threads
   // and 1-16 workgroups per compute unit (7.1 TB/s; 5.7-6.5 with more waves per compute unit)
@@ -103,7 +103,7 @@ extern "C" int32_t saap_stream_read_probe(const void* src, size_t bytes, void* s
 
 extern "C" int32_t saap_mfma_rate_probe(const void* operands, size_t bytes, int32_t iters, int32_t wgs_per_cu, void* sink,
                                         double* flop_out, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!operands || !sink || !aligned16(operands) || bytes < 64 || iters <= 0 || iters > (1 << 24) || wgs_per_cu <= 0 ||
       wgs_per_cu > 8)
     return SAAP_INVALID_ARG;
@@ -167,7 +167,7 @@ extern "C" size_t saap_workspace_bytes(int32_t op, const saap_shape* sh) {
 }
 
 extern "C" int32_t saap_workspace_reset(void* ws, size_t ws_bytes, void* stream) {
-  begin_call();
+  const Call call(stream);
   if (!ws || !aligned16(ws) || ws_bytes < SAAP_WS_HEADER_BYTES) return SAAP_INVALID_ARG;
   const size_t n = SAAP_WS_HEADER_BYTES / sizeof(uint32_t);
   hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
@@ -188,7 +188,7 @@ extern "C" const char* saap_status_string(int32_t status) {
 }
 
 extern "C" int32_t saap_device_compute_units(void) {
-  begin_call();
+  (void)hipGetLastError();
   int dev = 0;
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return -1;

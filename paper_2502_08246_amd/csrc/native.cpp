@@ -206,7 +206,7 @@ PyObject* tuple_of(std::initializer_list<const Out*> outs) {
 // A HIP graph holds the raw address of the buffer that its calls were given, and is replayed on any stream: the first
 // captured call takes the buffer of the calls before it away from their stream (which makes a new one when it needs it),
 // later captures use it too, and it is never freed.  Making or growing a buffer while the stream captures is refused.
-// Guarded by the interpreter lock.
+// The tables are guarded by the interpreter lock; the launches of two threads' calls on one stream by the library.
 struct StreamBuffer {
   c10::DeviceIndex device;
   hipStream_t stream;

@@ -120,3 +120,33 @@ def test_two_streams_at_once_give_what_one_gives():
     for w, results in zip(want, got):
         for r in results:
             assert torch.equal(r[0], w[0]) and torch.equal(r[1], w[1])
+
+
+@pytest.mark.gpu
+def test_two_threads_on_one_stream_give_what_one_gives():
+    """Calls of several launches on the default workspace, from two threads on the same stream."""
+    import threading
+    S, Hkv, R, N, B, scale = 1, 2, 64, 3000, 32, 1 / math.sqrt(128)
+    g = torch.Generator(device=DEV).manual_seed(4)
+    rand = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    K, q, xq = rand(S, Hkv, N, 128), rand(2, S, Hkv, R, 128), rand(2, 64, Hkv, 128)
+    ids = torch.randint(0, B, (S, Hkv, N), generator=g, device=DEV, dtype=torch.int32)
+    off, ln, _, Ks, _ = saap.build_bucket_index(ids, K, K, B)
+    W1, W2 = rand(Hkv, 64, 128) / 11, rand(Hkv, B, 64) / 8
+
+    def once(i):
+        mass, lse = saap.bucket_attention_mass_batch(q[i], Ks, off, ln, scale)
+        return mass, lse, saap.classify_queries(xq[i], W1, None, W2, None, Hkv)
+    want = [once(i) for i in range(2)]
+    torch.cuda.synchronize()
+    got = [[], []]
+    threads = [threading.Thread(target=lambda i=i: got[i].extend(once(i) for _ in range(50))) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for w, results in zip(want, got):
+        assert len(results) == 50
+        for r in results:
+            assert all(torch.equal(a, b) for a, b in zip(r, w))
