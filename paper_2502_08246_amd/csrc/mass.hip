@@ -125,8 +125,8 @@ constexpr int kMassPitch = 136;      // bf16 elements per LDS row (272 bytes: co
 constexpr int kMassTile = 32;        // keys per tile
 constexpr int kMassBuckets = 512;    // buckets per workgroup at most
 
-// NEG: the score scale is negative, the largest score is the smallest product.
-template <int QT, bool NEG>
+// SIGN of the score scale: below zero the largest score is the smallest product.
+template <int QT, int SIGN>
 __global__ void __launch_bounds__(256, 2)
 mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, const int32_t* __restrict__ off,
                  const int32_t* __restrict__ len, float2* __restrict__ part, long long rows, int B, int R,
@@ -219,18 +219,22 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
       for (int i = 0; i < QT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[i][st], acc[i], 0, 0, 0);
     }
     // register r of this lane: key t0 + 8*(r/4) + 4*half + r%4 against query `col`
+    float to_log2 = scale_log2;
     if (t.t0 + kMassTile > t.n) {                        // the bucket's last tile: rows past its end do not count
+      if (SIGN == 0) to_log2 = 1.f;                      // scaled here: zero times the mask would be no number
 #pragma unroll
       for (int i = 0; i < QT; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (t.t0 + 8 * (r / 4) + 4 * half + (r % 4) >= t.n) acc[i][r] = NEG ? INFINITY : -INFINITY;
+        for (int r = 0; r < 16; ++r) {
+          const bool in = t.t0 + 8 * (r / 4) + 4 * half + (r % 4) < t.n;
+          acc[i][r] = !in ? (SIGN < 0 ? INFINITY : -INFINITY) : SIGN == 0 ? acc[i][r] * 0.f : acc[i][r];
+        }
     }
     auto weights = [&](const f32x16_t& c, float ref) {
       float add[4];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float w = fast_exp2(fmaf(c[r], scale_log2, -ref));
+        const float w = fast_exp2(fmaf(c[r], to_log2, -ref));
         add[r % 4] = r < 4 ? w : add[r % 4] + w;
       }
       return (add[0] + add[1]) + (add[2] + add[3]);
@@ -241,8 +245,8 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
       if (__builtin_expect(__ballot(!(add < kFarAbove)) != 0ull, 0)) {      // the first tile, and rarely after it
         float best = acc[i][0];
 #pragma unroll
-        for (int r = 1; r < 16; ++r) best = NEG ? fminf(best, acc[i][r]) : fmaxf(best, acc[i][r]);
-        const float mn = fmaxf(m[i], best * scale_log2);   // stays where this half holds no key above it
+        for (int r = 1; r < 16; ++r) best = SIGN < 0 ? fminf(best, acc[i][r]) : fmaxf(best, acc[i][r]);
+        const float mn = fmaxf(m[i], best * to_log2);   // stays where this half holds no key above it
         add = weights(acc[i], mn);
         s[i] *= fast_exp2(m[i] - mn);
         m[i] = mn;
@@ -418,8 +422,9 @@ extern "C" int32_t saap_bucket_attention_mass_batch(const void* q, const void* K
     hipLaunchKernelGGL(kernel, dim3((unsigned)slices, (unsigned)qblocks, (unsigned)units), dim3(256), 0, hs, static_cast<const bf16_t*>(q),
                        static_cast<const bf16_t*>(Ksorted), off, len, part, (long long)Ncap, B, R, scale_log2);
   };
-  if (scale_log2 < 0.f) qt == 2 ? launch(mass_mfma_kernel<2, true>) : launch(mass_mfma_kernel<1, true>);
-  else qt == 2 ? launch(mass_mfma_kernel<2, false>) : launch(mass_mfma_kernel<1, false>);
+  if (scale_log2 < 0.f) qt == 2 ? launch(mass_mfma_kernel<2, -1>) : launch(mass_mfma_kernel<1, -1>);
+  else if (scale_log2 == 0.f) qt == 2 ? launch(mass_mfma_kernel<2, 0>) : launch(mass_mfma_kernel<1, 0>);
+  else qt == 2 ? launch(mass_mfma_kernel<2, 1>) : launch(mass_mfma_kernel<1, 1>);
   hipLaunchKernelGGL(mass_normalise_batch_kernel, dim3((unsigned)((R + 31) / 32), (unsigned)units), dim3(256), 0, hs, part,
                      mass, lse, B, R);
   return launch_status();

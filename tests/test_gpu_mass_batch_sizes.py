@@ -1,5 +1,5 @@
 """bucket_attention_mass_batch at the edges of its query tiles and key tiles, with empty buckets, with a negative score
-scale and with scores so far apart that the reference of the running sums has to move, against float64 numpy."""
+scale and one of zero, and with scores so far apart that the reference of the running sums has to move, against float64 numpy."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +22,8 @@ def saap():
 @pytest.mark.parametrize("R,lens,scale,spread", [
     (1, [1], 0.09, 1.0), (31, [0, 1, 31, 32, 33, 0, 65, 2], 0.09, 1.0), (128, [64] * 5, 0.09, 1.0), (129, [3, 0, 40] * 30, 0.09, 1.0),
     (256, [33, 95, 1, 0], -0.09, 1.0), (300, [10, 200, 31], 0.09, 40.0), (257, [70, 0, 5, 64, 90], -0.09, 40.0),
-    (40, [1, 0, 2] * 400, 0.09, 1.0), (130, [0, 0, 0], 0.09, 1.0)])
+    (40, [1, 0, 2] * 400, 0.09, 1.0), (130, [0, 0, 0], 0.09, 1.0),
+    (129, [3, 0, 32, 40], 0.0, 1.0), (256, [33, 95, 1, 64], -0.0, 1.0), (40, [33, 5, 64], 1e-40, 1.0)])
 def test_mass(saap, R, lens, scale, spread):
     Hkv, B, N = 2, len(lens), max(sum(lens), 1)
     g = torch.Generator(device=DEV).manual_seed(R)
