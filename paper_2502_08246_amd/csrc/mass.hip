@@ -134,7 +134,7 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
   typedef __attribute__((ext_vector_type(16))) float f32x16_t;
   __shared__ __align__(16) bf16_t s_k[2][kMassTile * kMassPitch];
   __shared__ int4 s_list[kMassBuckets];               // bucket, first row, length
-  __shared__ int s_live, s_tiles;
+  __shared__ int s_live[4], s_tiles;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   const int unit = blockIdx.z;
@@ -149,16 +149,30 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
   }
   const bf16_t* Ku = K + (size_t)unit * rows * kD;
   // The workgroup's buckets (every gridDim.x-th) that hold keys, in LDS, so that walking on to the next one is no trip to
-  // memory; their order does not matter.  The pairs of a bucket without keys are written here.
+  // memory, in ascending order: the reference below goes from bucket to bucket, so the order is part of the result's bits.
+  // The pairs of a bucket without keys are written here.
   auto pair_of = [&](int b, int i) { return part + ((size_t)unit * B + b) * R + q0 + 32 * i; };
-  if (tid == 0) s_live = s_tiles = 0;
+  if (tid == 0) s_tiles = 0;
   __syncthreads();
-  for (int b = blockIdx.x + tid * gridDim.x; b < B; b += 256 * gridDim.x) {      // at most kMassBuckets: checked on the host
-    const int n = len[(size_t)unit * B + b], first = off[(size_t)unit * (B + 1) + b];
-    if (n > 0) {
-      s_list[atomicAdd(&s_live, 1)] = make_int4(b, first, n, 0);
+  int n_before = 0;
+  for (int b0 = blockIdx.x; b0 < B; b0 += 256 * gridDim.x) {      // at most kMassBuckets: checked on the host
+    const int b = b0 + tid * gridDim.x, at = min(b, B - 1);
+    const int n = len[(size_t)unit * B + at], first = off[(size_t)unit * (B + 1) + at];
+    const bool live = b < B && n > 0;
+    const unsigned long long mask = __ballot(live);
+    if (lane == 0) s_live[wave] = __popcll(mask);
+    __syncthreads();
+    int place = n_before + __popcll(mask & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      place += w < wave ? s_live[w] : 0;
+      n_before += s_live[w];
+    }
+    if (live) {
+      s_list[place] = make_int4(b, first, n, 0);
       atomicAdd(&s_tiles, (n + kMassTile - 1) / kMassTile);
     }
+    __syncthreads();
   }
   for (int b = blockIdx.x; b < B; b += gridDim.x)
     if (half == 0 && len[(size_t)unit * B + b] <= 0)
@@ -166,7 +180,7 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
       for (int i = 0; i < QT; ++i)
         if (q0 + 32 * i < R) *pair_of(b, i) = make_float2(kNegBig, 0.f);
   __syncthreads();
-  const int n_live = __builtin_amdgcn_readfirstlane(s_live), n_tiles = __builtin_amdgcn_readfirstlane(s_tiles);
+  const int n_live = __builtin_amdgcn_readfirstlane(n_before), n_tiles = __builtin_amdgcn_readfirstlane(s_tiles);
   if (n_tiles == 0) return;
   // Tiles of 32 keys, bucket by bucket; the walk is the same in all waves (scalar registers) and, past the end, comes back
   // to the last bucket (valid loads that nobody uses).

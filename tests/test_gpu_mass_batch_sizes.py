@@ -49,3 +49,20 @@ def test_mass(saap, R, lens, scale, spread):
         tol = 1e-5 * max(1.0, np.abs(t).max())
         np.testing.assert_allclose(mass[0, h], want / total, rtol=tol, atol=1e-7)
         np.testing.assert_allclose(lse[0, h], (top + np.log(total))[:, 0], rtol=1e-5, atol=1e-4)
+
+
+@pytest.mark.parametrize("Hkv,R,B", [(2, 200, 1024), (64, 2048, 1024), (64, 512, 8192)])
+def test_the_same_inputs_give_the_same_bits(saap, Hkv, R, B):
+    """One, 256 and 512 buckets to a workgroup: the running reference goes through them in one order."""
+    g = torch.Generator(device=DEV).manual_seed(B)
+    N = 4 * B
+    ids = torch.randint(0, B, (1, Hkv, N), generator=g, device=DEV, dtype=torch.int32)
+    K = 3 * torch.randn(1, Hkv, N, 128, generator=g, device=DEV)
+    K *= torch.rand(1, Hkv, N, 1, generator=g, device=DEV) * 4          # the reference moves within a workgroup's buckets
+    K = K.to(torch.bfloat16)
+    off, ln, _, Ks, _ = saap.build_bucket_index(ids, K, K, B)
+    q = torch.randn(1, Hkv, R, 128, generator=g, device=DEV).to(torch.bfloat16)
+    mass, lse = saap.bucket_attention_mass_batch(q, Ks, off, ln, 0.09)
+    for _ in range(8):
+        again, again_lse = saap.bucket_attention_mass_batch(q, Ks, off, ln, 0.09)
+        assert torch.equal(mass, again) and torch.equal(lse, again_lse)
