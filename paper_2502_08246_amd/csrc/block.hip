@@ -187,6 +187,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t run_buffer(const bf16_t* rows,
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(rows), 0, (unsigned)n * kD * (unsigned)sizeof(bf16_t), 0x00027000);
 }
 
+// Whether either half of a word is an infinity or a NaN.
+__device__ __forceinline__ bool no_number(unsigned x) { return ((x & 0x7f80u) == 0x7f80u) | ((x & 0x7f800000u) == 0x7f800000u); }
+// Infinities and NaNs among a tile's values become zeros; whether there were any.
+__device__ __forceinline__ bool zero_no_numbers(u32x2_t (&vr)[16]) {
+  typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+  u16x2_t top = {0, 0};                                  // the largest exponent of either half
+#pragma unroll
+  for (int i = 0; i < 32; ++i) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2_t, vr[i / 2][i % 2] & 0x7f807f80u));
+  if (__builtin_expect(__ballot(top[0] == 0x7f80 || top[1] == 0x7f80) == 0ull, 1)) return false;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    const unsigned x = vr[i / 2][i % 2];
+    vr[i / 2][i % 2] = x & (((x & 0x7f80u) == 0x7f80u ? 0u : 0x0000ffffu) | ((x & 0x7f800000u) == 0x7f800000u ? 0u : 0xffff0000u));
+  }
+  return true;
+}
+
 // Keys [k0, k1) at K, V in tiles of 32, every `stride`-th key a tile's first.  The query of lane `col` attends the keys whose
 // position (pos[k], or k itself) is in [lo, hi); keys in [safe0, safe1) are in every query's range.
 constexpr int kPosRegs = kLongRun / 64;
@@ -196,9 +213,13 @@ struct Run {
   int k0, k1, lo, hi, safe0, safe1;
 };
 
+// A key outside a query's range has weight zero, and zero times an infinity or a NaN is no zero: where a tile's queries differ
+// in what they see, such values are zeroed and added afterwards, by a second walk that ordinary values never come to (taken
+// inside the loop it cost the loop its registers: 128 tokens over 128k keys 193.5 -> 199.9 us, this way 189.2 and 189.5).
 // The reference m of a row moves only when one of its scores is more than 8 (2^8 in weight) above it, so that the outputs are
 // rescaled (an exchange over the lanes) once or twice per run; by the row's own scores alone, whoever shares its tile.
-__device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stride, float scale_log2, const int* s_pos = nullptr) {
+__device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stride, float scale_log2, float* s_w /* [32][32] */,
+                                           const int* s_pos = nullptr) {
   const int k0 = __builtin_amdgcn_readfirstlane(run.k0), k1 = __builtin_amdgcn_readfirstlane(run.k1);
   const int safe0 = __builtin_amdgcn_readfirstlane(run.safe0), safe1 = __builtin_amdgcn_readfirstlane(run.safe1);
   if (k0 >= k1) return;
@@ -217,6 +238,32 @@ __device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stri
     for (int i = 0; i < 16; ++i)       // slot i % 8 of key group i / 8
       vr[i] = __builtin_amdgcn_raw_buffer_load_b64(vbuf, v_at + t * kRow + (16 * (i / 8) + (i % 8 < 4 ? i % 8 : i % 8 + 4)) * kRow, 0, 0);
   };
+  auto edge = [&](int t) { return t < safe0 || min(t + 32, k1) > safe1; };         // some key is outside some query's range
+  auto position = [&](int t) {
+    const int key = min(t + col, k1 - 1);
+    return s_pos ? s_pos[key] : run.pos ? run.pos[key] : key;
+  };
+  auto mask = [&](f32x16_t& s, int t) {
+    if (t + 32 > k1)                                     // the run's last tile
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = t + row_of(r, half) >= k1 ? -INFINITY : s[r];
+    if (edge(t)) {
+      const int pos = position(t);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int pk = row_value(pos, r, half);
+        s[r] = (pk < run.lo) | (pk >= run.hi) ? -INFINITY : s[r];
+      }
+    }
+  };
+  auto highest = [&](const f32x16_t& s) {
+    float top = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) top = fmaxf(top, s[r]);
+    return max_halves(top);
+  };
+  const float m_before = w.m;
+  bool no_numbers = false;
   load_k(k0);
   load_v(k0);
   for (int t = k0; t < k1; t += stride) {
@@ -229,21 +276,9 @@ __device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stri
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] *= scale_log2;
-    if (t + 32 > k1)                                     // the run's last tile
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = t + row_of(r, half) >= k1 ? -INFINITY : s[r];
-    if (t < safe0 || min(t + 32, k1) > safe1) {          // some key is outside some query's range
-      const int key = min(t + col, k1 - 1), pos = s_pos ? s_pos[key] : run.pos ? run.pos[key] : key;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int pk = row_value(pos, r, half);
-        s[r] = (pk < run.lo) | (pk >= run.hi) ? -INFINITY : s[r];
-      }
-    }
-    float top = s[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) top = fmaxf(top, s[r]);
-    top = max_halves(top);
+    mask(s, t);
+    if (edge(t)) no_numbers |= zero_no_numbers(vr);      // zero times an infinity or a NaN is no zero
+    const float top = highest(s);
     if (__ballot(top > w.m + 8.f) != 0ull) {
       const float mn = top > w.m + 8.f ? top : w.m, alpha = fast_exp2(w.m - mn);
       w.m = mn;
@@ -292,6 +327,44 @@ __device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stri
     __builtin_amdgcn_sched_barrier(0);
     load_v(nxt);
     __builtin_amdgcn_sched_barrier(0);
+  }
+  if (__builtin_expect(!no_numbers, 1)) return;
+  // The run's edge tiles held infinities or NaNs: they are added here, to the rows that attend them and with the weights
+  // that the walk above had (the same steps again), one key at a time.
+  float m = m_before;
+#pragma unroll 1
+  for (int t = k0; t < k1; t += stride) {
+    load_k(t);
+    f32x16_t s = {0};
+#pragma unroll
+    for (int st = 0; st < 8; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kr[st]), w.q[st], s, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] *= scale_log2;
+    mask(s, t);
+    const float top = highest(s);
+    m = top > m + 8.f ? top : m;
+    if (!edge(t)) continue;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s_w[row_of(r, half) * 32 + col] = fast_exp2(s[r] - m);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int pos = position(t);
+#pragma unroll 1
+    for (int key = 0; key < min(32, k1 - t); ++key) {
+      const int pk = __builtin_amdgcn_readlane(pos, key);
+      const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(vbuf, (t + key) * kRow + col * 8, 0, 0);
+      if (__ballot(no_number(v[0]) | no_number(v[1])) == 0ull) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float wt = s_w[key * 32 + row_of(r, half)], hi = __uint_as_float(__float_as_uint(wt) & 0xffff0000u);
+        const bool in = pk >= row_value(run.lo, r, half) && pk < row_value(run.hi, r, half);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = e % 2 ? bf16_hi(v[e / 2]) : bf16_lo(v[e / 2]);
+          if (in && !(fabsf(x) < INFINITY)) w.o[e][r] += x * hi + x * (wt - hi);
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
 
@@ -401,6 +474,7 @@ block_attend_kernel(BlockParams p) {
   const int n_kv = p.S * p.Hkv, t_tiles = (p.Tq + TT - 1) / TT, n_dense = n_kv * t_tiles * p.splits;
   const int n_short = (int)p.counters[kCountShort * kLine], n_long = (int)p.counters[kCountLong * kLine];
   WaveTile w;
+  float* s_w = s_o + wave * 32 * 32;                     // of attend_run: combine_waves uses s_o between its barriers
 
   // sink and recent keys: a wave takes a tile of consecutive tokens and a split of their recent keys, the waves of a
   // workgroup neighbouring tiles (the same keys, from the compute unit's L1)
@@ -417,7 +491,7 @@ block_attend_kernel(BlockParams p) {
     load_queries<G>(w, p, s, kvu - s * p.Hkv, item);
     w.clear();
     for (int part = 0; part < 2; ++part) {
-      attend_run(w, run, 32, p.scale_log2);
+      attend_run(w, run, 32, p.scale_log2, s_w);
       run = Run{p.K + base, p.V + base, nullptr, 0, split == 0 ? sp1.sink : 0, 0, sp.sink, 0, sp0.sink};
     }
     store_slots<G>(w, p, s, kvu - s * p.Hkv, item, tokens);
@@ -435,7 +509,7 @@ block_attend_kernel(BlockParams p) {
     const Run run{p.Ks + base, p.Vs + base, pos, (b.k_lo & ~127) + wave * 32, b.k_hi, b.sp.sink, b.sp.recent, b.s_lo, b.s_hi};
     load_queries<G>(w, p, s, kvu - s * p.Hkv, item);
     w.clear();
-    attend_run(w, run, 128, p.scale_log2);
+    attend_run(w, run, 128, p.scale_log2, s_w);
     combine_waves(w, s_ml, s_o);
     if (wave == 0) store_slots<G>(w, p, s, kvu - s * p.Hkv, item, tile.tokens);
     __syncthreads();                                     // this task's LDS is free
@@ -481,7 +555,7 @@ block_attend_kernel(BlockParams p) {
     }
     const size_t base = ((size_t)kvu * p.Ncap + tile.row) * kD;
     const Run run{p.Ks + base, p.Vs + base, nullptr, b.k_lo & ~31, b.k_hi, b.sp.sink, b.sp.recent, b.s_lo, b.s_hi};
-    attend_run(w, run, 32, p.scale_log2, s_pos[wave]);
+    attend_run(w, run, 32, p.scale_log2, s_w, s_pos[wave]);
     if (more) {
       tile = BucketTile{uniform(a.x), uniform(a.y), uniform(a.z), uniform(a.w), uniform(an)};
       fetch(tile);

@@ -64,3 +64,32 @@ def test_scores_that_are_no_numbers(saap, bad):  # noqa: F811
     assert torch.isnan(out[none]).all()
     assert_close(out[~none].cpu().numpy(), want[~none].cpu().numpy(), "bf16", "out")
     assert_close(lse[~none].cpu().numpy(), want_lse[~none].cpu().numpy(), "bf16", "lse")
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("Hq,Hkv,B,same", [(8, 2, 24, False), (8, 2, 24, True), (8, 2, 3, True), (2, 2, 6, False), (16, 2, 24, False)])
+def test_values_that_are_no_numbers_stay_with_the_tokens_that_attend_them(saap, Hq, Hkv, B, same, bad):  # noqa: F811
+    """Values that are not finite at a later token of the block, at the edge of the recent keys, at a sink key beyond some
+    tokens' range and at a bucket's member: what does not attend them (by the oracle) has the numbers of a cache without them,
+    bit for bit, also where the tokens of a tile differ in what they see.  B = 3: buckets shared out over waves."""
+    S, Nt, Tq, nprobe, p0, n_sink, n_recent = 2, 1500, 40, max(1, B // 4), np.array([1400, 0], dtype=np.int32), 12, 64
+    cache, ids, (off, ln, idx, Ks, Vs), q = setup(saap, "bf16", S, Hq, Hkv, Nt, B, Tq, 12)
+    rng = np.random.default_rng(4)
+    sel = np.stack([rng.permutation(B)[:nprobe] for _ in range(S * Hkv * Tq)]).reshape(S, Hkv, Tq, nprobe).astype(np.int32)
+    if same:
+        sel[:] = sel[:, :, :1]
+    V = cache["V"].clone()
+    V[0, 0, 1421, 3] = V[0, 1, 1400 - 64 + 20, 77] = V[0, 1, 700] = bad       # later token; edge of the recent keys; a member
+    V[1, 0, 5, 0], V[1, 0, 9, 127], V[1, 1, 30, 64] = bad, -bad, bad          # sink keys of the prompt's first tokens; a later one
+    sel_d, p0_d = torch.from_numpy(sel).to(DEV), torch.from_numpy(p0).to(DEV)
+
+    def attend(values):
+        index = saap.build_bucket_index(ids, cache["K"], values, B, 0)
+        return saap.prefill_sparse_attention(q, cache["K"], values, index[3], index[4], *index[:3], sel_d, p0_d, n_sink, n_recent, SCALE)
+    out, lse = attend(V)
+    clean, clean_lse = attend(cache["V"])
+    ro, _ = ref.prefill_sparse_attention(h(q), h(cache["K"]), h(V), ids.cpu().numpy(), sel, p0, n_sink, n_recent, SCALE, B)
+    fin = torch.from_numpy(np.isfinite(ro)).to(DEV)
+    assert 0 < (~fin).sum() < fin.numel() // 2
+    assert torch.equal(torch.isfinite(out), fin)
+    assert torch.equal(out[fin], clean[fin]) and torch.equal(lse, clean_lse)
