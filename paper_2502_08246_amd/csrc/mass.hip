@@ -275,6 +275,7 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
         const float S = s[i] * fast_exp2(m[i] - M) + so * fast_exp2(mo - M);
         if (half == 0 && q0 + 32 * i < R) *pair_of(t.b, i) = make_float2(M, S);
         s[i] = 0.f;
+        m[i] = m[i] < INFINITY ? m[i] : kNegBig;         // no reference for the buckets that follow
       }
     }
   };

@@ -66,3 +66,24 @@ def test_the_same_inputs_give_the_same_bits(saap, Hkv, R, B):
     for _ in range(8):
         again, again_lse = saap.bucket_attention_mass_batch(q, Ks, off, ln, 0.09)
         assert torch.equal(mass, again) and torch.equal(lse, again_lse)
+
+
+@pytest.mark.parametrize("scale", [0.09, -0.09])
+def test_an_infinite_score_stays_in_its_bucket(saap, scale):
+    """A key with an infinite feature, in a bucket that others of its workgroup follow: as the call for decode steps, which
+    takes every bucket by itself, gives it."""
+    B, N, R = 600, 24000, 8
+    g = torch.Generator(device=DEV).manual_seed(5)
+    ids = torch.randint(0, B, (8, 32, N // 8), generator=g, device=DEV, dtype=torch.int32)
+    K = torch.randn(8, 32, N // 8, 128, generator=g, device=DEV).to(torch.bfloat16)
+    q = torch.randn(8, 32, R, 128, generator=g, device=DEV).to(torch.bfloat16)
+    K[0, 0, 100, 7] = K[1, 3, 2000, 9] = float("inf")
+    off, ln, _, Ks, _ = saap.build_bucket_index(ids, K, K, B)
+    mass, lse = saap.bucket_attention_mass_batch(q, Ks, off, ln, scale)
+    want, want_lse = saap.bucket_attention_mass(q.view(8, 32 * R, 128), Ks, off, ln, scale)
+    want, want_lse = want.view_as(mass), want_lse.view_as(lse)
+    bad = ~torch.isfinite(want)
+    assert 0 < bad.sum() <= 2 * R and (lse[0, 0] == -float("inf")).any()
+    assert torch.equal(~torch.isfinite(mass), bad) and torch.equal(torch.isinf(lse), torch.isinf(want_lse))
+    # scores of magnitude 8 in sums of another order: as in test_mass
+    torch.testing.assert_close(mass[~bad], want[~bad], rtol=1e-4, atol=1e-7)
