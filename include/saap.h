@@ -81,7 +81,7 @@ enum {
   SAAP_OP_QUERY_MODEL_LOSS_GRADS = 9,  /* shape: Hkv = weight sets, N = rows per set, d, hidden, B */
   SAAP_OP_BUCKET_ATTENTION_MASS_BATCH = 10,  /* shape: S, Hkv, N = queries per KV head, B */
   SAAP_OP_PLANNED_DECODE_ATTENTION = 11,     /* shape: S, Hq, Hkv, mode */
-  SAAP_OP_PREFILL_SPARSE_ATTENTION = 12,     /* shape: S, Hq, Hkv, N = query tokens per sequence (Tq), nprobe */
+  SAAP_OP_PREFILL_SPARSE_ATTENTION = 12,     /* shape: S, Hq, Hkv, N = query tokens per sequence (Tq), nprobe, dtype */
   SAAP_OP_UPDATE_CENTROIDS_FROM_IDS = 13     /* shape: S, Hkv, N, B */
 };
 
@@ -772,12 +772,19 @@ int32_t saap_planned_decode_attention_fp8(const void* q, const uint8_t* K8, cons
  *   pos0 [S] int32, device;  out [S,Tq,Hq,d] of out_dtype;  lse [S,Tq,Hq] fp32 or NULL
  * Sink and recent keys are read from K, V; of a listed bucket only the members between them are
  * read from the sorted cache (they form one stretch of the bucket's rows, the members being
- * stored in ascending position).  Every (token, KV head) pair gets a visit plan and the keys of all
- * pairs are dealt to the workgroups in equal shares, as saap_planned_decode_attention does: the
- * tokens of a block see very different numbers of keys.
+ * stored in ascending position).  Two ways, the same rule:
+ *   bf16, Tq >= 8 and S*Tq*Hkv >= 64: the lists are inverted, for every bucket the tokens that list
+ *     it, and tiles of 32 / G tokens share the keys they read; one partial result per (token, listed
+ *     bucket), combined at the end.  For Nt, Ncap < 2^23, Tq <= 4096, nprobe up to about 1000 and
+ *     partial results of at most 1.5 GiB;
+ *   otherwise every (token, KV head) pair gets a visit plan and the keys of all pairs are dealt to
+ *     the workgroups in equal shares, as saap_planned_decode_attention does.
  * Limits: S*Tq*Hkv <= 4096 per call (longer blocks are split by the caller); the limits of
  * saap_planned_decode_attention with nruns = nprobe + 2.
- * Workspace: SAAP_OP_PREFILL_SPARSE_ATTENTION (S, Hq, Hkv, N = Tq, nprobe).
+ * Workspace: SAAP_OP_PREFILL_SPARSE_ATTENTION (S, Hq, Hkv, N = Tq, nprobe, dtype).  With dtype
+ * SAAP_BF16 it has room for the partial results of the first way (520 bytes per query head and listed
+ * bucket: 460 MB for 512 tokens of 32 heads with 51 buckets), with SAAP_F32 for the second only (12 MB
+ * there); a bf16 call that gets no more than that takes the second.
  */
 int32_t saap_prefill_sparse_attention(const void* q, const void* K, const void* V,
                                       const void* Ksorted, const void* Vsorted,

@@ -1905,7 +1905,7 @@ int32_t launch_attn(const AttnParams& p, const LaunchPlan& lp, int G, int dtype,
 size_t attn_workspace_bytes(long long units, int G) {
   return (size_t)SAAP_WS_HEADER_BYTES + (size_t)units * kMaxP * G * (kD + 2) * sizeof(float);
 }
-size_t prefill_workspace_bytes(long long S, int Tq, int Hq, int Hkv, int nprobe);
+size_t prefill_workspace_bytes(long long S, int Tq, int Hq, int Hkv, int nprobe, int dtype);
 size_t block_workspace_bytes(long long S, int Tq, int Hq, int Hkv, int nprobe);
 int32_t block_attention(const void* q, const void* K, const void* V, const void* Ks, const void* Vs, const int32_t* off,
                         const int32_t* len, const int32_t* idx, const int32_t* selected, const int32_t* pos0, int nprobe,
@@ -2424,10 +2424,19 @@ extern "C" int32_t saap_sparse_decode_attention_noalloc(const void* q, const voi
 }
 
 // ---- prefill-time sparse attention: shared key tiles (block.hip), or per-token visit plans and the planned attention ----
-size_t saap::prefill_workspace_bytes(long long S, int Tq, int Hq, int Hkv, int nprobe) {
+static size_t prefill_planned_bytes(long long units, int G, int nprobe) {
+  return planned_workspace_bytes(units, G) + (size_t)units * plan_stride(nprobe + 2) * sizeof(int32_t);
+}
+// bf16: the tokens of the block share key tiles (block.hip), from the size where that is the faster way: 8 tokens of 8 KV
+// heads took 23.5 us token by token and 19.5 there at 8192 keys, 55.0 and 46.9 at 131072; 4 tokens 18.1 and 19.3.  fp32, and
+// lists or rows beyond that file's limits: token by token.
+static bool tokens_share_tiles(long long units, int Tq, int dtype) {
+  return dtype == SAAP_BF16 && Tq >= 8 && units >= 64 && units <= kPlanMaxUnits;
+}
+size_t saap::prefill_workspace_bytes(long long S, int Tq, int Hq, int Hkv, int nprobe, int dtype) {
   const long long units = S * Tq * Hkv;
-  const size_t planned = planned_workspace_bytes(units, Hq / Hkv) + (size_t)units * plan_stride(nprobe + 2) * sizeof(int32_t);
-  const size_t block = block_workspace_bytes(S, Tq, Hq, Hkv, nprobe);
+  const size_t planned = prefill_planned_bytes(units, Hq / Hkv, nprobe);
+  const size_t block = tokens_share_tiles(units, Tq, dtype) ? block_workspace_bytes(S, Tq, Hq, Hkv, nprobe) : 0;
   return planned > block ? planned : block;
 }
 
@@ -2449,12 +2458,10 @@ extern "C" int32_t saap_prefill_sparse_attention(const void* q, const void* K, c
   if (nprobe + 2 > SAAP_MAX_BUCKETS) return SAAP_UNSUPPORTED;
   const long long units = (long long)S * Tq * Hkv;
   if (units > kPlanMaxUnits) return SAAP_UNSUPPORTED;
-  if (ws_bytes < prefill_workspace_bytes(S, Tq, Hq, Hkv, nprobe)) return SAAP_WORKSPACE_TOO_SMALL;
-  // bf16: the tokens of the block share key tiles (block.hip), from the size where that is the faster way: 8 tokens of 8 KV
-  // heads took 23.5 us token by token and 19.5 there at 8192 keys, 55.0 and 46.9 at 131072; 4 tokens 18.1 and 19.3.  fp32, and
-  // lists or rows beyond that file's limits: token by token.
-  if (dtype == SAAP_BF16 && Tq >= 8 && units >= 64 && B <= SAAP_MAX_BUCKETS && Nt < (1 << 23) && Ncap < (1 << 23) &&
-      block_workspace_bytes(S, Tq, Hq, Hkv, nprobe) != 0)
+  if (ws_bytes < prefill_planned_bytes(units, Hq / Hkv, nprobe)) return SAAP_WORKSPACE_TOO_SMALL;
+  const size_t block_bytes = block_workspace_bytes(S, Tq, Hq, Hkv, nprobe);
+  if (tokens_share_tiles(units, Tq, dtype) && B <= SAAP_MAX_BUCKETS && Nt < (1 << 23) && Ncap < (1 << 23) && block_bytes != 0 &&
+      ws_bytes >= block_bytes)
     return block_attention(q, K, V, Ksorted, Vsorted, off, len, idx, selected, pos0, nprobe, n_sink, n_recent, scale, out,
                            out_dtype == SAAP_BF16 ? 1 : 0, lse, S, Hq, Hkv, Tq, Nt, Ncap, B, ws, static_cast<hipStream_t>(stream));
   const int ps = plan_stride(nprobe + 2);

@@ -824,7 +824,7 @@ SAAP_FUNCTION(prefill_sparse_attention) {
   const int32_t Ncap = size(Ks, 2), B = size(ln, 2), nprobe = size(sel, 3), n_sink = a.integer(10), n_recent = a.integer(11);
   Out out(a, 14, {S, Tq, Hq, d}, a.dtype(13, at::kFloat), q), lse(a, 15, {S, Tq, Hq}, at::kFloat, q);
   saap_shape sh = shape_of(S, Hq, Hkv);
-  sh.N = Tq; sh.nprobe = nprobe;
+  sh.N = Tq; sh.nprobe = nprobe; sh.dtype = dtype_code(q);
   const Ws ws(a, 16, q, SAAP_OP_PREFILL_SPARSE_ATTENTION, sh);
   void *pq = ptr(q), *pk = ptr(K), *pv = ptr(V), *pks = ptr(Ks), *pvs = ptr(Vs), *po = ptr(out.t);
   const int32_t *poff = ptr_as<int32_t>(a.tensor(5)), *pl = ptr_as<int32_t>(ln), *pi = ptr_as<int32_t>(a.tensor(7));

@@ -106,3 +106,25 @@ def test_prefill_rejects_blocks_beyond_its_limits(saap):
     with pytest.raises(saap.SaapError) as e:
         saap.prefill_sparse_attention(q, K, K, K, K, off, ln, idx, sel, torch.zeros(1, dtype=torch.int32, device=DEV), 1, 8, SCALE)
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("dtype,Tq", [("f32", 40), ("bf16", 4), ("bf16", 40)])
+def test_prefill_attention_with_a_workspace_for_token_by_token(saap, dtype, Tq):
+    """What the call needs token by token is enough for it, whatever it would take with more."""
+    S, Hq, Hkv, Nt, B, nprobe, n_sink, n_recent = 1, 8, 2, 1500, 24, 6, 1, 64
+    cache, ids, (off, ln, idx, Ks, Vs), q = setup(saap, dtype, S, Hq, Hkv, Nt, B, Tq, 21)
+    p0 = np.array([1400], dtype=np.int32)
+    rng = np.random.default_rng(2)
+    sel = np.stack([rng.permutation(B)[:nprobe] for _ in range(Hkv * Tq)]).reshape(S, Hkv, Tq, nprobe).astype(np.int32)
+    units = S * Tq * Hkv
+    need = saap.workspace_bytes(saap.binding.OP_PLANNED_DECODE_ATTENTION, S=S * Tq, Hq=Hq, Hkv=Hkv) + \
+        4 * saap.visit_plan_ints(S * Tq, Hq, Hkv, nprobe + 2)
+    assert need >= saap.workspace_bytes(saap.binding.OP_PREFILL_SPARSE_ATTENTION, S=S, Hq=Hq, Hkv=Hkv, N=Tq, nprobe=nprobe) > units
+    ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
+    args = (cache["K"], cache["V"], Ks, Vs, off, ln, idx, torch.from_numpy(sel).to(DEV), torch.from_numpy(p0).to(DEV), n_sink, n_recent)
+    out, lse = saap.prefill_sparse_attention(q, *args, SCALE, ws=ws)
+    ro, rl = ref.prefill_sparse_attention(h(q), h(cache["K"]), h(cache["V"]), ids.cpu().numpy(), sel, p0, n_sink, n_recent, SCALE, B)
+    assert_close(out.cpu().numpy(), ro, dtype, "out")
+    assert_close(lse.cpu().numpy(), rl, dtype, "lse")
+    with pytest.raises(saap.SaapError):
+        saap.prefill_sparse_attention(q, *args, SCALE, ws=ws[:65536])
