@@ -53,12 +53,11 @@ template <auto Kernel>
 inline bool allow_lds(size_t lds) {
   static std::atomic<int> allowed[kMaxDevices];
   if (lds <= 48 * 1024) return true;
+  auto set = [](int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+  };
   const int dev = current_device();
-  if (dev >= 0 && allowed[dev].load(std::memory_order_relaxed) >= (int)lds) return true;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return false;
-  if (dev >= 0) allowed[dev].store((int)lds, std::memory_order_relaxed);
-  return true;
+  return dev >= 0 ? raise_limit(allowed[dev], (int)lds, set) : set((int)lds);
 }
 
 // Every entry point starts with `const Call call(stream)`: its launches are enqueued without another thread's between them

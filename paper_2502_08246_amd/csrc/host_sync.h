@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 
 namespace saap {
@@ -24,5 +25,18 @@ class InOrder {
   }
   std::lock_guard<std::recursive_mutex> lock_;
 };
+
+// Raises a limit to `need` by set(need) and remembers it: one thread at a time, so that what is remembered is what was set
+// last, and never down, since another thread may be about to launch with the larger one.
+template <typename Set>
+bool raise_limit(std::atomic<int>& limit, int need, Set set) {
+  if (limit.load(std::memory_order_acquire) >= need) return true;
+  static std::mutex one;
+  const std::lock_guard<std::mutex> lock(one);
+  if (limit.load(std::memory_order_relaxed) >= need) return true;
+  if (!set(need)) return false;
+  limit.store(need, std::memory_order_release);
+  return true;
+}
 
 }  // namespace saap
