@@ -98,6 +98,8 @@ struct Args {
       }
   }
   bool has(int i) const { return v[i] && v[i] != Py_None; }
+  // A tensor that something is read off here.  One that is only passed on is taken with maybe(): the C call says whether it
+  // may be missing.
   const Tensor& tensor(int i) const {
     if (!v[i] || !THPVariable_Check(v[i])) raise_type("a tensor is expected");
     return THPVariable_Unpack(v[i]);
@@ -360,7 +362,7 @@ SAAP_FUNCTION(assign_keys) {
 
 SAAP_FUNCTION(build_bucket_index) {
   SAAP_BEGIN(4, "bucket_ids", "K", "V", "B", "slack", "ws")
-  const Tensor &ids = a.tensor(0), &K = a.tensor(1), &V = a.tensor(2);
+  const Tensor& K = a.tensor(1);
   want_dims(K, 4);
   const int32_t S = size(K, 0), Hkv = size(K, 1), N = size(K, 2), d = size(K, 3);
   const int32_t B = a.integer(3), slack = a.integer(4, 0), Ncap = N + B * slack, dt = dtype_code(K);
@@ -369,8 +371,8 @@ SAAP_FUNCTION(build_bucket_index) {
   saap_shape sh = shape_of(S, 0, Hkv);
   sh.N = N; sh.B = B;
   const Ws ws(a, 5, K, SAAP_OP_BUILD_BUCKET_INDEX, sh);
-  const int32_t* pi = ptr_as<int32_t>(ids);
-  void *pk = ptr(K), *pv = ptr(V), *pks = ptr(Ks.t), *pvs = ptr(Vs.t);
+  const int32_t* pi = ptr_as<int32_t>(a.maybe(0));
+  void *pk = ptr(K), *pv = ptr(a.maybe(2)), *pks = ptr(Ks.t), *pvs = ptr(Vs.t);
   int32_t *po = ptr_as<int32_t>(off.t), *pl = ptr_as<int32_t>(len.t), *px = ptr_as<int32_t>(idx.t);
   void* st = stream();
   call("saap_build_bucket_index", [&] {
@@ -382,7 +384,7 @@ SAAP_FUNCTION(build_bucket_index) {
 
 SAAP_FUNCTION(build_windowed_index) {
   SAAP_BEGIN(7, "bucket_ids", "K", "V", "B", "slack", "n_sink", "n_recent", "ws")
-  const Tensor &ids = a.tensor(0), &K = a.tensor(1), &V = a.tensor(2);
+  const Tensor& K = a.tensor(1);
   want_dims(K, 4);
   const int32_t S = size(K, 0), Hkv = size(K, 1), N = size(K, 2), d = size(K, 3);
   const int32_t B = a.integer(3), slack = a.integer(4), n_sink = a.integer(5), n_recent = a.integer(6), dt = dtype_code(K);
@@ -395,8 +397,8 @@ SAAP_FUNCTION(build_windowed_index) {
   saap_shape sh = shape_of(S, 0, Hkv);
   sh.N = N; sh.B = B;
   const Ws ws(a, 7, K, SAAP_OP_BUILD_BUCKET_INDEX, sh);
-  const int32_t* pi = ptr_as<int32_t>(ids);
-  void *pk = ptr(K), *pv = ptr(V), *pks = ptr(Ks.t), *pvs = ptr(Vs.t);
+  const int32_t* pi = ptr_as<int32_t>(a.maybe(0));
+  void *pk = ptr(K), *pv = ptr(a.maybe(2)), *pks = ptr(Ks.t), *pvs = ptr(Vs.t);
   int32_t *po = ptr_as<int32_t>(off.t), *pl = ptr_as<int32_t>(len.t), *px = ptr_as<int32_t>(idx.t);
   void* st = stream();
   call("saap_build_windowed_index", [&] {
@@ -410,13 +412,13 @@ SAAP_FUNCTION(build_windowed_index) {
 
 SAAP_FUNCTION(quantize_kv) {
   SAAP_BEGIN(2, "Ks", "Vs", "ws")
-  const Tensor &Ks = a.tensor(0), &Vs = a.tensor(1);
+  const Tensor& Ks = a.tensor(0);
   want_dims(Ks, 4);
   const int32_t S = size(Ks, 0), Hkv = size(Ks, 1), Ncap = size(Ks, 2), d = size(Ks, 3), dt = dtype_code(Ks);
   Out K8(a, -1, {S, Hkv, Ncap, d}, at::kByte, Ks), V8(a, -1, {S, Hkv, Ncap, d}, at::kByte, Ks);
   Out ks(a, -1, {S, Hkv}, at::kFloat, Ks), vs(a, -1, {S, Hkv}, at::kFloat, Ks);
   const Ws ws(a, 2, Ks, SAAP_WS_HEADER_BYTES);
-  void *pk = ptr(Ks), *pv = ptr(Vs);
+  void *pk = ptr(Ks), *pv = ptr(a.maybe(1));
   uint8_t *p8 = ptr_as<uint8_t>(K8.t), *q8 = ptr_as<uint8_t>(V8.t);
   float *psk = ptr_as<float>(ks.t), *psv = ptr_as<float>(vs.t);
   void* st = stream();
@@ -500,26 +502,28 @@ int64_t plan_ints(int32_t S, int32_t Hq, int32_t Hkv, int32_t nruns, int32_t mod
   if (bytes == 0) raise_saap("saap_visit_plan_bytes", SAAP_INVALID_ARG);
   return (int64_t)(bytes / 4);
 }
-Out plan_buffer(const Args& a, int i, int64_t ints, const Tensor& like) {
-  if (a.has(i)) {
-    const Tensor& t = a.tensor(i);
-    if (t.scalar_type() != at::kInt || t.numel() < ints) {
-      PyErr_Format(PyExc_ValueError, "plan must be int32 with at least %lld elements", (long long)ints);
-      throw python_error();
-    }
+const Tensor* given_plan(const Args& a, int i, int64_t ints) {
+  const Tensor* t = a.maybe(i);
+  if (t && (t->scalar_type() != at::kInt || t->numel() < ints)) {
+    PyErr_Format(PyExc_ValueError, "plan must be int32 with at least %lld elements", (long long)ints);
+    throw python_error();
   }
+  return t;
+}
+Out plan_buffer(const Args& a, int i, int64_t ints, const Tensor& like) {
+  given_plan(a, i, ints);
   return Out(a, i, {ints}, at::kInt, like);
 }
 
 SAAP_FUNCTION(build_visit_plan) {
   SAAP_BEGIN(4, "selected", "off", "ln", "Hq", "mode", "resident_run", "plan")
-  const Tensor &sel = a.tensor(0), &off = a.tensor(1), &ln = a.tensor(2);
+  const Tensor &sel = a.tensor(0), &ln = a.tensor(2);
   want_dims(sel, 3);
   want_dims(ln, 3);
   const int32_t S = size(sel, 0), nprobe = size(sel, 2), Hkv = size(ln, 1), runs = size(ln, 2);
   const int32_t Hq = a.integer(3), mode = a.integer(4, SAAP_GROUP_SUM), resident = a.integer(5, -1);
   Out plan = plan_buffer(a, 6, plan_ints(S, Hq, Hkv, nprobe + (resident >= 0 ? 1 : 0), mode), ln);
-  const int32_t *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr, *po = ptr_as<int32_t>(off), *pl = ptr_as<int32_t>(ln);
+  const int32_t *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr, *po = ptr_as<int32_t>(a.maybe(1)), *pl = ptr_as<int32_t>(ln);
   int32_t* pp = ptr_as<int32_t>(plan.t);
   void* st = stream();
   call("saap_build_visit_plan", [&] { return saap_build_visit_plan(ps, po, pl, nprobe, mode, resident, pp, S, Hq, Hkv, runs, st); });
@@ -529,7 +533,7 @@ SAAP_FUNCTION(build_visit_plan) {
 
 SAAP_FUNCTION(select_buckets_planned) {
   SAAP_BEGIN(5, "scores", "off", "ln", "Hkv", "nprobe", "input_kind", "mode", "resident_run", "probs", "out", "plan", "ws")
-  const Tensor &scores = a.tensor(0), &off = a.tensor(1), &ln = a.tensor(2);
+  const Tensor& scores = a.tensor(0);
   want_dims(scores, 3);
   const int32_t S = size(scores, 0), Hq = size(scores, 1), B = size(scores, 2);
   const int32_t Hkv = a.integer(3), nprobe = a.integer(4), kind = a.integer(5, SAAP_PROBS), mode = a.integer(6, SAAP_GROUP_SUM);
@@ -538,7 +542,7 @@ SAAP_FUNCTION(select_buckets_planned) {
   Out plan = plan_buffer(a, 10, plan_ints(S, Hq, Hkv, nprobe + (resident >= 0 ? 1 : 0), mode), scores);
   const Ws ws(a, 11, scores, SAAP_OP_SELECT_BUCKETS, saap_shape{});
   float *ps = ptr_as<float>(scores), *pp = ptr_as<float>(a.maybe(8));
-  const int32_t *po = ptr_as<int32_t>(off), *pl = ptr_as<int32_t>(ln);
+  const int32_t *po = ptr_as<int32_t>(a.maybe(1)), *pl = ptr_as<int32_t>(a.maybe(2));
   int32_t *psel = ptr_as<int32_t>(sel.t), *pplan = ptr_as<int32_t>(plan.t);
   void* st = stream();
   call("saap_select_buckets_planned", [&] {
@@ -554,7 +558,7 @@ struct Attend {
   int32_t S, Hq, d, Hkv, rows;
   void *pq, *pk, *pv;
   Out out, lse;
-  Attend(const Args& a, const Tensor& q, const Tensor& K, const Tensor& V, int i_dtype, int i_out, int i_lse)
+  Attend(const Args& a, const Tensor& q, const Tensor& K, const Tensor* V, int i_dtype, int i_out, int i_lse)
       : out(a, i_out, (want_dims(q, 3), want_dims(K, 4), at::IntArrayRef({q.size(0), q.size(1), q.size(2)})),
             a.dtype(i_dtype, at::kFloat), q),
         lse(a, i_lse, {q.size(0), q.size(1)}, at::kFloat, q) {
@@ -568,12 +572,12 @@ struct Attend {
 SAAP_FUNCTION(sparse_decode_attention) {
   SAAP_BEGIN(7, "q", "Ks", "Vs", "off", "ln", "selected", "scale", "mode", "out_dtype", "out", "lse", "ws")
   const Tensor &q = a.tensor(0), &ln = a.tensor(4), &sel = a.tensor(5);
-  Attend t(a, q, a.tensor(1), a.tensor(2), 8, 9, 10);
+  Attend t(a, q, a.tensor(1), a.maybe(2), 8, 9, 10);
   want_dims(ln, 3);
   want_dims(sel, 3);
   const int32_t B = size(ln, 2), nprobe = size(sel, 2), mode = a.integer(7, SAAP_GROUP_SUM), dt = dtype_code(q);
   const Ws ws(a, 11, q, SAAP_OP_SPARSE_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv, mode));
-  const int32_t *po = ptr_as<int32_t>(a.tensor(3)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
+  const int32_t *po = ptr_as<int32_t>(a.maybe(3)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
   const float scale = (float)a.real(6);
   void *out = ptr(t.out.t), *st = nullptr;
   float* lse = ptr_as<float>(t.lse.t);
@@ -591,13 +595,13 @@ SAAP_FUNCTION(sparse_decode_attention_fp8) {
   SAAP_BEGIN(9, "q", "K8", "V8", "kscale", "vscale", "off", "ln", "selected", "scale", "mode", "out_dtype", "out", "lse", "ws")
   const Tensor &q = a.tensor(0), &K8 = a.tensor(1), &V8 = a.tensor(2), &ln = a.tensor(6), &sel = a.tensor(7);
   want_fp8_cache(q, K8, V8);
-  Attend t(a, q, K8, V8, 10, 11, 12);
+  Attend t(a, q, K8, &V8, 10, 11, 12);
   want_dims(ln, 3);
   want_dims(sel, 3);
   const int32_t B = size(ln, 2), nprobe = size(sel, 2), mode = a.integer(9, SAAP_GROUP_SUM);
   const Ws ws(a, 13, q, SAAP_OP_SPARSE_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv, mode));
   const float *ks = ptr_as<float>(a.maybe(3)), *vs = ptr_as<float>(a.maybe(4));
-  const int32_t *po = ptr_as<int32_t>(a.tensor(5)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
+  const int32_t *po = ptr_as<int32_t>(a.maybe(5)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
   const float scale = (float)a.real(8);
   void* out = ptr(t.out.t);
   float* lse = ptr_as<float>(t.lse.t);
@@ -615,13 +619,13 @@ SAAP_FUNCTION(sparse_decode_attention_fp8) {
 SAAP_FUNCTION(windowed_decode_attention) {
   SAAP_BEGIN(8, "q", "Ks", "Vs", "off", "ln", "selected", "resident_run", "scale", "mode", "out_dtype", "out", "lse", "ws")
   const Tensor &q = a.tensor(0), &ln = a.tensor(4), &sel = a.tensor(5);
-  Attend t(a, q, a.tensor(1), a.tensor(2), 9, 10, 11);
+  Attend t(a, q, a.tensor(1), a.maybe(2), 9, 10, 11);
   want_dims(ln, 3);
   want_dims(sel, 3);
   const int32_t runs = size(ln, 2), nprobe = size(sel, 2), resident = a.integer(6), mode = a.integer(8, SAAP_GROUP_SUM);
   const int32_t dt = dtype_code(q);
   const Ws ws(a, 12, q, SAAP_OP_SPARSE_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv, mode));
-  const int32_t *po = ptr_as<int32_t>(a.tensor(3)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
+  const int32_t *po = ptr_as<int32_t>(a.maybe(3)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
   const float scale = (float)a.real(7);
   void* out = ptr(t.out.t);
   float* lse = ptr_as<float>(t.lse.t);
@@ -640,13 +644,13 @@ SAAP_FUNCTION(windowed_decode_attention_fp8) {
              "out", "lse", "ws")
   const Tensor &q = a.tensor(0), &K8 = a.tensor(1), &V8 = a.tensor(2), &ln = a.tensor(6), &sel = a.tensor(7);
   want_fp8_cache(q, K8, V8);
-  Attend t(a, q, K8, V8, 11, 12, 13);
+  Attend t(a, q, K8, &V8, 11, 12, 13);
   want_dims(ln, 3);
   want_dims(sel, 3);
   const int32_t runs = size(ln, 2), nprobe = size(sel, 2), resident = a.integer(8), mode = a.integer(10, SAAP_GROUP_SUM);
   const Ws ws(a, 14, q, SAAP_OP_SPARSE_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv, mode));
   const float *ks = ptr_as<float>(a.maybe(3)), *vs = ptr_as<float>(a.maybe(4));
-  const int32_t *po = ptr_as<int32_t>(a.tensor(5)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
+  const int32_t *po = ptr_as<int32_t>(a.maybe(5)), *pl = ptr_as<int32_t>(ln), *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr;
   const float scale = (float)a.real(9);
   void* out = ptr(t.out.t);
   float* lse = ptr_as<float>(t.lse.t);
@@ -664,7 +668,7 @@ SAAP_FUNCTION(windowed_decode_attention_fp8) {
 SAAP_FUNCTION(dense_decode_attention) {
   SAAP_BEGIN(4, "q", "K", "V", "scale", "off", "ln", "out_dtype", "out", "lse", "ws")
   const Tensor& q = a.tensor(0);
-  Attend t(a, q, a.tensor(1), a.tensor(2), 6, 7, 8);
+  Attend t(a, q, a.tensor(1), a.maybe(2), 6, 7, 8);
   const Tensor *off = a.maybe(4), *ln = a.maybe(5);
   if (ln) want_dims(*ln, 3);
   const int32_t B = ln ? size(*ln, 2) : 0, dt = dtype_code(q);
@@ -687,7 +691,7 @@ SAAP_FUNCTION(dense_decode_attention_fp8) {
   SAAP_BEGIN(6, "q", "K8", "V8", "kscale", "vscale", "scale", "off", "ln", "out_dtype", "out", "lse", "ws")
   const Tensor &q = a.tensor(0), &K8 = a.tensor(1), &V8 = a.tensor(2);
   want_fp8_cache(q, K8, V8);
-  Attend t(a, q, K8, V8, 8, 9, 10);
+  Attend t(a, q, K8, &V8, 8, 9, 10);
   const Tensor *off = a.maybe(6), *ln = a.maybe(7);
   if (ln) want_dims(*ln, 3);
   const int32_t B = ln ? size(*ln, 2) : 0;
@@ -710,16 +714,16 @@ SAAP_FUNCTION(dense_decode_attention_fp8) {
 SAAP_FUNCTION(select_attend) {
   SAAP_BEGIN(8, "logits", "q", "Ks", "Vs", "off", "ln", "nprobe", "scale", "out_dtype", "selected", "out", "lse", "ws",
              "resident_run")
-  const Tensor &logits = a.tensor(0), &q = a.tensor(1), &ln = a.tensor(5);
-  Attend t(a, q, a.tensor(2), a.tensor(3), 8, 10, 11);
+  const Tensor &q = a.tensor(1), &ln = a.tensor(5);
+  Attend t(a, q, a.tensor(2), a.maybe(3), 8, 10, 11);
   want_dims(ln, 3);
   const int32_t nprobe = a.integer(6), resident = a.integer(13, -1), dt = dtype_code(q);
   // with a resident run the index has one run more than the logits have buckets
   const int32_t B = size(ln, 2) - (resident >= 0 ? 1 : 0);
   Out sel(a, 9, {t.S, t.Hkv, nprobe}, at::kInt, q);
   const Ws ws(a, 12, q, SAAP_OP_SPARSE_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv));
-  const float* pg = ptr_as<float>(logits);
-  const int32_t *po = ptr_as<int32_t>(a.tensor(4)), *pl = ptr_as<int32_t>(ln);
+  const float* pg = ptr_as<float>(a.maybe(0));
+  const int32_t *po = ptr_as<int32_t>(a.maybe(4)), *pl = ptr_as<int32_t>(ln);
   int32_t* ps = nprobe > 0 ? ptr_as<int32_t>(sel.t) : nullptr;
   const float scale = (float)a.real(7);
   void* out = ptr(t.out.t);
@@ -743,15 +747,15 @@ SAAP_FUNCTION(select_attend) {
 SAAP_FUNCTION(select_attend_fp8) {
   SAAP_BEGIN(10, "logits", "q", "K8", "V8", "kscale", "vscale", "off", "ln", "nprobe", "scale", "out_dtype", "selected", "out",
              "lse", "ws")
-  const Tensor &logits = a.tensor(0), &q = a.tensor(1), &K8 = a.tensor(2), &V8 = a.tensor(3), &ln = a.tensor(7);
+  const Tensor &q = a.tensor(1), &K8 = a.tensor(2), &V8 = a.tensor(3), &ln = a.tensor(7);
   want_fp8_cache(q, K8, V8);
-  Attend t(a, q, K8, V8, 10, 12, 13);
+  Attend t(a, q, K8, &V8, 10, 12, 13);
   want_dims(ln, 3);
   const int32_t nprobe = a.integer(8), B = size(ln, 2);
   Out sel(a, 11, {t.S, t.Hkv, nprobe}, at::kInt, q);
   const Ws ws(a, 14, q, SAAP_OP_SPARSE_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv));
-  const float *pg = ptr_as<float>(logits), *ks = ptr_as<float>(a.maybe(4)), *vs = ptr_as<float>(a.maybe(5));
-  const int32_t *po = ptr_as<int32_t>(a.tensor(6)), *pl = ptr_as<int32_t>(ln);
+  const float *pg = ptr_as<float>(a.maybe(0)), *ks = ptr_as<float>(a.maybe(4)), *vs = ptr_as<float>(a.maybe(5));
+  const int32_t *po = ptr_as<int32_t>(a.maybe(6)), *pl = ptr_as<int32_t>(ln);
   int32_t* ps = nprobe > 0 ? ptr_as<int32_t>(sel.t) : nullptr;
   const float scale = (float)a.real(9);
   void* out = ptr(t.out.t);
@@ -769,12 +773,11 @@ SAAP_FUNCTION(select_attend_fp8) {
 SAAP_FUNCTION(planned_decode_attention) {
   SAAP_BEGIN(6, "q", "Ks", "Vs", "plan", "nruns", "scale", "mode", "out_dtype", "out", "lse", "ws")
   const Tensor& q = a.tensor(0);
-  Attend t(a, q, a.tensor(1), a.tensor(2), 7, 8, 9);
+  Attend t(a, q, a.tensor(1), a.maybe(2), 7, 8, 9);
   const int32_t nruns = a.integer(4), mode = a.integer(6, SAAP_GROUP_SUM);
-  a.tensor(3);
-  const Out plan = plan_buffer(a, 3, plan_ints(t.S, t.Hq, t.Hkv, nruns, mode), q);
+  const Tensor* plan = given_plan(a, 3, plan_ints(t.S, t.Hq, t.Hkv, nruns, mode));
   const Ws ws(a, 10, q, SAAP_OP_PLANNED_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv, mode));
-  const int32_t *pp = ptr_as<int32_t>(plan.t), dt = dtype_code(q), od = t.out_code();
+  const int32_t *pp = ptr_as<int32_t>(plan), dt = dtype_code(q), od = t.out_code();
   const float scale = (float)a.real(5);
   void* out = ptr(t.out.t);
   float* lse = ptr_as<float>(t.lse.t);
@@ -791,13 +794,12 @@ SAAP_FUNCTION(planned_decode_attention_fp8) {
   SAAP_BEGIN(8, "q", "K8", "V8", "kscale", "vscale", "plan", "nruns", "scale", "mode", "out_dtype", "out", "lse", "ws")
   const Tensor &q = a.tensor(0), &K8 = a.tensor(1), &V8 = a.tensor(2);
   want_fp8_cache(q, K8, V8);
-  Attend t(a, q, K8, V8, 9, 10, 11);
+  Attend t(a, q, K8, &V8, 9, 10, 11);
   const int32_t nruns = a.integer(6), mode = a.integer(8, SAAP_GROUP_SUM);
-  a.tensor(5);
-  const Out plan = plan_buffer(a, 5, plan_ints(t.S, t.Hq, t.Hkv, nruns, mode), q);
+  const Tensor* plan = given_plan(a, 5, plan_ints(t.S, t.Hq, t.Hkv, nruns, mode));
   const Ws ws(a, 12, q, SAAP_OP_PLANNED_DECODE_ATTENTION, shape_of(t.S, t.Hq, t.Hkv, mode));
   const float *ks = ptr_as<float>(a.maybe(3)), *vs = ptr_as<float>(a.maybe(4));
-  const int32_t *pp = ptr_as<int32_t>(plan.t), od = t.out_code();
+  const int32_t *pp = ptr_as<int32_t>(plan), od = t.out_code();
   const float scale = (float)a.real(7);
   void* out = ptr(t.out.t);
   float* lse = ptr_as<float>(t.lse.t);
@@ -813,7 +815,7 @@ SAAP_FUNCTION(planned_decode_attention_fp8) {
 SAAP_FUNCTION(prefill_sparse_attention) {
   SAAP_BEGIN(13, "q", "K", "V", "Ks", "Vs", "off", "ln", "idx", "selected", "pos0", "n_sink", "n_recent", "scale", "out_dtype",
              "out", "lse", "ws")
-  const Tensor &q = a.tensor(0), &K = a.tensor(1), &V = a.tensor(2), &Ks = a.tensor(3), &Vs = a.tensor(4), &ln = a.tensor(6);
+  const Tensor &q = a.tensor(0), &K = a.tensor(1), &Ks = a.tensor(3), &ln = a.tensor(6);
   const Tensor& sel = a.tensor(8);
   want_dims(q, 4);
   want_dims(K, 4);
@@ -826,9 +828,9 @@ SAAP_FUNCTION(prefill_sparse_attention) {
   saap_shape sh = shape_of(S, Hq, Hkv);
   sh.N = Tq; sh.nprobe = nprobe; sh.dtype = dtype_code(q);
   const Ws ws(a, 16, q, SAAP_OP_PREFILL_SPARSE_ATTENTION, sh);
-  void *pq = ptr(q), *pk = ptr(K), *pv = ptr(V), *pks = ptr(Ks), *pvs = ptr(Vs), *po = ptr(out.t);
-  const int32_t *poff = ptr_as<int32_t>(a.tensor(5)), *pl = ptr_as<int32_t>(ln), *pi = ptr_as<int32_t>(a.tensor(7));
-  const int32_t *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr, *pp = ptr_as<int32_t>(a.tensor(9));
+  void *pq = ptr(q), *pk = ptr(K), *pv = ptr(a.maybe(2)), *pks = ptr(Ks), *pvs = ptr(a.maybe(4)), *po = ptr(out.t);
+  const int32_t *poff = ptr_as<int32_t>(a.maybe(5)), *pl = ptr_as<int32_t>(ln), *pi = ptr_as<int32_t>(a.maybe(7));
+  const int32_t *ps = nprobe > 0 ? ptr_as<int32_t>(sel) : nullptr, *pp = ptr_as<int32_t>(a.maybe(9));
   float* plse = ptr_as<float>(lse.t);
   const float scale = (float)a.real(12);
   const int32_t od = dtype_code(out.t), dt = dtype_code(q);
@@ -859,10 +861,10 @@ struct NewKeys {
     want_dims(ct, 3);
     want_dims(it, 3);
     S = size(xt, 0); Hkv = size(xt, 1); d = size(xt, 2); B = size(ct, 1); Ncap = size(it, 2);
-    x = ptr(xt); k = ptr(a.tensor(1)); v = ptr(a.tensor(2)); cent = ptr(ct);
+    x = ptr(xt); k = ptr(a.maybe(1)); v = ptr(a.maybe(2)); cent = ptr(ct);
     pos = ptr_as<int32_t>(a.maybe(3)); bias = ptr_as<float>(a.maybe(5));
-    off = ptr_as<int32_t>(a.tensor(6)); len = ptr_as<int32_t>(a.tensor(7)); idx = ptr_as<int32_t>(it);
-    K = ptr(a.tensor(9)); V = ptr(a.tensor(10));
+    off = ptr_as<int32_t>(a.maybe(6)); len = ptr_as<int32_t>(a.maybe(7)); idx = ptr_as<int32_t>(it);
+    K = ptr(a.maybe(9)); V = ptr(a.maybe(10));
     if (fp8) {
       kscale = ptr_as<float>(a.maybe(11));
       vscale = ptr_as<float>(a.maybe(12));
@@ -922,7 +924,7 @@ SAAP_FUNCTION(window_push) {
   const NewKeys n(a, false);
   Out flag = flag_buffer(a, 14, x), ids(a, 15, {n.S, n.Hkv}, at::kInt, x);
   const Ws ws(a, 16, x, SAAP_OP_WINDOW_PUSH, n.shape());
-  int32_t *pr = ptr_as<int32_t>(a.tensor(11)), *pi = ptr_as<int32_t>(ids.t), *pf = ptr_as<int32_t>(flag.t);
+  int32_t *pr = ptr_as<int32_t>(a.maybe(11)), *pi = ptr_as<int32_t>(ids.t), *pf = ptr_as<int32_t>(flag.t);
   const int32_t n_sink = a.integer(12), n_recent = a.integer(13), dt = dtype_code(x);
   void* st = stream();
   call("saap_window_push", [&] {
@@ -940,7 +942,7 @@ SAAP_FUNCTION(window_push_fp8) {
   const NewKeys n(a, true);
   Out flag = flag_buffer(a, 16, x), ids(a, 17, {n.S, n.Hkv}, at::kInt, x);
   const Ws ws(a, 18, x, SAAP_OP_WINDOW_PUSH, n.shape());
-  int32_t *pr = ptr_as<int32_t>(a.tensor(13)), *pi = ptr_as<int32_t>(ids.t), *pf = ptr_as<int32_t>(flag.t);
+  int32_t *pr = ptr_as<int32_t>(a.maybe(13)), *pi = ptr_as<int32_t>(ids.t), *pf = ptr_as<int32_t>(flag.t);
   const int32_t n_sink = a.integer(14), n_recent = a.integer(15);
   void* st = stream();
   call("saap_window_push_fp8", [&] {

@@ -63,6 +63,51 @@ def test_names_positions_and_outputs_passed_in():
 
 
 @pytest.mark.gpu
+def test_a_missing_pointer_is_the_librarys_error():
+    """Arguments that are only passed on: None is the library's invalid argument, whatever the call."""
+    S, Hkv, G, N, B, nprobe = 1, 2, 4, 64, 16, 3
+    bf16 = dict(dtype=torch.bfloat16, device=DEV)
+    i32 = dict(dtype=torch.int32, device=DEV)
+    q, K, cent = torch.zeros(S, Hkv * G, 128, **bf16), torch.zeros(S, Hkv, N, 128, **bf16), torch.zeros(Hkv, B, 128, **bf16)
+    K8, one = torch.zeros(S, Hkv, N, 128, dtype=torch.uint8, device=DEV), torch.ones(S, Hkv, device=DEV)
+    ids, idx = torch.zeros(S, Hkv, N, **i32), torch.zeros(S, Hkv, N, **i32)
+    off, ln = torch.zeros(S, Hkv, B + 1, **i32), torch.zeros(S, Hkv, B, **i32)
+    sel, logits, new = torch.zeros(S, Hkv, nprobe, **i32), torch.zeros(S, Hkv * G, B, device=DEV), K[:, :, 0].contiguous()
+    pos = torch.zeros(S, **i32)
+    plan = saap.build_visit_plan(sel, off, ln, Hkv * G)
+    calls = [
+        ("build_bucket_index", (ids, K, K, B), (0, 2)),
+        ("build_windowed_index", (ids, K, K, B, 2, 1, 8), (0, 2)),
+        ("quantize_kv", (K, K), (1,)),
+        ("build_visit_plan", (sel, off, ln, Hkv * G), (1,)),
+        ("select_buckets_planned", (logits, off, ln, Hkv, nprobe), (1, 2)),
+        ("sparse_decode_attention", (q, K, K, off, ln, sel, 0.1), (2, 3)),
+        ("windowed_decode_attention", (q, K, K, off, ln, sel, -1, 0.1), (2, 3)),
+        ("dense_decode_attention", (q, K, K, 0.1), (2,)),
+        ("select_attend", (logits, q, K, K, off, ln, nprobe, 0.1), (0, 3, 4)),
+        ("planned_decode_attention", (q, K, K, plan, nprobe, 0.1), (2, 3)),
+        ("sparse_decode_attention_fp8", (q, K8, K8, one, one, off, ln, sel, 0.1), (3, 4, 5)),
+        ("windowed_decode_attention_fp8", (q, K8, K8, one, one, off, ln, sel, -1, 0.1), (3, 4, 5)),
+        ("dense_decode_attention_fp8", (q, K8, K8, one, one, 0.1), (3, 4)),
+        ("select_attend_fp8", (logits, q, K8, K8, one, one, off, ln, nprobe, 0.1), (0, 4, 5, 6)),
+        ("planned_decode_attention_fp8", (q, K8, K8, one, one, plan, nprobe, 0.1), (3, 4, 5)),
+        ("prefill_sparse_attention", (q.view(S, 1, Hkv * G, 128), K, K, K, K, off, ln, idx, sel.view(S, Hkv, 1, nprobe),
+                                      pos, 1, 8, 0.1), (2, 4, 5, 7, 9)),
+        ("append_keys", (new, new, new, pos, cent, None, off, ln, idx, K, K), (1, 2, 6, 7, 9, 10)),
+        ("append_keys_fp8", (new, new, new, pos, cent, None, off, ln, idx, K8, K8, one, one), (6, 7, 9, 10, 11, 12)),
+        ("window_push", (new, new, new, pos, cent, None, off, ln, idx, K, K, ids, 1, 8), (1, 2, 6, 7, 9, 10, 11)),
+        ("window_push_fp8", (new, new, new, pos, cent, None, off, ln, idx, K8, K8, one, one, ids, 1, 8), (6, 7, 9, 10, 11, 12, 13)),
+    ]
+    for name, args, pointers in calls:
+        for i in pointers:
+            with pytest.raises(saap.SaapError) as e:
+                getattr(saap, name)(*args[:i], None, *args[i + 1:])
+            assert e.value.status == -1, (name, i)
+            with pytest.raises(TypeError):
+                getattr(saap, name)(*args[:i], [1], *args[i + 1:])
+
+
+@pytest.mark.gpu
 def test_every_stream_has_its_own_workspace_and_graphs_have_theirs():
     """The default workspace: one per stream, a zeroed header each, kept while it is large enough; a capture takes the
     one that the calls before it used, which no later eager call gets."""
