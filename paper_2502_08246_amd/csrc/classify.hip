@@ -351,7 +351,8 @@ mlp_out_rows_kernel(const bf16_t* __restrict__ planes, const bf16_t* __restrict_
   const int wm = wave / WN * 32, wn = wave % WN * (32 * TN);
 
   struct Staged { u32x4_t h[HL], w[WL]; };
-  // rows and hidden units past the end repeat valid ones; stash clears the units of h, which clears their products
+  // rows and hidden units past the end repeat valid ones; stash clears the units of both operands (zero times an infinite
+  // weight is no zero)
   auto fetch = [&](Staged& g, int c0) {
 #pragma unroll
     for (int i = 0; i < HL; ++i) {
@@ -367,16 +368,16 @@ mlp_out_rows_kernel(const bf16_t* __restrict__ planes, const bf16_t* __restrict_
   auto stash = [&](const Staged& g, int buf, int c0) {
     bf16_t* s_h = s_all + buf * kBuf;
     bf16_t* s_w = s_h + 3 * BM * kRowsPitch;
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int i = 0; i < HL; ++i) {
       const int q = tid + i * NT, pc = q % kPieces * 8;
-      const u32x4_t zero = {0u, 0u, 0u, 0u};
       *reinterpret_cast<u32x4_t*>(s_h + q / kPieces * kRowsPitch + pc) = c0 + pc < sh.hidden ? g.h[i] : zero;
     }
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
-      const int q = tid + i * NT;
-      *reinterpret_cast<u32x4_t*>(s_w + q / kPieces * kRowsPitch + q % kPieces * 8) = g.w[i];
+      const int q = tid + i * NT, pc = q % kPieces * 8;
+      *reinterpret_cast<u32x4_t*>(s_w + q / kPieces * kRowsPitch + pc) = c0 + pc < sh.hidden ? g.w[i] : zero;
     }
   };
 
@@ -453,12 +454,17 @@ __device__ __forceinline__ f32x4_t mfma_f32_rows(const float* a, const float* b,
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kDeep; ++u) {
-      // past the end a zero operand; no branch, into which the loads would sink
+      // past the end zeros for both operands (zero times an infinite weight is no zero); no branch, into which the loads
+      // would sink
       const bool in = k + 16 * u < k1;
       av[u].x = in ? av[u].x : 0.f;
       av[u].y = in ? av[u].y : 0.f;
       av[u].z = in ? av[u].z : 0.f;
       av[u].w = in ? av[u].w : 0.f;
+      bv[u].x = in ? bv[u].x : 0.f;
+      bv[u].y = in ? bv[u].y : 0.f;
+      bv[u].z = in ? bv[u].z : 0.f;
+      bv[u].w = in ? bv[u].w : 0.f;
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].x, bv[u].x, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].y, bv[u].y, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].z, bv[u].z, acc, 0, 0, 0);
