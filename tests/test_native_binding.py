@@ -110,7 +110,7 @@ def test_a_missing_pointer_is_the_librarys_error():
 @pytest.mark.gpu
 def test_every_stream_has_its_own_workspace_and_graphs_have_theirs():
     """The default workspace: one per stream, a zeroed header each, kept while it is large enough; a capture takes the
-    one that the calls before it used, which no later eager call gets."""
+    one that the calls before it used, which no later eager call gets, or the one of an earlier capture."""
     here = saap.workspace(1 << 20, DEV)
     assert saap.workspace(0, DEV).data_ptr() == here.data_ptr()
     side = torch.cuda.Stream()
@@ -127,9 +127,15 @@ def test_every_stream_has_its_own_workspace_and_graphs_have_theirs():
         inside = saap.workspace(0, DEV).data_ptr()
         with pytest.raises(RuntimeError):
             saap.workspace(1 << 40, DEV)                       # a capture cannot make one
-    assert inside == here.data_ptr()
     after = saap.workspace(0, DEV).data_ptr()
-    assert after not in (inside, there.data_ptr())
+    if inside == here.data_ptr():                              # the process's first capture took this stream's
+        assert after not in (inside, there.data_ptr())
+    else:                                                      # an earlier capture's serves all graphs
+        assert after == here.data_ptr() and inside != there.data_ptr()
+    again = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(again):
+        saap.select_buckets_from_logits(logits, 2, 5)
+        assert saap.workspace(0, DEV).data_ptr() == inside
     with torch.cuda.stream(side):
         assert saap.workspace(0, DEV).data_ptr() == there.data_ptr()
     for _ in range(3):
