@@ -535,7 +535,7 @@ int32_t saap_bucket_attention_mass(const void* q, const void* Ksorted,
  * bucket_attention_mass_batch -- saap_bucket_attention_mass for a training batch: R queries per
  * (sequence, KV head) instead of the G heads of a decode step (Section 4 "Query assignment
  * function": the rows of A * H_k for the sampled queries of a prompt).  The scores run on the
- * matrix cores, so the keys are read once per 128 queries.
+ * matrix cores, and the keys are read once per 128 or 256 queries.  The same inputs give the same bits.
  *   q [S,Hkv,R,d] bf16; Ksorted [S,Hkv,Ncap,d] bf16; off [S,Hkv,B+1], len [S,Hkv,B]
  *   mass [S,Hkv,R,B] fp32, out; lse [S,Hkv,R] fp32 or NULL, out
  * Workspace: SAAP_OP_BUCKET_ATTENTION_MASS_BATCH (S, Hkv, N = R, B): 8 bytes per (query, bucket).

@@ -150,11 +150,12 @@ def workspace(nbytes: int, device, asked_for: bool = True) -> torch.Tensor:
 
     Every stream has its own, zero-filled when it is made (which is what the header of arrival counters needs) and
     replaced by a larger one on demand: calls on different streams may run at the same time and never meet in one.  Pass
-    it to calls on the stream it was asked for on.  One that a program has asked for is never freed.  A HIP graph holds the RAW ADDRESS of the buffer that its calls were
-    given: a capture takes over the buffer that the eager calls before it have made, all graphs of a device share that
-    one (replay them one after the other, or capture with ws=), no eager call uses it again and it is never freed.
-    Growing while the current stream is capturing is refused (allocating there would also break the capture): run the
-    call once eagerly first, or pass ws= explicitly."""
+    it to calls on the stream it was asked for on.  One that a program has asked for is never freed.
+
+    A HIP graph holds the RAW ADDRESS of the buffer that its calls were given: a capture takes over the buffer that the
+    eager calls before it have made, all graphs of a device share that one (replay them one after the other, or capture
+    with ws=), no eager call uses it again and it is never freed.  Growing while the current stream is capturing is
+    refused (allocating there would also break the capture): run the call once eagerly first, or pass ws= explicitly."""
     device = torch.device(device)
     if device.type != "cuda":
         raise ValueError("SAAP workspaces live in GPU memory; there is no CPU path")

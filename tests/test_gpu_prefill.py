@@ -1,5 +1,6 @@
-"""GPU parity of prefill-time sparse attention (one visit plan per prompt token and KV head, then the planned
-attention) against the oracle's position-based definition, which knows neither index nor plans."""
+"""GPU parity of prefill-time sparse attention (bf16 blocks on shared key tiles; fp32, small blocks and small workspaces by
+one visit plan per prompt token and KV head) against the oracle's position-based definition, which knows neither index nor
+plans."""
 import math
 
 import numpy as np
