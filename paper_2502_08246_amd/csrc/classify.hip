@@ -332,7 +332,8 @@ constexpr int kManyRows = 64;                  // rows per weight set from which
 constexpr int kRowsChunk = 64;                 // hidden units per pass
 constexpr int kRowsPitch = kRowsChunk + 8;     // LDS row pitch in elements (144 bytes: conflict-free 16-byte reads)
 
-template <int WM, int WN, int TN>
+// PARTIAL: the hidden units do not fill their last chunk.
+template <int WM, int WN, int TN, bool PARTIAL>
 __global__ void __launch_bounds__(WM * WN * 64)
 mlp_out_rows_kernel(const bf16_t* __restrict__ planes, const bf16_t* __restrict__ W2, const float* __restrict__ b2,
                     float* __restrict__ scores, MlpShape sh) {
@@ -372,12 +373,12 @@ mlp_out_rows_kernel(const bf16_t* __restrict__ planes, const bf16_t* __restrict_
 #pragma unroll
     for (int i = 0; i < HL; ++i) {
       const int q = tid + i * NT, pc = q % kPieces * 8;
-      *reinterpret_cast<u32x4_t*>(s_h + q / kPieces * kRowsPitch + pc) = c0 + pc < sh.hidden ? g.h[i] : zero;
+      *reinterpret_cast<u32x4_t*>(s_h + q / kPieces * kRowsPitch + pc) = !PARTIAL || c0 + pc < sh.hidden ? g.h[i] : zero;
     }
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
       const int q = tid + i * NT, pc = q % kPieces * 8;
-      *reinterpret_cast<u32x4_t*>(s_w + q / kPieces * kRowsPitch + pc) = c0 + pc < sh.hidden ? g.w[i] : zero;
+      *reinterpret_cast<u32x4_t*>(s_w + q / kPieces * kRowsPitch + pc) = !PARTIAL || c0 + pc < sh.hidden ? g.w[i] : zero;
     }
   };
 
@@ -606,13 +607,16 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
     auto tiles = [&](int bm, int bn) { return (long long)((sh.rows_per_set + bm - 1) / bm) * ((B + bn - 1) / bn) * Hw; };
     auto launch_rows = [&](auto wm, auto wn, auto tn) -> int32_t {
       constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TN = decltype(tn)::value;
-      constexpr auto kernel = mlp_out_rows_kernel<WM, WN, TN>;
       constexpr size_t bytes = (size_t)2 * (3 * 32 * WM + 32 * WN * TN) * kRowsPitch * sizeof(bf16_t);
-      if (!allow_lds<kernel>(bytes)) return SAAP_HIP_ERROR;
-      hipLaunchKernelGGL(kernel, dim3((unsigned)Hw, (unsigned)((sh.rows_per_set + 32 * WM - 1) / (32 * WM)),
-                                      (unsigned)((B + 32 * WN * TN - 1) / (32 * WN * TN))), dim3(WM * WN * 64), bytes, hs,
-                         static_cast<const bf16_t*>(hbuf), static_cast<const bf16_t*>(W2), b2, scores, sh);
-      return SAAP_OK;
+      auto launch = [&](auto partial) -> int32_t {
+        constexpr auto kernel = mlp_out_rows_kernel<WM, WN, TN, decltype(partial)::value>;
+        if (!allow_lds<kernel>(bytes)) return SAAP_HIP_ERROR;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)Hw, (unsigned)((sh.rows_per_set + 32 * WM - 1) / (32 * WM)),
+                                        (unsigned)((B + 32 * WN * TN - 1) / (32 * WN * TN))), dim3(WM * WN * 64), bytes, hs,
+                           static_cast<const bf16_t*>(hbuf), static_cast<const bf16_t*>(W2), b2, scores, sh);
+        return SAAP_OK;
+      };
+      return hidden % kRowsChunk != 0 ? launch(std::true_type{}) : launch(std::false_type{});
     };
     typedef std::integral_constant<int, 1> one;
     typedef std::integral_constant<int, 2> two;
