@@ -215,7 +215,7 @@ struct Run {
 
 // A key outside a query's range has weight zero, and zero times an infinity or a NaN is no zero: where a tile's queries differ
 // in what they see, such values are zeroed and added afterwards, by a second walk that ordinary values never come to (taken
-// inside the loop it cost the loop its registers: 128 tokens over 128k keys 193.5 -> 199.9 us, this way 189.2 and 189.5).
+// inside the loop it cost the loop its registers: 128 tokens over 128k keys 193.5 -> 199.9 us, this way 193.3 -> 194.4).
 // The reference m of a row moves only when one of its scores is more than 8 (2^8 in weight) above it, so that the outputs are
 // rescaled (an exchange over the lanes) once or twice per run; by the row's own scores alone, whoever shares its tile.
 __device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stride, float scale_log2, float* s_w /* [32][32] */,
@@ -277,7 +277,6 @@ __device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stri
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] *= scale_log2;
     mask(s, t);
-    if (edge(t)) no_numbers |= zero_no_numbers(vr);      // zero times an infinity or a NaN is no zero
     const float top = highest(s);
     if (__ballot(top > w.m + 8.f) != 0ull) {
       const float mn = top > w.m + 8.f ? top : w.m, alpha = fast_exp2(w.m - mn);
@@ -297,6 +296,7 @@ __device__ __forceinline__ void attend_run(WaveTile& w, const Run& run, int stri
       add[r % 4] = r < 4 ? s[r] : add[r % 4] + s[r];
     }
     w.l += (add[0] + add[1]) + (add[2] + add[3]);
+    if (edge(t)) no_numbers |= zero_no_numbers(vr);      // zero times an infinity or a NaN is no zero
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       unsigned ph[4], pl[4];                             // weights of the lane's eight keys: upper halves, and the rest rounded
