@@ -10,17 +10,19 @@
 // the second on each tensor.  All arithmetic is fp32, every sum is taken by one thread or one
 // workgroup in a fixed order (no atomics), so a step is reproducible bit for bit.
 //
-// The five matrix products run on the matrix cores (v_mfma_f32_32x32x2_f32), bound by their fp32 rate (154 TFLOP/s in a
-// large product on this card).  fp32 matrix instructions take the vector units' time, so that every vector instruction per
-// slice costs them: operands are loaded 16 bytes at a time along their contiguous dimension, whichever operand is transposed,
-// at offsets made once, and read back from LDS four values of k at a time, double buffered with the next two slices' loads in
-// flight.  Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias
-// gradients are the column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as
-// they load it.
-// 8 weight sets, 1000 rows, 128 -> 512 -> 1024, the five products and two sums: 710 us with element loads, every slice's
-// loads waited for and the sums in launches of their own; 315 us with 64x64 tiles and address arithmetic in every slice; 281 us
-// now (107 of the 154 TFLOP/s).  What is left is the start and the stores of a product, 13 us each of 88, which nothing covers:
-// all tiles of a product run at once.
+// The five matrix products run on the matrix cores.  fp32 matrix instructions reach 154 TFLOP/s in a large product on this card
+// and take the vector units' time; bfloat16 ones do 16 times the work in the same cycles.  So the operands of a large product
+// are split into three bfloat16 each on their way to LDS (nothing is lost: 3 x 8 bits) and six products of those make one fp32
+// product, the five small ones summed apart: the gradients' error against float64 is 0.6 to 1.0 times that of fp32 matrix
+// instructions (8 x 1000 rows, 512 hidden units, 1024 buckets: dW1 3.8e-7 instead of 6.2e-7, dW2 3.2e-7 instead of 4.7e-7).
+// Operands with values that a bfloat16 does not hold (infinities, NaN, above 3.39e38) make the tile not finite; it is then
+// done again with fp32 instructions.  The first product stays in fp32, and so do results of few tiles (gemm_split_kernel).
+// Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
+// column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
+// 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 59 now (870 TFLOP/s of
+// bfloat16 products; a loop of nothing but these instructions on such data runs at 1.8 GHz: 27 us); all five and the two sums
+// 281 us before, 227 now.  What is left is the start and the stores of a product, 12 us that nothing covers (all tiles of a
+// product run at once), and the slices' barriers.
 #include <algorithm>
 
 #include "common.h"
@@ -45,52 +47,123 @@ struct GemmArgs {
   int m_first, n_first;                // gemm_split_kernel: where the launch's first tile starts
 };
 
-// One thread's share of a slice of an operand, R rows by SL values of k, four elements a piece, on its way to LDS.  KC: the
-// operand's contiguous dimension is k, LDS holds [row][k] and a lane reads four k at a time; else it is the row dimension, LDS
-// holds [k][row].  Either way product (g, j) of a slice sums k = 8 g + 4 (lane / 32) + j.  The pitches make both reads free of
-// bank conflicts.  VEC: rows start on 16 bytes and are whole pieces long.
-template <bool KC, bool VEC, int R, int SL>
+// fp32 values as sums of three bfloat16 each, to 24 bits and more: the nearest one, the nearest to what that leaves, and the
+// nearest to what is left then.  This takes the values' next plane, as pairs, and leaves the rest.
+template <int E>
+__device__ __forceinline__ void take_plane(float* rest, uint32_t* u) {
+#pragma unroll
+  for (int e = 0; e < E / 2; ++e) {
+    u[e] = pack_bf16(rest[2 * e], rest[2 * e + 1]);
+    rest[2 * e] -= bf16_lo(u[e]);
+    rest[2 * e + 1] -= bf16_hi(u[e]);
+  }
+}
+// The six products of planes that make a product of fp32 values, the smallest first; those of planes 1 and 2, and of 2 and 2,
+// are below 2^-26 of the whole.
+constexpr int kPlaneA[6] = {2, 0, 1, 1, 0, 0}, kPlaneB[6] = {0, 2, 1, 0, 1, 0};
+
+// One thread's share of a slice of an operand, R rows by 16 values of k, on its way to LDS.  LDS holds the
+// three planes, each [k / 8][row][k % 8]; a lane of the matrix cores takes eight values of k.  KC: the
+// operand's contiguous dimension is k (VEC: rows start on 16 bytes), else it is the row dimension (a wave loads 64 neighbouring
+// rows at one k).  The pitches keep reads and writes free of bank conflicts.
+constexpr int kSlice = 16;
+// (rows x K floats from p on, fewer than 2^29; no load relies on the buffer's bounds)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_buffer(const float* p, int rows, int K) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, rows * K * 4, 0x00027000);
+}
+template <bool KC, bool VEC, int R>
+struct PlaneLoader {
+  static constexpr int E = R * kSlice / kGemmThreads;     // consecutive values of k of one row: 8 or 4
+  static constexpr int kPitch = R + (KC ? 4 : 0), kPlane = kSlice / 8 * kPitch, kUnits = 3 * kPlane;   // units of 16 bytes
+  float r[E];
+  static __device__ __forceinline__ int row() { return KC ? threadIdx.x / (kSlice / E) : threadIdx.x % R; }
+  static __device__ __forceinline__ int first_k() { return E * (KC ? threadIdx.x % (kSlice / E) : threadIdx.x / R); }
+  // Byte offset of the thread's values from the slice's first: all that a lane adds to an address that the whole workgroup
+  // shares.  Rows past the end repeat the last one and are not stored.
+  static __device__ __forceinline__ int offset(int t0, int n_t, int K) {
+    const int t = min(t0 + row(), n_t - 1);
+    return 4 * (KC ? t * K + first_k() : first_k() * n_t + t);
+  }
+  // The slice from k0 on, or the last 16 values of k where it would reach past the end.
+  __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t x, int at, int k0, int n_t, int K) {
+    k0 = min(k0, K - kSlice);
+    if constexpr (KC && VEC) {
+#pragma unroll
+      for (int e = 0; e < E; e += 4) {
+        const u32x4_t u = __builtin_amdgcn_raw_buffer_load_b128(x, at + 4 * e, 4 * k0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[e + j] = __uint_as_float(u[j]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        r[e] = __uint_as_float(KC ? __builtin_amdgcn_raw_buffer_load_b32(x, at + 4 * e, 4 * k0, 0)
+                                  : __builtin_amdgcn_raw_buffer_load_b32(x, at, 4 * (k0 + e) * n_t, 0));
+    }
+  }
+  __device__ __forceinline__ void clear_from(int k) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) r[e] = first_k() + e < k ? r[e] : 0.f;
+  }
+  __device__ __forceinline__ void stash(uint4* s) const {
+    float rest[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) rest[e] = r[e];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      uint32_t u[E / 2];
+      take_plane<E>(rest, u);
+      uint4* at = s + p * kPlane + first_k() / 8 * kPitch + row();
+      if constexpr (E == 8) *at = make_uint4(u[0], u[1], u[2], u[3]);
+      else reinterpret_cast<uint2*>(at)[first_k() / 4 % 2] = make_uint2(u[0], u[1]);
+    }
+  }
+  __device__ __forceinline__ float sum() const {
+    float t = (r[0] + r[1]) + (r[2] + r[3]);
+    if constexpr (E == 8) t += (r[4] + r[5]) + (r[6] + r[7]);
+    return t;
+  }
+  static __device__ __forceinline__ bf16x8_t read(const uint4* s, int plane, int row, int kg) {
+    return __builtin_bit_cast(bf16x8_t, s[plane * kPlane + kg * kPitch + row]);
+  }
+};
+
+// The same in fp32 for operands whose contiguous dimension is k: R rows by SL values of k, four a piece.  LDS holds [row][k], a
+// lane reads four k at a time; product (g, j) of a slice sums k = 8 g + 4 (lane / 32) + j.
+template <bool VEC, int R, int SL>
 struct SliceLoader {
-  static constexpr int kPieces = R * SL / 4 / kGemmThreads, kPitch = KC ? SL + 4 : R + 8, kFloats = KC ? R * (SL + 4) : SL * (R + 8);
+  static constexpr int kPieces = R * SL / 4 / kGemmThreads, kPitch = SL + 4, kFloats = R * kPitch;
   float4 r[kPieces];
-  // piece i of this thread: element (row t, first of four k) or (first of four rows t, k) of the slice
+  // piece i of this thread: row t, four values from k on
   static __device__ __forceinline__ void place(int i, int& t, int& k) {
     const int q = threadIdx.x + i * kGemmThreads;
-    if constexpr (KC) { k = q % (SL / 4) * 4; t = q / (SL / 4); } else { t = q % (R / 4) * 4; k = q / (R / 4); }
+    k = q % (SL / 4) * 4;
+    t = q / (SL / 4);
   }
-  // Byte offsets of the pieces from the slice's first value (Offsets): all that a lane adds to an address that the whole workgroup shares.
   // (fp32 matrix products and ordinary vector instructions take the same units by turns: address arithmetic per slice cost a
-  // fifth of the products' time.)  Rows past the end repeat the last one and are not stored.
-  struct Offsets { unsigned at[VEC ? kPieces : 4 * kPieces]; };
+  // fifth of the products' time.)
+  struct Offsets { unsigned at[kPieces]; };
   static __device__ __forceinline__ Offsets offsets(int t0, int n_t, int K) {
     Offsets o;
 #pragma unroll
     for (int i = 0; i < kPieces; ++i) {
       int t, k;
       place(i, t, k);
-      if constexpr (VEC) {                                // ld is a multiple of 4: a piece is inside a row or outside
-        o.at[i] = 4u * (unsigned)(KC ? min(t0 + t, n_t - 1) * K + k : k * n_t + min(t0 + t, n_t - 4));
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          o.at[4 * i + e] = 4u * (unsigned)(KC ? min(t0 + t, n_t - 1) * K + k + e : k * n_t + min(t0 + t + e, n_t - 1));
-      }
+      o.at[i] = 4u * (unsigned)(min(t0 + t, n_t - 1) * K + k);
     }
     return o;
   }
   // The slice from k0 on; where it would reach past the end of k, the last SL values instead, of which stash() clears those
   // before k0.  (Cleared here, they would be waited for here.)
-  __device__ __forceinline__ void fetch(const float* X, const Offsets& o, int k0, int n_t, int K) {
-    const char* x = reinterpret_cast<const char*>(X + (size_t)min(k0, K - SL) * (KC ? 1 : n_t));
+  __device__ __forceinline__ void fetch(const float* X, const Offsets& o, int k0, int K) {
+    const char* x = reinterpret_cast<const char*>(X + min(k0, K - SL));
 #pragma unroll
     for (int i = 0; i < kPieces; ++i) {
       if constexpr (VEC) {
         r[i] = *reinterpret_cast<const float4*>(x + o.at[i]);
       } else {
-        r[i].x = *reinterpret_cast<const float*>(x + o.at[4 * i]);
-        r[i].y = *reinterpret_cast<const float*>(x + o.at[4 * i + 1]);
-        r[i].z = *reinterpret_cast<const float*>(x + o.at[4 * i + 2]);
-        r[i].w = *reinterpret_cast<const float*>(x + o.at[4 * i + 3]);
+        const float* p = reinterpret_cast<const float*>(x + o.at[i]);
+        r[i] = make_float4(p[0], p[1], p[2], p[3]);
       }
     }
   }
@@ -102,22 +175,16 @@ struct SliceLoader {
       place(i, t, k);
       if (before > 0) {
         r[i].x = k >= before ? r[i].x : 0.f;
-        r[i].y = k + (KC ? 1 : 0) >= before ? r[i].y : 0.f;
-        r[i].z = k + (KC ? 2 : 0) >= before ? r[i].z : 0.f;
-        r[i].w = k + (KC ? 3 : 0) >= before ? r[i].w : 0.f;
+        r[i].y = k + 1 >= before ? r[i].y : 0.f;
+        r[i].z = k + 2 >= before ? r[i].z : 0.f;
+        r[i].w = k + 3 >= before ? r[i].w : 0.f;
       }
-      *reinterpret_cast<float4*>(s + (KC ? t * kPitch + k : k * kPitch + t)) = r[i];
+      *reinterpret_cast<float4*>(s + t * kPitch + k) = r[i];
     }
   }
   // the lane's four values of k of group g, of row `row`
   static __device__ __forceinline__ float4 read(const float* s, int row, int g, int half) {
-    const int k = 8 * g + 4 * half;
-    if constexpr (KC) {
-      return *reinterpret_cast<const float4*>(s + row * kPitch + k);
-    } else {
-      const float* x = s + k * kPitch + row;
-      return make_float4(x[0], x[kPitch], x[2 * kPitch], x[3 * kPitch]);
-    }
+    return *reinterpret_cast<const float4*>(s + row * kPitch + 8 * g + 4 * half);
   }
 };
 
@@ -146,22 +213,77 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, int w, int m0, int
   }
 }
 
-// C = A' B'; A' is M x K, B' is K x N.  A workgroup of two by two waves owns a tile of 64 TM x 64, a wave TM matrix tiles of 32.
-template <bool TA, bool TB, int EPI, bool VEC, int TM, int SL>
+constexpr int kDirect = 32;
+template <bool KC, bool VEC>
+struct DirectOperand {
+  float r[4][4];                                         // [g][j]: k = k0 + 8 g + 4 (lane / 32) + j, the same for both operands
+  __device__ __forceinline__ void fetch(const float* X, int t0, int k0, int n_t, int K) {
+    const int lane = threadIdx.x & 63, half = lane >> 5, t = min(t0 + (lane & 31), n_t - 1);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int k = k0 + 8 * g + 4 * half;
+      if constexpr (KC && VEC) {
+        const float4 v = *reinterpret_cast<const float4*>(X + (size_t)t * K + min(k, K - 4));
+        r[g][0] = v.x; r[g][1] = v.y; r[g][2] = v.z; r[g][3] = v.w;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[g][j] = KC ? X[(size_t)t * K + min(k + j, K - 1)] : X[(size_t)min(k + j, K - 1) * n_t + t];
+      }
+    }
+  }
+  __device__ __forceinline__ void clear(int k0, int K) {
+    const int half = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[g][j] = k0 + 8 * g + 4 * half + j < K ? r[g][j] : 0.f;
+  }
+};
+
+// A matrix tile of the product in fp32, operands straight from memory (a lane loads what the matrix cores take from it).
+template <bool TA, bool TB, bool VEC>
+__device__ __forceinline__ f32x16_t fp32_tile(const GemmArgs& g, const float* A, const float* B, int m0, int n0) {
+  f32x16_t acc = {0};
+  DirectOperand<!TA, VEC> a;
+  DirectOperand<TB, VEC> b;
+#pragma unroll 1
+  for (int k0 = 0; k0 < g.K; k0 += kDirect) {
+    a.fetch(A, m0, k0, g.M, g.K);
+    b.fetch(B, n0, k0, g.N, g.K);
+    if (k0 + kDirect > g.K) {
+      a.clear(k0, g.K);
+      b.clear(k0, g.K);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.r[q][j], b.r[q][j], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// Whether the wave's tile holds numbers only.  (x - x is 0 for a number and NaN otherwise.)
+__device__ __forceinline__ bool all_finite(const f32x16_t& v) {
+  float d = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) d += v[r] - v[r];
+  return __ballot(d != 0.f) == 0;
+}
+
+// C = A B^T in fp32 (the first product).  A workgroup of two by two waves owns a tile of 64 TM x 64, a wave TM matrix tiles of 32.
+template <int EPI, bool VEC, int TM, int SL>
 __global__ void __launch_bounds__(kGemmThreads, 4)
-gemm_kernel(GemmArgs g) {
+gemm_f32_kernel(GemmArgs g) {
   constexpr int BM = 64 * TM, BN = 64;
-  typedef SliceLoader<!TA, VEC, BM, SL> LoadA;
-  typedef SliceLoader<TB, VEC, BN, SL> LoadB;
+  typedef SliceLoader<VEC, BM, SL> LoadA;
+  typedef SliceLoader<VEC, BN, SL> LoadB;
   __shared__ __align__(16) float s_ab[2][LoadA::kFloats + LoadB::kFloats];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
   const float* A = g.A + (size_t)w * g.sA;
   const float* B = g.B + (size_t)w * g.sB;
   const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32;
   const int col = lane & 31, half = lane >> 5;
-  const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
-  float4 csum = make_float4(0.f, 0.f, 0.f, 0.f);                // of the thread's four columns of A (TA: they are always the same)
   f32x16_t acc[TM];
 #pragma unroll
   for (int a = 0; a < TM; ++a) acc[a] = (f32x16_t){0};
@@ -170,19 +292,13 @@ gemm_kernel(GemmArgs g) {
   const typename LoadB::Offsets ob = LoadB::offsets(n0, g.N, g.K);
   struct Staged { LoadA a; LoadB b; };
   auto fetch = [&](Staged& st, int k0) {
-    st.a.fetch(A, oa, k0, g.M, g.K);
-    st.b.fetch(B, ob, k0, g.N, g.K);
+    st.a.fetch(A, oa, k0, g.K);
+    st.b.fetch(B, ob, k0, g.K);
     __builtin_amdgcn_sched_barrier(0);                          // left alone the compiler moves the loads behind the products
   };
   auto stash = [&](Staged& st, int buf, int k0) {
     st.a.stash(s_ab[buf], k0, g.K);
     st.b.stash(s_ab[buf] + LoadA::kFloats, k0, g.K);
-    if (TA && sums) {
-#pragma unroll
-      for (int i = 0; i < LoadA::kPieces; ++i) {
-        csum.x += st.a.r[i].x; csum.y += st.a.r[i].y; csum.z += st.a.r[i].z; csum.w += st.a.r[i].w;
-      }
-    }
   };
   auto compute = [&](int buf) {
     const float* sa = s_ab[buf];
@@ -220,11 +336,90 @@ gemm_kernel(GemmArgs g) {
     stash(even, 0, (c + 2) * SL);
     __syncthreads();
   }
+#pragma unroll
+  for (int t = 0; t < TM; ++t) store_tile<EPI, 16>(g, w, m0 + wm + 32 * t, n0 + wn + col, half, acc[t]);
+}
+
+// C = A' B'; A' is M x K, B' is K x N.  Two by two waves own a tile of 64 TM x 64, a wave TM matrix tiles of 32.
+template <bool TA, bool TB, int EPI, bool VEC, int TM>
+__global__ void __launch_bounds__(kGemmThreads, 2)
+gemm_kernel(GemmArgs g) {
+  constexpr int BM = 64 * TM, BN = 64;
+  typedef PlaneLoader<!TA, VEC, BM> LoadA;
+  typedef PlaneLoader<TB, VEC, BN> LoadB;
+  constexpr int kUnits = LoadA::kUnits + LoadB::kUnits;
+  __shared__ uint4 s_ab[2 * kUnits];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
+  const float* A = g.A + (size_t)w * g.sA;
+  const float* B = g.B + (size_t)w * g.sB;
+  const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32;
+  const int col = lane & 31, half = lane >> 5;
+  const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
+  float csum = 0.f;                                             // of the thread's row of A' (TA: it is always the same)
+  f32x16_t acc[TM], low[TM];                                    // the sums of the products of planes 0, and of the others
+#pragma unroll
+  for (int t = 0; t < TM; ++t) acc[t] = low[t] = (f32x16_t){0};
+
+  const int oa = LoadA::offset(m0, g.M, g.K), ob = LoadB::offset(n0, g.N, g.K);
+  const __amdgpu_buffer_rsrc_t ra = operand_buffer(A, g.M, g.K), rb = operand_buffer(B, g.N, g.K);
+  struct Staged { LoadA a; LoadB b; };
+  Staged even, odd;
+  auto fetch = [&](Staged& st, int k0) {
+    st.a.fetch(ra, oa, k0, g.M, g.K);
+    st.b.fetch(rb, ob, k0, g.N, g.K);
+  };
+  auto stash = [&](const Staged& st, int buf, bool live) {
+    st.a.stash(s_ab + buf * kUnits);
+    st.b.stash(s_ab + buf * kUnits + LoadA::kUnits);
+    if (TA) csum += __int_as_float(__float_as_int(st.a.sum()) & -(int)live);    // (a select would become a branch)
+  };
+  // the slice in buffer `buf`; the split of the next one runs under its products
+  auto step = [&](Staged& st, int buf, int k0_next) {
+    const uint4* sa = s_ab + buf * kUnits;
+    const uint4* sb = sa + LoadA::kUnits;
+    bf16x8_t a[TM][3], b[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      b[p] = LoadB::read(sb, p, wn + col, half);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) a[t][p] = LoadA::read(sa, p, wm + 32 * t + col, half);
+    }
+    stash(st, buf ^ 1, k0_next < g.K);
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int t = 0; t < TM; ++t) {
+        f32x16_t& sum = i < 5 ? low[t] : acc[t];
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kPlaneA[i]], b[kPlaneB[i]], sum, 0, 0, 0);
+      }
+    // moved up, the loads would get other registers than the values that they replace, and be waited for when copied over
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(st, k0_next + 2 * kSlice);
+    __syncthreads();
+  };
+  // the first slice is the one that may be short: the values of one operand past its end are taken out (an infinity or NaN of
+  // the other there spoils the tile, which is then done again)
+  const int n_slices = (g.K + kSlice - 1) / kSlice, first = g.K - (n_slices - 1) * kSlice;
+  fetch(even, 0);
+  fetch(odd, first);
+  even.a.clear_from(first);
+  stash(even, 0, true);
+  fetch(even, first + kSlice);
+  __syncthreads();
+  int k0 = first;
+  int pairs = n_slices / 2;                                     // at least one: k is 32 at least
+  do {
+    step(odd, 0, k0);
+    step(even, 1, k0 + kSlice);
+    k0 += 2 * kSlice;
+  } while (--pairs > 0);
+  if (n_slices & 1) step(odd, 0, k0);
   if (TA && sums) {
-    // the threads that loaded the same columns add up in a fixed order
-    constexpr int kGroups = kGemmThreads / (BM / 4);
-    float* s = s_ab[0];                                           // [kGroups][BM]
-    *reinterpret_cast<float4*>(s + tid / (BM / 4) * BM + tid % (BM / 4) * 4) = csum;
+    // the threads that loaded the same row add up in a fixed order
+    constexpr int kGroups = kGemmThreads / BM;
+    float* s = reinterpret_cast<float*>(s_ab);                  // [kGroups][BM]
+    s[tid] = csum;
     __syncthreads();
     if (tid < BM && m0 + tid < g.M) {
       float t = 0.f;
@@ -234,42 +429,21 @@ gemm_kernel(GemmArgs g) {
     }
   }
 #pragma unroll
-  for (int t = 0; t < TM; ++t) store_tile<EPI, 16>(g, w, m0 + wm + 32 * t, n0 + wn + col, half, acc[t]);
+  for (int t = 0; t < TM; ++t) {
+    const int tm = m0 + wm + 32 * t, tn = n0 + wn;
+    acc[t] += low[t];
+    // not a number, infinite, or too large for a bfloat16: as fp32 products have it
+    if (!all_finite(acc[t])) acc[t] = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
+    store_tile<EPI, 16>(g, w, tm, tn + col, half, acc[t]);
+  }
 }
 
-// The same for results of few tiles: a workgroup owns one matrix tile, its four waves a quarter of the k each, operands straight
-// from memory (a lane loads what the matrix cores take from it), the next slice's loads in flight.  8 sets of 512 x 128 over
-// 1000 rows: 27 us in the kernel above, here 18.
-template <bool KC, bool VEC>
-struct DirectOperand {
-  float r[4][4];                                         // [g][j]: k = k0 + 8 g + 4 (lane / 32) + j
-  __device__ __forceinline__ void fetch(const float* X, int t0, int k0, int n_t, int K) {
-    const int lane = threadIdx.x & 63, half = lane >> 5, t = min(t0 + (lane & 31), n_t - 1);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int k = k0 + 8 * g + 4 * half;
-      if constexpr (KC && VEC) {
-        const float4 v = *reinterpret_cast<const float4*>(X + (size_t)t * K + min(k, K - 4));
-        r[g][0] = v.x; r[g][1] = v.y; r[g][2] = v.z; r[g][3] = v.w;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r[g][j] = KC ? X[(size_t)t * K + min(k + j, K - 1)] : X[(size_t)min(k + j, K - 1) * n_t + t];
-      }
-    }
-  }
-  __device__ __forceinline__ void clear(int k0, int K) {
-    const int half = (threadIdx.x & 63) >> 5;
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) r[g][j] = k0 + 8 * g + 4 * half + j < K ? r[g][j] : 0.f;
-  }
-};
-
+// C = A' B' in fp32 for results of few tiles: a workgroup owns one matrix tile, its four waves a quarter of the k each, operands straight
+// from memory (a lane loads what the matrix cores take from it), the next slice's loads in flight.
 template <bool TA, bool TB, int EPI, bool VEC>
 __global__ void __launch_bounds__(kGemmThreads, VEC ? 4 : 2)
 gemm_split_kernel(GemmArgs g) {
-  constexpr int kSlice = 32, kStep = 4 * kSlice;
+  constexpr int kStep = 4 * kDirect;
   __shared__ float4 s_red[4 * 4 * 64];                   // [wave][four registers][lane]
   __shared__ float s_sum[4 * 32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
@@ -286,7 +460,7 @@ gemm_split_kernel(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
   };
   auto compute = [&](Staged& st, int k0) {
-    if (k0 + kSlice > g.K) {
+    if (k0 + kDirect > g.K) {
       st.a.clear(k0, g.K);
       st.b.clear(k0, g.K);
     }
@@ -300,8 +474,8 @@ gemm_split_kernel(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
   };
   Staged even, odd;
-  fetch(even, wave * kSlice);
-  for (int k0 = wave * kSlice; k0 < g.K; k0 += 2 * kStep) {
+  fetch(even, wave * kDirect);
+  for (int k0 = wave * kDirect; k0 < g.K; k0 += 2 * kStep) {
     fetch(odd, k0 + kStep);                              // past the end: the last values again, not used
     compute(even, k0);
     fetch(even, k0 + 2 * kStep);
@@ -325,38 +499,57 @@ gemm_split_kernel(GemmArgs g) {
     g.colsum[(size_t)w * g.sColsum + m0 + col] = (s_sum[col] + s_sum[32 + col]) + (s_sum[64 + col] + s_sum[96 + col]);
 }
 
-// 128 x 64 tiles where they give every compute unit the four workgroups it has room for, or else 64 x 64 (with slices twice as
-// long for the same LDS): a product is then one round of workgroups.  Below a workgroup per compute unit a tile's k is shared
-// out over four waves, and so it is where k is shorter than a slice or an operand too large for offsets of 32 bits; that one
-// takes several launches where a grid dimension has no room for its smaller tiles.
+// 128 x 64 tiles where they give every compute unit two workgroups, or else 64 x 64 (8 sets, 500 rows, 288 x 512: 10 us less in all
+// than with the larger ones).  Below a workgroup per compute unit a tile's k is shared out over four waves (1 set, 1000 rows,
+// 512 x 1024: 82 us in all, 120 with 64 x 64 tiles), and so it is where k is shorter than two slices or an operand too large for
+// offsets of 32 bits; that one takes several launches where a grid dimension has no room for its smaller tiles.
 constexpr long long kMostTiles = 65535;
-template <bool TA, bool TB, int EPI, bool VEC>
+template <bool TA, bool TB, int EPI, bool VEC, bool F32>
 void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
   auto grid = [&](int bm, int bn) { return dim3((unsigned)Hw, (unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + bm - 1) / bm)); };
   auto count = [&](int bm, int bn) { const dim3 d = grid(bm, bn); return (long long)d.x * d.y * d.z; };
   const bool tiled = g.K >= 32 && (long long)g.M * g.K < (1ll << 29) && (long long)g.N * g.K < (1ll << 29) && g.N <= kMostTiles * 64;
-  if (tiled && count(128, 64) >= 4LL * device_cus())
-    hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 2, 16>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
-  else if (tiled && count(64, 64) >= device_cus())
-    hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 1, 32>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
-  else
-    for (long long m = 0; m < g.M; m += kMostTiles * 32)
-      for (long long n = 0; n < g.N; n += kMostTiles * 32) {
-        GemmArgs part = g;
-        part.m_first = (int)m;
-        part.n_first = (int)n;
-        auto tiles = [](long long left) { return (unsigned)std::min((left + 31) / 32, kMostTiles); };
-        hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC>), dim3((unsigned)Hw, tiles(g.N - n), tiles(g.M - m)), dim3(kGemmThreads), 0,
-                           hs, part);
-      }
+  if constexpr (F32) {
+    static_assert(!TA && TB, "rows of both operands along k");
+    // 128 x 64 tiles where they give every compute unit the four workgroups it has room for, or else 64 x 64 with slices twice as
+    // long for the same LDS
+    if (tiled && count(128, 64) >= 4LL * device_cus()) {
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, VEC, 2, 16>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
+      return;
+    }
+    if (tiled && count(64, 64) >= device_cus()) {
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, VEC, 1, 32>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
+      return;
+    }
+  } else {
+    if (tiled && count(128, 64) >= 2LL * device_cus()) {
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 2>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
+      return;
+    }
+    if (tiled && count(64, 64) >= device_cus()) {
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 1>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
+      return;
+    }
+  }
+  for (long long m = 0; m < g.M; m += kMostTiles * 32)
+    for (long long n = 0; n < g.N; n += kMostTiles * 32) {
+      GemmArgs part = g;
+      part.m_first = (int)m;
+      part.n_first = (int)n;
+      auto tiles = [](long long left) { return (unsigned)std::min((left + 31) / 32, kMostTiles); };
+      hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC>), dim3((unsigned)Hw, tiles(g.N - n), tiles(g.M - m)), dim3(kGemmThreads),
+                         0, hs, part);
+    }
 }
 
-template <bool TA, bool TB, int EPI>
+// F32: every product and sum in fp32, for the first product: a hidden unit's sign decides which gradients flow through it, and
+// a unit that another rounding moves across zero moves them by far more than a rounding.
+template <bool TA, bool TB, int EPI, bool F32 = false>
 void gemm(const GemmArgs& g, int Hw, hipStream_t hs) {
   // 16-byte loads need rows of both operands that start on 16 bytes
   auto rows_aligned = [](const float* p, int ld, long long stride) { return aligned16(p) && ld % 4 == 0 && stride % 4 == 0; };
-  if (rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB)) gemm_sized<TA, TB, EPI, true>(g, Hw, hs);
-  else gemm_sized<TA, TB, EPI, false>(g, Hw, hs);
+  if (rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB)) gemm_sized<TA, TB, EPI, true, F32>(g, Hw, hs);
+  else gemm_sized<TA, TB, EPI, false, F32>(g, Hw, hs);
 }
 
 __global__ void widen_kernel(const bf16_t* __restrict__ x, float* __restrict__ y, size_t n) {
@@ -639,10 +832,10 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
   const dim3 per_elem((unsigned)(((size_t)R * hidden + 255) / 256), (unsigned)Hw);
   if (!bn) {
     // h = relu(x W1^T + b1)
-    gemm<false, true, EPI_BIAS_RELU>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
+    gemm<false, true, EPI_BIAS_RELU, true>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
   } else {
     // a = x W1^T + b1;  h = relu(gamma * normalised(a) + beta)
-    gemm<false, true, EPI_BIAS>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
+    gemm<false, true, EPI_BIAS, true>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
     hipLaunchKernelGGL(bn_stats_kernel, per_col, dim3(kBnThreads), 0, hs, pre, stats, bn->running_mean, bn->running_var, R, hidden,
                        bn->eps, bn->momentum);
     hipLaunchKernelGGL(bn_relu_kernel, per_elem, dim3(256), 0, hs, pre, stats, bn->gamma, bn->beta, h, R, hidden);

@@ -1,0 +1,69 @@
+"""The training products that run as sums of bfloat16 products: lengths of k around the slices, and values that the split does
+not hold."""
+import pytest
+import torch
+
+from test_gpu_train import DEV, problem, to_dev
+from test_gpu_train import saap  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(x, T, params):
+    ps = [p.double().requires_grad_() for p in params]
+    want = []
+    for w in range(x.shape[0]):
+        z = torch.relu(x[w].double() @ ps[0][w].T + ps[1][w]) @ ps[2][w].T + ps[3][w]
+        t = T[w].double()
+        want.append(torch.where(t > 0, t * (t.clamp_min(1e-300).log() - torch.log_softmax(z, -1)), 0 * z).sum(-1).mean())
+    want = torch.stack(want)
+    want.sum().backward()
+    return want.detach(), [p.grad for p in ps]
+
+
+@pytest.mark.parametrize("R", [32, 33, 47, 48, 49, 64, 65])
+@pytest.mark.parametrize("hidden,B", [(256, 260), (255, 261)])
+def test_lengths_of_k(saap, R, hidden, B):  # noqa: F811
+    """The weight gradients sum over R: one slice of 16 and a second that overlaps it, odd and even numbers of slices.  fp32 sums of
+    at most 261 terms in chains of a slice: 3e-6."""
+    x, T, params = problem(R, 16, R, 16, hidden, B, torch.float32)
+    x, T, params = x.to(DEV), T.to(DEV), to_dev(params)
+    loss, grads = saap.query_model_loss_grads(x, T, params)
+    want, ref = reference(x, T, params)
+    torch.testing.assert_close(loss.double(), want, rtol=1e-5, atol=0.0)
+    for name, got, g in zip(("dW1", "db1", "dW2", "db2"), grads, ref):
+        dims = tuple(range(1, got.dim()))
+        assert ((got.double() - g).norm(dim=dims) <= 3e-6 * g.norm(dim=dims)).all(), name
+
+
+@pytest.mark.parametrize("R,hidden,B", [(512, 256, 512), (129, 256, 512)])
+def test_values_beyond_bfloat16(saap, R, hidden, B):  # noqa: F811
+    """A unit that no row turns on, with output weights that round to infinity in bfloat16: they add nothing, as in fp32."""
+    Hw, d, off = 16, 32, 5
+    x, T, (W1, b1, W2, b2) = problem(3, Hw, R, d, hidden, B, torch.float32)
+    b1[:, off], W2[:, :, off] = -1e4, 0.0
+    x, T, params = x.to(DEV), T.to(DEV), to_dev((W1, b1, W2, b2))
+    huge = tuple(p.clone() for p in params)
+    huge[2][:, :, off] = 3.4e38
+    assert torch.isfinite(huge[2]).all() and torch.isinf(huge[2].to(torch.bfloat16)).any()
+    want, ref = reference(x, T, params)
+    loss, grads = saap.query_model_loss_grads(x, T, huge)
+    torch.testing.assert_close(loss.double(), want, rtol=1e-5, atol=0.0)
+    for name, got, g in zip(("dW1", "db1", "dW2", "db2"), grads, ref):
+        assert ((got.double() - g).norm() <= 3e-6 * g.norm()), name
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_a_weight_that_is_no_number_spoils_its_set_only(saap, bad):  # noqa: F811
+    x, T, params = problem(4, 16, 256, 32, 256, 512, torch.float32)
+    x, T, params = x.to(DEV), T.to(DEV), to_dev(params)
+    broken = tuple(p.clone() for p in params)
+    broken[2][3, 7, 9] = bad
+    want_loss, want = saap.query_model_loss_grads(x, T, params)
+    loss, grads = saap.query_model_loss_grads(x, T, broken)
+    assert loss[3].isnan()
+    others = torch.arange(16, device=DEV) != 3
+    assert torch.equal(loss[others], want_loss[others])
+    for name, got, g in zip(("dW1", "db1", "dW2", "db2"), grads, want):
+        assert torch.equal(got[others], g[others]), name
+        assert got[3].isnan().any(), name
