@@ -176,6 +176,12 @@ __device__ __forceinline__ float across_rows(float x, F op) {
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // {own, lane ^ 32}
   return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
+// The value of lane ^ 32.
+__device__ __forceinline__ float other_half(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // {own, other} in lanes 0..31, {other, own} above
+  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
 __device__ __forceinline__ float sum_rows(float x) { return across_rows(x, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ float max_rows(float x) { return across_rows(x, [](float a, float b) { return fmaxf(a, b); }); }
 

@@ -117,17 +117,21 @@ void launch_mass(const void* q, const void* K, const int32_t* off, const int32_t
 // ---- many queries per KV head (a training batch): scores on the matrix cores -----------------------
 // 32 QT queries per wave sit in registers as the B operand of v_mfma_f32_32x32x16_bf16 (one lane per query and half of
 // the key rows); the keys of a bucket stream through LDS in tiles of 32 as the A operand (padded rows, whole-row loads,
-// double buffered, two tiles of loads in flight), so that one lane sees 16 scores of its query per tile and keeps the
+// double buffered, the next tile's loads in flight), so that one lane sees 16 scores of its query per tile and keeps the
 // bucket's running maximum and sum for it.  A workgroup takes every n_slices-th bucket.  part[(unit*B + b)*R + q] = (m, s).
 // Per tile and 32 queries a wave issues 8 matrix instructions (256 cycles) and about 50 vector instructions, 16 of them
-// exponentials at a fraction of the rate: the vector pipe bounds it, three workgroups per compute unit overlap the pipes.  8 heads, 1000 queries, 131072 keys: 486 us with one key tile waited for at a time, 350 us now.
+// exponentials at half the rate (280 cycles); the two kinds overlap only in part whatever their order (a loop of nothing else:
+// 455 ns for two such tiles on random numbers, where the sum is 531), so that waves in flight decide: 128 registers, four
+// workgroups per compute unit.  8 heads, 1000 queries, 131072 keys: 486 us with one key tile waited for at a time, 359 with two
+// tiles of loads in flight and three workgroups, 347 now; 323 with neither masks, pairs nor barriers.  (The weights of a tile
+// under the products of the next in one wave need 32 more registers: 395 to 420 us.)
 constexpr int kMassPitch = 136;      // bf16 elements per LDS row (272 bytes: conflict-free b128 reads)
 constexpr int kMassTile = 32;        // keys per tile
 constexpr int kMassBuckets = 512;    // buckets per workgroup at most
 
 // SIGN of the score scale: below zero the largest score is the smallest product.
 template <int QT, int SIGN>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, 4)
 mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, const int32_t* __restrict__ off,
                  const int32_t* __restrict__ len, float2* __restrict__ part, long long rows, int B, int R,
                  float scale_log2) {
@@ -199,10 +203,12 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
   struct Staged { u32x4_t p[2]; };        // native vectors: a uint4 here ends up in scratch memory
   // 32 rows x 16 pieces of 16 bytes, two per thread; rows past the bucket repeat its last key
   auto fetch = [&](Staged& g, const Tile& t) {
+    const char* rows_at = reinterpret_cast<const char*>(Ku + (size_t)(t.first + t.t0) * kD);      // the whole workgroup's
+    const unsigned last = t.n - 1 - t.t0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int pi = tid + 256 * i, r = pi >> 4, pc = pi & 15;
-      g.p[i] = *reinterpret_cast<const u32x4_t*>(Ku + (size_t)(t.first + min(t.t0 + r, t.n - 1)) * kD + pc * 8);
+      const unsigned pi = tid + 256 * i, r = pi >> 4, pc = pi & 15;
+      g.p[i] = *reinterpret_cast<const u32x4_t*>(rows_at + (min(r, last) * (kD * 2) + pc * 16));
     }
   };
   auto stash = [&](const Staged& g, int buf) {
@@ -236,11 +242,12 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
     float to_log2 = scale_log2;
     if (t.t0 + kMassTile > t.n) {                        // the bucket's last tile: rows past its end do not count
       if (SIGN == 0) to_log2 = 1.f;                      // scaled here: zero times the mask would be no number
+      const int left = t.n - t.t0 - 4 * half;
 #pragma unroll
-      for (int i = 0; i < QT; ++i)
+      for (int r = 0; r < 16; ++r)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool in = t.t0 + 8 * (r / 4) + 4 * half + (r % 4) < t.n;
+        for (int i = 0; i < QT; ++i) {
+          const bool in = 8 * (r / 4) + (r % 4) < left;
           acc[i][r] = !in ? (SIGN < 0 ? INFINITY : -INFINITY) : SIGN == 0 ? acc[i][r] * 0.f : acc[i][r];
         }
     }
@@ -268,37 +275,32 @@ mass_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K, con
       s[i] += add;
     }
     if (t.t0 + kMassTile >= t.n) {                       // the bucket is complete; lanes l and l+32 hold the same query
+      float2* const pairs = part + ((size_t)unit * B + t.b) * R;
 #pragma unroll
       for (int i = 0; i < QT; ++i) {
-        const float mo = __shfl_xor(m[i], 32), so = __shfl_xor(s[i], 32);
+        const float mo = other_half(m[i]), so = other_half(s[i]);
         const float M = fmaxf(m[i], mo);
         const float S = s[i] * fast_exp2(m[i] - M) + so * fast_exp2(mo - M);
-        if (half == 0 && q0 + 32 * i < R) *pair_of(t.b, i) = make_float2(M, S);
+        if (half == 0 && q0 + 32 * i < R) pairs[(unsigned)(q0 + 32 * i)] = make_float2(M, S);
         s[i] = 0.f;
         m[i] = m[i] < INFINITY ? m[i] : kNegBig;         // no reference for the buckets that follow
       }
     }
   };
-  // straight-line loads and stores (no early exit between them): behind branches the staging registers go to scratch
   Tile t0 = enter(0), t1 = after(t0);
-  Staged even, odd;
-  fetch(even, t0);
-  fetch(odd, t1);
-  stash(even, 0);
+  Staged st;
+  fetch(st, t0);
+  stash(st, 0);
+  fetch(st, t1);
   __syncthreads();
-  for (int c = 0; c < n_tiles; c += 2) {
+  for (int c = 0; c < n_tiles; ++c) {
+    stash(st, (c + 1) & 1);
     const Tile t2 = after(t1);
-    fetch(even, t2);
-    compute(0, t0);
-    stash(odd, 1);
+    fetch(st, t2);
+    compute(c & 1, t0);
     __syncthreads();
-    const Tile t3 = after(t2);
-    fetch(odd, t3);
-    if (c + 1 < n_tiles) compute(1, t1);
-    stash(even, 0);
-    __syncthreads();
-    t0 = t2;
-    t1 = t3;
+    t0 = t1;
+    t1 = t2;
   }
 }
 
