@@ -6,15 +6,14 @@
 // order):
 //   1. hist      every workgroup counts the bucket ids of its slice of positions
 //   2. colscan   per bucket, exclusive scan of the slice counts over slices -> len, slice bases
-//   3. offscan   per (sequence, head), exclusive scan of (len + slack) over buckets -> off
-//   4. scatter   one workgroup per slice; every wave walks its part of the slice in order, 64 positions at a
+//   3. scatter   exclusive scan of (len + slack) over the buckets -> off; one workgroup per slice; every wave walks its part of the slice in order, 64 positions at a
 //                time; the rank of a position among equal ids inside the 64 comes from ballots, the waves' and
 //                the buckets' running positions are kept in LDS -> idx
-//   5. permute   rows of K and V are copied to their slot, 16 bytes per lane, whole rows
-// A short context is one slice: order_small does steps 1 to 4 in one launch.
+//   4. permute   rows of K and V are copied to their slot, 16 bytes per lane, whole rows
+// A short context is one slice: order_small does steps 1 to 3 in one launch.
 //
 // With a resident block (attention sink + recent keys, Section 3 "Per-head attention span")
-// only the positions [lo, hi) go through steps 1-4; the resident positions are placed by
+// only the positions [lo, hi) go through steps 1-3; the resident positions are placed by
 // their slot rule into one more run behind the B buckets, and window_push moves one key per
 // decode step from that run into its bucket.
 #include "common.h"
@@ -71,35 +70,6 @@ colscan_kernel(int32_t* __restrict__ slice_hist, int32_t* __restrict__ len, int 
     run += c;
   }
   len[(size_t)unit * lstride + b] = run;
-}
-
-// One workgroup per unit: off[0] = 0, off[b+1] = off[b] + len[b] + slack.  With a resident
-// block (W >= 0) len has B+1 and off B+2 entries per unit: len[B] = n_res, off[B+1] = off[B] + W.
-__global__ void __launch_bounds__(1024)
-offscan_kernel(int32_t* __restrict__ len, int32_t* __restrict__ off, int B, int slack, int W, int n_res) {
-  __shared__ int s_wsum[16];
-  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per = (B + blockDim.x - 1) / blockDim.x;
-  const int b0 = tid * per, b1 = min(b0 + per, B);
-  const int lstride = W >= 0 ? B + 1 : B;
-  int32_t* l = len + (size_t)unit * lstride;
-  int32_t* o = off + (size_t)unit * (lstride + 1);
-  int mine = 0;
-  for (int b = b0; b < b1; ++b) mine += l[b] + slack;
-  const int incl = (int)wave_prefix_sum((unsigned)mine);
-  if (lane == 63) s_wsum[wave] = incl;
-  __syncthreads();
-  int run = incl - mine;
-  for (int w = 0; w < wave; ++w) run += s_wsum[w];
-  if (tid == 0) o[0] = 0;
-  for (int b = b0; b < b1; ++b) {
-    run += l[b] + slack;
-    o[b + 1] = run;
-    if (W >= 0 && b == B - 1) {
-      o[B + 1] = run + W;
-      l[B] = n_res;
-    }
-  }
 }
 
 // Resident key j of a unit (j-th resident position in ascending order): its place in the resident run, its id kept
@@ -168,15 +138,19 @@ __device__ __forceinline__ void place_round(int b, int n, int id_bits, const int
 // behind the last run: every entry of idx is written, and the row copy reads them all.
 constexpr int kScatterThreads = 256, kScatterWaves = kScatterThreads / 64;
 __global__ void __launch_bounds__(kScatterThreads)
-scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slice_base,
-               const int32_t* __restrict__ off, int32_t* __restrict__ idx, int N, int Ncap, int B,
-               int n_slices, int id_bits, int lo, int hi, int ostride, int slack) {
-  extern __shared__ int s_next[];                        // [B] | counters [waves][words]
+scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slice_base, int32_t* __restrict__ len,
+               int32_t* __restrict__ off, int32_t* __restrict__ idx, int N, int Ncap, int B,
+               int n_slices, int id_bits, int lo, int hi, int slack, int W, int n_res) {
+  extern __shared__ int s_next[];                        // [B] | off [B + 1] | counters [waves][words]
+  __shared__ int s_wsum[kScatterWaves];
   const int unit = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int words = (B + 1) / 2;
-  unsigned* s_cnt = reinterpret_cast<unsigned*>(s_next + B);
+  int* s_off = s_next + B;
+  unsigned* s_cnt = reinterpret_cast<unsigned*>(s_off + B + 1);
   const int32_t* base = slice_base + ((size_t)unit * n_slices + slice) * B;
-  const int32_t* o = off + (size_t)unit * ostride;
+  const int lstride = W >= 0 ? B + 1 : B;
+  int32_t* l = len + (size_t)unit * lstride;
+  int32_t* o = off + (size_t)unit * (lstride + 1);
   int32_t* ix = idx + (size_t)unit * Ncap;
   const int32_t* idu = ids + (size_t)unit * N;
   constexpr int kRounds = kSlice / kScatterThreads;      // of 64 positions per wave
@@ -188,8 +162,27 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
     mine[k] = n >= lo && n < hi ? idu[n] : -1;           // hi <= N
   }
   for (int i = tid; i < kScatterWaves * words; i += kScatterThreads) s_cnt[i] = 0u;
-  for (int b = tid; b < B; b += kScatterThreads) s_next[b] = o[b] + base[b];
+  for (int b = tid; b < B; b += kScatterThreads) {
+    s_next[b] = base[b];
+    s_off[b + 1] = l[b] + slack;
+  }
   __syncthreads();
+  // every slice scans the runs of its unit for itself: 1.0 us more here (8 units of 65536 positions; 3 us of 60 for 64 of 131072)
+  // where a launch between the column scan and this one took 4.6
+  const int per = (B + kScatterThreads - 1) / kScatterThreads, b0 = min(tid * per, B), b1 = min(b0 + per, B);
+  int run_of = 0;
+  for (int b = b0; b < b1; ++b) run_of += s_off[b + 1];
+  const int incl = (int)wave_prefix_sum((unsigned)run_of);
+  if (lane == 63) s_wsum[wave] = incl;
+  __syncthreads();
+  int at = incl - run_of;
+  for (int w = 0; w < wave; ++w) at += s_wsum[w];
+  if (tid == 0) s_off[0] = 0;
+  for (int b = b0; b < b1; ++b) {
+    s_next[b] += at;
+    at += s_off[b + 1];
+    s_off[b + 1] = at;
+  }
 #pragma unroll
   for (int k = 0; k < kRounds; ++k) {
     if (mine[k] >= B) mine[k] = -1;
@@ -210,14 +203,22 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
 #pragma unroll
   for (int k = 0; k < kRounds; ++k) place_round(mine[k], n0 + k * 64 + lane, id_bits, s_next, s_cnt + wave * words, ix);
   for (int b = slice + wave * n_slices; slack > 0 && b < B; b += n_slices * kScatterWaves) {
-    const int end = o[b + 1];
+    const int end = s_off[b + 1];
     for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
   }
+  // the unit's off; with a resident block (W >= 0) one more run of W slots closes it, n_res of them in use
+  if (slice == 0) {
+    for (int b = tid; b <= B; b += kScatterThreads) o[b] = s_off[b];
+    if (W >= 0 && tid == 0) {
+      o[B + 1] = s_off[B] + W;
+      l[B] = n_res;
+    }
+  }
   // keys with ids outside [0,B) are dropped: as many slots stay empty behind the last run
-  for (int j = o[ostride - 1] + slice * kScatterThreads + tid; j < Ncap; j += n_slices * kScatterThreads) ix[j] = -1;
+  for (int j = s_off[B] + max(W, 0) + slice * kScatterThreads + tid; j < Ncap; j += n_slices * kScatterThreads) ix[j] = -1;
 }
 
-// Steps 1 to 4 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
+// Steps 1 to 3 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
 // waves per unit, each wave counting and then placing its sixteenth of the positions.  Five launches of 2 to 3 us become
 // one (8 heads of 5003 keys: 26 -> 10 us).
 constexpr int kSmallKeys = 16384, kSmallBuckets = 2048, kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
@@ -695,7 +696,7 @@ size_t build_workspace_bytes(long long units, int N, int B) {
 
 using namespace saap;
 
-// off, len and idx of the index (steps 1 to 4).  W < 0: plain index (B runs); otherwise the index with a resident run of
+// off, len and idx of the index (steps 1 to 3).  W < 0: plain index (B runs); otherwise the index with a resident run of
 // W slots behind the B buckets and its ids in res_ids.  slice_hist: scratch of units * slices * B counters.
 void saap::order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int32_t* idx, int32_t* res_ids, int32_t* slice_hist,
                       long long units, int N, int Ncap, int B, int slack, int W, int n_sink, int n_recent, hipStream_t hs) {
@@ -716,11 +717,10 @@ void saap::order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int
   hipLaunchKernelGGL(hist_kernel, dim3(n_slices, (unsigned)units), dim3(256), next_bytes, hs, bucket_ids, slice_hist, N, B, n_slices,
                      lo, hi);
   hipLaunchKernelGGL(colscan_kernel, dim3((B + 255) / 256, (unsigned)units), dim3(256), 0, hs, slice_hist, len, B, n_slices, lstride);
-  hipLaunchKernelGGL(offscan_kernel, dim3((unsigned)units), dim3(1024), 0, hs, len, off, B, slack, W, n_res);
-  const size_t lds = next_bytes + kScatterWaves * wave_bytes;
+  const size_t lds = 2 * next_bytes + sizeof(int) + kScatterWaves * wave_bytes;
   (void)allow_lds<scatter_kernel>(lds);
-  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)units, n_slices), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, off, idx,
-                     N, Ncap, B, n_slices, id_bits, lo, hi, lstride + 1, slack);
+  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)units, n_slices), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, len, off,
+                     idx, N, Ncap, B, n_slices, id_bits, lo, hi, slack, W, n_res);
   if (W > 0)
     hipLaunchKernelGGL(resident_kernel, dim3((unsigned)((W + 255) / 256), (unsigned)units), dim3(256), 0, hs, bucket_ids, off, idx,
                        res_ids, N, Ncap, B, n_sink, n_recent, n_res);

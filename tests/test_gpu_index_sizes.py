@@ -114,3 +114,21 @@ def test_centroids_from_ids(saap, S, N, B, dtype):
         got = saap.update_centroids_from_ids(x, ids, cent, normalize)
         assert torch.equal(got, want)
         assert torch.equal(got[:, B - 1], cent[:, B - 1])
+
+
+@pytest.mark.parametrize("N,B,slack,window", [
+    (16400, 255, 1, None), (18432, 256, 0, (1, 2047)), (20000, 257, 3, (2, 30)), (17000, 8191, 1, None), (40961, 8192, 0, (1, 2047)),
+    (300000, 2, 1, None)])
+def test_runs_scanned_by_every_slice(saap, N, B, slack, window):
+    """More than one slice, bucket counts around a multiple of a workgroup's threads and the largest."""
+    S, Hkv = (1, 1) if N > 100000 else (1, 2)
+    ids = np.random.default_rng(N + B).integers(0, B, (S, Hkv, N)).astype(np.int32)
+    K = torch.zeros(S, Hkv, N, 128, dtype=torch.bfloat16, device=DEV)
+    hK = np.zeros((S, Hkv, N, 128), np.float32)
+    d_ids = torch.from_numpy(ids).to(DEV)
+    if window:
+        got, want = saap.build_windowed_index(d_ids, K, K, B, slack, *window), ref.build_windowed_index(ids, hK, hK, B, slack, *window)
+    else:
+        got, want = saap.build_bucket_index(d_ids, K, K, B, slack), ref.build_bucket_index(ids, hK, hK, B, slack)
+    for g, w in zip(got[:3], want[:3]):
+        assert np.array_equal(g.cpu().numpy(), w)
