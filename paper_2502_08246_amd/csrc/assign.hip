@@ -314,6 +314,7 @@ assign_exact_f32_kernel(const float* __restrict__ x, const float* __restrict__ c
 constexpr int kGroupKeys = 32;
 constexpr int kCandCap = 2048;
 constexpr int kRescoreThreads = 512, kRescoreWaves = kRescoreThreads / 64;
+constexpr int kHalfPitch = kD / 2 + 8;   // bf16 elements per LDS row of half a centroid row (144 bytes: conflict-free b128 reads)
 constexpr int kKeepTiles = 4;      // matrix tiles per wave whose scores stay in registers between the passes
 
 // double-precision score of centroid row c against key row xr (in order), rows of 16-byte pieces
@@ -371,9 +372,11 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
   __shared__ double s_wbest[kRescoreWaves];
   __shared__ int s_wid[kRescoreWaves];
   __shared__ int s_flag;
+  __shared__ __align__(16) bf16_t s_half[kRescoreWaves][kCentTile * kHalfPitch];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   const int h = blockIdx.x;
+  const float norm = cmax[h];
   const unsigned n_rows = counters[h];
   const unsigned n_groups = (n_rows + kGroupKeys - 1) / kGroupKeys;
   rows += (size_t)h * list_cap;
@@ -408,15 +411,33 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
 
     // scores of centroid tile t for the 32 keys: register r of this lane is centroid
     // 32*t + 8*(r/4) + 4*half + r%4 against key `col`
-    auto tile_load = [&](int t, bf16x8_t (&a)[8]) {
-      const bf16_t* cr = cu + (size_t)min(t * kCentTile + col, B - 1) * kD + half * 8;
+    // Whole lines are loaded (a half row per eight lanes) and turned round in the wave's LDS: loads in the operand's layout touch
+    // a line four times, and a group's 256 KB (1024 centroids) then took 9.5 us to come, 5.3 like this (8 heads of 65536 keys, a
+    // few groups each: 21.1 -> 15.1 us with the candidates listed by bits).
+    struct Tile { u32x4_t p[2][4]; };                    // [half of the features][rows lane / 8 + 8 i]
+    auto tile_load = [&](int t, Tile& a) {
 #pragma unroll
-      for (int st = 0; st < 8; ++st) a[st] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(cr + st * 16));
+      for (int i = 0; i < 4; ++i) {
+        const bf16_t* cr = cu + (size_t)min(t * kCentTile + (lane >> 3) + 8 * i, B - 1) * kD + (lane & 7) * 8;
+        a.p[0][i] = *reinterpret_cast<const u32x4_t*>(cr);
+        a.p[1][i] = *reinterpret_cast<const u32x4_t*>(cr + kD / 2);
+      }
     };
-    auto tile_product = [&](const bf16x8_t (&a)[8]) {
+    auto tile_product = [&](const Tile& a) {
+      bf16_t* s = s_half[wave];                          // LDS accesses of one wave run in order
       f32x16_t acc = {0};
 #pragma unroll
-      for (int st = 0; st < 8; ++st) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[st], xb[st], acc, 0, 0, 0);
+      for (int f = 0; f < 2; ++f) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4_t*>(s + ((lane >> 3) + 8 * i) * kHalfPitch + (lane & 7) * 8) = a.p[f][i];
+        __builtin_amdgcn_wave_barrier();
+        bf16x8_t c[4];
+#pragma unroll
+        for (int st = 0; st < 4; ++st) c[st] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(s + col * kHalfPitch + st * 16 + half * 8));
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int st = 0; st < 4; ++st) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c[st], xb[4 * f + st], acc, 0, 0, 0);
+      }
       return acc;
     };
     auto centroid_of = [&](int t, int r) { return t * kCentTile + 8 * (r / 4) + 4 * half + (r % 4); };
@@ -428,7 +449,7 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
       }
     };
     auto tile_scores = [&](int t) {
-      bf16x8_t a[8];
+      Tile a;
       tile_load(t, a);
       f32x16_t acc = tile_product(a);
       add_bias(acc, t);
@@ -440,11 +461,20 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
         if (centroid_of(t, r) < B) mx = fmaxf(mx, acc[r]);
       return mx;
     };
-    auto tile_candidates = [&](const f32x16_t& acc, int t, float lim) {
+    // bit r: the score in register r is a candidate's
+    auto tile_hits = [&](const f32x16_t& acc, float lim) {
+      unsigned hits = 0u;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int b = centroid_of(t, r);
-        if (b < B && col < n_here && !(acc[r] < lim)) {
+      for (int r = 0; r < 16; ++r) hits |= !(acc[r] < lim) ? 1u << r : 0u;
+      return hits;
+    };
+    // the candidates of two tiles, `hits` 16 bits of each (bits in turn: a branch per register costs more than the few bits set)
+    auto list_candidates = [&](unsigned hits, int t_low, int t_high) {
+      while (hits != 0u) {
+        const int bit = __ffs((int)hits) - 1;
+        hits &= hits - 1u;
+        const int b = centroid_of(bit < 16 ? t_low : t_high, bit & 15);
+        if (b < B && col < n_here) {
           const unsigned i = atomicAdd(&s_ncand, 1u);
           if (i < (unsigned)kCandCap) s_cand[i] = (col << 24) | b;
         }
@@ -459,7 +489,7 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
     int wave_t = wave;
     asm volatile("" : "+v"(wave_t));
     {
-      bf16x8_t a[kKeepTiles][8];
+      Tile a[kKeepTiles];
 #pragma unroll
       for (int k = 0; k < kKeepTiles; ++k) tile_load(min(wave_t + k * kRescoreWaves, n_tiles - 1), a[k]);
       __builtin_amdgcn_sched_barrier(0);     // left alone the compiler keeps three or four loads in flight
@@ -483,16 +513,17 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
       float m = s_max[0][tid];
       for (int w = 1; w < kRescoreWaves; ++w) m = fmaxf(m, s_max[w][tid]);
       // two fp32 scores are compared: the same bound as for the first matrix pass
-      s_lim[tid] = m - (tol * cmax[h] * sqrtf(xnorm2) + 5e-6f * fabsf(m));
+      s_lim[tid] = m - (tol * norm * sqrtf(xnorm2) + 5e-6f * fabsf(m));
     }
     __syncthreads();
     const float lim = s_lim[col];
+    static_assert(kKeepTiles % 2 == 0, "tiles in pairs");
 #pragma unroll
-    for (int k = 0; k < kKeepTiles; ++k) {
-      const int t = wave_t + k * kRescoreWaves;
-      if (t < n_tiles) tile_candidates(kept[k], t, lim);
+    for (int k = 0; k < kKeepTiles; k += 2) {
+      const int t = wave_t + k * kRescoreWaves;            // a tile past the end lists centroids past B: dropped
+      list_candidates(tile_hits(kept[k], lim) | tile_hits(kept[k + 1], lim) << 16, t, t + kRescoreWaves);
     }
-    for (int t = wave_t + kKeepTiles * kRescoreWaves; t < n_tiles; t += kRescoreWaves) tile_candidates(tile_scores(t), t, lim);
+    for (int t = wave_t + kKeepTiles * kRescoreWaves; t < n_tiles; t += kRescoreWaves) list_candidates(tile_hits(tile_scores(t), lim), t, t);
     __syncthreads();
     SAAP_TRACE(3);
     const unsigned n_cand = s_ncand;
