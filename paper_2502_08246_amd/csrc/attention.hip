@@ -58,7 +58,6 @@ struct AttnParams {
   int independent;        // unit = (sequence, query head) instead of (sequence, KV head)
   int masked_lists;       // MASKED kernels: lists per unit in `selected` (one per head), nsel entries each
   int use_table;          // list mode: build the per-chunk run table (pays off from a few chunks per workgroup)
-  int stage;              // list mode: copy the unit's len/off arrays to LDS (needs nseg <= 2*NT, B <= 8*NT)
   int out_bf16;
   int n_dense;            // keys per unit in dense mode
   float scale_log2;       // scale * log2(e)
@@ -892,63 +891,29 @@ __global__ void __launch_bounds__(NT) attn_kernel(AttnParams p) {
     const int32_t* offu = p.off + (size_t)kvu * (p.B + 1);
     const int32_t* sel = p.selected ? p.selected + (size_t)unit * p.nsel : nullptr;
     int mine = 0;
-    if (p.stage) {
-      // One memory round trip instead of two: the selected list and the unit's whole len/off
-      // arrays are fetched together into LDS, the gather by bucket id then reads LDS.
-      int* s_len = seghi + p.max_chunks;                // [B]
-      int* s_off = s_len + p.B;                         // [B]
-      int sv[2], lv[8], ov[8];
+    // Two dependent round trips, list then lengths and first rows, with all loads of a trip in flight.  (Copying the unit's whole
+    // len and off arrays to LDS beside the list saves one of them but pulls 8 bytes per bucket into every workgroup: 12.7 instead of
+    // 12.2 us for 51 of 1024 buckets, 27.6 instead of 27.0 for 205 of 4096.)
+    for (int j = j0; j < j1; j += 2) {
+      int b[2], ln[2], first[2];
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        const int j = tid + k * NT;
-        sv[k] = j < p.nsel ? sel[j] : p.resident;      // entry nsel (if any) is the always-visited run
+        const int at = min(j + k, nseg - 1);             // entry nsel (if any) is the always-visited run
+        b[k] = at < p.nsel ? (sel ? sel[at] : at) : p.resident;
+        b[k] = min(max(b[k], 0), p.B - 1);               // a damaged list must not turn into a read outside the index
       }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int b = tid + k * NT;
-        if (b < p.B) {
-          lv[k] = lenu[b];
-          ov[k] = offu[b];
-        }
+      for (int k = 0; k < 2; ++k) {
+        ln[k] = lenu[b[k]];
+        first[k] = offu[b[k]];
       }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int b = tid + k * NT;
-        if (b < p.B) {
-          s_len[b] = lv[k];
-          s_off[b] = ov[k];
+      for (int k = 0; k < 2; ++k)
+        if (j + k < j1) {
+          pre[j + k + 1] = ln[k];     // temporarily the length; turned into a prefix below
+          rowoff[j + k] = first[k];
+          mine += ln[k];
         }
-      }
-      int bsel[2];                                       // per <= 2 in this mode
-      if (per == 1) {
-        // thread j already holds entry j of the list
-        bsel[0] = sv[0];
-        __syncthreads();
-      } else {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int j = tid + k * NT;
-          if (j < nseg) pre[j + 1] = sv[k];             // bucket id for now
-        }
-        __syncthreads();
-        for (int j = j0; j < j1; ++j) bsel[j - j0] = pre[j + 1];
-        __syncthreads();
-      }
-      for (int j = j0; j < j1; ++j) {
-        const int b = bsel[j - j0];
-        const int ln = s_len[b];
-        pre[j + 1] = ln;
-        rowoff[j] = s_off[b];
-        mine += ln;
-      }
-    } else {
-      for (int j = j0; j < j1; ++j) {
-        const int b = j < p.nsel ? (sel ? sel[j] : j) : p.resident;
-        const int ln = lenu[b];
-        pre[j + 1] = ln;            // temporarily the length; turned into a prefix below
-        rowoff[j] = offu[b];
-        mine += ln;
-      }
     }
     const int incl = (int)wave_prefix_sum((unsigned)mine);
     if (lane == 63) s_wsum[wave] = incl;
@@ -1770,7 +1735,7 @@ __global__ void __launch_bounds__(256) prefill_plan_kernel(const int32_t* __rest
 static int key_bytes(int dtype) { return dtype == kDtypeFp8 ? 2 * kD : dtype == SAAP_BF16 ? 4 * kD : 8 * kD; }
 
 struct LaunchPlan {
-  int P, threads, stage, max_chunks;
+  int P, threads, max_chunks;
   size_t lds;
 };
 
@@ -1820,8 +1785,6 @@ LaunchPlan plan_launch(int n_units, long long est_keys_per_unit, long long max_k
   lp.threads = threads;
   lp.max_chunks = (int)(((max_keys_per_unit + chunk - 1) / chunk + P - 1) / P + 1);
   size_t a = list ? (size_t)(2 * nseg + 1 + 2 * lp.max_chunks) * sizeof(int) : 0;
-  lp.stage = !masked && list && has_selection && nseg <= 2 * threads && B <= 8 * threads && env_int("SAAP_ATTN_STAGE", 1);
-  if (lp.stage) a += (size_t)2 * B * sizeof(int);
   if (masked) a += (size_t)(nseg + B) * sizeof(int);     // heads per run, heads per bucket
   const size_t b = (size_t)(threads / 64) * G * (kD + 2) * sizeof(float) + G * sizeof(float);
   const size_t c = (size_t)(P * G + 2 * G + 4) * sizeof(float) + (size_t)threads * sizeof(float4);
@@ -2117,7 +2080,6 @@ static int32_t sparse_attention(const void* q, const void* Ksorted, const void* 
   const long long est = (long long)Ncap * (masked ? nseg : nprobe) / B + (resident_run >= 0 ? 2048 : 0);
   LaunchPlan lp = plan_launch((int)units, est, Ncap, G, nseg, true, B, nseg > 0, key_bytes(dtype), masked);
   p.P = lp.P;
-  p.stage = lp.stage;
   p.max_chunks = lp.max_chunks;
   p.use_table = (est + (long long)lp.P * (lp.threads / 16 * (G == 8 ? 2 : 4)) - 1) / ((long long)lp.P * (lp.threads / 16 * (G == 8 ? 2 : 4))) > 2;
   if (masked) return launch_masked(p, lp, G, dtype, static_cast<hipStream_t>(stream));
@@ -2175,7 +2137,6 @@ static int32_t dense_attention(const void* q, const void* K, const void* V, cons
   p.n_dense = N; p.scale_log2 = scale * kLog2e; p.kscale = kscale; p.vscale = vscale;
   LaunchPlan lp = plan_launch((int)units, N, N, G, p.nseg, off != nullptr, B, false, key_bytes(dtype));
   p.P = lp.P;
-  p.stage = 0;
   p.max_chunks = lp.max_chunks;
   p.use_table = 1;
   hipStream_t hs = static_cast<hipStream_t>(stream);
@@ -2300,7 +2261,6 @@ static int32_t select_attend(const float* logits, const void* q, const void* Kso
   LaunchPlan lp = plan_launch((int)units, est, Ncap, G, nseg, true, runs, true, key_bytes(dtype));
   if (lp.threads != 512) return two_calls();               // only a tuning override asks for another shape
   p.P = lp.P;
-  p.stage = 0;
   p.max_chunks = lp.max_chunks;
   p.use_table = (est + (long long)lp.P * (lp.threads / 16 * (G == 8 ? 2 : 4)) - 1) / ((long long)lp.P * (lp.threads / 16 * (G == 8 ? 2 : 4))) > 2;
   p.sel_n_sort = geo.n_sort;
