@@ -595,18 +595,25 @@ __device__ __forceinline__ float2 merge_load2(const float2* p) {
 typedef float f32x4_asm __attribute__((ext_vector_type(4)));
 // Eight 16-byte loads at agent scope (sc1: past this XCD's L2), issued back to back; entries with on[k]
 // false load the first address and are zeroed.  The loads are written in assembly because the compiler
-// offers atomic loads of at most 8 bytes; the wait that follows them names every destination, so no use
-// of the values can move before it.
+// offers atomic loads of at most 8 bytes, and wait in the block that issues them: its outputs are written when it ends, and
+// (early clobber) share no register with an address.
 template <bool COHERENT>
 __device__ __forceinline__ void merge_load4x8(const float4* const (&ptr)[8], const bool (&on)[8], float4 (&v)[8]) {
   if constexpr (COHERENT) {
     f32x4_asm r[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(r[k]) : "v"(ptr[k]) : "memory");
-    asm volatile("s_waitcnt vmcnt(0)"
-                 : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7])
-                 :
-                 : "memory");
+    asm volatile(
+        "global_load_dwordx4 %0, %8, off sc1\n\t"
+        "global_load_dwordx4 %1, %9, off sc1\n\t"
+        "global_load_dwordx4 %2, %10, off sc1\n\t"
+        "global_load_dwordx4 %3, %11, off sc1\n\t"
+        "global_load_dwordx4 %4, %12, off sc1\n\t"
+        "global_load_dwordx4 %5, %13, off sc1\n\t"
+        "global_load_dwordx4 %6, %14, off sc1\n\t"
+        "global_load_dwordx4 %7, %15, off sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+        : "v"(ptr[0]), "v"(ptr[1]), "v"(ptr[2]), "v"(ptr[3]), "v"(ptr[4]), "v"(ptr[5]), "v"(ptr[6]), "v"(ptr[7])
+        : "memory");
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = on[k] ? make_float4(r[k].x, r[k].y, r[k].z, r[k].w) : make_float4(0.f, 0.f, 0.f, 0.f);
   } else {
