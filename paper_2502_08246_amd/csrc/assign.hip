@@ -662,8 +662,9 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
     hipLaunchKernelGGL(assign_mfma_kernel<false>, grid, dim3(256), 0, hs, xb, cb, bias, cmax, bucket_ids,
                        flagged, n_flagged, list_cap, Hkv, N, B, tol);
   unsigned* stat = reinterpret_cast<unsigned*>(cmax) + 4095;
-  // workgroups per head: enough to fill the chip twice over all heads together
-  const unsigned per_head = (unsigned)((cus * 2 + Hkv - 1) / Hkv);
+  // workgroups per head: one per compute unit over all heads together, as many as run at once (two rounds of them, most with no
+  // group to score, ended 3 us later)
+  const unsigned per_head = (unsigned)((cus + Hkv - 1) / Hkv);
   hipLaunchKernelGGL(assign_rescore_kernel, dim3((unsigned)Hkv, per_head), dim3(kRescoreThreads), 0, hs, xb, cb, bias, cmax,
                      bucket_ids, flagged, n_flagged, stat, list_cap, Hkv, B, tol);
   return launch_status();
