@@ -258,17 +258,22 @@ order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, i
     for (int k = 0; k < kDeep; ++k)
       if (v[k] >= 0) wave_count_add(cnt, v[k], 1u);
   }
+  load_ids(n0, v);                                       // again, for the placing
   __syncthreads();
   // exclusive prefix over the waves (at most 16384 per half word), totals, and the buckets' offsets
   constexpr int kPairs = kSmallBuckets / 2 / kSmallThreads;                      // pairs of buckets per thread
   static_assert(kPairs == 1, "one pair of buckets per thread");
   unsigned tot = 0u;
-  if (tid < words)
+  if (tid < words) {
+    unsigned c[kSmallWaves];                             // read before the first is written: one LDS latency
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) c[w] = s_cnt[w * words + tid];
+#pragma unroll
     for (int w = 0; w < kSmallWaves; ++w) {
-      const unsigned c = s_cnt[w * words + tid];
       s_cnt[w * words + tid] = tot;
-      tot += c;
+      tot += c[w];
     }
+  }
   const int b0 = 2 * tid, len0 = (int)(tot & 0xffffu), len1 = (int)(tot >> 16);
   const int mine = (b0 < B ? len0 + slack : 0) + (b0 + 1 < B ? len1 + slack : 0);
   const int incl = (int)wave_prefix_sum((unsigned)mine);
@@ -296,16 +301,19 @@ order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, i
   }
   __syncthreads();
   for (int n = n0; n < n1; n += 64 * kDeep) {
-    load_ids(n, v);
+    int now[kDeep];
+#pragma unroll
+    for (int k = 0; k < kDeep; ++k) now[k] = v[k];
+    if (n + 64 * kDeep < n1) load_ids(n + 64 * kDeep, v);
 #pragma unroll
     for (int k = 0; k < kDeep; ++k)
-      if (n + k * 64 < n1) place_round(v[k], n + k * 64 + lane, id_bits, s_next, cnt, ix);
+      if (n + k * 64 < n1) place_round(now[k], n + k * 64 + lane, id_bits, s_next, cnt, ix);
   }
   // free slots: the end of a bucket is the start of the next
   const int all = s_end;
-  for (int b = wave; slack > 0 && b < B; b += kSmallWaves) {
-    const int end = b + 1 < B ? s_next[b + 1] : all;
-    for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
+  for (int i = tid; i < B * slack; i += kSmallThreads) {
+    const int b = i / slack;
+    ix[(b + 1 < B ? s_next[b + 1] : all) - slack + (i - b * slack)] = -1;
   }
   for (int j = all + max(W, 0) + tid; j < Ncap; j += kSmallThreads) ix[j] = -1;       // behind the last run: dropped keys
   if (W > 0)
