@@ -358,6 +358,54 @@ mass_normalise_batch_kernel(const float2* __restrict__ part, float* __restrict__
   }
 }
 
+// The same for up to 32 PER buckets: 32 threads to a query, each holding its pairs, which are read once and all in flight together
+// (8 x 1000 queries and 1024 buckets: 32.7 us in the kernel above, 22.6 here, 98 MB).
+template <int PER>
+__global__ void __launch_bounds__(1024)
+mass_normalise_held_kernel(const float2* __restrict__ part, float* __restrict__ mass, float* __restrict__ lse, int B, int R) {
+  constexpr int kGroups = 32, kTile = 256;               // buckets per tile on the way out
+  __shared__ float s_m[kGroups][32], s_l[kGroups][32];
+  __shared__ float s_tile[32][kTile + 1];
+  const int tid = threadIdx.x, ql = tid & 31, bg = tid >> 5;
+  const int unit = blockIdx.y, q0 = blockIdx.x * 32;
+  const float2* pu = part + (size_t)unit * B * R + min(q0 + ql, R - 1);
+  float2 p[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) p[u] = pu[(size_t)min(bg + kGroups * u, B - 1) * R];
+  float M = kNegBig, L = 0.f;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) M = fmaxf(M, p[u].x);
+  s_m[bg][ql] = M;
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) M = fmaxf(M, s_m[g][ql]);
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    p[u].y *= fast_exp2(p[u].x - M);
+    if (bg + kGroups * u < B) L += p[u].y;
+  }
+  s_l[bg][ql] = L;
+  __syncthreads();
+  L = 0.f;
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) L += s_l[g][ql];      // fixed order
+  const float inv = L > 0.f ? 1.0f / L : 0.f;
+  if (bg == 0 && q0 + ql < R && lse) lse[(size_t)unit * R + q0 + ql] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
+#pragma unroll
+  for (int t = 0; t < PER * kGroups / kTile; ++t) {
+    if (t * kTile >= B) break;
+    if (t > 0) __syncthreads();                          // the tile before has been written out
+#pragma unroll
+    for (int u = 0; u < kTile / kGroups; ++u) s_tile[ql][bg + kGroups * u] = p[t * (kTile / kGroups) + u].y * inv;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 32 * kTile / 1024; ++i) {
+      const int row = (tid >> 8) + 4 * i, b = t * kTile + (tid & 255);
+      if (q0 + row < R && b < B) mass[((size_t)unit * R + q0 + row) * B + b] = s_tile[row][tid & 255];
+    }
+  }
+}
+
 }  // namespace
 
 size_t mass_batch_workspace_bytes(long long units, long long R, int B) {
@@ -442,7 +490,10 @@ extern "C" int32_t saap_bucket_attention_mass_batch(const void* q, const void* K
   if (scale_log2 < 0.f) qt == 2 ? launch(mass_mfma_kernel<2, -1>) : launch(mass_mfma_kernel<1, -1>);
   else if (scale_log2 == 0.f) qt == 2 ? launch(mass_mfma_kernel<2, 0>) : launch(mass_mfma_kernel<1, 0>);
   else qt == 2 ? launch(mass_mfma_kernel<2, 1>) : launch(mass_mfma_kernel<1, 1>);
-  hipLaunchKernelGGL(mass_normalise_batch_kernel, dim3((unsigned)((R + 31) / 32), (unsigned)units), dim3(256), 0, hs, part,
-                     mass, lse, B, R);
+  // (pairs of more buckets than 1024 do not fit the registers: read twice)
+  const dim3 grid((unsigned)((R + 31) / 32), (unsigned)units);
+  if (B <= 256) hipLaunchKernelGGL(mass_normalise_held_kernel<8>, grid, dim3(1024), 0, hs, part, mass, lse, B, R);
+  else if (B <= 1024) hipLaunchKernelGGL(mass_normalise_held_kernel<32>, grid, dim3(1024), 0, hs, part, mass, lse, B, R);
+  else hipLaunchKernelGGL(mass_normalise_batch_kernel, grid, dim3(256), 0, hs, part, mass, lse, B, R);
   return launch_status();
 }

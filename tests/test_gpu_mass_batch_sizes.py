@@ -87,3 +87,9 @@ def test_an_infinite_score_stays_in_its_bucket(saap, scale):
     assert torch.equal(~torch.isfinite(mass), bad) and torch.equal(torch.isinf(lse), torch.isinf(want_lse))
     # scores of magnitude 8 in sums of another order: as in test_mass
     torch.testing.assert_close(mass[~bad], want[~bad], rtol=1e-4, atol=1e-7)
+
+
+@pytest.mark.parametrize("R,B", [(1, 1), (31, 31), (33, 255), (32, 256), (40, 257), (5, 511), (33, 1023), (64, 1024), (33, 1025)])
+def test_mass_rows_of_odd_lengths(saap, R, B):
+    """Rows held in registers (up to 256 and up to 1024 buckets) and rows read twice: every third bucket empty."""
+    test_mass(saap, R, [(2, 0, 3)[b % 3] for b in range(B)], 0.09, 1.0)
