@@ -49,10 +49,12 @@ cent_norm_kernel(const bf16_t* __restrict__ cent, float* __restrict__ cmax, int 
   }
 }
 
-template <bool HAS_BIAS>
+// NORMS: the workgroup makes the largest norm of its head itself, from the rows on their way to LDS, and the head's first one
+// leaves it in cmax (see the launch).
+template <bool HAS_BIAS, bool NORMS>
 __global__ void __launch_bounds__(256, 2)
 assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent, const float* __restrict__ bias,
-                   const float* __restrict__ cmax, int32_t* __restrict__ ids, int32_t* __restrict__ flagged,
+                   float* __restrict__ cmax, int32_t* __restrict__ ids, int32_t* __restrict__ flagged,
                    unsigned* __restrict__ n_flagged, size_t list_cap, int Hkv, int N, int B, float tol) {
   __shared__ __align__(16) bf16_t s_c[2][kSlab * kPitch];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -104,11 +106,17 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
       stage[i] = *reinterpret_cast<const u32x4_t*>(cu + (size_t)b * kD + pc * 8);
     }
   };
+  float norm2 = 0.f;                             // NORMS: the largest squared norm of the rows that the thread's row of lanes has stored
   auto stash = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < kSlab / 16; ++i) {
       const int piece = tid + i * 256, r = piece >> 4, pc = piece & 15;
       *reinterpret_cast<u32x4_t*>(&s_c[buf][r * kPitch + pc * 8]) = stage[i];
+      if constexpr (NORMS) {
+        Vec8<bf16_t> v;
+        v.r = make_uint4(stage[i][0], stage[i][1], stage[i][2], stage[i][3]);
+        norm2 = fmaxf(norm2, sum16(v.dot(v)));
+      }
     }
   };
   fetch(0);
@@ -200,10 +208,22 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   step(0, 0, a0, a1, b0, b1, (n_slabs - 1) * 2 + 1, false, true);
 
   // lanes l and l+32 own the same key: merge their candidates, lower id on equal packed scores
-  const float tol_c = tol * cmax[h];
   __shared__ unsigned s_listed, s_list_base;
+  __shared__ float s_norm2[4];
   if (tid == 0) s_listed = 0u;
+  if constexpr (NORMS) {
+    norm2 = max_rows(norm2);
+    if (lane == 0) s_norm2[wave] = norm2;
+  }
   __syncthreads();
+  float norm;
+  if constexpr (NORMS) {
+    norm = sqrtf(fmaxf(fmaxf(s_norm2[0], s_norm2[1]), fmaxf(s_norm2[2], s_norm2[3]))) * 1.0001f;
+    if (tid == 0 && blockIdx.x == 0 && unit < Hkv) cmax[h] = norm;
+  } else {
+    norm = cmax[h];
+  }
+  const float tol_c = tol * norm;
   bool listed[2];
   unsigned slot[2];
 #pragma unroll
@@ -653,14 +673,17 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
   // fp32 accumulation of 128 exact products: |error| <= 128 * 2^-24 * |x| |c| per score; two scores
   // are compared, and a factor 4 of head-room covers the matrix core's internal summation order.
   const float tol = 8.0f * 128.0f * 5.9604645e-8f;
-  hipLaunchKernelGGL(cent_norm_kernel, dim3((unsigned)Hkv), dim3(kNormThreads), 0, hs, cb, cmax, B);
   const dim3 grid((unsigned)((N + kRowsPerWg - 1) / kRowsPerWg), (unsigned)units);
-  if (bias)
-    hipLaunchKernelGGL(assign_mfma_kernel<true>, grid, dim3(256), 0, hs, xb, cb, bias, cmax, bucket_ids, flagged,
-                       n_flagged, list_cap, Hkv, N, B, tol);
-  else
-    hipLaunchKernelGGL(assign_mfma_kernel<false>, grid, dim3(256), 0, hs, xb, cb, bias, cmax, bucket_ids,
-                       flagged, n_flagged, list_cap, Hkv, N, B, tol);
+  // The norms take a workgroup some 0.1 us per slab of centroids and round of workgroups (two per compute unit), a launch of their
+  // own 2.5 us and, behind other work, 4.7.
+  const long long rounds = ((long long)grid.x * units + 2 * cus - 1) / (2 * cus);
+  const bool own_norms = rounds * ((B + kSlab - 1) / kSlab) <= 16;
+  if (!own_norms) hipLaunchKernelGGL(cent_norm_kernel, dim3((unsigned)Hkv), dim3(kNormThreads), 0, hs, cb, cmax, B);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, hs, xb, cb, bias, cmax, bucket_ids, flagged, n_flagged, list_cap, Hkv, N, B, tol);
+  };
+  if (bias) own_norms ? launch(assign_mfma_kernel<true, true>) : launch(assign_mfma_kernel<true, false>);
+  else own_norms ? launch(assign_mfma_kernel<false, true>) : launch(assign_mfma_kernel<false, false>);
   unsigned* stat = reinterpret_cast<unsigned*>(cmax) + 4095;
   // workgroups per head: one per compute unit over all heads together, as many as run at once (two rounds of them, most with no
   // group to score, ended 3 us later)
