@@ -7,16 +7,19 @@
 // and fold_batch_norm turns the trained layer into plain W1, b1 for inference.
 // query_model_loss_grads computes L and the gradients of all four parameter tensors for a batch,
 // adam_update applies one Adam step to a tensor; a training step is the first call followed by
-// the second on each tensor.  All arithmetic is fp32, every sum is taken by one thread or one
-// workgroup in a fixed order (no atomics), so a step is reproducible bit for bit.
+// the second on each tensor.  All arithmetic is fp32 or, in the large products, as exact as fp32 (below); every sum is
+// taken by one thread or one workgroup in a fixed order (no atomics), so a step is reproducible bit for bit.
 //
 // The five matrix products run on the matrix cores.  fp32 matrix instructions reach 154 TFLOP/s in a large product on this card
 // and take the vector units' time; bfloat16 ones do 16 times the work in the same cycles.  So the operands of a large product
-// are split into three bfloat16 each on their way to LDS (nothing is lost: 3 x 8 bits) and six products of those make one fp32
-// product, the five small ones summed apart: the gradients' error against float64 is 0.6 to 1.0 times that of fp32 matrix
-// instructions (8 x 1000 rows, 512 hidden units, 1024 buckets: dW1 3.8e-7 instead of 6.2e-7, dW2 3.2e-7 instead of 4.7e-7).
-// Operands with values that a bfloat16 does not hold (infinities, NaN, above 3.39e38) make the tile not finite; it is then
-// done again with fp32 instructions.  The first product stays in fp32, and so do results of few tiles (gemm_split_kernel).
+// are split into three bfloat16 each on their way to LDS (nothing is lost: 3 x 8 bits, the values scaled up before the split so
+// that the last bits of the smallest ones are bfloat16 values too) and six products of those make one fp32 product, the five
+// small ones summed apart: the gradients' error against float64 is 0.6 to 1.0 times that of fp32 matrix instructions (8 x 1000
+// rows, 512 hidden units, 1024 buckets: dW1 3.8e-7 instead of 6.2e-7, dW2 3.2e-7 instead of 4.7e-7).  A sum of one term only,
+// where nothing averages out, is 1.03 times as far off: the products of planes left out are up to 2^-26 of it.
+// Operands whose scaled values a bfloat16 does not hold (infinities, NaN, from 2^104 on) make the tile not finite, and so do sums
+// from 2^80 on; it is then done again with fp32 instructions.  The first product stays in fp32, and so do results of few tiles
+// (gemm_split_kernel).
 // Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
 // column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
 // 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 59 now (870 TFLOP/s of
@@ -49,6 +52,10 @@ struct GemmArgs {
 
 // fp32 values as sums of three bfloat16 each, to 24 bits and more: the nearest one, the nearest to what that leaves, and the
 // nearest to what is left then.  This takes the values' next plane, as pairs, and leaves the rest.
+// An fp32 value is a multiple of 2^-149, the smallest normal bfloat16 is 2^-126: scaled by 2^24 (exact) a value of any size keeps
+// its 24 bits.  (Unscaled, the third plane of values below 2^-110 and then the second fall below the smallest bfloat16: 9e-6 of
+// products of operands near 2^-118, which fp32 instructions have to 5e-7.  The multiplication takes 2 to 4 % of a product's time.)
+constexpr float kUp = 16777216.f, kDown = 1.f / (kUp * kUp);
 template <int E>
 __device__ __forceinline__ void take_plane(float* rest, uint32_t* u) {
 #pragma unroll
@@ -108,7 +115,7 @@ struct PlaneLoader {
   __device__ __forceinline__ void stash(uint4* s) const {
     float rest[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) rest[e] = r[e];
+    for (int e = 0; e < E; ++e) rest[e] = r[e] * kUp;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       uint32_t u[E / 2];
@@ -431,8 +438,8 @@ gemm_kernel(GemmArgs g) {
 #pragma unroll
   for (int t = 0; t < TM; ++t) {
     const int tm = m0 + wm + 32 * t, tn = n0 + wn;
-    acc[t] += low[t];
-    // not a number, infinite, or too large for a bfloat16: as fp32 products have it
+    acc[t] = (acc[t] + low[t]) * kDown;
+    // not a number, infinite, or too large for a scaled bfloat16: as fp32 products have it
     if (!all_finite(acc[t])) acc[t] = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
     store_tile<EPI, 16>(g, w, tm, tn + col, half, acc[t]);
   }

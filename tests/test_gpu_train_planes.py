@@ -53,6 +53,29 @@ def test_values_beyond_bfloat16(saap, R, hidden, B):  # noqa: F811
         assert ((got.double() - g).norm() <= 3e-6 * g.norm()), name
 
 
+# dz follows the scale of T, h and the second operand of dW1 that of x, da that of W2.  The third is the same problem with no value
+# near an end of the range.
+@pytest.mark.parametrize("Hw,R,hidden,B", [(16, 320, 512, 512), (16, 640, 512, 1024)])
+@pytest.mark.parametrize("scales,plain,tol", [
+    ((0, -100, 0), (0, 0, 0), 1e-7), ((-118, 20, 0), (-70, 20, 0), 1e-7), ((0, 20, -118), (0, 20, -70), 1e-7),
+    ((0, 100, 0), (0, 0, 0), 2e-6)])
+def test_products_of_operands_of_any_size(saap, Hw, R, hidden, B, scales, plain, tol):  # noqa: F811
+    """Powers of two on x, T and W2 (with W2 or h below 2^-60 the logits are b2): the gradients are the plain problem's times powers
+    of two.  Down to 2^-126 that is exact, and the few values below it are off by 2^-32 of the others: 1e-7.  Sums beyond 2^80 are made
+    with fp32 instructions: as far apart as the two ways are (6e-7 and 4e-7 from float64, twice that)."""
+    x, T, (W1, b1, W2, b2) = problem(11, Hw, R, 128, hidden, B, torch.float32)
+
+    def gradients(ex, eT, eW):
+        params = to_dev((W1, 0 * b1, W2 * 2.0 ** eW, b2))
+        return [g.double() for g in saap.query_model_loss_grads((x * 2.0 ** ex).to(DEV), (T * 2.0 ** eT).to(DEV), params)[1]]
+
+    (ex, eT, eW), got, want = (s - p for s, p in zip(scales, plain)), gradients(*scales), gradients(*plain)
+    for name, g, w, e in zip(("dW1", "db1", "dW2", "db2"), got, want, (ex + eT + eW, eT + eW, ex + eT, eT)):
+        w = w * 2.0 ** e
+        dims = tuple(range(1, w.dim()))
+        assert (w.norm(dim=dims) > 0).all() and ((g - w).norm(dim=dims) <= tol * w.norm(dim=dims)).all(), name
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_a_weight_that_is_no_number_spoils_its_set_only(saap, bad):  # noqa: F811
     x, T, params = problem(4, 16, 256, 32, 256, 512, torch.float32)
