@@ -22,7 +22,8 @@ def saap():
 
 @pytest.mark.parametrize("heads", [1, 2, 4, 8])
 @pytest.mark.parametrize("B,nprobe", [(16, 1), (64, 8), (144, 2), (1000, 51), (1024, 128), (2048, 129), (4096, 205), (4096, 385),
-                                      (8192, 1000), (8192, 1025), (512, 250)])
+                                      (4096, 1024), (8192, 1000), (8192, 1025),
+                                      (512, 250)])
 @pytest.mark.parametrize("spread", [0.0, 0.01, 1.0, 40.0])
 def test_lists_from_logits(saap, heads, B, nprobe, spread):
     Hkv = 2
