@@ -490,9 +490,13 @@ extern "C" int32_t saap_bucket_attention_mass_batch(const void* q, const void* K
   if (scale_log2 < 0.f) qt == 2 ? launch(mass_mfma_kernel<2, -1>) : launch(mass_mfma_kernel<1, -1>);
   else if (scale_log2 == 0.f) qt == 2 ? launch(mass_mfma_kernel<2, 0>) : launch(mass_mfma_kernel<1, 0>);
   else qt == 2 ? launch(mass_mfma_kernel<2, 1>) : launch(mass_mfma_kernel<1, 1>);
-  // (pairs of more buckets than 1024 do not fit the registers: read twice)
+  // Pairs held in registers where their 32 threads a query each have more than four (up to 128 buckets the smaller workgroups are as
+  // fast: 8 x 64 rows of 128 4.4 us, 4.7 held), in as few registers as do (288 buckets, 1000 rows: 11.4 us read twice, 11.8 with 32
+  // pairs a thread, 9.9 with 16); those of more than 1024 buckets do not fit.
   const dim3 grid((unsigned)((R + 31) / 32), (unsigned)units);
-  if (B <= 256) hipLaunchKernelGGL(mass_normalise_held_kernel<8>, grid, dim3(1024), 0, hs, part, mass, lse, B, R);
+  if (B <= 128) hipLaunchKernelGGL(mass_normalise_batch_kernel, grid, dim3(256), 0, hs, part, mass, lse, B, R);
+  else if (B <= 256) hipLaunchKernelGGL(mass_normalise_held_kernel<8>, grid, dim3(1024), 0, hs, part, mass, lse, B, R);
+  else if (B <= 512) hipLaunchKernelGGL(mass_normalise_held_kernel<16>, grid, dim3(1024), 0, hs, part, mass, lse, B, R);
   else if (B <= 1024) hipLaunchKernelGGL(mass_normalise_held_kernel<32>, grid, dim3(1024), 0, hs, part, mass, lse, B, R);
   else hipLaunchKernelGGL(mass_normalise_batch_kernel, grid, dim3(256), 0, hs, part, mass, lse, B, R);
   return launch_status();

@@ -89,7 +89,9 @@ def test_an_infinite_score_stays_in_its_bucket(saap, scale):
     torch.testing.assert_close(mass[~bad], want[~bad], rtol=1e-4, atol=1e-7)
 
 
-@pytest.mark.parametrize("R,B", [(1, 1), (31, 31), (33, 255), (32, 256), (40, 257), (5, 511), (33, 1023), (64, 1024), (33, 1025)])
+@pytest.mark.parametrize("R,B", [
+    (1, 1), (31, 31), (40, 128), (33, 129), (33, 255), (32, 256), (40, 257), (5, 511), (40, 512), (33, 513), (33, 1023), (64, 1024),
+    (33, 1025)])
 def test_mass_rows_of_odd_lengths(saap, R, B):
-    """Rows held in registers (up to 256 and up to 1024 buckets) and rows read twice: every third bucket empty."""
+    """Rows held in registers (129 to 1024 buckets) and rows read twice: every third bucket empty."""
     test_mass(saap, R, [(2, 0, 3)[b % 3] for b in range(B)], 0.09, 1.0)
