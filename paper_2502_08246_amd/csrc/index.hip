@@ -6,9 +6,9 @@
 // order):
 //   1. hist      every workgroup counts the bucket ids of its slice of positions
 //   2. colscan   per bucket, exclusive scan of the slice counts over slices -> len, slice bases
-//   3. scatter   exclusive scan of (len + slack) over the buckets -> off; one workgroup per slice; every wave walks its part of the slice in order, 64 positions at a
-//                time; the rank of a position among equal ids inside the 64 comes from ballots, the waves' and
-//                the buckets' running positions are kept in LDS -> idx
+//   3. scatter   exclusive scan of (len + slack) over the buckets -> off; one workgroup per slice; every wave walks
+//                its part of the slice in order, 64 positions at a time; the rank of a position among equal ids
+//                inside the 64 comes from ballots, the waves' and the buckets' running positions are kept in LDS -> idx
 //   4. permute   rows of K and V are copied to their slot, 16 bytes per lane, whole rows
 // A short context is one slice: order_small does steps 1 to 3 in one launch.
 //
@@ -21,7 +21,7 @@
 namespace saap {
 namespace {
 
-constexpr int kSlice = 2048;   // positions per slice (one histogram / one scatter wave each)
+constexpr int kSlice = 2048;   // positions per slice (one workgroup of the histogram and of the scatter each)
 
 __global__ void __launch_bounds__(256)
 hist_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ slice_hist, int N, int B, int n_slices,
@@ -136,17 +136,22 @@ __device__ __forceinline__ void place_round(int b, int n, int id_bits, const int
 // of one share an L2, where the 4-byte stores of many slices to a line of idx meet (64 units of 131072 positions: 105 -> 58 us;
 // 8 of 65536: 9.6 -> 7.9).  The workgroup also marks the free slots of every n_slices-th bucket and its share of those
 // behind the last run: every entry of idx is written, and the row copy reads them all.
+// KW: 64 KW runs to a wave, B <= 256 KW; their lengths and earlier slices' counts are loaded with the ids, all in flight together.
+// Scan and scatter, 8 units of 500000 positions, 4096 / 8192 buckets: 48 / 146 us with the scan in a launch of its own, 84 / 275 with
+// 16 / 32 neighbouring runs a thread and an array more in LDS, 41 / 110 now; 64 units of 131072, 1024 / 4096 buckets: 56 / 106, 53 / 178
+// and 52 / 91.
 constexpr int kScatterThreads = 256, kScatterWaves = kScatterThreads / 64;
+template <int KW>
 __global__ void __launch_bounds__(kScatterThreads)
 scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slice_base, int32_t* __restrict__ len,
                int32_t* __restrict__ off, int32_t* __restrict__ idx, int N, int Ncap, int B,
                int n_slices, int id_bits, int lo, int hi, int slack, int W, int n_res) {
-  extern __shared__ int s_next[];                        // [B] | off [B + 1] | counters [waves][words]
+  // Runs' starts for this slice [B, to a multiple of four] | counters [waves][words]
+  extern __shared__ __align__(16) int s_next[];
   __shared__ int s_wsum[kScatterWaves];
   const int unit = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int words = (B + 1) / 2;
-  int* s_off = s_next + B;
-  unsigned* s_cnt = reinterpret_cast<unsigned*>(s_off + B + 1);
+  const int words = (B + 1) / 2, padded = (B + 3) & ~3;
+  unsigned* s_cnt = reinterpret_cast<unsigned*>(s_next + padded);
   const int32_t* base = slice_base + ((size_t)unit * n_slices + slice) * B;
   const int lstride = W >= 0 ? B + 1 : B;
   int32_t* l = len + (size_t)unit * lstride;
@@ -161,35 +166,63 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
     const int n = n0 + k * 64 + lane;
     mine[k] = n >= lo && n < hi ? idu[n] : -1;           // hi <= N
   }
+  // the wave's share of the runs, [w0, w1): their lengths, and what earlier slices place in them
+  const int w0 = wave * 64 * KW, w1 = min(w0 + 64 * KW, B);
+  int run[KW], earlier[KW];
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    const int b = min(w0 + k * 64 + lane, B - 1);
+    run[k] = l[b];
+    earlier[k] = base[b];
+  }
   for (int i = tid; i < kScatterWaves * words; i += kScatterThreads) s_cnt[i] = 0u;
-  for (int b = tid; b < B; b += kScatterThreads) {
-    s_next[b] = base[b];
-    s_off[b + 1] = l[b] + slack;
+  // Every slice scans the runs of its unit for itself: a launch between the column scan and this one takes 4.6 us (10.8 at 8192
+  // buckets).  Each wave turns its runs round in the place of their starts, four neighbouring ones to a lane: no bank conflicts,
+  // and no more LDS than without the scan.
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    const int b = w0 + k * 64 + lane;
+    if (b < padded) s_next[b] = b < B ? run[k] + slack : 0;
   }
-  __syncthreads();
-  // every slice scans the runs of its unit for itself: 1.0 us more here (8 units of 65536 positions; 3 us of 60 for 64 of 131072)
-  // where a launch between the column scan and this one took 4.6
-  const int per = (B + kScatterThreads - 1) / kScatterThreads, b0 = min(tid * per, B), b1 = min(b0 + per, B);
-  int run_of = 0;
-  for (int b = b0; b < b1; ++b) run_of += s_off[b + 1];
-  const int incl = (int)wave_prefix_sum((unsigned)run_of);
-  if (lane == 63) s_wsum[wave] = incl;
-  __syncthreads();
-  int at = incl - run_of;
-  for (int w = 0; w < wave; ++w) at += s_wsum[w];
-  if (tid == 0) s_off[0] = 0;
-  for (int b = b0; b < b1; ++b) {
-    s_next[b] += at;
-    at += s_off[b + 1];
-    s_off[b + 1] = at;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the wave's own writes, in other lanes
+  int4 four[KW / 4];
+  int total = 0;
+#pragma unroll
+  for (int k = 0; k < KW / 4; ++k) {
+    const int b = w0 + k * 256 + 4 * lane;
+    four[k] = b < B ? *reinterpret_cast<const int4*>(s_next + b) : make_int4(0, 0, 0, 0);
+    total += (four[k].x + four[k].y) + (four[k].z + four[k].w);
   }
+  total = (int)wave_prefix_sum((unsigned)total);
+  if (lane == 63) s_wsum[wave] = total;
+  __syncthreads();
 #pragma unroll
   for (int k = 0; k < kRounds; ++k) {
     if (mine[k] >= B) mine[k] = -1;
     if (mine[k] >= 0) wave_count_add(s_cnt + wave * words, mine[k], 1u);
   }
+  int at = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kScatterWaves; ++w) {
+    at += w < wave ? s_wsum[w] : 0;
+    all += s_wsum[w];
+  }
+#pragma unroll
+  for (int k = 0; k < KW / 4; ++k) {
+    const int4 v = four[k];
+    const int sum = (v.x + v.y) + (v.z + v.w), incl = (int)wave_prefix_sum((unsigned)sum), first = at + incl - sum;
+    const int b = w0 + k * 256 + 4 * lane;
+    if (b < B) *reinterpret_cast<int4*>(s_next + b) = make_int4(first, first + v.x, first + v.x + v.y, first + v.x + v.y + v.z);
+    at += __builtin_amdgcn_readlane(incl, 63);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    const int b = w0 + k * 64 + lane;
+    if (b < B) s_next[b] += earlier[k];
+  }
   __syncthreads();
-  // exclusive prefix over the waves; at most 2048 per half word, no carry between the two
+  // exclusive prefix of the counters over the waves; at most 2048 per half word, no carry between the two
   for (int i = tid; i < words; i += kScatterThreads) {
     unsigned run = 0u;
 #pragma unroll
@@ -202,25 +235,36 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kRounds; ++k) place_round(mine[k], n0 + k * 64 + lane, id_bits, s_next, s_cnt + wave * words, ix);
-  for (int b = slice + wave * n_slices; slack > 0 && b < B; b += n_slices * kScatterWaves) {
-    const int end = s_off[b + 1];
-    for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
+  // free slots: those of the wave's runs slice, slice + n_slices, ...; a run ends where the next starts
+  const int first_marked = w0 + (slice + n_slices - w0 % n_slices) % n_slices;
+  for (int m0 = first_marked; slack > 0 && m0 < w1; m0 += 64 * n_slices) {
+    const int next = m0 + lane * n_slices + 1;
+    const int ends = next < w1 ? s_next[next] - base[next] : at;
+    const int n_marked = min(64, (w1 - m0 + n_slices - 1) / n_slices);
+    for (int i = 0; i < n_marked; ++i) {
+      const int end = __builtin_amdgcn_readlane(ends, i);
+      for (int j = lane; j < slack; j += 64) ix[end - slack + j] = -1;
+    }
   }
-  // the unit's off; with a resident block (W >= 0) one more run of W slots closes it, n_res of them in use
+  // the unit's off (no slice is earlier than the first); with a resident block (W >= 0) one more run of W slots closes it, n_res
+  // of them in use
   if (slice == 0) {
-    for (int b = tid; b <= B; b += kScatterThreads) o[b] = s_off[b];
-    if (W >= 0 && tid == 0) {
-      o[B + 1] = s_off[B] + W;
-      l[B] = n_res;
+    for (int b = tid; b < B; b += kScatterThreads) o[b] = s_next[b];
+    if (tid == 0) {
+      o[B] = all;
+      if (W >= 0) {
+        o[B + 1] = all + W;
+        l[B] = n_res;
+      }
     }
   }
   // keys with ids outside [0,B) are dropped: as many slots stay empty behind the last run
-  for (int j = s_off[B] + max(W, 0) + slice * kScatterThreads + tid; j < Ncap; j += n_slices * kScatterThreads) ix[j] = -1;
+  for (int j = all + max(W, 0) + slice * kScatterThreads + tid; j < Ncap; j += n_slices * kScatterThreads) ix[j] = -1;
 }
 
 // Steps 1 to 3 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
-// waves per unit, each wave counting and then placing its sixteenth of the positions.  Five launches of 2 to 3 us become
-// one (8 heads of 5003 keys: 26 -> 10 us).
+// waves per unit, each wave counting and then placing its sixteenth of the positions.  Launches of 2 to 3 us each, five when this
+// was measured, become one (8 heads of 5003 keys: 26 -> 10 us).
 constexpr int kSmallKeys = 16384, kSmallBuckets = 2048, kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
 __global__ void __launch_bounds__(kSmallThreads)
 order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
@@ -725,10 +769,18 @@ void saap::order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int
   hipLaunchKernelGGL(hist_kernel, dim3(n_slices, (unsigned)units), dim3(256), next_bytes, hs, bucket_ids, slice_hist, N, B, n_slices,
                      lo, hi);
   hipLaunchKernelGGL(colscan_kernel, dim3((B + 255) / 256, (unsigned)units), dim3(256), 0, hs, slice_hist, len, B, n_slices, lstride);
-  const size_t lds = 2 * next_bytes + sizeof(int) + kScatterWaves * wave_bytes;
-  (void)allow_lds<scatter_kernel>(lds);
-  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)units, n_slices), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, len, off,
-                     idx, N, Ncap, B, n_slices, id_bits, lo, hi, slack, W, n_res);
+  const size_t lds = (size_t)((B + 3) & ~3) * sizeof(int) + kScatterWaves * wave_bytes;
+  auto scatter = [&](auto runs) {
+    constexpr int KW = decltype(runs)::value;
+    (void)allow_lds<scatter_kernel<KW>>(lds);
+    hipLaunchKernelGGL(scatter_kernel<KW>, dim3((unsigned)units, n_slices), dim3(kScatterThreads), lds, hs, bucket_ids, slice_hist, len,
+                       off, idx, N, Ncap, B, n_slices, id_bits, lo, hi, slack, W, n_res);
+  };
+  static_assert(SAAP_MAX_BUCKETS <= 256 * 32, "runs of a scatter workgroup");
+  if (B <= 1024) scatter(std::integral_constant<int, 4>{});
+  else if (B <= 2048) scatter(std::integral_constant<int, 8>{});
+  else if (B <= 4096) scatter(std::integral_constant<int, 16>{});
+  else scatter(std::integral_constant<int, 32>{});
   if (W > 0)
     hipLaunchKernelGGL(resident_kernel, dim3((unsigned)((W + 255) / 256), (unsigned)units), dim3(256), 0, hs, bucket_ids, off, idx,
                        res_ids, N, Ncap, B, n_sink, n_recent, n_res);

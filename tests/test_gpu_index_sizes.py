@@ -118,9 +118,10 @@ def test_centroids_from_ids(saap, S, N, B, dtype):
 
 @pytest.mark.parametrize("N,B,slack,window", [
     (16400, 255, 1, None), (18432, 256, 0, (1, 2047)), (20000, 257, 3, (2, 30)), (17000, 8191, 1, None), (40961, 8192, 0, (1, 2047)),
-    (300000, 2, 1, None)])
+    (300000, 2, 1, None), (16385, 1024, 70, None), (16385, 1030, 2, None), (20000, 2051, 3, (1, 30)), (150000, 4099, 1, None)])
 def test_runs_scanned_by_every_slice(saap, N, B, slack, window):
-    """More than one slice, bucket counts around a multiple of a workgroup's threads and the largest."""
+    """More than one slice, bucket counts around a multiple of a workgroup's threads (four runs each), no multiple of four, several
+    rounds of a wave and the largest."""
     S, Hkv = (1, 1) if N > 100000 else (1, 2)
     ids = np.random.default_rng(N + B).integers(0, B, (S, Hkv, N)).astype(np.int32)
     K = torch.zeros(S, Hkv, N, 128, dtype=torch.bfloat16, device=DEV)
