@@ -5,11 +5,14 @@
 // One workgroup per list.  Every bucket becomes a 64-bit key
 //     (order-preserving image of the fp32 score) << 32 | (0xFFFFFFFF - bucket id)
 // so keys are unique and "larger key" means (higher score, then lower id).
-//   * radix kernel (nprobe well below B): a most-significant-digit radix select over the 32-bit
-//     score images (four passes of 8 bits, LDS histogram + one-wave scan) finds the score of the
-//     nprobe-th bucket; buckets above it, and the lowest-id buckets equal to it, are compacted
-//     and only those nprobe keys are put in order (by counting larger keys for lists up to
-//     1024, by a bitonic network beyond).
+//   * radix kernel (nprobe well below B).  Lists of up to 1024 buckets from logits: one histogram of 512
+//     bins over the sums of softmax rows finds the bin of the nprobe-th bucket and the places of every
+//     bin in the list; the buckets from that bin on go there and are ranked inside their bin.  Other
+//     scores, longer lists and logits that pile up in few bins: a most-significant-digit radix select
+//     over the 32-bit score images (8 bits a pass, LDS histogram + one-wave scan) finds the score of the
+//     nprobe-th bucket; buckets above it, and the lowest-id buckets equal to it, are compacted and only
+//     those nprobe keys are put in order (by counting larger keys for lists up to 1024, by a bitonic
+//     network beyond).
 //   * sort kernel (nprobe close to B): all keys are sorted in LDS with a bitonic network.
 // Both give exactly the (score descending, id ascending) order of the definition.
 #include "select_body.h"
@@ -69,8 +72,6 @@ select_kernel(const float* __restrict__ scores, int32_t* __restrict__ selected, 
   }
 }
 
-
-// max / sum over the 64 lanes of a wave on DPP and row swaps (no LDS crossbar); every lane gets it
 template <int EPT, bool LOGITS>
 __global__ void __launch_bounds__(1024)
 select_radix_kernel(const float* __restrict__ scores, float* __restrict__ probs, int32_t* __restrict__ selected,

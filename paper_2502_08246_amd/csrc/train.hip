@@ -22,10 +22,10 @@
 // (gemm_split_kernel).
 // Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
 // column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
-// 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 59 now (870 TFLOP/s of
-// bfloat16 products; a loop of nothing but these instructions on such data runs at 1.8 GHz: 27 us); all five and the two sums
-// 281 us before, 227 now.  What is left is the start and the stores of a product, 12 us that nothing covers (all tiles of a
-// product run at once), and the slices' barriers.
+// 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 60 to 63 now, the scaling
+// included (825 TFLOP/s of bfloat16 products; a loop of nothing but these instructions on such data runs at 1.8 GHz: 27 us); all
+// five and the two sums 281 us before, 221 now.  What is left is the start and the stores of a product, 12 us that nothing covers
+// (all tiles of a product run at once), and the slices' barriers.
 #include <algorithm>
 
 #include "common.h"
@@ -54,7 +54,8 @@ struct GemmArgs {
 // nearest to what is left then.  This takes the values' next plane, as pairs, and leaves the rest.
 // An fp32 value is a multiple of 2^-149, the smallest normal bfloat16 is 2^-126: scaled by 2^24 (exact) a value of any size keeps
 // its 24 bits.  (Unscaled, the third plane of values below 2^-110 and then the second fall below the smallest bfloat16: 9e-6 of
-// products of operands near 2^-118, which fp32 instructions have to 5e-7.  The multiplication takes 2 to 4 % of a product's time.)
+// products of operands near 2^-118, which fp32 instructions have to 5e-7.  The multiplication takes 4 to 6 % of a product's time:
+// 57 to 59 us without it, 60 to 63 with.)
 constexpr float kUp = 16777216.f, kDown = 1.f / (kUp * kUp);
 template <int E>
 __device__ __forceinline__ void take_plane(float* rest, uint32_t* u) {
