@@ -22,10 +22,10 @@
 // (gemm_split_kernel).
 // Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
 // column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
-// 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 60 to 63 now, the scaling
-// included (825 TFLOP/s of bfloat16 products; a loop of nothing but these instructions on such data runs at 1.8 GHz: 27 us); all
-// five and the two sums 281 us before, 221 now.  What is left is the start and the stores of a product, 12 us that nothing covers
-// (all tiles of a product run at once), and the slices' barriers.
+// 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 49 to 53 now, the scaling
+// included (1.0 PFLOP/s of bfloat16 products; a loop of nothing but these instructions on such data runs at 1.8 GHz: 27 us).  What is
+// left is the start and the stores of a product, 12 us that nothing covers (all tiles of a product run at once), and the slices'
+// barriers.
 #include <algorithm>
 
 #include "common.h"
@@ -79,13 +79,15 @@ constexpr int kSlice = 16;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_buffer(const float* p, int rows, int K) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, rows * K * 4, 0x00027000);
 }
-template <bool KC, bool VEC, int R>
+template <bool KC, bool VEC, int R, int THREADS>
 struct PlaneLoader {
-  static constexpr int E = R * kSlice / kGemmThreads;     // consecutive values of k of one row: 8 or 4
+  static constexpr int E = R * kSlice / THREADS;          // consecutive values of k of one row: 8 or 4
   static constexpr int kPitch = R + (KC ? 4 : 0), kPlane = kSlice / 8 * kPitch, kUnits = 3 * kPlane;   // units of 16 bytes
+  static_assert(E == 8 || E == 4, "whole pieces of a row's values");
   float r[E];
-  static __device__ __forceinline__ int row() { return KC ? threadIdx.x / (kSlice / E) : threadIdx.x % R; }
-  static __device__ __forceinline__ int first_k() { return E * (KC ? threadIdx.x % (kSlice / E) : threadIdx.x / R); }
+  static __device__ __forceinline__ int tid() { return threadIdx.x % THREADS; }          // THREADS threads share an operand's slice
+  static __device__ __forceinline__ int row() { return KC ? tid() / (kSlice / E) : tid() % R; }
+  static __device__ __forceinline__ int first_k() { return E * (KC ? tid() % (kSlice / E) : tid() / R); }
   // Byte offset of the thread's values from the slice's first: all that a lane adds to an address that the whole workgroup
   // shares.  Rows past the end repeat the last one and are not stored.
   static __device__ __forceinline__ int offset(int t0, int n_t, int K) {
@@ -113,10 +115,11 @@ struct PlaneLoader {
 #pragma unroll
     for (int e = 0; e < E; ++e) r[e] = first_k() + e < k ? r[e] : 0.f;
   }
-  __device__ __forceinline__ void stash(uint4* s) const {
+  // up: kUp, or 0 for a slice that does not count
+  __device__ __forceinline__ void stash(uint4* s, float up) const {
     float rest[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) rest[e] = r[e] * kUp;
+    for (int e = 0; e < E; ++e) rest[e] = r[e] * up;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       uint32_t u[E / 2];
@@ -348,26 +351,31 @@ gemm_f32_kernel(GemmArgs g) {
   for (int t = 0; t < TM; ++t) store_tile<EPI, 16>(g, w, m0 + wm + 32 * t, n0 + wn + col, half, acc[t]);
 }
 
-// C = A' B'; A' is M x K, B' is K x N.  Two by two waves own a tile of 64 TM x 64, a wave TM matrix tiles of 32.
-template <bool TA, bool TB, int EPI, bool VEC, int TM>
-__global__ void __launch_bounds__(kGemmThreads, 2)
+// C = A' B'; A' is M x K, B' is K x N.  Two by WN waves own a tile of 64 TM x 32 WN TN, a wave TM x TN matrix tiles of 32.  KS: the
+// workgroup has as many such groups of waves, which share out k and add up at the end.
+template <bool TA, bool TB, int EPI, bool VEC, int TM, int TN, int WN, int KS>
+__global__ void __launch_bounds__(128 * WN * KS, KS > 2 ? 1 : 2)
 gemm_kernel(GemmArgs g) {
-  constexpr int BM = 64 * TM, BN = 64;
-  typedef PlaneLoader<!TA, VEC, BM> LoadA;
-  typedef PlaneLoader<TB, VEC, BN> LoadB;
+  constexpr int kThreads = 128 * WN, BM = 64 * TM, BN = 32 * WN * TN;
+  typedef PlaneLoader<!TA, VEC, BM, kThreads> LoadA;
+  typedef PlaneLoader<TB, VEC, BN, kThreads> LoadB;
   constexpr int kUnits = LoadA::kUnits + LoadB::kUnits;
-  __shared__ uint4 s_ab[2 * kUnits];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ uint4 s_all[KS * 2 * kUnits];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x % kThreads >> 6;
+  const int part = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;       // of k
   const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
   const float* A = g.A + (size_t)w * g.sA;
   const float* B = g.B + (size_t)w * g.sB;
-  const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32;
+  const int wm = wave / WN * 32 * TM, wn = wave % WN * 32 * TN;
   const int col = lane & 31, half = lane >> 5;
+  uint4* const s_ab = s_all + part * 2 * kUnits;
   const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
   float csum = 0.f;                                             // of the thread's row of A' (TA: it is always the same)
-  f32x16_t acc[TM], low[TM];                                    // the sums of the products of planes 0, and of the others
+  f32x16_t acc[TM][TN], low[TM][TN];                            // the sums of the products of planes 0, and of the others
 #pragma unroll
-  for (int t = 0; t < TM; ++t) acc[t] = low[t] = (f32x16_t){0};
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int u = 0; u < TN; ++u) acc[t][u] = low[t][u] = (f32x16_t){0};
 
   const int oa = LoadA::offset(m0, g.M, g.K), ob = LoadB::offset(n0, g.N, g.K);
   const __amdgpu_buffer_rsrc_t ra = operand_buffer(A, g.M, g.K), rb = operand_buffer(B, g.N, g.K);
@@ -378,71 +386,120 @@ gemm_kernel(GemmArgs g) {
     st.b.fetch(rb, ob, k0, g.N, g.K);
   };
   auto stash = [&](const Staged& st, int buf, bool live) {
-    st.a.stash(s_ab + buf * kUnits);
-    st.b.stash(s_ab + buf * kUnits + LoadA::kUnits);
+    st.a.stash(s_ab + buf * kUnits, KS > 1 && !live ? 0.f : kUp);
+    st.b.stash(s_ab + buf * kUnits + LoadA::kUnits, kUp);
     if (TA) csum += __int_as_float(__float_as_int(st.a.sum()) & -(int)live);    // (a select would become a branch)
   };
   // the slice in buffer `buf`; the split of the next one runs under its products
-  auto step = [&](Staged& st, int buf, int k0_next) {
+  auto step = [&](Staged& st, int buf, int k0_next, int end) {
     const uint4* sa = s_ab + buf * kUnits;
     const uint4* sb = sa + LoadA::kUnits;
-    bf16x8_t a[TM][3], b[3];
+    bf16x8_t a[TM][3], b[TN][3];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-      b[p] = LoadB::read(sb, p, wn + col, half);
+#pragma unroll
+      for (int u = 0; u < TN; ++u) b[u][p] = LoadB::read(sb, p, wn + 32 * u + col, half);
 #pragma unroll
       for (int t = 0; t < TM; ++t) a[t][p] = LoadA::read(sa, p, wm + 32 * t + col, half);
     }
-    stash(st, buf ^ 1, k0_next < g.K);
+    stash(st, buf ^ 1, k0_next < end);
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
-      for (int t = 0; t < TM; ++t) {
-        f32x16_t& sum = i < 5 ? low[t] : acc[t];
-        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kPlaneA[i]], b[kPlaneB[i]], sum, 0, 0, 0);
-      }
+      for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int u = 0; u < TN; ++u) {
+          f32x16_t& sum = i < 5 ? low[t][u] : acc[t][u];
+          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kPlaneA[i]], b[u][kPlaneB[i]], sum, 0, 0, 0);
+        }
     // moved up, the loads would get other registers than the values that they replace, and be waited for when copied over
     __builtin_amdgcn_sched_barrier(0);
     fetch(st, k0_next + 2 * kSlice);
     __syncthreads();
   };
-  // the first slice is the one that may be short: the values of one operand past its end are taken out (an infinity or NaN of
-  // the other there spoils the tile, which is then done again)
-  const int n_slices = (g.K + kSlice - 1) / kSlice, first = g.K - (n_slices - 1) * kSlice;
-  fetch(even, 0);
-  fetch(odd, first);
-  even.a.clear_from(first);
-  stash(even, 0, true);
-  fetch(even, first + kSlice);
+  // The first slice of all is the one that may be short: the values of one operand past its end are taken out (an infinity or NaN
+  // of the other there spoils the tile, which is then done again, and so does one of a slice that counts for another part only).
+  const int n_slices = (g.K + kSlice - 1) / kSlice, short_by = n_slices * kSlice - g.K;
+  const int per = (n_slices + KS - 1) / KS;                     // slices of a part; one that has fewer goes through the motions
+  const int i0 = part * per, end = KS > 1 ? min(g.K, (i0 + per) * kSlice - short_by) : g.K;
+  auto start = [&](int i) { return i * kSlice - short_by; };    // of slice i >= 1, and where the values after slice 0 start
+  fetch(even, max(start(i0), 0));
+  fetch(odd, start(i0 + 1));
+  if (i0 == 0) even.a.clear_from(kSlice - short_by);
+  stash(even, 0, max(start(i0), 0) < end);
+  fetch(even, start(i0 + 2));
   __syncthreads();
-  int k0 = first;
-  int pairs = n_slices / 2;                                     // at least one: k is 32 at least
+  int k0 = start(i0 + 1);
+  int pairs = per / 2;
   do {
-    step(odd, 0, k0);
-    step(even, 1, k0 + kSlice);
+    step(odd, 0, k0, end);
+    step(even, 1, k0 + kSlice, end);
     k0 += 2 * kSlice;
   } while (--pairs > 0);
-  if (n_slices & 1) step(odd, 0, k0);
+  if (per & 1) step(odd, 0, k0, end);
   if (TA && sums) {
     // the threads that loaded the same row add up in a fixed order
-    constexpr int kGroups = kGemmThreads / BM;
-    float* s = reinterpret_cast<float*>(s_ab);                  // [kGroups][BM]
-    s[tid] = csum;
+    constexpr int kGroups = KS * kThreads / BM;
+    float* s = reinterpret_cast<float*>(s_all);                 // [kGroups][BM]
+    s[threadIdx.x] = csum;
     __syncthreads();
-    if (tid < BM && m0 + tid < g.M) {
+    if (threadIdx.x < BM && m0 + (int)threadIdx.x < g.M) {
       float t = 0.f;
 #pragma unroll
-      for (int i = 0; i < kGroups; ++i) t += s[i * BM + tid];
-      g.colsum[(size_t)w * g.sColsum + m0 + tid] = t;
+      for (int i = 0; i < kGroups; ++i) t += s[i * BM + threadIdx.x];
+      g.colsum[(size_t)w * g.sColsum + m0 + threadIdx.x] = t;
     }
+    if (KS > 1) __syncthreads();
   }
+  // not a number, infinite, or too large for a scaled bfloat16: as fp32 products have it
+  if constexpr (KS == 1) {
 #pragma unroll
-  for (int t = 0; t < TM; ++t) {
-    const int tm = m0 + wm + 32 * t, tn = n0 + wn;
-    acc[t] = (acc[t] + low[t]) * kDown;
-    // not a number, infinite, or too large for a scaled bfloat16: as fp32 products have it
-    if (!all_finite(acc[t])) acc[t] = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
-    store_tile<EPI, 16>(g, w, tm, tn + col, half, acc[t]);
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int u = 0; u < TN; ++u) {
+        const int tm = m0 + wm + 32 * t, tn = n0 + wn + 32 * u;
+        acc[t][u] = (acc[t][u] + low[t][u]) * kDown;
+        if (!all_finite(acc[t][u])) acc[t][u] = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
+        store_tile<EPI, 16>(g, w, tm, tn + col, half, acc[t][u]);
+      }
+  } else {
+    // part i adds up registers 16 / KS * i and on of all parts, in order
+    static_assert(TM == 1 && TN == 1 && (KS == 2 || KS == 4), "a matrix tile per wave");
+    constexpr int kWaves = kThreads / 64, kQuads = 4 / KS;
+    static_assert(KS * kWaves * 4 * 64 <= KS * 2 * kUnits, "the parts' sums take the operands' place");
+    float4* s = reinterpret_cast<float4*>(s_all);               // [part][wave][four registers][lane]
+    const f32x16_t mine = acc[0][0] + low[0][0];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      s[((part * kWaves + wave) * 4 + q) * 64 + lane] = make_float4(mine[4 * q], mine[4 * q + 1], mine[4 * q + 2], mine[4 * q + 3]);
+    __syncthreads();
+    const int tm = m0 + wm, tn = n0 + wn;
+    f32x4_t sum[kQuads];
+    float d = 0.f;
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q) {
+      sum[q] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        const float4 v = s[((i * kWaves + wave) * 4 + part * kQuads + q) * 64 + lane];
+        sum[q] += (f32x4_t){v.x, v.y, v.z, v.w};
+      }
+      sum[q] *= kDown;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d += sum[q][r] - sum[q][r];
+    }
+    if (__ballot(d != 0.f) != 0) {
+      const f32x16_t all = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
+#pragma unroll
+      for (int i = 0; i < KS; ++i)
+        if (i == part)
+#pragma unroll
+          for (int q = 0; q < kQuads; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[q][r] = all[4 * (i * kQuads + q) + r];
+    }
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q) store_tile<EPI, 4>(g, w, tm + 8 * (part * kQuads + q), tn + col, half, sum[q]);
   }
 }
 
@@ -507,10 +564,16 @@ gemm_split_kernel(GemmArgs g) {
     g.colsum[(size_t)w * g.sColsum + m0 + col] = (s_sum[col] + s_sum[32 + col]) + (s_sum[64 + col] + s_sum[96 + col]);
 }
 
-// 128 x 64 tiles where they give every compute unit two workgroups, or else 64 x 64 (8 sets, 500 rows, 288 x 512: 10 us less in all
-// than with the larger ones).  Below a workgroup per compute unit a tile's k is shared out over four waves (1 set, 1000 rows,
-// 512 x 1024: 82 us in all, 120 with 64 x 64 tiles), and so it is where k is shorter than two slices or an operand too large for
-// offsets of 32 bits; that one takes several launches where a grid dimension has no room for its smaller tiles.
+// Products of planes: 128 x 128 tiles of eight waves where every compute unit has one (8 sets, 1000 rows, 512 x 1024: 49 to 53 us a
+// product; 62 to 68 with 128 x 64 and four waves, which split twice as many values for a matrix instruction and read their operands
+// from LDS no slower than that takes), unless half of the last column stays empty and there are few of them (8192 rows, 64 columns:
+// 64 us with 128 x 64, 87; 192: 45 and 49; 576: 40 either way).  64 x 64 with more than two workgroups per compute unit.  Below that a
+// slice's chain (operands from LDS, split, products, barrier: 0.7 us) is what takes the time, so that more waves share out k: two
+// groups (4 sets, 1000 rows, 512 x 1024: 42 -> 37 us; 8 sets, 96 x 1024: 32 -> 24), four where every compute unit has one workgroup
+// at most (20 of those 24; 1 set, 512 x 1024: 20 -> 16).
+// With fewer than 512 matrix tiles a tile's k is shared out over four waves in fp32 (8 sets, 1024 rows, 192 x 128: 9 us, 17), and so it
+// is where k is too short to be shared out or an operand too large for offsets of 32 bits; that one takes several launches where a
+// grid dimension has no room for its smaller tiles.
 constexpr long long kMostTiles = 65535;
 template <bool TA, bool TB, int EPI, bool VEC, bool F32>
 void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
@@ -530,13 +593,16 @@ void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
       return;
     }
   } else {
-    if (tiled && count(128, 64) >= 2LL * device_cus()) {
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 2>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
-      return;
-    }
-    if (tiled && count(64, 64) >= device_cus()) {
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, VEC, 1>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
-      return;
+    auto launch = [&](auto kernel, int bm, int bn, int threads) { hipLaunchKernelGGL(kernel, grid(bm, bn), dim3(threads), 0, hs, g); };
+    const int columns = (g.N + 63) / 64;
+    const bool half_empty = columns < 7 && columns % 2 == 1;      // the last tile of 128 columns, and it counts
+    if (tiled && half_empty && count(128, 64) >= 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 2, 1, 2, 1>, 128, 64, 256);
+    if (tiled && !half_empty && count(128, 128) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 2, 1, 4, 1>, 128, 128, 512);
+    if (tiled && count(64, 64) > 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 1>, 64, 64, 256);
+    if (tiled && count(32, 32) >= 2LL * device_cus()) {
+      if (count(64, 64) <= device_cus() && g.K >= 128) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 4>, 64, 64, 1024);
+      if (g.K >= 64) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 2>, 64, 64, 512);
+      if (count(64, 64) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 1>, 64, 64, 256);
     }
   }
   for (long long m = 0; m < g.M; m += kMostTiles * 32)
