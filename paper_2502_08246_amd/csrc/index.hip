@@ -407,7 +407,6 @@ template <> __device__ __forceinline__ double to_f64<bf16_t>(bf16_t v) {
   return (double)__uint_as_float((uint32_t)v << 16);
 }
 
-constexpr int kPushSlab = 64;         // centroids per workgroup (one wave) of window_push_kernel
 
 // Eight bf16 elements (one 16-byte piece of a row) -> double.
 __device__ __forceinline__ void widen8(const uint4& u, double* o) {
@@ -499,15 +498,17 @@ __device__ __forceinline__ void wave_best(double& best, int& best_id) {
   }
 }
 
-// Best candidate of one slab of centroids, as exchanged between the workgroups of a unit.
+// A slab's centroids that may be the key's, as exchanged between the workgroups of a unit: the largest lower bound of an exact
+// score, the centroids whose upper bound reaches it (two of n; hi[0] is the largest where there are more).
 struct PushPartial {
-  double score;
-  int id;
-  int pad;
+  float lo, hi[2];
+  int id[2], n;
 };
 
-// window_push: P = ceil(B / 64) one-wave workgroups per (sequence, KV head), each scoring a slab of
-// 64 centroids (one per lane); the last to arrive picks the bucket and does the bookkeeping.
+// window_push: P workgroups per (sequence, KV head), each with a slab of the centroids; the last to arrive picks the bucket and does
+// the bookkeeping.  Scores are fp32 first, whole rows of 16 lanes each, with bounds on how far the exact one can be: as a rule
+// one centroid's upper bound reaches the largest lower bound of all, and that is the bucket, as double-precision scores define
+// it.  Otherwise those that do are scored exactly (all of them, if a slab has more than two).
 // Which key is displaced and where it goes does not depend on the new key's bucket: every
 // workgroup reads that state up front (the loads overlap the scoring), slab 0 copies the displaced
 // row to its bucket, and the last workgroup, which runs after all of these reads, writes the new
@@ -524,8 +525,10 @@ __device__ __forceinline__ C to_cache(T v, float inv_scale) {
   }
 }
 
+constexpr int kPushThreads = 256, kPushRows = 8 /* of a 16-lane group in flight */, kPushSlab = kPushRows * kPushThreads / 16;
+
 template <typename T, typename C = T>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(kPushThreads)
 window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, const T* __restrict__ v_new,
                    const int32_t* __restrict__ pos_new, const T* __restrict__ cent, const float* __restrict__ bias,
                    const int32_t* __restrict__ off, int32_t* __restrict__ len, int32_t* __restrict__ idx,
@@ -533,11 +536,15 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
                    const float* __restrict__ vscale, int32_t* __restrict__ res_ids,
                    int32_t* __restrict__ new_ids, int32_t* __restrict__ overflow, PushPartial* __restrict__ part,
                    unsigned* __restrict__ counters, int Hkv, int Ncap, int B, int runs, int n_sink, int n_recent,
-                   int P, int cpl /* centroids per lane: a workgroup scores 64 * cpl */) {
+                   int P, int cpl /* kPushSlab * cpl centroids to a workgroup */) {
   // runs = B + 1: index with a resident run.  runs = B: plain index (append_keys): W = 0, every key
   // goes straight into its bucket, res_ids is not touched and pos_new may be null (idx gets -2).
   __shared__ double s_x[kD];
-  const int slab = blockIdx.x, unit = blockIdx.y, h = unit % Hkv, lane = threadIdx.x;
+  __shared__ __align__(16) T s_xt[kD];
+  __shared__ float s_lo[kPushThreads / 64], s_top[kPushThreads / 64], s_hi[2];
+  __shared__ int s_n, s_id[2], s_state[6], s_list[2 * 64];
+  const int slab = blockIdx.x, unit = blockIdx.y, h = unit % Hkv, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int sub = tid & 15, grp = tid >> 4;
   SAAP_TRACE(0);
   const int W = n_sink + n_recent;
   const int32_t* o = off + (size_t)unit * (runs + 1);
@@ -546,87 +553,213 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
   int32_t* rid = res_ids + (size_t)unit * W;
   C* Ku = Ks + (size_t)unit * Ncap * kD;
   C* Vu = Vs + (size_t)unit * Ncap * kD;
-  const float k_inv = kscale ? 1.0f / kscale[unit] : 1.f, v_inv = vscale ? 1.0f / vscale[unit] : 1.f;   // powers of two
+  const T* cu = cent + (size_t)h * B * kD;
+  const float* bu = bias ? bias + (size_t)h * B : nullptr;
 
-  // ---- the new key, and what can be decided without its bucket (same values in every lane) ----
-  const T x0 = x_new[(size_t)unit * kD + lane], x1 = x_new[(size_t)unit * kD + 64 + lane];
-  const T k0 = k_new[(size_t)unit * kD + lane], k1 = k_new[(size_t)unit * kD + 64 + lane];
-  const T v0 = v_new[(size_t)unit * kD + lane], v1 = v_new[(size_t)unit * kD + 64 + lane];
+  // ---- the loads that wait for nothing: the new key, its position, the first centroids ----
+  const T xe = x_new[(size_t)unit * kD + (tid & (kD - 1))];
   const int pos = pos_new ? pos_new[unit / Hkv] : 0x7fffffff;
   const int res_base = o[B];
+  const int row0 = slab * kPushSlab * cpl;
+  Vec8<T> c[kPushRows];
+  auto load_rows = [&](int it) {
+#pragma unroll
+    for (int i = 0; i < kPushRows; ++i) c[i].load(cu + (size_t)min(row0 + it * kPushSlab + grp + 16 * i, B - 1) * kD + sub * 8);
+  };
+  load_rows(0);
+  T k0 = T(0), k1 = T(0), v0 = T(0), v1 = T(0);
+  float k_inv = 1.f, v_inv = 1.f;                // powers of two
+  if (wave == 0) {
+    k0 = k_new[(size_t)unit * kD + lane], k1 = k_new[(size_t)unit * kD + 64 + lane];
+    v0 = v_new[(size_t)unit * kD + lane], v1 = v_new[(size_t)unit * kD + 64 + lane];
+    if (kscale) k_inv = 1.0f / kscale[unit];
+    if (vscale) v_inv = 1.0f / vscale[unit];
+  }
+  // ---- what can be decided without the bucket, by the last wave (same values in every lane) ----
   // -1: refused   0: slot of a run that is still filling   1: ring slot, a key is displaced   2: no ring
   const int kind = pos < 0 ? -1 : pos < W ? 0 : n_recent > 0 ? 1 : 2;
-  int slot = -1, dst = -1, e = -1, cur = 0, moved_pos = -1;
-  bool refused = kind < 0;
-  if (kind == 0) {
-    slot = res_base + pos;                     // r(pos) = pos while the run is not full
-  } else if (kind == 1) {
-    const int r = n_sink + (pos - n_sink) % n_recent;
-    e = rid[r];
-    // e outside [0,B) means the caller broke the protocol (pushes out of order, foreign state):
-    // refuse like a full bucket instead of indexing with it
-    const bool ok = e >= 0 && e < B;
-    cur = ok ? l[e] : 0;
-    if (ok && o[e] + cur < o[e + 1]) {
-      slot = res_base + r;
-      dst = o[e] + cur;
-      moved_pos = ix[slot];
-    } else {
-      refused = true;
+  if (wave == kPushThreads / 64 - 1) {
+    int slot = -1, dst = -1, e = -1, cur = 0, moved_pos = -1;
+    bool refused = kind < 0;
+    if (kind == 0) {
+      slot = res_base + pos;                     // r(pos) = pos while the run is not full
+    } else if (kind == 1) {
+      const int r = n_sink + (pos - n_sink) % n_recent;
+      const int from = res_base + r;
+      e = rid[r];
+      moved_pos = ix[from];
+      const C a0 = Ku[(size_t)from * kD + lane], a1 = Ku[(size_t)from * kD + 64 + lane];
+      const C b0 = Vu[(size_t)from * kD + lane], b1 = Vu[(size_t)from * kD + 64 + lane];
+      // e outside [0,B) means the caller broke the protocol (pushes out of order, foreign state):
+      // refuse like a full bucket instead of indexing with it
+      const bool ok = e >= 0 && e < B;
+      cur = ok ? l[e] : 0;
+      if (ok && o[e] + cur < o[e + 1]) {
+        slot = from;
+        dst = o[e] + cur;
+        if (slab == 0) {                         // the displaced row: ring slot -> its bucket
+          Ku[(size_t)dst * kD + lane] = a0;
+          Ku[(size_t)dst * kD + 64 + lane] = a1;
+          Vu[(size_t)dst * kD + lane] = b0;
+          Vu[(size_t)dst * kD + 64 + lane] = b1;
+        }
+      } else {
+        refused = true;
+      }
+    }
+    if (lane == 0) {
+      s_state[0] = slot; s_state[1] = dst; s_state[2] = e; s_state[3] = cur; s_state[4] = moved_pos; s_state[5] = refused;
     }
   }
-  if (slab == 0 && dst >= 0) {                 // the displaced row: ring slot -> its bucket
-    Ku[(size_t)dst * kD + lane] = Ku[(size_t)slot * kD + lane];
-    Ku[(size_t)dst * kD + 64 + lane] = Ku[(size_t)slot * kD + 64 + lane];
-    Vu[(size_t)dst * kD + lane] = Vu[(size_t)slot * kD + lane];
-    Vu[(size_t)dst * kD + 64 + lane] = Vu[(size_t)slot * kD + 64 + lane];
+  if (tid < kD) {
+    s_x[tid] = to_f64<T>(xe);
+    s_xt[tid] = xe;
   }
-
-  // ---- this slab's best centroid ----
-  s_x[lane] = to_f64<T>(x0);
-  s_x[64 + lane] = to_f64<T>(x1);
+  if (tid == 0) s_n = 0;
   __syncthreads();
   SAAP_TRACE(1);
-  double best = 0.0;
-  int best_id = -1;
-  for (int c = 0; c < cpl; ++c) {                // ascending ids per lane: ties keep the lowest
-    const int bc = (slab * cpl + c) * kPushSlab + lane;
-    if (bc < B) {
-      double t = score_row<T>(cent + ((size_t)h * B + bc) * kD, s_x);
-      if (bias) t += (double)bias[(size_t)h * B + bc];
-      take_better(best, best_id, t, bc);
+
+  // ---- this slab's centroids: lane `sub` < 8 of a group keeps row grp + 16 sub of every round ----
+  Vec8<T> xv;
+  xv.load(s_xt + sub * 8);
+  const float xn2 = sum16(xv.dot(xv));
+  // |fp32 score - exact score| <= 128 2^-24 |x| |c|, with head-room of four for the order of the sum, and the addition of the bias;
+  // products below the smallest fp32 number may be lost.  Norms that are themselves next to nothing bound nothing.
+  constexpr float kTol = 4.0f * 128.0f * 5.9604645e-8f, kTiny = 1e-30f;
+  float lo = -INFINITY, top[3] = {-INFINITY, -INFINITY, -INFINITY};
+  int top_id[2] = {-1, -1};
+  for (int it = 0; it < cpl; ++it) {
+    float score = 0.f, n2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < kPushRows; ++i) {
+      const float d = sum16(c[i].dot(xv)), q = sum16(c[i].dot(c[i]));
+      score = sub == i ? d : score;
+      n2 = sub == i ? q : n2;
+    }
+    if (it + 1 < cpl) load_rows(it + 1);
+    const int b = row0 + it * kPushSlab + grp + 16 * sub;
+    if (sub < kPushRows && b < B) {
+      if (bu) score += bu[b];
+      const float err = n2 > kTiny && xn2 > kTiny ? kTol * sqrtf(xn2) * sqrtf(n2) + 2.5e-7f * fabsf(score) + 2e-36f : INFINITY;
+      const bool known = fabsf(score) < INFINITY && err < INFINITY;        // infinities and NaN: nothing is known
+      const float up = known ? score + err : INFINITY, down = known ? score - err : -INFINITY;
+      lo = fmaxf(lo, down);
+      if (up > top[0]) {
+        top[2] = top[1];
+        top[1] = top[0];
+        top_id[1] = top_id[0];
+        top[0] = up;
+        top_id[0] = b;
+      } else if (up > top[1]) {
+        top[2] = top[1];
+        top[1] = up;
+        top_id[1] = b;
+      } else {
+        top[2] = fmaxf(top[2], up);
+      }
     }
   }
   SAAP_TRACE(2);
-  wave_best(best, best_id);
+  {
+    const float wave_lo = wave_max(lo), wave_top = wave_max(top[0]);
+    if (lane == 0) {
+      s_lo[wave] = wave_lo;
+      s_top[wave] = wave_top;
+    }
+  }
+  __syncthreads();
+  lo = fmaxf(fmaxf(s_lo[0], s_lo[1]), fmaxf(s_lo[2], s_lo[3]));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (top_id[i] >= 0 && top[i] >= lo) {
+      const int at = atomicAdd(&s_n, 1);
+      if (at < 2) {
+        s_id[at] = top_id[i];
+        s_hi[at] = top[i];
+      }
+    }
+  if (top_id[1] >= 0 && top[2] >= lo && top[2] > -INFINITY) atomicAdd(&s_n, 1);
+  __syncthreads();
+  if (wave != 0) return;
   SAAP_TRACE(3);
+  int n_cand = s_n, id0 = s_id[0];
+  const int id1 = n_cand > 1 ? s_id[1] : -1;
+  unsigned long long whole = n_cand > 2;         // slabs of which every centroid is scored exactly
   if (P > 1) {
     if (lane == 0) {
-      PushPartial* mine = part + (size_t)unit * P + slab;
-      __hip_atomic_store(&mine->score, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&mine->id, best_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const float hi0 = n_cand > 2 ? fmaxf(fmaxf(s_top[0], s_top[1]), fmaxf(s_top[2], s_top[3])) : s_hi[0], hi1 = n_cand > 1 ? s_hi[1] : -INFINITY;
+      auto pair = [](unsigned a, unsigned b) { return (unsigned long long)b << 32 | a; };
+      unsigned long long* mine = reinterpret_cast<unsigned long long*>(part + (size_t)unit * P + slab);
+      __hip_atomic_store(mine, pair(__float_as_uint(lo), __float_as_uint(hi0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(mine + 1, pair(__float_as_uint(hi1), (unsigned)id0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(mine + 2, pair((unsigned)id1, (unsigned)n_cand), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // every load above has returned and every store has been acknowledged before the arrival counts
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     unsigned old = 0;
     if (lane == 0) old = __hip_atomic_fetch_add(&counters[unit], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = (unsigned)__shfl((int)old, 0);
+    old = (unsigned)__builtin_amdgcn_readfirstlane((int)old);
     SAAP_TRACE(4);
     if (old != (unsigned)(P - 1)) return;
     // every partial was stored through to the device's coherent level and acknowledged before its arrival was
     // counted: loads of the same scope see it, and no cache has to be invalidated for them
-    best = 0.0;
-    best_id = -1;
-    for (int i = lane; i < P; i += 64) {       // ascending slabs per lane
-      PushPartial* q = part + (size_t)unit * P + i;
-      const double qs = __hip_atomic_load(&q->score, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int qi = __hip_atomic_load(&q->id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      take_better(best, best_id, qs, qi);
-    }
-    wave_best(best, best_id);
+    unsigned long long* q = reinterpret_cast<unsigned long long*>(part + (size_t)unit * P + min(lane, P - 1));      // P <= 64
+    const unsigned long long q0 = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long q1 = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long q2 = __hip_atomic_load(q + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool mine = lane < P;
+    const float hi0 = __uint_as_float((unsigned)(q0 >> 32)), hi1 = __uint_as_float((unsigned)q1);
+    const int n = (int)(q2 >> 32);
+    lo = wave_max(mine ? __uint_as_float((unsigned)q0) : -INFINITY);
+    const bool one = mine && n <= 2 && hi0 >= lo, two = mine && n == 2 && hi1 >= lo;
+    whole = __ballot(mine && n > 2 && hi0 >= lo);
+    const unsigned long long first = __ballot(one), second = __ballot(two), below = (1ull << lane) - 1ull;
+    n_cand = __popcll(first) + __popcll(second);
+    if (one) s_list[__popcll(first & below)] = (int)(q1 >> 32);
+    if (two) s_list[__popcll(first) + __popcll(second & below)] = (int)(unsigned)q2;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    id0 = s_list[0];
     SAAP_TRACE(5);
     if (lane == 0) __hip_atomic_store(&counters[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    if (lane == 0) {
+      s_list[0] = id0;
+      s_list[1] = id1;
+    }
+    n_cand = whole ? 0 : n_cand;
   }
+  int best_id = id0;
+  if (whole || n_cand != 1) {                    // more than one may be the largest
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    double best = 0.0;
+    best_id = -1;
+    const int lists = (n_cand + 63) / 64, per_slab = kPushSlab / 64 * cpl, rounds = lists + __popcll(whole) * per_slab;
+    int from = -1;
+    for (int r = 0; r < rounds; ++r) {
+      asm volatile("" ::: "memory");             // hoisted out of the loop, the key's doubles would hold 256 registers
+      int bc = -1;
+      if (r < lists) {
+        if (64 * r + lane < n_cand) bc = s_list[64 * r + lane];
+      } else {
+        const int q = (r - lists) % per_slab;
+        if (q == 0) {                            // the next slab
+          from = (__ffsll(whole) - 1) * 64 * per_slab;
+          whole &= whole - 1ull;
+        }
+        bc = from + 64 * q + lane;
+      }
+      if (bc < 0 || bc >= B) continue;
+      double t = score_row<T>(cu + (size_t)bc * kD, s_x);
+      if (bu) t += (double)bu[bc];
+      take_better(best, best_id, t, bc);
+    }
+    wave_best(best, best_id);
+  }
+  best_id = __builtin_amdgcn_readfirstlane(best_id);
+  int slot = s_state[0];
+  const int dst = s_state[1], e = s_state[2], moved_pos = s_state[4];
+  int cur = s_state[3];
+  bool refused = s_state[5] != 0;
 
   // ---- bookkeeping, by the one workgroup that knows the bucket ----
   const int b = best_id;
@@ -723,13 +856,15 @@ recopy_kernel(const int32_t* __restrict__ off, const int32_t* __restrict__ len, 
 }  // namespace
 
 size_t push_workspace_bytes(long long units, int B) {
-  const long long P = (B + kPushSlab - 1) / kPushSlab;       // the most workgroups per unit any plan uses
-  return (size_t)SAAP_WS_HEADER_BYTES + (size_t)units * P * sizeof(PushPartial);
+  static_assert(SAAP_MAX_BUCKETS <= 64 * kPushSlab, "a lane per workgroup of a unit");
+  // 24 bytes for every 128 centroids, of units with more than one workgroup, are never more than this
+  static_assert(sizeof(PushPartial) == 24 && kPushSlab == 128, "as stated");
+  return (size_t)SAAP_WS_HEADER_BYTES + (size_t)units * ((B + 63) / 64) * 16;
 }
 
-// Centroids per lane of the scoring workgroups: one when few units leave the device empty, more
+// Rounds of the scoring workgroups: one when few units leave the device empty, more
 // when there are enough units to fill it anyway (about two workgroups per compute unit in all).
-static int push_centroids_per_lane(long long units, int B) {
+static int push_rounds(long long units, int B) {
   const long long slabs = (B + kPushSlab - 1) / kPushSlab;
   long long want = 2LL * device_cus() / units;                // workgroups per unit
   if (want < 1) want = 1;
@@ -889,19 +1024,19 @@ extern "C" int32_t saap_window_push(const void* x_new, const void* k_new, const 
   if (units > 65535 || units * sizeof(unsigned) > SAAP_WS_HEADER_BYTES) return SAAP_UNSUPPORTED;
   if (ws_bytes < push_workspace_bytes(units, B)) return SAAP_WORKSPACE_TOO_SMALL;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const int cpl = push_centroids_per_lane(units, B);
+  const int cpl = push_rounds(units, B);
   const int P = (B + kPushSlab * cpl - 1) / (kPushSlab * cpl);
   unsigned* counters = static_cast<unsigned*>(ws);
   PushPartial* part = reinterpret_cast<PushPartial*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
   const dim3 grid((unsigned)P, (unsigned)units);
   if (dtype == SAAP_BF16)
-    hipLaunchKernelGGL(window_push_kernel<bf16_t>, grid, dim3(64), 0, hs, static_cast<const bf16_t*>(x_new),
+    hipLaunchKernelGGL(window_push_kernel<bf16_t>, grid, dim3(kPushThreads), 0, hs, static_cast<const bf16_t*>(x_new),
                        static_cast<const bf16_t*>(k_new), static_cast<const bf16_t*>(v_new), pos_new,
                        static_cast<const bf16_t*>(centroids), bias, off, len, idx, static_cast<bf16_t*>(Ksorted),
                        static_cast<bf16_t*>(Vsorted), nullptr, nullptr, resident_ids, new_bucket_ids, overflow_flag, part, counters,
                        Hkv, Ncap, B, B + 1, n_sink, n_recent, P, cpl);
   else
-    hipLaunchKernelGGL(window_push_kernel<float>, grid, dim3(64), 0, hs, static_cast<const float*>(x_new),
+    hipLaunchKernelGGL(window_push_kernel<float>, grid, dim3(kPushThreads), 0, hs, static_cast<const float*>(x_new),
                        static_cast<const float*>(k_new), static_cast<const float*>(v_new), pos_new,
                        static_cast<const float*>(centroids), bias, off, len, idx, static_cast<float*>(Ksorted),
                        static_cast<float*>(Vsorted), nullptr, nullptr, resident_ids, new_bucket_ids, overflow_flag, part, counters,
@@ -928,7 +1063,7 @@ extern "C" int32_t saap_append_keys(const void* x_new, const void* k_new, const 
   if (units > 65535 || units * sizeof(unsigned) > SAAP_WS_HEADER_BYTES) return SAAP_UNSUPPORTED;
   if (ws_bytes < push_workspace_bytes(units, B)) return SAAP_WORKSPACE_TOO_SMALL;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const int cpl = push_centroids_per_lane(units, B);
+  const int cpl = push_rounds(units, B);
   const int P = (B + kPushSlab * cpl - 1) / (kPushSlab * cpl);
   unsigned* counters = static_cast<unsigned*>(ws);
   PushPartial* part = reinterpret_cast<PushPartial*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
@@ -936,13 +1071,13 @@ extern "C" int32_t saap_append_keys(const void* x_new, const void* k_new, const 
   int32_t* no_resident = nullptr;
   // the push kernel on a plain index: no resident run, the key goes straight into its bucket
   if (dtype == SAAP_BF16)
-    hipLaunchKernelGGL(window_push_kernel<bf16_t>, grid, dim3(64), 0, hs, static_cast<const bf16_t*>(x_new),
+    hipLaunchKernelGGL(window_push_kernel<bf16_t>, grid, dim3(kPushThreads), 0, hs, static_cast<const bf16_t*>(x_new),
                        static_cast<const bf16_t*>(k_new), static_cast<const bf16_t*>(v_new), pos_new,
                        static_cast<const bf16_t*>(centroids), bias, off, len, idx, static_cast<bf16_t*>(Ksorted),
                        static_cast<bf16_t*>(Vsorted), nullptr, nullptr, no_resident, new_bucket_ids, overflow_flag, part, counters, Hkv,
                        Ncap, B, B, 0, 0, P, cpl);
   else
-    hipLaunchKernelGGL(window_push_kernel<float>, grid, dim3(64), 0, hs, static_cast<const float*>(x_new),
+    hipLaunchKernelGGL(window_push_kernel<float>, grid, dim3(kPushThreads), 0, hs, static_cast<const float*>(x_new),
                        static_cast<const float*>(k_new), static_cast<const float*>(v_new), pos_new,
                        static_cast<const float*>(centroids), bias, off, len, idx, static_cast<float*>(Ksorted),
                        static_cast<float*>(Vsorted), nullptr, nullptr, no_resident, new_bucket_ids, overflow_flag, part, counters, Hkv,
@@ -968,11 +1103,11 @@ static int32_t push_fp8(const void* x_new, const void* k_new, const void* v_new,
   const long long units = (long long)S * Hkv;
   if (units > 65535 || units * sizeof(unsigned) > SAAP_WS_HEADER_BYTES) return SAAP_UNSUPPORTED;
   if (ws_bytes < push_workspace_bytes(units, B)) return SAAP_WORKSPACE_TOO_SMALL;
-  const int cpl = push_centroids_per_lane(units, B);
+  const int cpl = push_rounds(units, B);
   const int P = (B + kPushSlab * cpl - 1) / (kPushSlab * cpl);
   unsigned* counters = static_cast<unsigned*>(ws);
   PushPartial* part = reinterpret_cast<PushPartial*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
-  hipLaunchKernelGGL((window_push_kernel<bf16_t, fp8_t>), dim3((unsigned)P, (unsigned)units), dim3(64), 0,
+  hipLaunchKernelGGL((window_push_kernel<bf16_t, fp8_t>), dim3((unsigned)P, (unsigned)units), dim3(kPushThreads), 0,
                      static_cast<hipStream_t>(stream), static_cast<const bf16_t*>(x_new),
                      static_cast<const bf16_t*>(k_new), static_cast<const bf16_t*>(v_new), pos_new,
                      static_cast<const bf16_t*>(centroids), bias, off, len, idx, K8, V8, kscale, vscale, res_ids,
