@@ -20,6 +20,8 @@
 // Operands whose scaled values a bfloat16 does not hold (infinities, NaN, from 2^104 on) make the tile not finite, and so do sums
 // from 2^80 on; it is then done again with fp32 instructions.  The first product stays in fp32, and so do results of few tiles
 // (gemm_split_kernel).
+// Features in bfloat16 are read as they are: one plane in the last product, widened on their way to LDS in the first (a launch of its
+// own that widened them took 5 us).
 // Bounds are free (R, B, hidden; rows that are no multiple of 16 bytes are read element by element).  The bias gradients are the
 // column sums of an operand of a weight gradient: the workgroups of the first tile column add them up as they load it.
 // 8 weight sets, 1000 rows, 128 -> 512 -> 1024: the three large products 93 us each with fp32 instructions, 49 to 53 now, the scaling
@@ -38,8 +40,8 @@ constexpr int kGemmThreads = 256;
 enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_MASK = 3 };
 
 struct GemmArgs {
-  const float* A;      // TA ? [K,M] : [M,K]
-  const float* B;      // TB ? [N,K] : [K,N]
+  const void* A;       // TA ? [K,M] : [M,K]   (EA: float, or bf16_t for features that come as such)
+  const void* B;       // TB ? [N,K] : [K,N]   (EB)
   float* C;            // [M,N]
   const float* bias;   // [N]   (EPI_BIAS, EPI_BIAS_RELU)
   const float* aux;    // [M,N] (EPI_MASK: C = aux > 0 ? acc : 0)
@@ -75,14 +77,18 @@ constexpr int kPlaneA[6] = {2, 0, 1, 1, 0, 0}, kPlaneB[6] = {0, 2, 1, 0, 1, 0};
 // operand's contiguous dimension is k (VEC: rows start on 16 bytes), else it is the row dimension (a wave loads 64 neighbouring
 // rows at one k).  The pitches keep reads and writes free of bank conflicts.
 constexpr int kSlice = 16;
-// (rows x K floats from p on, fewer than 2^29; no load relies on the buffer's bounds)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_buffer(const float* p, int rows, int K) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, rows * K * 4, 0x00027000);
+// (rows x K values from p on, fewer than 2^29; no load relies on the buffer's bounds)
+template <typename E>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_buffer(const E* p, int rows, int K) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<E*>(p), 0, rows * K * (int)sizeof(E), 0x00027000);
 }
-template <bool KC, bool VEC, int R, int THREADS>
+// T: float, or bf16_t: one plane holds the value.
+template <bool KC, bool VEC, int R, int THREADS, typename T>
 struct PlaneLoader {
+  static constexpr int kPlanes = sizeof(T) == 4 ? 3 : 1;
+  static_assert(sizeof(T) == 4 || !KC, "bfloat16 operands that are contiguous along k: not needed");
   static constexpr int E = R * kSlice / THREADS;          // consecutive values of k of one row: 8 or 4
-  static constexpr int kPitch = R + (KC ? 4 : 0), kPlane = kSlice / 8 * kPitch, kUnits = 3 * kPlane;   // units of 16 bytes
+  static constexpr int kPitch = R + (KC ? 4 : 0), kPlane = kSlice / 8 * kPitch, kUnits = kPlanes * kPlane;   // units of 16 bytes
   static_assert(E == 8 || E == 4, "whole pieces of a row's values");
   float r[E];
   static __device__ __forceinline__ int tid() { return threadIdx.x % THREADS; }          // THREADS threads share an operand's slice
@@ -92,12 +98,15 @@ struct PlaneLoader {
   // shares.  Rows past the end repeat the last one and are not stored.
   static __device__ __forceinline__ int offset(int t0, int n_t, int K) {
     const int t = min(t0 + row(), n_t - 1);
-    return 4 * (KC ? t * K + first_k() : first_k() * n_t + t);
+    return (int)sizeof(T) * (KC ? t * K + first_k() : first_k() * n_t + t);
   }
   // The slice from k0 on, or the last 16 values of k where it would reach past the end.
   __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t x, int at, int k0, int n_t, int K) {
     k0 = min(k0, K - kSlice);
-    if constexpr (KC && VEC) {
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) r[e] = __uint_as_float((unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(x, at, 2 * (k0 + e) * n_t, 0) << 16);
+    } else if constexpr (KC && VEC) {
 #pragma unroll
       for (int e = 0; e < E; e += 4) {
         const u32x4_t u = __builtin_amdgcn_raw_buffer_load_b128(x, at + 4 * e, 4 * k0, 0);
@@ -121,7 +130,7 @@ struct PlaneLoader {
 #pragma unroll
     for (int e = 0; e < E; ++e) rest[e] = r[e] * up;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
+    for (int p = 0; p < kPlanes; ++p) {
       uint32_t u[E / 2];
       take_plane<E>(rest, u);
       uint4* at = s + p * kPlane + first_k() / 8 * kPitch + row();
@@ -139,9 +148,24 @@ struct PlaneLoader {
   }
 };
 
+// Four neighbouring values (VEC: they start on a multiple of four).
+template <bool VEC>
+__device__ __forceinline__ float4 four_of(const float* p) {
+  if constexpr (VEC) return *reinterpret_cast<const float4*>(p);
+  return make_float4(p[0], p[1], p[2], p[3]);
+}
+template <bool VEC>
+__device__ __forceinline__ float4 four_of(const bf16_t* p) {
+  if constexpr (VEC) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    return make_float4(bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y));
+  }
+  return make_float4(Vec8<bf16_t>::widen(p[0]), Vec8<bf16_t>::widen(p[1]), Vec8<bf16_t>::widen(p[2]), Vec8<bf16_t>::widen(p[3]));
+}
+
 // The same in fp32 for operands whose contiguous dimension is k: R rows by SL values of k, four a piece.  LDS holds [row][k], a
 // lane reads four k at a time; product (g, j) of a slice sums k = 8 g + 4 (lane / 32) + j.
-template <bool VEC, int R, int SL>
+template <bool VEC, int R, int SL, typename T>
 struct SliceLoader {
   static constexpr int kPieces = R * SL / 4 / kGemmThreads, kPitch = SL + 4, kFloats = R * kPitch;
   float4 r[kPieces];
@@ -160,23 +184,16 @@ struct SliceLoader {
     for (int i = 0; i < kPieces; ++i) {
       int t, k;
       place(i, t, k);
-      o.at[i] = 4u * (unsigned)(min(t0 + t, n_t - 1) * K + k);
+      o.at[i] = (unsigned)sizeof(T) * (unsigned)(min(t0 + t, n_t - 1) * K + k);
     }
     return o;
   }
   // The slice from k0 on; where it would reach past the end of k, the last SL values instead, of which stash() clears those
   // before k0.  (Cleared here, they would be waited for here.)
-  __device__ __forceinline__ void fetch(const float* X, const Offsets& o, int k0, int K) {
+  __device__ __forceinline__ void fetch(const T* X, const Offsets& o, int k0, int K) {
     const char* x = reinterpret_cast<const char*>(X + min(k0, K - SL));
 #pragma unroll
-    for (int i = 0; i < kPieces; ++i) {
-      if constexpr (VEC) {
-        r[i] = *reinterpret_cast<const float4*>(x + o.at[i]);
-      } else {
-        const float* p = reinterpret_cast<const float*>(x + o.at[i]);
-        r[i] = make_float4(p[0], p[1], p[2], p[3]);
-      }
-    }
+    for (int i = 0; i < kPieces; ++i) r[i] = four_of<VEC>(reinterpret_cast<const T*>(x + o.at[i]));
   }
   __device__ __forceinline__ void stash(float* s, int k0, int K) {
     const int before = k0 - min(k0, K - SL);              // values of the slice that belong to the one before it
@@ -225,20 +242,20 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, int w, int m0, int
 }
 
 constexpr int kDirect = 32;
-template <bool KC, bool VEC>
+template <bool KC, bool VEC, typename T>
 struct DirectOperand {
   float r[4][4];                                         // [g][j]: k = k0 + 8 g + 4 (lane / 32) + j, the same for both operands
-  __device__ __forceinline__ void fetch(const float* X, int t0, int k0, int n_t, int K) {
+  __device__ __forceinline__ void fetch(const T* X, int t0, int k0, int n_t, int K) {
     const int lane = threadIdx.x & 63, half = lane >> 5, t = min(t0 + (lane & 31), n_t - 1);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int k = k0 + 8 * g + 4 * half;
       if constexpr (KC && VEC) {
-        const float4 v = *reinterpret_cast<const float4*>(X + (size_t)t * K + min(k, K - 4));
+        const float4 v = four_of<true>(X + (size_t)t * K + min(k, K - 4));
         r[g][0] = v.x; r[g][1] = v.y; r[g][2] = v.z; r[g][3] = v.w;
       } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) r[g][j] = KC ? X[(size_t)t * K + min(k + j, K - 1)] : X[(size_t)min(k + j, K - 1) * n_t + t];
+        for (int j = 0; j < 4; ++j) r[g][j] = Vec8<T>::widen(KC ? X[(size_t)t * K + min(k + j, K - 1)] : X[(size_t)min(k + j, K - 1) * n_t + t]);
       }
     }
   }
@@ -252,11 +269,11 @@ struct DirectOperand {
 };
 
 // A matrix tile of the product in fp32, operands straight from memory (a lane loads what the matrix cores take from it).
-template <bool TA, bool TB, bool VEC>
-__device__ __forceinline__ f32x16_t fp32_tile(const GemmArgs& g, const float* A, const float* B, int m0, int n0) {
+template <bool TA, bool TB, bool VEC, typename EA, typename EB>
+__device__ __forceinline__ f32x16_t fp32_tile(const GemmArgs& g, const EA* A, const EB* B, int m0, int n0) {
   f32x16_t acc = {0};
-  DirectOperand<!TA, VEC> a;
-  DirectOperand<TB, VEC> b;
+  DirectOperand<!TA, VEC, EA> a;
+  DirectOperand<TB, VEC, EB> b;
 #pragma unroll 1
   for (int k0 = 0; k0 < g.K; k0 += kDirect) {
     a.fetch(A, m0, k0, g.M, g.K);
@@ -282,17 +299,17 @@ __device__ __forceinline__ bool all_finite(const f32x16_t& v) {
 }
 
 // C = A B^T in fp32 (the first product).  A workgroup of two by two waves owns a tile of 64 TM x 64, a wave TM matrix tiles of 32.
-template <int EPI, bool VEC, int TM, int SL>
+template <int EPI, bool VEC, int TM, int SL, typename EA>
 __global__ void __launch_bounds__(kGemmThreads, 4)
 gemm_f32_kernel(GemmArgs g) {
   constexpr int BM = 64 * TM, BN = 64;
-  typedef SliceLoader<VEC, BM, SL> LoadA;
-  typedef SliceLoader<VEC, BN, SL> LoadB;
+  typedef SliceLoader<VEC, BM, SL, EA> LoadA;
+  typedef SliceLoader<VEC, BN, SL, float> LoadB;
   __shared__ __align__(16) float s_ab[2][LoadA::kFloats + LoadB::kFloats];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
-  const float* A = g.A + (size_t)w * g.sA;
-  const float* B = g.B + (size_t)w * g.sB;
+  const EA* A = static_cast<const EA*>(g.A) + (size_t)w * g.sA;
+  const float* B = static_cast<const float*>(g.B) + (size_t)w * g.sB;
   const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32;
   const int col = lane & 31, half = lane >> 5;
   f32x16_t acc[TM];
@@ -353,19 +370,19 @@ gemm_f32_kernel(GemmArgs g) {
 
 // C = A' B'; A' is M x K, B' is K x N.  Two by WN waves own a tile of 64 TM x 32 WN TN, a wave TM x TN matrix tiles of 32.  KS: the
 // workgroup has as many such groups of waves, which share out k and add up at the end.
-template <bool TA, bool TB, int EPI, bool VEC, int TM, int TN, int WN, int KS>
+template <bool TA, bool TB, int EPI, bool VEC, typename EB, int TM, int TN, int WN, int KS>
 __global__ void __launch_bounds__(128 * WN * KS, KS > 2 ? 1 : 2)
 gemm_kernel(GemmArgs g) {
   constexpr int kThreads = 128 * WN, BM = 64 * TM, BN = 32 * WN * TN;
-  typedef PlaneLoader<!TA, VEC, BM, kThreads> LoadA;
-  typedef PlaneLoader<TB, VEC, BN, kThreads> LoadB;
+  typedef PlaneLoader<!TA, VEC, BM, kThreads, float> LoadA;
+  typedef PlaneLoader<TB, VEC, BN, kThreads, EB> LoadB;
   constexpr int kUnits = LoadA::kUnits + LoadB::kUnits;
   __shared__ uint4 s_all[KS * 2 * kUnits];
   const int lane = threadIdx.x & 63, wave = threadIdx.x % kThreads >> 6;
   const int part = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;       // of k
   const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
-  const float* A = g.A + (size_t)w * g.sA;
-  const float* B = g.B + (size_t)w * g.sB;
+  const float* A = static_cast<const float*>(g.A) + (size_t)w * g.sA;
+  const EB* B = static_cast<const EB*>(g.B) + (size_t)w * g.sB;
   const int wm = wave / WN * 32 * TM, wn = wave % WN * 32 * TN;
   const int col = lane & 31, half = lane >> 5;
   uint4* const s_ab = s_all + part * 2 * kUnits;
@@ -394,11 +411,12 @@ gemm_kernel(GemmArgs g) {
   auto step = [&](Staged& st, int buf, int k0_next, int end) {
     const uint4* sa = s_ab + buf * kUnits;
     const uint4* sb = sa + LoadA::kUnits;
-    bf16x8_t a[TM][3], b[TN][3];
+    bf16x8_t a[TM][3], b[TN][LoadB::kPlanes];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
 #pragma unroll
-      for (int u = 0; u < TN; ++u) b[u][p] = LoadB::read(sb, p, wn + 32 * u + col, half);
+      for (int u = 0; u < TN; ++u)
+        if (p < LoadB::kPlanes) b[u][p] = LoadB::read(sb, p, wn + 32 * u + col, half);
 #pragma unroll
       for (int t = 0; t < TM; ++t) a[t][p] = LoadA::read(sa, p, wm + 32 * t + col, half);
     }
@@ -409,6 +427,7 @@ gemm_kernel(GemmArgs g) {
       for (int t = 0; t < TM; ++t)
 #pragma unroll
         for (int u = 0; u < TN; ++u) {
+          if (kPlaneB[i] >= LoadB::kPlanes) continue;
           f32x16_t& sum = i < 5 ? low[t][u] : acc[t][u];
           sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kPlaneA[i]], b[u][kPlaneB[i]], sum, 0, 0, 0);
         }
@@ -505,20 +524,20 @@ gemm_kernel(GemmArgs g) {
 
 // C = A' B' in fp32 for results of few tiles: a workgroup owns one matrix tile, its four waves a quarter of the k each, operands straight
 // from memory (a lane loads what the matrix cores take from it), the next slice's loads in flight.
-template <bool TA, bool TB, int EPI, bool VEC>
-__global__ void __launch_bounds__(kGemmThreads, VEC ? 4 : 2)
+template <bool TA, bool TB, int EPI, bool VEC, typename EA, typename EB>
+__global__ void __launch_bounds__(kGemmThreads, !VEC ? 2 : sizeof(EB) == 2 ? 3 : 4)
 gemm_split_kernel(GemmArgs g) {
   constexpr int kStep = 4 * kDirect;
   __shared__ float4 s_red[4 * 4 * 64];                   // [wave][four registers][lane]
   __shared__ float s_sum[4 * 32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
   const int w = blockIdx.x, n0 = g.n_first + (int)blockIdx.y * 32, m0 = g.m_first + (int)blockIdx.z * 32;
-  const float* A = g.A + (size_t)w * g.sA;
-  const float* B = g.B + (size_t)w * g.sB;
+  const EA* A = static_cast<const EA*>(g.A) + (size_t)w * g.sA;
+  const EB* B = static_cast<const EB*>(g.B) + (size_t)w * g.sB;
   const bool sums = TA && g.colsum != nullptr && n0 == 0;
   float csum = 0.f;                                      // of the lane's column of A, this half's k
   f32x16_t acc = {0};
-  struct Staged { DirectOperand<!TA, VEC> a; DirectOperand<TB, VEC> b; };
+  struct Staged { DirectOperand<!TA, VEC, EA> a; DirectOperand<TB, VEC, EB> b; };
   auto fetch = [&](Staged& st, int k0) {
     st.a.fetch(A, m0, k0, g.M, g.K);
     st.b.fetch(B, n0, k0, g.N, g.K);
@@ -571,39 +590,39 @@ gemm_split_kernel(GemmArgs g) {
 // slice's chain (operands from LDS, split, products, barrier: 0.7 us) is what takes the time, so that more waves share out k: two
 // groups (4 sets, 1000 rows, 512 x 1024: 42 -> 37 us; 8 sets, 96 x 1024: 32 -> 24), four where every compute unit has one workgroup
 // at most (20 of those 24; 1 set, 512 x 1024: 20 -> 16).
-// With fewer than 512 matrix tiles a tile's k is shared out over four waves in fp32 (8 sets, 1024 rows, 192 x 128: 9 us, 17), and so it
-// is where k is too short to be shared out or an operand too large for offsets of 32 bits; that one takes several launches where a
-// grid dimension has no room for its smaller tiles.
+// With fewer than 512 matrix tiles, or 640 where k is short, a tile's k is shared out over four waves in fp32 (8 sets, 1024 rows, 192 x
+// 128: 9 us, 17; 4 sets, 100 rows, 512 x 256: 6.5 us, 8.0), and so it is where k is too short to be shared out or an operand too large
+// for offsets of 32 bits; that one takes several launches where a grid dimension has no room for its smaller tiles.
 constexpr long long kMostTiles = 65535;
-template <bool TA, bool TB, int EPI, bool VEC, bool F32>
+template <bool TA, bool TB, int EPI, bool VEC, bool F32, typename EA, typename EB>
 void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
   auto grid = [&](int bm, int bn) { return dim3((unsigned)Hw, (unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + bm - 1) / bm)); };
   auto count = [&](int bm, int bn) { const dim3 d = grid(bm, bn); return (long long)d.x * d.y * d.z; };
   const bool tiled = g.K >= 32 && (long long)g.M * g.K < (1ll << 29) && (long long)g.N * g.K < (1ll << 29) && g.N <= kMostTiles * 64;
   if constexpr (F32) {
-    static_assert(!TA && TB, "rows of both operands along k");
+    static_assert(!TA && TB && sizeof(EB) == 4, "rows of both operands along k");
     // 128 x 64 tiles where they give every compute unit the four workgroups it has room for, or else 64 x 64 with slices twice as
     // long for the same LDS
     if (tiled && count(128, 64) >= 4LL * device_cus()) {
-      hipLaunchKernelGGL((gemm_f32_kernel<EPI, VEC, 2, 16>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, VEC, 2, 16, EA>), grid(128, 64), dim3(kGemmThreads), 0, hs, g);
       return;
     }
     if (tiled && count(64, 64) >= device_cus()) {
-      hipLaunchKernelGGL((gemm_f32_kernel<EPI, VEC, 1, 32>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, VEC, 1, 32, EA>), grid(64, 64), dim3(kGemmThreads), 0, hs, g);
       return;
     }
   } else {
+    static_assert(sizeof(EA) == 4, "three planes");
     auto launch = [&](auto kernel, int bm, int bn, int threads) { hipLaunchKernelGGL(kernel, grid(bm, bn), dim3(threads), 0, hs, g); };
     const int columns = (g.N + 63) / 64;
     const bool half_empty = columns < 7 && columns % 2 == 1;      // the last tile of 128 columns, and it counts
-    if (tiled && half_empty && count(128, 64) >= 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 2, 1, 2, 1>, 128, 64, 256);
-    if (tiled && !half_empty && count(128, 128) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 2, 1, 4, 1>, 128, 128, 512);
-    if (tiled && count(64, 64) > 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 1>, 64, 64, 256);
-    if (tiled && count(32, 32) >= 2LL * device_cus()) {
-      if (count(64, 64) <= device_cus() && g.K >= 128) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 4>, 64, 64, 1024);
-      if (g.K >= 64) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 2>, 64, 64, 512);
-      if (count(64, 64) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, 1, 1, 2, 1>, 64, 64, 256);
-    }
+    if (tiled && half_empty && count(128, 64) >= 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 2, 1, 2, 1>, 128, 64, 256);
+    if (tiled && !half_empty && count(128, 128) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 2, 1, 4, 1>, 128, 128, 512);
+    if (tiled && count(64, 64) > 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 1>, 64, 64, 256);
+    if (tiled && g.K >= 128 && count(64, 64) <= device_cus() && count(32, 32) >= 2LL * device_cus())
+      return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 4>, 64, 64, 1024);
+    if (tiled && g.K >= 64 && 2 * count(32, 32) >= 5LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 2>, 64, 64, 512);
+    if (tiled && count(64, 64) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 1>, 64, 64, 256);
   }
   for (long long m = 0; m < g.M; m += kMostTiles * 32)
     for (long long n = 0; n < g.N; n += kMostTiles * 32) {
@@ -611,24 +630,19 @@ void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
       part.m_first = (int)m;
       part.n_first = (int)n;
       auto tiles = [](long long left) { return (unsigned)std::min((left + 31) / 32, kMostTiles); };
-      hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC>), dim3((unsigned)Hw, tiles(g.N - n), tiles(g.M - m)), dim3(kGemmThreads),
+      hipLaunchKernelGGL((gemm_split_kernel<TA, TB, EPI, VEC, EA, EB>), dim3((unsigned)Hw, tiles(g.N - n), tiles(g.M - m)), dim3(kGemmThreads),
                          0, hs, part);
     }
 }
 
 // F32: every product and sum in fp32, for the first product: a hidden unit's sign decides which gradients flow through it, and
 // a unit that another rounding moves across zero moves them by far more than a rounding.
-template <bool TA, bool TB, int EPI, bool F32 = false>
+template <bool TA, bool TB, int EPI, bool F32 = false, typename EA = float, typename EB = float>
 void gemm(const GemmArgs& g, int Hw, hipStream_t hs) {
-  // 16-byte loads need rows of both operands that start on 16 bytes
-  auto rows_aligned = [](const float* p, int ld, long long stride) { return aligned16(p) && ld % 4 == 0 && stride % 4 == 0; };
-  if (rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB)) gemm_sized<TA, TB, EPI, true, F32>(g, Hw, hs);
-  else gemm_sized<TA, TB, EPI, false, F32>(g, Hw, hs);
-}
-
-__global__ void widen_kernel(const bf16_t* __restrict__ x, float* __restrict__ y, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) y[i] = __uint_as_float((uint32_t)x[i] << 16);
+  // loads of four values need rows of both operands that start on a multiple of four
+  auto rows_aligned = [](const void* p, int ld, long long stride) { return aligned16(p) && ld % 4 == 0 && stride % 4 == 0; };
+  if (rows_aligned(g.A, TA ? g.M : g.K, g.sA) && rows_aligned(g.B, TB ? g.K : g.N, g.sB)) gemm_sized<TA, TB, EPI, true, F32, EA, EB>(g, Hw, hs);
+  else gemm_sized<TA, TB, EPI, false, F32, EA, EB>(g, Hw, hs);
 }
 
 // Sum of a workgroup's values, in a fixed order; every thread gets it.  s_red: 256/64 + 1 floats.
@@ -856,10 +870,10 @@ adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restric
 
 }  // namespace
 
-// header | x widened [Hw,R,d] | h [Hw,R,hidden] | z then dL/dz [Hw,R,B] | dL/da [Hw,R,hidden] | row losses [Hw,R]
+// header | h [Hw,R,hidden] | z then dL/dz [Hw,R,B] | dL/da [Hw,R,hidden] | row losses [Hw,R]
 //        | batch-norm variant: pre-activations a [Hw,R,hidden] | column statistics [Hw,4,hidden]
 size_t train_workspace_bytes(long long Hw, long long R, int d, int hidden, int B) {
-  return (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * R * ((size_t)d + 3 * (size_t)hidden + B + 1) * sizeof(float) +
+  return (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * R * (3 * (size_t)hidden + B + 1) * sizeof(float) +
          (size_t)Hw * 4 * hidden * sizeof(float);
 }
 
@@ -886,18 +900,11 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
   if (Hw > 65535 || R > 65535 * 64) return SAAP_UNSUPPORTED;
   if (ws_bytes < train_workspace_bytes(Hw, R, d, hidden, B)) return SAAP_WORKSPACE_TOO_SMALL;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  float* xf = reinterpret_cast<float*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
-  float* h = xf + (size_t)Hw * R * d;
+  float* h = reinterpret_cast<float*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES);
   float* z = h + (size_t)Hw * R * hidden;
   float* da = z + (size_t)Hw * R * B;
   float* loss_rows = da + (size_t)Hw * R * hidden;
-  const float* xin = static_cast<const float*>(x);
-  if (x_dtype == SAAP_BF16) {
-    const size_t n = (size_t)Hw * R * d;
-    hipLaunchKernelGGL(widen_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, static_cast<const bf16_t*>(x),
-                       xf, n);
-    xin = xf;
-  }
+  const bool narrow = x_dtype == SAAP_BF16;
   const long long sx = (long long)R * d, sh = (long long)R * hidden, sz = (long long)R * B;
   const long long sW1 = (long long)hidden * d, sW2 = (long long)B * hidden;
   float* pre = loss_rows + (size_t)Hw * R;          // batch-norm variant only
@@ -906,10 +913,12 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
   const dim3 per_elem((unsigned)(((size_t)R * hidden + 255) / 256), (unsigned)Hw);
   if (!bn) {
     // h = relu(x W1^T + b1)
-    gemm<false, true, EPI_BIAS_RELU, true>({xin, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
+    const GemmArgs g = {x, params->W1, h, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0};
+    narrow ? gemm<false, true, EPI_BIAS_RELU, true, bf16_t>(g, Hw, hs) : gemm<false, true, EPI_BIAS_RELU, true>(g, Hw, hs);
   } else {
     // a = x W1^T + b1;  h = relu(gamma * normalised(a) + beta)
-    gemm<false, true, EPI_BIAS, true>({xin, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0}, Hw, hs);
+    const GemmArgs g = {x, params->W1, pre, params->b1, nullptr, R, hidden, d, sx, sW1, sh, hidden, 0, nullptr, 0, 0, 0};
+    narrow ? gemm<false, true, EPI_BIAS, true, bf16_t>(g, Hw, hs) : gemm<false, true, EPI_BIAS, true>(g, Hw, hs);
     hipLaunchKernelGGL(bn_stats_kernel, per_col, dim3(kBnThreads), 0, hs, pre, stats, bn->running_mean, bn->running_var, R, hidden,
                        bn->eps, bn->momentum);
     hipLaunchKernelGGL(bn_relu_kernel, per_elem, dim3(256), 0, hs, pre, stats, bn->gamma, bn->beta, h, R, hidden);
@@ -931,7 +940,8 @@ static int32_t loss_grads(const void* x, const float* target, const saap_mlp_f32
     hipLaunchKernelGGL(bn_backward_kernel, per_elem, dim3(256), 0, hs, pre, da, stats, bn->gamma, R, hidden);
   }
   // dW1 = da^T x, db1 = column sums of da
-  gemm<true, false, EPI_NONE>({da, xin, grads->W1, nullptr, nullptr, hidden, d, R, sh, sx, sW1, 0, 0, grads->b1, hidden, 0, 0}, Hw, hs);
+  const GemmArgs g = {da, x, grads->W1, nullptr, nullptr, hidden, d, R, sh, sx, sW1, 0, 0, grads->b1, hidden, 0, 0};
+  narrow ? gemm<true, false, EPI_NONE, false, float, bf16_t>(g, Hw, hs) : gemm<true, false, EPI_NONE>(g, Hw, hs);
   return launch_status();
 }
 

@@ -44,3 +44,22 @@ def test_huge_weight_in_any_group(saap, unit):  # noqa: F811
     torch.testing.assert_close(loss.double(), want, rtol=1e-5, atol=0.0)
     for name, got, g in zip(("dW1", "db1", "dW2", "db2"), grads, ref):
         assert ((got.double() - g).norm() <= 3e-6 * g.norm()), name
+
+
+@pytest.mark.parametrize("Hw,R,d,hidden,B", [
+    (16, 129, 128, 256, 40), (16, 131, 129, 254, 33),      # dW1 in four groups
+    (16, 70, 200, 512, 40), (16, 67, 201, 500, 40),        # two
+    (16, 40, 512, 320, 40), (32, 36, 256, 512, 40), (32, 35, 64, 2048, 40),      # one, 128 x 128, 128 x 64
+    (2, 20, 12, 20, 24), (3, 33, 13, 30, 25), (8, 1000, 128, 512, 64),           # few tiles; the first product's large ones
+])
+def test_features_in_bfloat16(saap, Hw, R, d, hidden, B):  # noqa: F811
+    """Against the same features in fp32, whose values are the same: all but dW1 bit for bit, and dW1 as far off as fp32 sums of R
+    terms in another order may be (4e-7 from float64 each: 1e-6)."""
+    x, T, params = problem(R + d, Hw, R, d, hidden, B, torch.bfloat16)
+    x, T, params = x.to(torch.bfloat16).to(DEV), T.to(DEV), to_dev(params)
+    loss, grads = saap.query_model_loss_grads(x, T, params)
+    want_loss, want = saap.query_model_loss_grads(x.float(), T, params)
+    assert torch.equal(loss, want_loss)
+    for name, got, g in zip(("dW1", "db1", "dW2", "db2"), grads, want):
+        dims = tuple(range(1, got.dim()))
+        assert ((got - g).norm(dim=dims) <= 1e-6 * g.norm(dim=dims)).all() if name == "dW1" else torch.equal(got, g), name
