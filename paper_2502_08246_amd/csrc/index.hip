@@ -10,12 +10,14 @@
 //                its part of the slice in order, 64 positions at a time; the rank of a position among equal ids
 //                inside the 64 comes from ballots, the waves' and the buckets' running positions are kept in LDS -> idx
 //   4. permute   rows of K and V are copied to their slot, 16 bytes per lane, whole rows
-// A short context is one slice: order_small does steps 1 to 3 in one launch.
+// A short context takes one launch: order_direct does steps 1 to 3.
 //
 // With a resident block (attention sink + recent keys, Section 3 "Per-head attention span")
 // only the positions [lo, hi) go through steps 1-3; the resident positions are placed by
 // their slot rule into one more run behind the B buckets, and window_push moves one key per
 // decode step from that run into its bucket.
+#include <algorithm>
+
 #include "common.h"
 
 namespace saap {
@@ -262,81 +264,103 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
   for (int j = all + max(W, 0) + slice * kScatterThreads + tid; j < Ncap; j += n_slices * kScatterThreads) ix[j] = -1;
 }
 
-// Steps 1 to 3 for a context of one slice (up to kSmallKeys positions and kSmallBuckets buckets): one workgroup of 16
-// waves per unit, each wave counting and then placing its sixteenth of the positions.  Launches of 2 to 3 us each, five when this
-// was measured, become one (8 heads of 5003 keys: 26 -> 10 us).
-constexpr int kSmallKeys = 16384, kSmallBuckets = 2048, kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
-__global__ void __launch_bounds__(kSmallThreads)
-order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
-                   int32_t* __restrict__ res_ids, int N, int Ncap, int B, int id_bits, int lo, int hi, int slack, int W, int n_sink,
-                   int n_recent, int n_res) {
-  extern __shared__ int s_next[];                        // [B] | counters [waves][words]
-  __shared__ int s_wsum[kSmallWaves], s_end;
-  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Steps 1 to 3 in one launch for contexts of up to kDirectKeys positions and kDirectBuckets buckets: workgroups of 16 waves take 1024
+// ROUNDS positions each, hold their ids, and where a unit has several workgroups each counts the others' ids for itself (the L2
+// serves them; a position takes an LDS addition, 5 us for 64 Ki of them, which is where three launches are as good: 18 and 17 us at
+// 8 heads of 65536).  8 heads of 5003 keys 8.6 us with ids loaded again for the placing, 7.9 now (26 as five launches); of 16384 keys
+// 18.0 -> 10.9, one workgroup for 16384 positions and three launches before; of 30000 keys 17.9 -> 13.7; 64 of 16384: 17.8 -> 12.8.
+constexpr int kDirectKeys = 49152, kDirectBuckets = 2048, kDirectThreads = 1024, kDirectWaves = kDirectThreads / 64;
+template <int ROUNDS>
+__global__ void __launch_bounds__(kDirectThreads)
+order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
+                    int32_t* __restrict__ res_ids, int N, int Ncap, int B, int id_bits, int lo, int hi, int slack, int W, int n_sink,
+                    int n_recent, int n_res) {
+  // first slots of this part [B] | counters [waves][words] | with several parts: ids before this part [B], after it [B]
+  extern __shared__ int s_next[];
+  __shared__ int s_wsum[kDirectWaves], s_end;
+  const int unit = blockIdx.x, part = blockIdx.y, n_parts = gridDim.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int words = (B + 1) / 2;
   unsigned* s_cnt = reinterpret_cast<unsigned*>(s_next + B);
   unsigned* cnt = s_cnt + wave * words;
+  int* s_before = reinterpret_cast<int*>(s_cnt + kDirectWaves * words);
+  int* s_after = s_before + B;
   const int32_t* idu = ids + (size_t)unit * N;
   int32_t* ix = idx + (size_t)unit * Ncap;
   const int lstride = W >= 0 ? B + 1 : B;
   int32_t* l = len + (size_t)unit * lstride;
   int32_t* o = off + (size_t)unit * (lstride + 1);
-  const int per = ((hi - lo + kSmallWaves - 1) / kSmallWaves + 63) & ~63;      // positions per wave
-  const int n0 = lo + wave * per, n1 = min(n0 + per, hi);
-  constexpr int kDeep = 4;                               // rounds of ids in flight
-  auto load_ids = [&](int n, int (&v)[kDeep]) {
+  constexpr int kPart = kDirectThreads * ROUNDS;
+  const int p0 = lo + part * kPart, p1 = min(p0 + kPart, hi);
+  const int per = ((p1 - p0 + kDirectWaves - 1) / kDirectWaves + 63) & ~63;      // positions per wave, at most 64 ROUNDS
+  const int n0 = p0 + wave * per, n1 = min(n0 + per, p1);
+  int v[ROUNDS];
 #pragma unroll
-    for (int k = 0; k < kDeep; ++k) {
-      const int at = n + k * 64 + lane;
-      v[k] = idu[min(at, N - 1)];
-      if (at >= n1 || v[k] < 0 || v[k] >= B) v[k] = -1;
-    }
-  };
-  int v[kDeep];
-  load_ids(n0, v);                                       // in flight while the counters are cleared
-  for (int i = tid; i < kSmallWaves * words; i += kSmallThreads) s_cnt[i] = 0u;
+  for (int k = 0; k < ROUNDS; ++k) v[k] = idu[min(n0 + k * 64 + lane, N - 1)];
+  for (int i = tid; i < kDirectWaves * words + (n_parts > 1 ? 2 * B : 0); i += kDirectThreads) s_cnt[i] = 0u;
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k)
+    if (n0 + k * 64 + lane >= n1 || v[k] < 0 || v[k] >= B) v[k] = -1;
   __syncthreads();
-  for (int n = n0; n < n1; n += 64 * kDeep) {
-    if (n > n0) load_ids(n, v);
 #pragma unroll
-    for (int k = 0; k < kDeep; ++k)
-      if (v[k] >= 0) wave_count_add(cnt, v[k], 1u);
+  for (int k = 0; k < ROUNDS; ++k)
+    if (v[k] >= 0) wave_count_add(cnt, v[k], 1u);
+  if (n_parts > 1) {
+    constexpr int kDeep = 8;                             // loads of a thread in flight
+    auto count_others = [&](int from, int to, int* s) {
+      for (int n = from + tid; n < to; n += kDeep * kDirectThreads) {
+        int u[kDeep];
+#pragma unroll
+        for (int k = 0; k < kDeep; ++k) u[k] = idu[min(n + k * kDirectThreads, N - 1)];
+#pragma unroll
+        for (int k = 0; k < kDeep; ++k)
+          if (n + k * kDirectThreads < to && u[k] >= 0 && u[k] < B) atomicAdd(&s[u[k]], 1);
+      }
+    };
+    count_others(lo, p0, s_before);
+    count_others(p1, hi, s_after);
   }
-  load_ids(n0, v);                                       // again, for the placing
   __syncthreads();
   // exclusive prefix over the waves (at most 16384 per half word), totals, and the buckets' offsets
-  constexpr int kPairs = kSmallBuckets / 2 / kSmallThreads;                      // pairs of buckets per thread
-  static_assert(kPairs == 1, "one pair of buckets per thread");
+  static_assert(kDirectBuckets / 2 == kDirectThreads, "one pair of buckets per thread");
   unsigned tot = 0u;
   if (tid < words) {
-    unsigned c[kSmallWaves];                             // read before the first is written: one LDS latency
+    unsigned c[kDirectWaves];                            // read before the first is written: one LDS latency
 #pragma unroll
-    for (int w = 0; w < kSmallWaves; ++w) c[w] = s_cnt[w * words + tid];
+    for (int w = 0; w < kDirectWaves; ++w) c[w] = s_cnt[w * words + tid];
 #pragma unroll
-    for (int w = 0; w < kSmallWaves; ++w) {
+    for (int w = 0; w < kDirectWaves; ++w) {
       s_cnt[w * words + tid] = tot;
       tot += c[w];
     }
   }
-  const int b0 = 2 * tid, len0 = (int)(tot & 0xffffu), len1 = (int)(tot >> 16);
-  const int mine = (b0 < B ? len0 + slack : 0) + (b0 + 1 < B ? len1 + slack : 0);
+  const int b0 = 2 * tid;
+  int lens[2] = {(int)(tot & 0xffffu), (int)(tot >> 16)}, before[2] = {0, 0};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (n_parts > 1 && b0 + i < B) {
+      before[i] = s_before[b0 + i];
+      lens[i] += before[i] + s_after[b0 + i];
+    }
+  const int mine = (b0 < B ? lens[0] + slack : 0) + (b0 + 1 < B ? lens[1] + slack : 0);
   const int incl = (int)wave_prefix_sum((unsigned)mine);
   if (lane == 63) s_wsum[wave] = incl;
   __syncthreads();
   int run = incl - mine;
   for (int w = 0; w < wave; ++w) run += s_wsum[w];
-  if (tid == 0) o[0] = 0;
+  if (tid == 0 && part == 0) o[0] = 0;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int b = b0 + i;
     if (b < B) {
-      s_next[b] = run;
-      l[b] = i ? len1 : len0;
-      run += (i ? len1 : len0) + slack;
-      o[b + 1] = run;
+      s_next[b] = run + before[i];
+      run += lens[i] + slack;
+      if (part == 0) {
+        l[b] = lens[i];
+        o[b + 1] = run;
+      }
       if (b == B - 1) {
         s_end = run;
-        if (W >= 0) {
+        if (W >= 0 && part == 0) {
           o[B + 1] = run + W;
           l[B] = n_res;
         }
@@ -344,24 +368,19 @@ order_small_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, i
     }
   }
   __syncthreads();
-  for (int n = n0; n < n1; n += 64 * kDeep) {
-    int now[kDeep];
 #pragma unroll
-    for (int k = 0; k < kDeep; ++k) now[k] = v[k];
-    if (n + 64 * kDeep < n1) load_ids(n + 64 * kDeep, v);
-#pragma unroll
-    for (int k = 0; k < kDeep; ++k)
-      if (n + k * 64 < n1) place_round(now[k], n + k * 64 + lane, id_bits, s_next, cnt, ix);
-  }
+  for (int k = 0; k < ROUNDS; ++k)
+    if (n0 + k * 64 < n1) place_round(v[k], n0 + k * 64 + lane, id_bits, s_next, cnt, ix);
   // free slots: the end of a bucket is the start of the next
-  const int all = s_end;
-  for (int i = tid; i < B * slack; i += kSmallThreads) {
+  const int all = s_end, step = n_parts * kDirectThreads, first = part * kDirectThreads + tid;
+  for (int i = first; i < B * slack; i += step) {
     const int b = i / slack;
-    ix[(b + 1 < B ? s_next[b + 1] : all) - slack + (i - b * slack)] = -1;
+    const int end = b + 1 < B ? s_next[b + 1] - (n_parts > 1 ? s_before[b + 1] : 0) : all;
+    ix[end - slack + (i - b * slack)] = -1;
   }
-  for (int j = all + max(W, 0) + tid; j < Ncap; j += kSmallThreads) ix[j] = -1;       // behind the last run: dropped keys
+  for (int j = all + max(W, 0) + first; j < Ncap; j += step) ix[j] = -1;       // behind the last run: dropped keys
   if (W > 0)
-    for (int j = tid; j < W; j += kSmallThreads) place_resident(j, idu, ix, res_ids + (size_t)unit * W, all, N, n_sink, n_recent, n_res);
+    for (int j = first; j < W; j += step) place_resident(j, idu, ix, res_ids + (size_t)unit * W, all, N, n_sink, n_recent, n_res);
 }
 
 // Copy rows into their slots: out[slot] = in[idx[slot]] for member slots (0 <= idx[slot] < N).  ZERO: free slots are set
@@ -895,10 +914,20 @@ void saap::order_keys(const int32_t* bucket_ids, int32_t* off, int32_t* len, int
   const int lo = windowed ? (N <= W ? 0 : n_sink) : 0;
   const int hi = windowed ? (N <= W ? 0 : N - n_recent) : N;
   const size_t next_bytes = (size_t)B * sizeof(int), wave_bytes = (size_t)(B + 1) / 2 * sizeof(unsigned);
-  if (N <= kSmallKeys && B <= kSmallBuckets && allow_lds<order_small_kernel>(next_bytes + kSmallWaves * wave_bytes)) {
-    hipLaunchKernelGGL(order_small_kernel, dim3((unsigned)units), dim3(kSmallThreads), next_bytes + kSmallWaves * wave_bytes, hs,
-                       bucket_ids, len, off, idx, res_ids, N, Ncap, B, id_bits, lo, hi, slack, W, n_sink, n_recent, n_res);
-    return;
+  // One launch where it has room for a workgroup per compute unit at most, or two where each holds as much as it can.
+  if (N <= kDirectKeys && B <= kDirectBuckets) {
+    auto direct = [&](auto rounds, int most) {
+      constexpr int R = decltype(rounds)::value;
+      const long long parts = std::max(1, (hi - lo + kDirectThreads * R - 1) / (kDirectThreads * R));
+      const size_t lds = next_bytes + kDirectWaves * wave_bytes + (parts > 1 ? 2 * next_bytes : 0);
+      if ((parts > 1 && units * parts > most) || !allow_lds<order_direct_kernel<R>>(lds)) return false;
+      hipLaunchKernelGGL(order_direct_kernel<R>, dim3((unsigned)units, (unsigned)parts), dim3(kDirectThreads), lds, hs, bucket_ids, len, off,
+                         idx, res_ids, N, Ncap, B, id_bits, lo, hi, slack, W, n_sink, n_recent, n_res);
+      return true;
+    };
+    const int cus = device_cus();
+    if (hi - lo <= kDirectThreads * 4 && direct(std::integral_constant<int, 4>{}, cus)) return;
+    if (direct(std::integral_constant<int, 8>{}, cus) || direct(std::integral_constant<int, 16>{}, 2 * cus)) return;
   }
   const int n_slices = (N + kSlice - 1) / kSlice, lstride = windowed ? B + 1 : B;
   hipLaunchKernelGGL(hist_kernel, dim3(n_slices, (unsigned)units), dim3(256), next_bytes, hs, bucket_ids, slice_hist, N, B, n_slices,
