@@ -95,16 +95,16 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // pass fetches the last slab again and stores it into the idle buffer), which keeps them out of
   // control flow; behind a branch the compiler parked them in scratch memory and waited for every
   // load right after issuing it.
-  typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
+  // Rows past the last centroid are read as zeros (what a buffer load gives beyond the buffer's end): they score 0, and a padded
+  // winner is re-scored (id >= B below).  With centroid 0 in their place every key of bucket 0 had two equal best scores and was
+  // re-scored too (2 heads of 2082 keys, 48 buckets: re-scoring 11.5 us, 4.9 now).  A loop without the rows' 64-bit addresses is
+  // the faster one besides: 8 heads of 131072 keys, 1024 buckets, 257 -> 251 us.
   u32x4_t stage[kSlab / 16];
+  const __amdgpu_buffer_rsrc_t rows_of_c = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(cu), 0, (int)((unsigned)B * (kD * 2)), 0x00027000);
   auto fetch = [&](int t) {
 #pragma unroll
-    for (int i = 0; i < kSlab / 16; ++i) {
-      const int piece = tid + i * 256, r = piece >> 4, pc = piece & 15;
-      int b = t * kSlab + r;
-      if (b >= B) b = 0;   // padding repeats centroid 0; a padded winner is re-scored (id >= B below)
-      stage[i] = *reinterpret_cast<const u32x4_t*>(cu + (size_t)b * kD + pc * 8);
-    }
+    for (int i = 0; i < kSlab / 16; ++i)
+      stage[i] = __builtin_amdgcn_raw_buffer_load_b128(rows_of_c, (int)((unsigned)t * (kSlab * kD * 2) + (tid + i * 256) * 16), 0, 0);
   };
   float norm2 = 0.f;                             // NORMS: the largest squared norm of the rows that the thread's row of lanes has stored
   auto stash = [&](int buf) {
@@ -398,6 +398,8 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
   const int h = blockIdx.x;
   const float norm = cmax[h];
   const unsigned n_rows = counters[h];
+  unsigned total = 0;                                    // of all heads' lists, for the last workgroup to leave
+  for (int i = tid; i < Hkv; i += kRescoreThreads) total += counters[i];
   const unsigned n_groups = (n_rows + kGroupKeys - 1) / kGroupKeys;
   rows += (size_t)h * list_cap;
   const bf16_t* cu = cent + (size_t)h * B * kD;
@@ -514,7 +516,10 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
       for (int k = 0; k < kKeepTiles; ++k) tile_load(min(wave_t + k * kRescoreWaves, n_tiles - 1), a[k]);
       __builtin_amdgcn_sched_barrier(0);     // left alone the compiler keeps three or four loads in flight
 #pragma unroll
-      for (int k = 0; k < kKeepTiles; ++k) kept[k] = tile_product(a[k]);
+      for (int k = 0; k < kKeepTiles; ++k) {
+        kept[k] = (f32x16_t){0};
+        if (wave_t + k * kRescoreWaves < n_tiles) kept[k] = tile_product(a[k]);
+      }
     }
 #pragma unroll
     for (int k = 0; k < kKeepTiles; ++k) add_bias(kept[k], min(wave_t + k * kRescoreWaves, n_tiles - 1));
@@ -614,11 +619,7 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
   if (tid == 0) s_flag = atomicAdd(counters + Hkv, 1u) == gridDim.x * gridDim.y - 1 ? 1 : 0;
   __syncthreads();
   if (s_flag) {
-    unsigned total = 0;
-    for (int i = tid; i < Hkv; i += kRescoreThreads) {
-      total += __hip_atomic_load(counters + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      counters[i] = 0u;
-    }
+    for (int i = tid; i < Hkv; i += kRescoreThreads) counters[i] = 0u;
     if (tid == 0) {
       *stat = 0u;
       counters[Hkv] = 0u;

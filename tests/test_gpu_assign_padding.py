@@ -1,0 +1,47 @@
+"""Numbers of centroids that leave rows of the last slab empty: keys that score below zero everywhere (what an empty row would win), keys
+of the first and of the last bucket, with and without biases; and the centroid step where buckets are long."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_08246_amd as saap
+from oracle import ref
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("B", [1, 2, 16, 31, 33, 63, 64, 65, 80, 127, 1000])
+@pytest.mark.parametrize("kind", ["any", "below", "first", "last", "zero"])
+@pytest.mark.parametrize("biased", [False, True])
+def test_empty_rows_of_the_last_slab(B, kind, biased):
+    g = torch.Generator().manual_seed(B)
+    S, Hkv, N = 2, 2, 300
+    c = torch.randn(Hkv, B, 128, generator=g) + 1.0
+    x = torch.randn(S, Hkv, N, 128, generator=g)
+    if kind == "below":
+        x = x * 0.5 - 2.0
+    if kind in ("first", "last"):
+        x = 0.3 * x + 5 * c[None, :, [0 if kind == "first" else B - 1]]
+    if kind == "zero":
+        x = x * 0
+    x, c = x.to(torch.bfloat16), c.to(torch.bfloat16)
+    bias = torch.randn(Hkv, B, generator=g) * 3 - 40 if biased else None
+    want = ref.assign_keys(x.float().numpy(), c.float().numpy(), None if bias is None else bias.numpy())
+    got = saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV)).cpu().numpy()
+    assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("lens", [[0, 1, 15, 16, 17], [127, 128, 129, 0, 255], [256, 257, 96, 500, 3], [700, 64, 65, 63, 1024]])
+def test_centroid_step_of_long_buckets(lens):
+    """fp32 sums of bfloat16 values in a fixed order: 1e-6 of the rows' scale, and the result's own rounding to bfloat16."""
+    B, N = len(lens), sum(lens)
+    ids = torch.from_numpy(np.random.default_rng(N).permutation(np.repeat(np.arange(B), lens)).astype(np.int32)).view(1, 1, N)
+    x = torch.randn(1, 1, N, 128, generator=torch.Generator().manual_seed(N)).to(torch.bfloat16)
+    old = torch.randn(1, B, 128, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    new = saap.update_centroids_from_ids(x.to(DEV), ids.to(DEV), old.to(DEV), normalize=False)
+    new = new.cpu().double()[0]
+    for b in range(B):
+        rows = x[0, 0][ids[0, 0] == b].double()
+        want = rows.mean(0) if lens[b] else old[0, b].double()
+        assert ((new[b] - want).abs() <= 2.0 ** -8 * want.abs() + 1e-6).all(), b
