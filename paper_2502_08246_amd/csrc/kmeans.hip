@@ -14,8 +14,12 @@ namespace saap {
 namespace {
 
 // idx: null (x grouped by bucket) or [S,Hkv,Ncap], the row of each slot.
-template <typename T, bool GATHER>
-__global__ void __launch_bounds__(256)
+// DEEP rows of a 16-lane group in flight: four where a bucket is a round or two of them (eight workgroups per compute unit: 8 heads of
+// 65536 keys, 1024 buckets, 27 us; 30 with eight), eight for longer ones, whose places are then looked up a round ahead (4 heads
+// of 120000 keys, 512 buckets: 52 us with four and a look-up and the rows' loads one after the other, 36 now;
+// 8 of 4736, 16 buckets: 13.5, 9.0; 8 of 65536, 656 buckets: 27.7, 25.4).
+template <typename T, bool GATHER, int DEEP>
+__global__ void __launch_bounds__(256, DEEP > 4 ? 4 : 8)
 centroid_update_kernel(const T* __restrict__ x, const int32_t* __restrict__ idx, const int32_t* __restrict__ off, const int32_t* __restrict__ len,
                        const T* __restrict__ cent_old, T* __restrict__ cent_new, int S, int Hkv, int Ncap, int B,
                        int normalize) {
@@ -33,19 +37,23 @@ centroid_update_kernel(const T* __restrict__ x, const int32_t* __restrict__ idx,
     count += n;
     const T* rows = x + (GATHER ? unit * Ncap : unit * Ncap + first) * kD + sub * 8;
     const int32_t* ix = GATHER ? idx + unit * Ncap + first : nullptr;
-    constexpr int kDeep = 4;                             // rows of a 16-lane group in flight
-    for (int r = grp; r < n; r += 16 * kDeep) {
-      int at[kDeep];
+    int at[DEEP];
+    auto look_up = [&](int r) {
 #pragma unroll
-      for (int u = 0; u < kDeep; ++u) {
+      for (int u = 0; u < DEEP; ++u) {
         at[u] = min(r + 16 * u, n - 1);
         if constexpr (GATHER) at[u] = ix[at[u]];
       }
-      Vec8<T> v[kDeep];
+    };
+    if (DEEP > 4 && n > 0) look_up(grp);
+    for (int r = grp; r < n; r += 16 * DEEP) {
+      if (DEEP == 4) look_up(r);
+      Vec8<T> v[DEEP];
 #pragma unroll
-      for (int u = 0; u < kDeep; ++u) v[u].load(rows + (size_t)at[u] * kD);
+      for (int u = 0; u < DEEP; ++u) v[u].load(rows + (size_t)at[u] * kD);
+      if (DEEP > 4) look_up(r + 16 * DEEP);
 #pragma unroll
-      for (int u = 0; u < kDeep; ++u) {
+      for (int u = 0; u < DEEP; ++u) {
         float f[8];
         v[u].to_float(f);
         const bool in = r + 16 * u < n;
@@ -87,8 +95,12 @@ centroid_update_kernel(const T* __restrict__ x, const int32_t* __restrict__ idx,
 template <typename T, bool GATHER>
 void launch_update(const void* x, const int32_t* idx, const int32_t* off, const int32_t* len, const void* cent_old, void* cent_new,
                    int S, int Hkv, int Ncap, int B, int normalize, hipStream_t hs) {
-  hipLaunchKernelGGL((centroid_update_kernel<T, GATHER>), dim3((unsigned)B, (unsigned)Hkv), dim3(256), 0, hs, static_cast<const T*>(x),
-                     idx, off, len, static_cast<const T*>(cent_old), static_cast<T*>(cent_new), S, Hkv, Ncap, B, normalize);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)B, (unsigned)Hkv), dim3(256), 0, hs, static_cast<const T*>(x), idx, off, len,
+                       static_cast<const T*>(cent_old), static_cast<T*>(cent_new), S, Hkv, Ncap, B, normalize);
+  };
+  if (sizeof(T) == 2 && Ncap >= 96ll * B) launch(centroid_update_kernel<T, GATHER, sizeof(T) == 2 ? 8 : 4>);
+  else launch(centroid_update_kernel<T, GATHER, 4>);
 }
 
 size_t align16(size_t n) { return (n + 15) & ~(size_t)15; }
