@@ -341,6 +341,7 @@ mlp_out_rows_kernel(const bf16_t* __restrict__ planes, const bf16_t* __restrict_
   constexpr int NT = WM * WN * 64, BM = 32 * WM, BN = 32 * WN * TN;
   constexpr int kPieces = kRowsChunk / 8;                                          // 16-byte pieces of a row and chunk
   constexpr int HL = 3 * BM * kPieces / NT, WL = BN * kPieces / NT;                // loads per thread and chunk
+  static_assert(HL * NT == 3 * BM * kPieces && WL * NT == BN * kPieces, "the same loads for every thread");
   constexpr int kBuf = (3 * BM + BN) * kRowsPitch;                                 // elements of one LDS buffer
   extern __shared__ __align__(16) unsigned char smem[];
   bf16_t* s_all = reinterpret_cast<bf16_t*>(smem);     // [2][ 3 planes of h: [BM][pitch] | W2: [BN][pitch] ]
@@ -603,7 +604,10 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
   if (!fs && sh.rows_per_set >= kManyRows) {
     hipLaunchKernelGGL(mlp_hidden_bf16_kernel<HIDDEN_PLANES>, g1, dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
                        static_cast<const bf16_t*>(W1), b1, hbuf, sh);
-    // 128 x 128 tiles once they fill the compute units, 64 x 64 before
+    // Tiles of 128 x 128 and 64 x 128 (as many waves, half the products) run one to a compute unit, a round of the former takes twice the
+    // time; 64 x 64 before every other compute unit has a tile.  8 weight sets, 512 units: 512 rows, 1024 buckets 20.2, 22.3 and 26.7 us
+    // (one round, two, two), 552 rows, 880 buckets 30.4, 21.1 and 25.4 (two, two, two of two to a compute unit); 1264 rows, 128 buckets,
+    // 256 units 11.7, 8.6 and 9.8; 240 rows, 496 buckets, 416 units 15.2, 10.4 and 10.1.
     auto tiles = [&](int bm, int bn) { return (long long)((sh.rows_per_set + bm - 1) / bm) * ((B + bn - 1) / bn) * Hw; };
     auto launch_rows = [&](auto wm, auto wn, auto tn) -> int32_t {
       constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TN = decltype(tn)::value;
@@ -621,7 +625,9 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
     typedef std::integral_constant<int, 1> one;
     typedef std::integral_constant<int, 2> two;
     typedef std::integral_constant<int, 4> four;
-    if (tiles(128, 128) >= device_cus()) return launch_rows(four{}, two{}, two{});
+    auto rounds = [&](int bm, int bn) { return (tiles(bm, bn) + device_cus() - 1) / device_cus(); };
+    if (2 * rounds(128, 128) <= rounds(64, 128)) return launch_rows(four{}, two{}, two{});
+    if (2 * tiles(64, 128) > device_cus()) return launch_rows(two{}, four{}, one{});
     return launch_rows(two{}, two{}, one{});
   }
   hipLaunchKernelGGL(mlp_hidden_bf16_kernel<HIDDEN_F32>, g1, dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
