@@ -5,26 +5,29 @@
 // bytes the decode attention reads per key.
 //   scale = 2^e, e the smallest integer with max|x| <= 448 * 2^e (1 for an all-zero unit)
 //   code  = round-to-nearest-even of x / scale (the chip's v_cvt_pk_fp8_f32)
-// Three launches for K and V together: per-unit maxima (atomic max on the bit pattern, which
-// orders non-negative floats), the conversion, and clearing the maxima again.
+// Two launches for K and V together: per-unit maxima (atomic max on the bit pattern, which orders non-negative floats, one per
+// workgroup), and the conversion, whose last workgroup of a unit clears its maximum again.
+#include <algorithm>
+
 #include "common.h"
 
 namespace saap {
 namespace {
 
 constexpr int kQThreads = 256;
-constexpr int kQSlices = 64;      // workgroups per (tensor, unit) in both passes
+constexpr int kQSlices = 64;      // workgroups per (tensor, unit) in both passes, at least (gridDim.x)
 constexpr int kQUnroll = 4;       // 16-byte (bf16) loads a thread has in flight
 
 template <typename T>
 __global__ void __launch_bounds__(kQThreads)
 absmax_kernel(const T* __restrict__ K, const T* __restrict__ V, unsigned* __restrict__ amax_bits, size_t pieces,
-              int units) {
+              int units, int stride) {
+  __shared__ float s_m[kQThreads / 64];
   const int unit = blockIdx.y, tensor = blockIdx.z;
   const T* x = (tensor ? V : K) + (size_t)unit * pieces * 8;
   float m = 0.f;
   // four loads in flight per thread (a piece past the end reads the last one again: the maximum does not change)
-  const size_t step = (size_t)kQSlices * kQThreads;
+  const size_t step = (size_t)gridDim.x * kQThreads;
   for (size_t i = (size_t)blockIdx.x * kQThreads + threadIdx.x; i < pieces; i += kQUnroll * step) {
     Vec8<T> v[kQUnroll];
 #pragma unroll
@@ -37,9 +40,13 @@ absmax_kernel(const T* __restrict__ K, const T* __restrict__ V, unsigned* __rest
       for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(f[e]));
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) atomicMax(&amax_bits[tensor * units + unit], __float_as_uint(m));
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+  __syncthreads();
+  // A line of its own for every unit, where there is room, and one update per workgroup: updates of a line wait for each other
+  // (2 units of 2466 rows: 14.0 us with one per wave in neighbouring words, 3.4 now; 8 of 6027: 51, 6.5).
+  if (threadIdx.x == 0)
+    atomicMax(&amax_bits[(size_t)(tensor * units + unit) * stride], __float_as_uint(fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]))));
 }
 
 // 2^e with the smallest e such that amax <= 448 * 2^e; 448 = 0.875 * 2^9
@@ -53,20 +60,33 @@ __device__ __forceinline__ int unit_exponent(float amax) {
 template <typename T>
 __global__ void __launch_bounds__(kQThreads)
 quantize_kernel(const T* __restrict__ K, const T* __restrict__ V, uint8_t* __restrict__ K8, uint8_t* __restrict__ V8,
-                const unsigned* __restrict__ amax_bits, float* __restrict__ kscale, float* __restrict__ vscale,
-                size_t pieces, int units) {
+                unsigned* __restrict__ amax_bits, float* __restrict__ kscale, float* __restrict__ vscale,
+                size_t pieces, int units, int stride) {
   const int unit = blockIdx.y, tensor = blockIdx.z;
   const T* x = (tensor ? V : K) + (size_t)unit * pieces * 8;
   uint2* y = reinterpret_cast<uint2*>((tensor ? V8 : K8) + (size_t)unit * pieces * 8);
-  const float amax = __uint_as_float(amax_bits[tensor * units + unit]);
+  unsigned* const word = amax_bits + (size_t)(tensor * units + unit) * stride;       // the maximum, and workgroups that have read it
+  __shared__ float s_amax;
+  const size_t step = (size_t)gridDim.x * kQThreads, first = (size_t)blockIdx.x * kQThreads + threadIdx.x;
+  Vec8<T> v[kQUnroll];
+  auto load = [&](size_t i) {
+#pragma unroll
+    for (int u = 0; u < kQUnroll; ++u) v[u].load_stream(x + min(i + u * step, pieces - 1) * 8);
+  };
+  // One thread reads the maximum, for all of them, while the first rows are on their way, and counts the workgroup; the answer is not
+  // waited for until the rows are done.  The last workgroup of the unit to have read it clears it for the next call (a launch that
+  // clears takes 4 us).
+  if (threadIdx.x == 0) s_amax = __uint_as_float(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  load(first);
+  __syncthreads();
+  const float amax = s_amax;
+  unsigned before = 0u;
+  if (stride > 1 && threadIdx.x == 0) before = __hip_atomic_fetch_add(word + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int e = amax > 0.f ? unit_exponent(amax) : 0;
   const float inv = ldexpf(1.f, -e);
   if (blockIdx.x == 0 && threadIdx.x == 0) (tensor ? vscale : kscale)[unit] = ldexpf(1.f, e);
-  const size_t step = (size_t)kQSlices * kQThreads;
-  for (size_t i = (size_t)blockIdx.x * kQThreads + threadIdx.x; i < pieces; i += kQUnroll * step) {
-    Vec8<T> v[kQUnroll];
-#pragma unroll
-    for (int u = 0; u < kQUnroll; ++u) v[u].load_stream(x + min(i + u * step, pieces - 1) * 8);
+  for (size_t i = first; i < pieces; i += kQUnroll * step) {
+    if (i != first) load(i);
 #pragma unroll
     for (int u = 0; u < kQUnroll; ++u) {
       float f[8];
@@ -78,6 +98,10 @@ quantize_kernel(const T* __restrict__ K, const T* __restrict__ V, uint8_t* __res
       hi = __builtin_amdgcn_cvt_pk_fp8_f32(f[6] * inv, f[7] * inv, hi, true);
       if (i + u * step < pieces) y[i + u * step] = make_uint2((unsigned)lo, (unsigned)hi);
     }
+  }
+  if (stride > 1 && threadIdx.x == 0 && before == gridDim.x - 1) {
+    __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(word + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -105,21 +129,29 @@ extern "C" int32_t saap_quantize_kv(const void* Ksorted, const void* Vsorted, ui
   if (units > 65535 || 2 * units * sizeof(unsigned) > SAAP_WS_HEADER_BYTES) return SAAP_UNSUPPORTED;
   if (ws_bytes < SAAP_WS_HEADER_BYTES) return SAAP_WORKSPACE_TOO_SMALL;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  unsigned* amax_bits = reinterpret_cast<unsigned*>(ws);   // header words [2 * units], zero on entry and on exit
+  unsigned* amax_bits = reinterpret_cast<unsigned*>(ws);   // header words, zero on entry and on exit
+  // words between the maxima of two units: a line of 64 bytes, or two (the maximum and the count of its readers); with more units than
+  // that the maxima alone, cleared by a launch
+  auto fits = [&](int words) { return 2 * units * words * (long long)sizeof(unsigned) <= SAAP_WS_HEADER_BYTES; };
+  const int stride = fits(16) ? 16 : fits(2) ? 2 : 1;
   const size_t pieces = (size_t)Ncap * kD / 8;
-  const dim3 grid(kQSlices, (unsigned)units, 2);
+  // Four workgroups per compute unit where a few units have rows for them (one head of 139264 rows: 87 us with 64 workgroups to a
+  // tensor, 48 with 512).
+  const long long filling = 2LL * device_cus() / units, with_work = (long long)(pieces / (kQThreads * kQUnroll));
+  const dim3 grid((unsigned)std::max<long long>(kQSlices, std::min(filling, with_work)), (unsigned)units, 2);
   if (dtype == SAAP_BF16) {
     hipLaunchKernelGGL(absmax_kernel<bf16_t>, grid, dim3(kQThreads), 0, hs, static_cast<const bf16_t*>(Ksorted),
-                       static_cast<const bf16_t*>(Vsorted), amax_bits, pieces, (int)units);
+                       static_cast<const bf16_t*>(Vsorted), amax_bits, pieces, (int)units, stride);
     hipLaunchKernelGGL(quantize_kernel<bf16_t>, grid, dim3(kQThreads), 0, hs, static_cast<const bf16_t*>(Ksorted),
-                       static_cast<const bf16_t*>(Vsorted), K8, V8, amax_bits, kscale, vscale, pieces, (int)units);
+                       static_cast<const bf16_t*>(Vsorted), K8, V8, amax_bits, kscale, vscale, pieces, (int)units, stride);
   } else {
     hipLaunchKernelGGL(absmax_kernel<float>, grid, dim3(kQThreads), 0, hs, static_cast<const float*>(Ksorted),
-                       static_cast<const float*>(Vsorted), amax_bits, pieces, (int)units);
+                       static_cast<const float*>(Vsorted), amax_bits, pieces, (int)units, stride);
     hipLaunchKernelGGL(quantize_kernel<float>, grid, dim3(kQThreads), 0, hs, static_cast<const float*>(Ksorted),
-                       static_cast<const float*>(Vsorted), K8, V8, amax_bits, kscale, vscale, pieces, (int)units);
+                       static_cast<const float*>(Vsorted), K8, V8, amax_bits, kscale, vscale, pieces, (int)units, stride);
   }
-  hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((2 * units + 255) / 256)), dim3(256), 0, hs, amax_bits,
+  if (stride == 1)
+    hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((2 * units + 255) / 256)), dim3(256), 0, hs, amax_bits,
                      (int)(2 * units));
   return launch_status();
 }
