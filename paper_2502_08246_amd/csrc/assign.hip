@@ -13,7 +13,7 @@
 //     bound is scored again, 32 such keys of a head at a time: one more matrix-core pass (two
 //     beyond 1024 buckets) finds every centroid within the bound of the key's maximum, and only
 //     those (typically two) are scored in double precision.
-//   * fp32 inputs: a plain double-precision kernel scores every key against every centroid.
+//   * fp32 inputs: the same with fp32 matrix instructions, close keys scored by the workgroup that found them.
 // No score matrix is ever written to memory.
 #include "common.h"
 
@@ -267,7 +267,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
       flagged[(size_t)h * list_cap + s_list_base + slot[rt]] = (int32_t)((size_t)unit * N + row_base + rt * 32 + col);
 }
 
-// fp32 inputs: double-precision scoring of every key against every centroid (in-order sum,
+// fp32 inputs, few keys: double-precision scoring of every key against every centroid (in-order sum,
 // lowest id on ties).  One workgroup per key, grid-stride.
 __global__ void __launch_bounds__(256)
 assign_exact_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, const float* __restrict__ bias,
@@ -630,6 +630,231 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
   SAAP_TRACE(6);
 }
 
+// fp32 inputs.  Scores on the fp32 matrix instructions: 128 keys to a workgroup, 32 of them in a wave's registers, centroids
+// through LDS in tiles of 32 rows.  A lane has 16 scores of its key per tile and keeps the best, its id and the second best.  Keys whose two are closer
+// than the scores' error take a second walk over the tiles, which lists the centroids within the error of the best; those are
+// scored in double precision, one to a thread, which defines the result (in-order sums, lowest id on ties).  Keys with a score that
+// does not compare, with norms out of the ordinary, or of a workgroup that lists too many, are scored against every centroid.
+// (8 heads of 3815 keys, 96 centroids: 189 us with every key scored so, 16.5 now; one head of 8000, 240 centroids: 122,
+// 31; 8 of 8192, 256: 974, 53.)
+constexpr int kF32Keys = 128, kF32Pitch = kD + 4;        // floats per LDS row (conflict-free 16-byte reads)
+constexpr int kF32Cand = 1024;
+__global__ void __launch_bounds__(256, 2)
+assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, const float* __restrict__ bias,
+                  int32_t* __restrict__ ids, int Hkv, int N, int B, float tol) {
+  typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+  __shared__ __align__(16) float s_c[2][kCentTile * kF32Pitch];
+  __shared__ float s_norm2[4];
+  __shared__ unsigned s_close, s_odd, s_ncand;
+  __shared__ int s_list[kF32Keys];                       // keys that are scored against every centroid
+  __shared__ int s_cand[kF32Cand];                       // key of the workgroup << 24 | centroid
+  __shared__ unsigned long long s_cscore[kF32Cand], s_kbest[kF32Keys];
+  __shared__ int s_kid[kF32Keys];
+  double* const s_x = reinterpret_cast<double*>(s_cscore);               // [kD]; a key at a time against every centroid
+  double* const s_best = s_x + kD;                                       // [256]
+  int* const s_id = s_cand;                                              // [256]
+  static_assert(kF32Cand >= kD + 256, "room for them");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int unit = blockIdx.y, h = unit % Hkv;
+  const int col = lane & 31, half = lane >> 5;
+  const float* cu = cent + (size_t)h * B * kD;
+  const float* bu = bias ? bias + (size_t)h * B : nullptr;
+  const int row = blockIdx.x * kF32Keys + wave * 32 + col;
+  // the lane's features 8 g + 4 half .. + 3 of its key: the four k of matrix instructions 4 g .. 4 g + 3
+  float4 xb[16];
+  {
+    const float* xr = x + ((size_t)unit * N + min(row, N - 1)) * kD + 4 * half;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) xb[g] = *reinterpret_cast<const float4*>(xr + 8 * g);
+  }
+  // rows past the last centroid repeat it and do not count
+  float4 stage[4];
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = tid + 256 * i;
+      stage[i] = *reinterpret_cast<const float4*>(cu + (size_t)min(t * kCentTile + (p >> 5), B - 1) * kD + (p & 31) * 4);
+    }
+  };
+  auto square = [](const float4& v) { return fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w))); };
+  float norm2 = 0.f;
+  auto stash = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = tid + 256 * i;
+      *reinterpret_cast<float4*>(&s_c[buf][(p >> 5) * kF32Pitch + (p & 31) * 4]) = stage[i];
+      const float q = sum16(square(stage[i]));
+      norm2 = fmaxf(norm2, q + __shfl_xor(q, 16));
+    }
+  };
+  const int n_tiles = (B + kCentTile - 1) / kCentTile;
+  // f(score, centroid) for the lane's scores, tile by tile; rows past the last centroid are left out
+  auto walk = [&](auto f) {
+    fetch(0);
+    stash(0);
+    fetch(min(1, n_tiles - 1));
+    __syncthreads();
+    for (int t = 0; t < n_tiles; ++t) {
+      f32x16_t acc = {0};
+      const float* c = &s_c[t & 1][col * kF32Pitch + 4 * half];
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        const float4 a = *reinterpret_cast<const float4*>(c + 8 * g);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, xb[g].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, xb[g].y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, xb[g].z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, xb[g].w, acc, 0, 0, 0);
+      }
+      stash((t + 1) & 1);
+      fetch(min(t + 2, n_tiles - 1));
+      // register r: centroid 8*(r/4) + 4*half + r%4 of the tile
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int b = t * kCentTile + 8 * (r / 4) + 4 * half + (r % 4);
+        if (b < B) f(bu ? acc[r] + bu[b] : acc[r], b);
+      }
+      __syncthreads();
+    }
+  };
+  float xn2 = 0.f, xmax = 0.f;
+#pragma unroll
+  for (int g = 0; g < 16; ++g) {
+    xn2 += square(xb[g]);
+    xmax = fmaxf(fmaxf(xmax, fmaxf(fabsf(xb[g].x), fabsf(xb[g].y))), fmaxf(fabsf(xb[g].z), fabsf(xb[g].w)));
+  }
+  xn2 += __shfl_xor(xn2, 32);
+  xmax = fmaxf(xmax, __shfl_xor(xmax, 32));
+  if (tid == 0) s_close = s_odd = s_ncand = 0u;
+  float best = -INFINITY, second = -INFINITY;
+  int id = 0;
+  bool bad = false;                                      // a score that is no number
+  walk([&](float v, int b) {
+    bad |= !(v == v);
+    second = fmaxf(second, fminf(best, v));
+    id = v > best ? b : id;
+    best = fmaxf(best, v);
+  });
+  norm2 = max_rows(norm2);
+  if (lane == 0) s_norm2[wave] = norm2;
+  __syncthreads();
+  norm2 = fmaxf(fmaxf(s_norm2[0], s_norm2[1]), fmaxf(s_norm2[2], s_norm2[3]));
+  // lanes l and l+32 hold the same key
+  const float ob = __shfl_xor(best, 32), os = __shfl_xor(second, 32);
+  const int oid = __shfl_xor(id, 32), obad = __shfl_xor((int)bad, 32);
+  second = fmaxf(fmaxf(second, os), fminf(best, ob));
+  id = ob > best || (ob == best && oid < id) ? oid : id;
+  best = fmaxf(best, ob);
+  // both scores' errors (tol), the additions of their biases, products below the smallest fp32 number
+  const float thr = tol * sqrtf(norm2) * sqrtf(xn2) + 5e-7f * fabsf(best) + 4e-36f;
+  // norms next to nothing bound nothing; but a key of zeros has its biases for scores, exactly
+  constexpr float kTiny = 1e-30f;
+  const bool odd = bad || obad != 0 || !(xn2 < INFINITY) || !(norm2 < INFINITY) || (xmax > 0.f && !(norm2 > kTiny && xn2 > kTiny));
+  const bool close = !odd && xmax > 0.f && !(best - second > thr);
+  const int key = wave * 32 + col;
+  if (row < N && B > 1 && half == 0) {
+    if (odd) s_list[atomicAdd(&s_odd, 1u)] = row;
+    else if (close) atomicAdd(&s_close, 1u);
+  }
+  if (row < N && half == 0) ids[(size_t)unit * N + row] = id;
+  if (tid < kF32Keys) {
+    s_kbest[tid] = 0ull;
+    s_kid[tid] = 0x7fffffff;
+  }
+  __syncthreads();
+  if (s_close > 0u && B > 1) {
+    const float limit = close && row < N ? best - thr : INFINITY;
+    walk([&](float v, int b) {
+      if (v >= limit) {
+        const unsigned i = atomicAdd(&s_ncand, 1u);
+        if (i < (unsigned)kF32Cand) s_cand[i] = key << 24 | b;
+      }
+    });
+    const unsigned n_cand = s_ncand;
+    if (n_cand <= (unsigned)kF32Cand) {
+      for (unsigned i = tid; i < n_cand; i += 256) {
+        const int c = s_cand[i], at = c >> 24;
+        const float* xk = x + ((size_t)unit * N + blockIdx.x * kF32Keys + at) * kD;
+        const float* ck = cu + (size_t)(c & 0xffffff) * kD;
+        double t = 0.0;
+        for (int q = 0; q < kD; q += 16) {
+          float4 a[4], w[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            a[j] = *reinterpret_cast<const float4*>(xk + q + 4 * j);
+            w[j] = *reinterpret_cast<const float4*>(ck + q + 4 * j);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            t = fma((double)a[j].x, (double)w[j].x, t);
+            t = fma((double)a[j].y, (double)w[j].y, t);
+            t = fma((double)a[j].z, (double)w[j].z, t);
+            t = fma((double)a[j].w, (double)w[j].w, t);
+          }
+        }
+        if (bu) t += (double)bu[c & 0xffffff];
+        const unsigned long long o = ordered_bits(t);
+        s_cscore[i] = o;
+        atomicMax(&s_kbest[at], o);
+      }
+      __syncthreads();
+      for (unsigned i = tid; i < n_cand; i += 256)
+        if (s_cscore[i] == s_kbest[s_cand[i] >> 24]) atomicMin(&s_kid[s_cand[i] >> 24], s_cand[i] & 0xffffff);
+      __syncthreads();
+      if (close && half == 0 && row < N) ids[(size_t)unit * N + row] = s_kid[key];       // every key's best is a candidate
+    } else if (close && half == 0 && row < N) {
+      s_list[atomicAdd(&s_odd, 1u)] = row;
+    }
+    __syncthreads();
+  }
+  const int n_listed = (int)s_odd;
+  for (int i = 0; i < n_listed; ++i) {
+    const size_t g = (size_t)unit * N + s_list[i];
+    if (tid < kD) s_x[tid] = (double)x[g * kD + tid];
+    __syncthreads();
+    double most = 0.0;
+    int most_id = -1;
+    for (int b = tid; b < B; b += 256) {
+      asm volatile("" ::: "memory");                     // hoisted out of the loop, the key's doubles would hold 256 registers
+      const float4* c = reinterpret_cast<const float4*>(cu + (size_t)b * kD);
+      double t = 0.0;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        float4 v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = c[16 * q + j];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const double* xs = s_x + 64 * q + 4 * j;
+          t = fma(xs[0], (double)v[j].x, t);
+          t = fma(xs[1], (double)v[j].y, t);
+          t = fma(xs[2], (double)v[j].z, t);
+          t = fma(xs[3], (double)v[j].w, t);
+        }
+      }
+      if (bu) t += (double)bu[b];
+      if (most_id < 0 || t > most) {
+        most = t;
+        most_id = b;
+      }
+    }
+    s_best[tid] = most;
+    s_id[tid] = most_id;
+    __syncthreads();
+    for (int n = 128; n > 0; n >>= 1) {
+      if (tid < n) {
+        const int other = s_id[tid + n], mine = s_id[tid];
+        const double o = s_best[tid + n];
+        if (other >= 0 && (mine < 0 || o > s_best[tid] || (o == s_best[tid] && other < mine))) {
+          s_best[tid] = o;
+          s_id[tid] = other;
+        }
+      }
+      __syncthreads();
+    }
+    if (tid == 0) ids[g] = s_id[0];
+  }
+}
+
 }  // namespace
 
 // header | cmax[<=4095 floats] + 1 word: keys re-scored by the last call (16 KiB) | flagged row list [rows] int32
@@ -658,10 +883,19 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const int cus = device_cus();
 
+  // fp32 accumulation of 128 products (exact ones of bf16 values, rounded ones of fp32 values): |error| <= 128 * 2^-24 * |x| |c| per
+  // score; two scores are compared, and a factor 4 of head-room covers the matrix core's internal summation order.
+  const float tol = 8.0f * 128.0f * 5.9604645e-8f;
   if (dtype == SAAP_F32) {
-    const long long grid = rows < (long long)cus * 8 ? rows : (long long)cus * 8;
-    hipLaunchKernelGGL(assign_exact_f32_kernel, dim3((unsigned)grid), dim3(256), 0, hs, static_cast<const float*>(x),
-                       static_cast<const float*>(centroids), bias, bucket_ids, rows, Hkv, N, B);
+    // A round of workgroups that each score one key exactly is the faster way for few keys: 1000 keys, 16 / 32 centroids 6.8 / 7.0 us, 7.8 /
+    // 8.2 on the matrix cores; 2000 keys, 16 / 64 centroids 7.7 / 11.6 and 7.8 / 11.2; 3000 keys, 32 centroids 13.0 and 8.4.
+    if (rows <= 8ll * cus) {
+      hipLaunchKernelGGL(assign_exact_f32_kernel, dim3((unsigned)rows), dim3(256), 0, hs, static_cast<const float*>(x),
+                         static_cast<const float*>(centroids), bias, bucket_ids, rows, Hkv, N, B);
+      return launch_status();
+    }
+    hipLaunchKernelGGL(assign_f32_kernel, dim3((unsigned)((N + kF32Keys - 1) / kF32Keys), (unsigned)units), dim3(256), 0, hs,
+                       static_cast<const float*>(x), static_cast<const float*>(centroids), bias, bucket_ids, Hkv, N, B, tol);
     return launch_status();
   }
 
@@ -671,9 +905,6 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
   int32_t* flagged = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + SAAP_WS_HEADER_BYTES + 16384);
   const bf16_t* xb = static_cast<const bf16_t*>(x);
   const bf16_t* cb = static_cast<const bf16_t*>(centroids);
-  // fp32 accumulation of 128 exact products: |error| <= 128 * 2^-24 * |x| |c| per score; two scores
-  // are compared, and a factor 4 of head-room covers the matrix core's internal summation order.
-  const float tol = 8.0f * 128.0f * 5.9604645e-8f;
   const dim3 grid((unsigned)((N + kRowsPerWg - 1) / kRowsPerWg), (unsigned)units);
   // The norms take a workgroup some 0.1 us per slab of centroids and round of workgroups (two per compute unit), a launch of their
   // own 2.5 us and, behind other work, 4.7.

@@ -14,9 +14,10 @@ DEV = "cuda:0"
 @pytest.mark.parametrize("B", [1, 2, 16, 31, 33, 63, 64, 65, 80, 127, 1000])
 @pytest.mark.parametrize("kind", ["any", "below", "first", "last", "zero"])
 @pytest.mark.parametrize("biased", [False, True])
-def test_empty_rows_of_the_last_slab(B, kind, biased):
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_empty_rows_of_the_last_slab(B, kind, biased, dtype):
     g = torch.Generator().manual_seed(B)
-    S, Hkv, N = 2, 2, 300
+    S, Hkv, N = (2, 2, 300) if dtype == torch.bfloat16 else (2, 2, 520)      # fp32: more keys than the ones scored exactly at once
     c = torch.randn(Hkv, B, 128, generator=g) + 1.0
     x = torch.randn(S, Hkv, N, 128, generator=g)
     if kind == "below":
@@ -25,7 +26,10 @@ def test_empty_rows_of_the_last_slab(B, kind, biased):
         x = 0.3 * x + 5 * c[None, :, [0 if kind == "first" else B - 1]]
     if kind == "zero":
         x = x * 0
-    x, c = x.to(torch.bfloat16), c.to(torch.bfloat16)
+    if dtype == torch.float32 and B > 2:                   # equal and nearly equal centroids
+        c[:, B // 2] = c[:, 0]
+        c[:, 1] = c[:, 0] * (1 + 2.0 ** -22)
+    x, c = x.to(dtype), c.to(dtype)
     bias = torch.randn(Hkv, B, generator=g) * 3 - 40 if biased else None
     want = ref.assign_keys(x.float().numpy(), c.float().numpy(), None if bias is None else bias.numpy())
     got = saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV)).cpu().numpy()
