@@ -746,9 +746,10 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
   best = fmaxf(best, ob);
   // both scores' errors (tol), the additions of their biases, products below the smallest fp32 number
   const float thr = tol * sqrtf(norm2) * sqrtf(xn2) + 5e-7f * fabsf(best) + 4e-36f;
-  // norms next to nothing bound nothing; but a key of zeros has its biases for scores, exactly
-  constexpr float kTiny = 1e-30f;
-  const bool odd = bad || obad != 0 || !(xn2 < INFINITY) || !(norm2 < INFINITY) || (xmax > 0.f && !(norm2 > kTiny && xn2 > kTiny));
+  // norms next to nothing bound nothing; but a key of zeros has its biases for scores, exactly; scores near the end of fp32's range
+  // (biases of infinity) may have overflowed, and no limit can be taken from them
+  constexpr float kTiny = 1e-30f, kHuge = 1e37f;
+  const bool odd = bad || obad != 0 || !(xn2 < INFINITY) || !(norm2 < INFINITY) || (xmax > 0.f && !(norm2 > kTiny && xn2 > kTiny && fabsf(best) < kHuge));
   const bool close = !odd && xmax > 0.f && !(best - second > thr);
   const int key = wave * 32 + col;
   if (row < N && B > 1 && half == 0) {

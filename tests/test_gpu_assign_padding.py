@@ -1,5 +1,5 @@
 """Numbers of centroids that leave rows of the last slab empty: keys that score below zero everywhere (what an empty row would win), keys
-of the first and of the last bucket, with and without biases; and the centroid step where buckets are long."""
+of the first and of the last bucket, with and without biases, and biases at the end of the range; and the centroid step where buckets are long."""
 import numpy as np
 import pytest
 import torch
@@ -34,6 +34,24 @@ def test_empty_rows_of_the_last_slab(B, kind, biased, dtype):
     want = ref.assign_keys(x.float().numpy(), c.float().numpy(), None if bias is None else bias.numpy())
     got = saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV)).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("N", [130, 2500])                # scored exactly at once; on the matrix cores
+@pytest.mark.parametrize("B", [16, 200])
+@pytest.mark.parametrize("kind", ["one +inf", "two +inf", "some -inf", "all -inf", "some lowest", "all lowest", "sum beyond the largest"])
+def test_fp32_biases_at_the_end_of_the_range(N, B, kind):
+    g = torch.Generator().manual_seed(N + B)
+    c, x = torch.randn(1, B, 128, generator=g), torch.randn(1, 1, N, 128, generator=g)
+    bias = torch.randn(1, B, generator=g)
+    most = torch.finfo(torch.float32).max
+    if kind == "sum beyond the largest":
+        c = c * 1e33
+        bias[0, 3], bias[0, B - 2] = most, most
+    else:
+        value = {"+inf": np.inf, "-inf": -np.inf, "lowest": -most}[kind.split()[1]]
+        bias[0, {"one": [5], "two": [B - 1, 7], "some": list(range(0, B, 3)), "all": list(range(B))}[kind.split()[0]]] = value
+    want = ref.assign_keys(x.numpy(), c.numpy(), bias.numpy())
+    assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV), bias.to(DEV)).cpu().numpy(), want)
 
 
 @pytest.mark.parametrize("lens", [[0, 1, 15, 16, 17], [127, 128, 129, 0, 255], [256, 257, 96, 500, 3], [700, 64, 65, 63, 1024]])
