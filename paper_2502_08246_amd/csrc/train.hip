@@ -871,9 +871,10 @@ adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restric
 }  // namespace
 
 // header | h [Hw,R,hidden] | z then dL/dz [Hw,R,B] | dL/da [Hw,R,hidden] | row losses [Hw,R]
-//        | batch-norm variant: pre-activations a [Hw,R,hidden] | column statistics [Hw,4,hidden]
+//        | batch-norm variant: pre-activations a [Hw,R,hidden] | column statistics [Hw,4,hidden] | [Hw,R,d], not used: the size is part
+//        of the interface
 size_t train_workspace_bytes(long long Hw, long long R, int d, int hidden, int B) {
-  return (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * R * (3 * (size_t)hidden + B + 1) * sizeof(float) +
+  return (size_t)SAAP_WS_HEADER_BYTES + (size_t)Hw * R * ((size_t)d + 3 * (size_t)hidden + B + 1) * sizeof(float) +
          (size_t)Hw * 4 * hidden * sizeof(float);
 }
 
