@@ -1775,6 +1775,20 @@ static bool narrow_shape_pays(int n_units, long long est_keys_per_unit, int G, i
   return 0.08 * stream_us > merge_us;
 }
 
+// Three workgroups per unit, two to a compute unit, where one to a unit would leave a third to a half of the compute units without any
+// (129 to 170 units on 256): a compute unit then has two thirds of a unit at most, and a unit of long buckets is shared out.  That is
+// the faster way where a compute unit's own work on a key is what takes the time: 8-bit and fp32 rows, and 16-bit rows of eight heads.
+// 16-bit rows of fewer heads come at what the memory gives either way (160 units of 3072 keys, 4 heads 44.9 us with one, 47.4 with
+// three; 1536 keys 27.2, 30.6).  The partial results take 2 to 4 us, so that short lists keep one, longer ones where a key is cheap
+// (8-bit rows, 4 heads, 136 units of 1536 keys 19.3, 19.6, 2048 keys 24.9, 24.3; bf16, 8 heads, selection inside, 168 units of 1536 keys
+// 39.8, 41.3, 2560 keys 57.0, 54.1; fp32, 4 heads, 1536 keys 73.5, 61.8).  168 units of 3072 keys: 8-bit rows, 8 heads 65.3, 47.4, 2 heads
+// 35.5, 29.5, 4 heads 33.2, 31.5; fp32, 4 heads 125.9, 104.2; bf16, 8 heads 63.7, 55.4.  136 units whose buckets differ much,
+// 8-bit rows, 4 heads, 3072 keys on average: 53.5, 41.6.
+static bool three_pay(int n_units, long long est_keys_per_unit, int G, int key_bytes) {
+  if (2LL * device_cus() / n_units != 3 || (key_bytes == 4 * kD && G != 8)) return false;
+  return est_keys_per_unit >= (key_bytes == 4 * kD || (key_bytes == 2 * kD && G == 4) ? 2560 : 1536);
+}
+
 LaunchPlan plan_launch(int n_units, long long est_keys_per_unit, long long max_keys_per_unit, int G, int nseg,
                        bool list, int B, bool has_selection, int key_bytes, bool masked = false) {
   const int kb = G == 8 ? 2 : 4;
@@ -1785,6 +1799,7 @@ LaunchPlan plan_launch(int n_units, long long est_keys_per_unit, long long max_k
   const int wgs_per_cu = env_int("SAAP_ATTN_WGS_PER_CU", threads == 256 ? 2 : 1);
   const long long chunk = (long long)(threads / 16) * kb;   // keys per workgroup batch
   long long P = plan_p(n_units, est_keys_per_unit, threads, wgs_per_cu, kb, !has_selection);
+  if (has_selection && !masked && threads == 512 && P == 1 && three_pay(n_units, est_keys_per_unit, G, key_bytes)) P = 3;
   const int force_p = env_int("SAAP_ATTN_P", 0);
   if (force_p > 0 && force_p <= kMaxP) P = force_p;
   LaunchPlan lp;
