@@ -15,6 +15,7 @@
 //     those (typically two) are scored in double precision.
 //   * fp32 inputs: the same with fp32 matrix instructions, close keys scored by the workgroup that found them.
 // No score matrix is ever written to memory.
+#include "assign_close.h"
 #include "common.h"
 
 namespace saap {
@@ -744,17 +745,11 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
   second = fmaxf(fmaxf(second, os), fminf(best, ob));
   id = ob > best || (ob == best && oid < id) ? oid : id;
   best = fmaxf(best, ob);
-  // both scores' errors (tol), the additions of their biases, products below the smallest fp32 number
-  const float thr = tol * sqrtf(norm2) * sqrtf(xn2) + 5e-7f * fabsf(best) + 4e-36f;
-  // norms next to nothing bound nothing; but a key of zeros has its biases for scores, exactly; scores near the end of fp32's range
-  // (biases of infinity) may have overflowed, and no limit can be taken from them
-  constexpr float kTiny = 1e-30f, kHuge = 1e37f;
-  const bool odd = bad || obad != 0 || !(xn2 < INFINITY) || !(norm2 < INFINITY) || (xmax > 0.f && !(norm2 > kTiny && xn2 > kTiny && fabsf(best) < kHuge));
-  const bool close = !odd && xmax > 0.f && !(best - second > thr);
+  const KeyScores ks = decide_key(best, second, bad || obad != 0, xmax, xn2, norm2, tol, row < N);
   const int key = wave * 32 + col;
-  if (row < N && B > 1 && half == 0) {
-    if (odd) s_list[atomicAdd(&s_odd, 1u)] = row;
-    else if (close) atomicAdd(&s_close, 1u);
+  if (B > 1 && half == 0) {
+    if (ks.odd) s_list[atomicAdd(&s_odd, 1u)] = row;
+    else if (ks.close) atomicAdd(&s_close, 1u);
   }
   if (row < N && half == 0) ids[(size_t)unit * N + row] = id;
   if (tid < kF32Keys) {
@@ -763,9 +758,8 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
   }
   __syncthreads();
   if (s_close > 0u && B > 1) {
-    const float limit = close && row < N ? best - thr : INFINITY;
     walk([&](float v, int b) {
-      if (v >= limit) {
+      if (ks.lists(v)) {
         const unsigned i = atomicAdd(&s_ncand, 1u);
         if (i < (unsigned)kF32Cand) s_cand[i] = key << 24 | b;
       }
@@ -801,8 +795,8 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
       for (unsigned i = tid; i < n_cand; i += 256)
         if (s_cscore[i] == s_kbest[s_cand[i] >> 24]) atomicMin(&s_kid[s_cand[i] >> 24], s_cand[i] & 0xffffff);
       __syncthreads();
-      if (close && half == 0 && row < N) ids[(size_t)unit * N + row] = s_kid[key];       // every key's best is a candidate
-    } else if (close && half == 0 && row < N) {
+      if (ks.close && half == 0) ids[(size_t)unit * N + row] = s_kid[key];       // every key's best is a candidate
+    } else if (ks.close && half == 0) {
       s_list[atomicAdd(&s_odd, 1u)] = row;
     }
     __syncthreads();
