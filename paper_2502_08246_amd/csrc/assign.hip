@@ -635,11 +635,13 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
 // through LDS in tiles of 32 rows.  A lane has 16 scores of its key per tile and keeps the best, its id and the second best.  Keys whose two are closer
 // than the scores' error take a second walk over the tiles, which lists the centroids within the error of the best; those are
 // scored in double precision, one to a thread, which defines the result (in-order sums, lowest id on ties).  Keys with a score that
-// does not compare, with norms out of the ordinary, or of a workgroup that lists too many, are scored against every centroid.
+// does not compare, with norms out of the ordinary, or of a workgroup that lists too many, are scored against every centroid, 32 at a time
+// from tiles in LDS (all keys, equal centroids: 8 heads of 3840 keys, 96 centroids 573 us with one key after the other, 108 so; 8 of
+// 8192, 256: 1081, 323; one head of 8064, 240: 778, 257, which a workgroup per key did in 114: there are 63 workgroups here).
 // (8 heads of 3815 keys, 96 centroids: 189 us with every key scored so, 16.5 now; one head of 8000, 240 centroids: 122,
 // 31; 8 of 8192, 256: 974, 53.)
 constexpr int kF32Keys = 128, kF32Pitch = kD + 4;        // floats per LDS row (conflict-free 16-byte reads)
-constexpr int kF32Cand = 1024;
+constexpr int kF32Cand = 1024, kScanKeys = 32;
 __global__ void __launch_bounds__(256, 2)
 assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, const float* __restrict__ bias,
                   int32_t* __restrict__ ids, int Hkv, int N, int B, float tol) {
@@ -651,10 +653,6 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
   __shared__ int s_cand[kF32Cand];                       // key of the workgroup << 24 | centroid
   __shared__ unsigned long long s_cscore[kF32Cand], s_kbest[kF32Keys];
   __shared__ int s_kid[kF32Keys];
-  double* const s_x = reinterpret_cast<double*>(s_cscore);               // [kD]; a key at a time against every centroid
-  double* const s_best = s_x + kD;                                       // [256]
-  int* const s_id = s_cand;                                              // [256]
-  static_assert(kF32Cand >= kD + 256, "room for them");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int unit = blockIdx.y, h = unit % Hkv;
   const int col = lane & 31, half = lane >> 5;
@@ -679,11 +677,17 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
   };
   auto square = [](const float4& v) { return fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w))); };
   float norm2 = 0.f;
-  auto stash = [&](int buf) {
+  auto store = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int p = tid + 256 * i;
       *reinterpret_cast<float4*>(&s_c[buf][(p >> 5) * kF32Pitch + (p & 31) * 4]) = stage[i];
+    }
+  };
+  auto stash = [&](int buf) {
+    store(buf);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
       const float q = sum16(square(stage[i]));
       norm2 = fmaxf(norm2, q + __shfl_xor(q, 16));
     }
@@ -801,52 +805,67 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
     }
     __syncthreads();
   }
+  // every centroid, 32 keys at a time: a thread has a centroid of the tile and four of the keys (or one, of eight)
   const int n_listed = (int)s_odd;
-  for (int i = 0; i < n_listed; ++i) {
-    const size_t g = (size_t)unit * N + s_list[i];
-    if (tid < kD) s_x[tid] = (double)x[g * kD + tid];
-    __syncthreads();
-    double most = 0.0;
-    int most_id = -1;
-    for (int b = tid; b < B; b += 256) {
-      asm volatile("" ::: "memory");                     // hoisted out of the loop, the key's doubles would hold 256 registers
-      const float4* c = reinterpret_cast<const float4*>(cu + (size_t)b * kD);
-      double t = 0.0;
+  float* const s_keys = &s_c[1][0];                      // [kScanKeys][kD]
+  static_assert(kScanKeys * kD <= kCentTile * kF32Pitch, "room for them");
+  for (int first = 0; first < n_listed; first += kScanKeys) {
+    const int n_here = min(kScanKeys, n_listed - first), slot = tid >> 5, c_of = tid & 31;
+    for (int p = tid; p < n_here * 32; p += 256)
+      *reinterpret_cast<float4*>(s_keys + p * 4) = *reinterpret_cast<const float4*>(x + ((size_t)unit * N + s_list[first + (p >> 5)]) * kD + (p & 31) * 4);
+    double most[kScanKeys / 8];
+    int most_id[kScanKeys / 8];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        float4 v[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = c[16 * q + j];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const double* xs = s_x + 64 * q + 4 * j;
-          t = fma(xs[0], (double)v[j].x, t);
-          t = fma(xs[1], (double)v[j].y, t);
-          t = fma(xs[2], (double)v[j].z, t);
-          t = fma(xs[3], (double)v[j].w, t);
-        }
-      }
-      if (bu) t += (double)bu[b];
-      if (most_id < 0 || t > most) {
-        most = t;
-        most_id = b;
-      }
+    for (int k = 0; k < kScanKeys / 8; ++k) {
+      most[k] = 0.0;
+      most_id[k] = -1;
     }
-    s_best[tid] = most;
-    s_id[tid] = most_id;
-    __syncthreads();
-    for (int n = 128; n > 0; n >>= 1) {
-      if (tid < n) {
-        const int other = s_id[tid + n], mine = s_id[tid];
-        const double o = s_best[tid + n];
-        if (other >= 0 && (mine < 0 || o > s_best[tid] || (o == s_best[tid] && other < mine))) {
-          s_best[tid] = o;
-          s_id[tid] = other;
+    fetch(0);
+    for (int t = 0; t < n_tiles; ++t) {
+      store(0);
+      fetch(min(t + 1, n_tiles - 1));
+      __syncthreads();
+      double sum[kScanKeys / 8] = {0.0};
+      auto score = [&](auto per) {                       // (a branch inside the loop would have every LDS read waited for)
+#pragma unroll 4
+        for (int q = 0; q < kD; q += 4) {
+          const float4 c = *reinterpret_cast<const float4*>(&s_c[0][c_of * kF32Pitch + q]);
+#pragma unroll
+          for (int k = 0; k < decltype(per)::value; ++k) {
+            const float4 v = *reinterpret_cast<const float4*>(s_keys + (slot + 8 * k) * kD + q);
+            sum[k] = fma((double)v.x, (double)c.x, sum[k]);
+            sum[k] = fma((double)v.y, (double)c.y, sum[k]);
+            sum[k] = fma((double)v.z, (double)c.z, sum[k]);
+            sum[k] = fma((double)v.w, (double)c.w, sum[k]);
+          }
+        }
+      };
+      if (n_here > 8) score(std::integral_constant<int, kScanKeys / 8>{});
+      else score(std::integral_constant<int, 1>{});
+      const int b = t * kCentTile + c_of;
+      const double add = bu && b < B ? (double)bu[b] : 0.0;
+#pragma unroll
+      for (int k = 0; k < kScanKeys / 8; ++k) {
+        if (bu) sum[k] += add;
+        if (b < B && (most_id[k] < 0 || sum[k] > most[k])) {
+          most[k] = sum[k];
+          most_id[k] = b;
         }
       }
       __syncthreads();
     }
-    if (tid == 0) ids[g] = s_id[0];
+#pragma unroll
+    for (int k = 0; k < kScanKeys / 8; ++k) {
+      for (int n = 16; n > 0; n >>= 1) {
+        const double o = __shfl_xor(most[k], n);
+        const int o_id = __shfl_xor(most_id[k], n);
+        if (better(o, o_id, most[k], most_id[k])) {
+          most[k] = o;
+          most_id[k] = o_id;
+        }
+      }
+      if (c_of == 0 && slot + 8 * k < n_here) ids[(size_t)unit * N + s_list[first + slot + 8 * k]] = most_id[k];
+    }
   }
 }
 

@@ -27,3 +27,28 @@ def test_close_keys_beside_infinite_scores(N, B, special):
             x[0, :, at, 7] = special
     want = ref.assign_keys(x.numpy(), c.numpy(), None)
     assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV)).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("B", [2, 33, 255, 256, 257, 600])
+@pytest.mark.parametrize("kind", ["few", "equal centroids", "zero centroids", "bias +inf", "tiny keys"])
+def test_keys_scored_against_every_centroid(B, kind):
+    """Four keys at a time: none to five of them in a workgroup, or all its keys."""
+    g = torch.Generator().manual_seed(B)
+    N = 4100
+    c, x = torch.randn(2, B, 128, generator=g), torch.randn(1, 2, N, 128, generator=g)
+    bias = None
+    if kind == "few":
+        for wg in range(N // 128):
+            x[:, :, 128 * wg:128 * wg + wg % 6] *= 1e-18   # sums of squares too small to bound anything
+        x[:, :, N - 3:] *= 1e-18
+    if kind == "equal centroids":                          # more candidates than a workgroup lists
+        c[:] = c[:, :1]
+    if kind == "zero centroids":
+        c = 0 * c
+    if kind == "bias +inf":
+        bias = torch.randn(2, B, generator=g)
+        bias[:, B // 2] = bias[:, B - 1] = np.inf
+    if kind == "tiny keys":
+        x = x * 1e-18
+    want = ref.assign_keys(x.numpy(), c.numpy(), None if bias is None else bias.numpy())
+    assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV)).cpu().numpy(), want)
