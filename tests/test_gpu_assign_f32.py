@@ -52,3 +52,18 @@ def test_keys_scored_against_every_centroid(B, kind):
         x = x * 1e-18
     want = ref.assign_keys(x.numpy(), c.numpy(), None if bias is None else bias.numpy())
     assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV)).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("close", [1, 8, 9, 127])
+def test_few_close_keys_and_many(close):
+    """Up to eight close keys of a workgroup are scored against every centroid, more of them against the centroids they list."""
+    g = torch.Generator().manual_seed(close)
+    c = torch.randn(1, 300, 128, generator=g)
+    c[:, 7] = c[:, 250] * (1 + 2.0 ** -22)
+    c[:, 77] = c[:, 250]
+    x = 0.05 * torch.randn(1, 1, 4000, 128, generator=g) + 3 * c[:, torch.arange(4000) % 70 + 8][None]
+    for wg in range(32):
+        at = torch.arange(128 * wg, min(128 * wg + close, 4000))
+        x[:, :, at] = 3 * c[:, 250] + 1e-4 * torch.randn(1, 1, len(at), 128, generator=g)
+    want = ref.assign_keys(x.numpy(), c.numpy(), None)
+    assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV)).cpu().numpy(), want)
