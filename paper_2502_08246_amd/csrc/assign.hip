@@ -269,47 +269,45 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
 }
 
 // fp32 inputs, few keys: double-precision scoring of every key against every centroid (in-order sum,
-// lowest id on ties).  One workgroup per key, grid-stride.
+// lowest id on ties).  One workgroup per key.
 __global__ void __launch_bounds__(256)
 assign_exact_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, const float* __restrict__ bias,
-                        int32_t* __restrict__ ids, long long n_rows, int Hkv, int N, int B) {
+                        int32_t* __restrict__ ids, int Hkv, int N, int B) {
   __shared__ double s_x[kD];
   __shared__ double s_best[256];
   __shared__ int s_id[256];
   const int tid = threadIdx.x;
-  for (long long g = blockIdx.x; g < n_rows; g += gridDim.x) {
-    const int h = (int)((g / N) % Hkv);
-    __syncthreads();
-    if (tid < kD) s_x[tid] = (double)x[(size_t)g * kD + tid];
-    __syncthreads();
-    double best = 0.0;
-    int best_id = -1;
-    for (int b = tid; b < B; b += blockDim.x) {
-      const float* c = cent + ((size_t)h * B + b) * kD;
-      double t = 0.0;
-      for (int j = 0; j < kD; ++j) t = fma(s_x[j], (double)c[j], t);
-      if (bias) t += (double)bias[(size_t)h * B + b];
-      if (best_id < 0 || t > best) {
-        best = t;
-        best_id = b;
-      }
+  const long long g = blockIdx.x;
+  const int h = (int)((g / N) % Hkv);
+  if (tid < kD) s_x[tid] = (double)x[(size_t)g * kD + tid];
+  __syncthreads();
+  double best = 0.0;
+  int best_id = -1;
+  for (int b = tid; b < B; b += blockDim.x) {
+    const float* c = cent + ((size_t)h * B + b) * kD;
+    double t = 0.0;
+    for (int j = 0; j < kD; ++j) t = fma(s_x[j], (double)c[j], t);
+    if (bias) t += (double)bias[(size_t)h * B + b];
+    if (best_id < 0 || t > best) {
+      best = t;
+      best_id = b;
     }
-    s_best[tid] = best;
-    s_id[tid] = best_id;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) {
-        const int oid = s_id[tid + s], mid = s_id[tid];
-        const double ob = s_best[tid + s];
-        if (oid >= 0 && (mid < 0 || ob > s_best[tid] || (ob == s_best[tid] && oid < mid))) {
-          s_best[tid] = ob;
-          s_id[tid] = oid;
-        }
-      }
-      __syncthreads();
-    }
-    if (tid == 0) ids[g] = s_id[0];
   }
+  s_best[tid] = best;
+  s_id[tid] = best_id;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (tid < s) {
+      const int oid = s_id[tid + s], mid = s_id[tid];
+      const double ob = s_best[tid + s];
+      if (oid >= 0 && (mid < 0 || ob > s_best[tid] || (ob == s_best[tid] && oid < mid))) {
+        s_best[tid] = ob;
+        s_id[tid] = oid;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) ids[g] = s_id[0];
 }
 
 // Re-scoring of the listed keys (bf16).  The keys are listed per KV head; a workgroup takes 32
@@ -907,11 +905,15 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
   // score; two scores are compared, and a factor 4 of head-room covers the matrix core's internal summation order.
   const float tol = 8.0f * 128.0f * 5.9604645e-8f;
   if (dtype == SAAP_F32) {
-    // A round of workgroups that each score one key exactly is the faster way for few keys: 1000 keys, 16 / 32 centroids 6.8 / 7.0 us, 7.8 /
-    // 8.2 on the matrix cores; 2000 keys, 16 / 64 centroids 7.7 / 11.6 and 7.8 / 11.2; 3000 keys, 32 centroids 13.0 and 8.4.
-    if (rows <= 8ll * cus) {
+    // A workgroup per key that scores it exactly, or matrix instructions for 128 keys of a (sequence, head) at a time: both take a time
+    // that grows with the centroids, the former with the keys (2048 keys, 64 / 256 / 1024 centroids 11.1 / 34 / 119 us), the latter with
+    // the rounds of two workgroups per compute unit, however few keys they hold (10.7 / 30 / 108 us a round without close keys, 16 /
+    // 45 / 162 with some).  512 sequences of 8 heads, 64 centroids: one key each 19 us exactly, 90 otherwise, four 62 and 89; 64 of 8 heads,
+    // eight keys each 19 and 15 to 20.
+    const long long wgs_of_unit = (N + kF32Keys - 1) / kF32Keys, rounds = (wgs_of_unit * units + 2 * cus - 1) / (2 * cus);
+    if (rows <= 8ll * cus * rounds) {
       hipLaunchKernelGGL(assign_exact_f32_kernel, dim3((unsigned)rows), dim3(256), 0, hs, static_cast<const float*>(x),
-                         static_cast<const float*>(centroids), bias, bucket_ids, rows, Hkv, N, B);
+                         static_cast<const float*>(centroids), bias, bucket_ids, Hkv, N, B);
       return launch_status();
     }
     hipLaunchKernelGGL(assign_f32_kernel, dim3((unsigned)((N + kF32Keys - 1) / kF32Keys), (unsigned)units), dim3(256), 0, hs,

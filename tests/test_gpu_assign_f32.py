@@ -67,3 +67,15 @@ def test_few_close_keys_and_many(close):
         x[:, :, at] = 3 * c[:, 250] + 1e-4 * torch.randn(1, 1, len(at), 128, generator=g)
     want = ref.assign_keys(x.numpy(), c.numpy(), None)
     assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV)).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("S,Hkv,N", [(512, 8, 1), (512, 8, 4), (512, 8, 5), (700, 1, 5), (700, 1, 6), (2, 1, 1024), (3, 1, 683), (1, 3, 1)])
+@pytest.mark.parametrize("B", [3, 40])
+def test_few_keys_of_many_heads(S, Hkv, N, B):
+    """Numbers of keys on both sides of the line between a workgroup per key and a workgroup per 128 keys of a head, on a device of 256
+    compute units."""
+    g = torch.Generator().manual_seed(S * N + B)
+    c, x = torch.randn(Hkv, B, 128, generator=g), torch.randn(S, Hkv, N, 128, generator=g)
+    c[:, B - 1] = c[:, 0]
+    want = ref.assign_keys(x.numpy(), c.numpy(), None)
+    assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV)).cpu().numpy(), want)
