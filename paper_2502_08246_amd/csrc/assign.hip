@@ -15,6 +15,8 @@
 //     those (typically two) are scored in double precision.
 //   * fp32 inputs: the same with fp32 matrix instructions, close keys scored by the workgroup that found them.
 // No score matrix is ever written to memory.
+#include <type_traits>
+
 #include "assign_close.h"
 #include "common.h"
 
@@ -51,8 +53,8 @@ cent_norm_kernel(const bf16_t* __restrict__ cent, float* __restrict__ cmax, int 
 }
 
 // NORMS: the workgroup makes the largest norm of its head itself, from the rows on their way to LDS, and the head's first one
-// leaves it in cmax (see the launch).
-template <bool HAS_BIAS, bool NORMS>
+// leaves it in cmax (see the launch).  RAGGED: the last slab has rows past the last centroid.
+template <bool HAS_BIAS, bool NORMS, bool RAGGED>
 __global__ void __launch_bounds__(256, 2)
 assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent, const float* __restrict__ bias,
                    float* __restrict__ cmax, int32_t* __restrict__ ids, int32_t* __restrict__ flagged,
@@ -96,10 +98,11 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // pass fetches the last slab again and stores it into the idle buffer), which keeps them out of
   // control flow; behind a branch the compiler parked them in scratch memory and waited for every
   // load right after issuing it.
-  // Rows past the last centroid are read as zeros (what a buffer load gives beyond the buffer's end): they score 0, and a padded
-  // winner is re-scored (id >= B below).  With centroid 0 in their place every key of bucket 0 had two equal best scores and was
-  // re-scored too (2 heads of 2082 keys, 48 buckets: re-scoring 11.5 us, 4.9 now).  A loop without the rows' 64-bit addresses is
-  // the faster one besides: 8 heads of 131072 keys, 1024 buckets, 257 -> 251 us.
+  // Rows past the last centroid are read as zeros (what a buffer load gives beyond the buffer's end) and do not count (track_pair).  With
+  // centroid 0 in their place every key of bucket 0 had two equal best scores and was re-scored (2 heads of 2082 keys, 48 buckets:
+  // re-scoring 11.5 us, 4.9 now); with a score of 0 every key that scores below zero everywhere (8 heads of 16384 such keys, 48 buckets
+  // 187 us in all, 24 now).  A loop without the rows' 64-bit addresses is the faster one besides: 8 heads of 131072 keys, 1024
+  // buckets, 257 -> 251 us.
   u32x4_t stage[kSlab / 16];
   const __amdgpu_buffer_rsrc_t rows_of_c = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(cu), 0, (int)((unsigned)B * (kD * 2)), 0x00027000);
   auto fetch = [&](int t) {
@@ -126,6 +129,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   __syncthreads();
 
   const uint32_t keep = 0xFFFFFFF0u;
+  constexpr float kLowest = -3.402823466e38f;
   float best[2], second[2];
   int best_tile[2];
 #pragma unroll
@@ -145,16 +149,22 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // of this lane is centroid 8*(r/4) + 4*half + r%4 of matrix tile `tile` (global tile number).
   // Two scores per step: with s <= b the second largest of {b, s, x, y} is max(s, med3(b, x, y)),
   // the largest max3(b, x, y): 2.5 vector instructions per score with the tag, not 3.
-  auto track_pair = [&](const f32x16_t& c0, const f32x16_t& c1, int tile, int r) {
+  // last: of a ragged last slab, whose rows past the last centroid score less than any other (the lowest finite value: with a tag in
+  // its place an infinity would be a NaN); one wins where no score compares, and the key is re-scored (id >= B below).
+  auto track_pair = [&](auto last, const f32x16_t& c0, const f32x16_t& c1, int tile, int r) {
     float p0[2], p1[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       float s0 = c0[r + u], s1 = c1[r + u];
+      const int b = tile * kCentTile + 8 * ((r + u) / 4) + 4 * half + ((r + u) % 4);
       if (HAS_BIAS) {
-        const int b = tile * kCentTile + 8 * ((r + u) / 4) + 4 * half + ((r + u) % 4);
         const float bv = bias[(size_t)h * B + (b < B ? b : 0)];
         s0 += bv;
         s1 += bv;
+      }
+      if constexpr (decltype(last)::value) {
+        s0 = b < B ? s0 : kLowest;
+        s1 = b < B ? s1 : kLowest;
       }
       p0[u] = __uint_as_float((__float_as_uint(s0) & keep) | (uint32_t)(r + u));
       p1[u] = __uint_as_float((__float_as_uint(s1) & keep) | (uint32_t)(r + u));
@@ -169,7 +179,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // matrix instructions, 2 x 8 passes) is paired with one register pair of ranking (ten vector
   // instructions) between scheduling fences; left alone the compiler issues all sixteen matrix
   // instructions first and the two pipes run one after the other.
-  auto step = [&](int buf, int sub, f32x16_t& n0, f32x16_t& n1, const f32x16_t& o0, const f32x16_t& o1,
+  auto step = [&](auto last, int buf, int sub, f32x16_t& n0, f32x16_t& n1, const f32x16_t& o0, const f32x16_t& o1,
                   int tile_old, bool has_new, bool has_old) {
     const float old0 = best[0], old1 = best[1];
     bf16x8_t a = a_frag(buf, sub, 0);
@@ -186,7 +196,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
         n1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[1][st], n1, 0, 0, 0);
         a = a_next;
       }
-      if (has_old) track_pair(o0, o1, tile_old, 2 * st);
+      if (has_old) track_pair(last, o0, o1, tile_old, 2 * st);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (has_old) {
@@ -195,18 +205,20 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
     }
   };
 
+  const std::false_type inner;
+  const std::integral_constant<bool, RAGGED> last;       // (rows that all count are not looked at: 254 us at 1024 buckets, 258 at 1000)
   f32x16_t a0, a1, b0 = {0}, b1 = {0};   // b0, b1: not read by the first step
-  step(0, 0, a0, a1, b0, b1, 0, true, false);
+  step(inner, 0, 0, a0, a1, b0, b1, 0, true, false);
   for (int t = 0; t < n_slabs - 1; ++t) {
     const int buf = t & 1;
-    step(buf, 1, b0, b1, a0, a1, t * 2 + 0, true, true);
+    step(inner, buf, 1, b0, b1, a0, a1, t * 2 + 0, true, true);
     stash(buf ^ 1);
     fetch(min(t + 2, n_slabs - 1));
     __syncthreads();
-    step(buf ^ 1, 0, a0, a1, b0, b1, t * 2 + 1, true, true);
+    step(inner, buf ^ 1, 0, a0, a1, b0, b1, t * 2 + 1, true, true);
   }
-  step((n_slabs - 1) & 1, 1, b0, b1, a0, a1, (n_slabs - 1) * 2 + 0, true, true);
-  step(0, 0, a0, a1, b0, b1, (n_slabs - 1) * 2 + 1, false, true);
+  step(last, (n_slabs - 1) & 1, 1, b0, b1, a0, a1, (n_slabs - 1) * 2 + 0, true, true);
+  step(last, 0, 0, a0, a1, b0, b1, (n_slabs - 1) * 2 + 1, false, true);
 
   // lanes l and l+32 own the same key: merge their candidates, lower id on equal packed scores
   __shared__ unsigned s_listed, s_list_base;
@@ -249,8 +261,8 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
     if (half == 0 && row < N) {
       const size_t g = (size_t)unit * N + row;
       ids[g] = id;
-      // error bound of the fp32 accumulation plus the 4 mantissa bits used for the register tag
-      const float thr = tol_c * sqrtf(xnorm2[rt]) + 5e-6f * fabsf(nb);
+      // error bound of the fp32 accumulation plus the 4 mantissa bits used for the register tag (of a score of zero: all that it has)
+      const float thr = tol_c * sqrtf(xnorm2[rt]) + 5e-6f * fabsf(nb) + 4e-36f;
       if (!(nb - ns > thr) || id >= B) {
         listed[rt] = true;
         slot[rt] = atomicAdd(&s_listed, 1u);
@@ -933,11 +945,14 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
   const long long rounds = ((long long)grid.x * units + 2 * cus - 1) / (2 * cus);
   const bool own_norms = rounds * ((B + kSlab - 1) / kSlab) <= 16;
   if (!own_norms) hipLaunchKernelGGL(cent_norm_kernel, dim3((unsigned)Hkv), dim3(kNormThreads), 0, hs, cb, cmax, B);
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, hs, xb, cb, bias, cmax, bucket_ids, flagged, n_flagged, list_cap, Hkv, N, B, tol);
+  auto launch = [&](auto has_bias, auto norms, auto ragged) {
+    hipLaunchKernelGGL((assign_mfma_kernel<decltype(has_bias)::value, decltype(norms)::value, decltype(ragged)::value>), grid, dim3(256), 0, hs,
+                       xb, cb, bias, cmax, bucket_ids, flagged, n_flagged, list_cap, Hkv, N, B, tol);
   };
-  if (bias) own_norms ? launch(assign_mfma_kernel<true, true>) : launch(assign_mfma_kernel<true, false>);
-  else own_norms ? launch(assign_mfma_kernel<false, true>) : launch(assign_mfma_kernel<false, false>);
+  auto as_constant = [](bool v, auto f) { v ? f(std::true_type{}) : f(std::false_type{}); };
+  as_constant(bias != nullptr, [&](auto has_bias) {
+    as_constant(own_norms, [&](auto norms) { as_constant(B % kSlab != 0, [&](auto ragged) { launch(has_bias, norms, ragged); }); });
+  });
   unsigned* stat = reinterpret_cast<unsigned*>(cmax) + 4095;
   // workgroups per head: one per compute unit over all heads together, as many as run at once (two rounds of them, most with no
   // group to score, ended 3 us later)

@@ -67,3 +67,28 @@ def test_centroid_step_of_long_buckets(lens):
         rows = x[0, 0][ids[0, 0] == b].double()
         want = rows.mean(0) if lens[b] else old[0, b].double()
         assert ((new[b] - want).abs() <= 2.0 ** -8 * want.abs() + 1e-6).all(), b
+
+
+@pytest.mark.parametrize("B", [16, 80, 1000])
+@pytest.mark.parametrize("biased", [False, True])
+def test_empty_rows_bring_no_key_to_the_second_scoring(B, biased):
+    """Keys that score below zero (or below the first centroid's bias) everywhere: only those whose best two are close are scored again,
+    as many as with the centroids of the last slab repeated up to its end."""
+    g = torch.Generator().manual_seed(B)
+    N = 3000
+    c = torch.randn(1, B, 128, generator=g) + 1.0
+    x = 0.5 * torch.randn(1, 1, N, 128, generator=g) - 2.0
+    bias = -torch.rand(1, B, generator=g) if biased else None
+    if biased:
+        bias[0, 0] = 500.0
+        x[:, :, :, 0], c[:, 0, 0] = -60.0, 60.0            # the first centroid has the largest bias and never wins
+    x, c = x.to(torch.bfloat16), c.to(torch.bfloat16)
+    want = ref.assign_keys(x.float().numpy(), c.float().numpy(), None if bias is None else bias.numpy())
+    ws = torch.zeros(65536 + 16384 + 4 * N, dtype=torch.uint8, device=DEV)
+    got = saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV), ws=ws).cpu().numpy()
+    assert np.array_equal(got, want) and (not biased or (want != 0).all())
+    again = ws[65536 + 16380:65536 + 16384].view(torch.int32).item()       # keys that the call has scored again
+    s = x[0, 0].double() @ c[0].double().T + (0.0 if bias is None else bias.double())
+    best = s.topk(2, dim=1).values
+    bound = 8 * 128 * 2.0 ** -24 * x[0, 0].double().norm(dim=1) * c[0].double().norm(dim=1).max() + 1e-5 * best.abs().amax(1)
+    assert again <= int((best[:, 0] - best[:, 1] <= 1.01 * bound).sum())
