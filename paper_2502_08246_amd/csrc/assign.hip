@@ -100,8 +100,8 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // load right after issuing it.
   // Rows past the last centroid are read as zeros (what a buffer load gives beyond the buffer's end) and do not count (track_pair).  With
   // centroid 0 in their place every key of bucket 0 had two equal best scores and was re-scored (2 heads of 2082 keys, 48 buckets:
-  // re-scoring 11.5 us, 4.9 now); with a score of 0 every key that scores below zero everywhere (8 heads of 16384 such keys, 48 buckets
-  // 187 us in all, 24 now).  A loop without the rows' 64-bit addresses is the faster one besides: 8 heads of 131072 keys, 1024
+  // re-scoring 11.5 us, 4.9 now); with a score of 0 every key that scores below zero everywhere (8 heads of 16384 such keys, 48
+  // buckets: 187 us in all, 20 now).  A loop without the rows' 64-bit addresses is the faster one besides: 8 heads of 131072 keys, 1024
   // buckets, 257 -> 251 us.
   u32x4_t stage[kSlab / 16];
   const __amdgpu_buffer_rsrc_t rows_of_c = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(cu), 0, (int)((unsigned)B * (kD * 2)), 0x00027000);
@@ -528,7 +528,8 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
       __builtin_amdgcn_sched_barrier(0);     // left alone the compiler keeps three or four loads in flight
 #pragma unroll
       for (int k = 0; k < kKeepTiles; ++k) {
-        kept[k] = (f32x16_t){0};
+        // a tile that is not there has no candidates (scores of zero would be listed, one by one, where all others are below zero)
+        kept[k] = (f32x16_t){0} - INFINITY;
         if (wave_t + k * kRescoreWaves < n_tiles) kept[k] = tile_product(a[k]);
       }
     }
