@@ -518,16 +518,22 @@ __device__ __forceinline__ void wave_best(double& best, int& best_id) {
 }
 
 // A slab's centroids that may be the key's, as exchanged between the workgroups of a unit: the largest lower bound of an exact
-// score, the centroids whose upper bound reaches it (two of n; hi[0] is the largest where there are more).
+// score, the n centroids whose upper bound reaches it.  n = 3: the best of the slab by exact scores.
 struct PushPartial {
-  float lo, hi[2];
-  int id[2], n;
+  float lo, hi0;
+  union {
+    struct { float hi1; int id0; } bounds;
+    double exact;
+  };
+  int id, n;                                     // id of the second, or of the exact best
 };
 
 // window_push: P workgroups per (sequence, KV head), each with a slab of the centroids; the last to arrive picks the bucket and does
 // the bookkeeping.  Scores are fp32 first, whole rows of 16 lanes each, with bounds on how far the exact one can be: as a rule
 // one centroid's upper bound reaches the largest lower bound of all, and that is the bucket, as double-precision scores define
-// it.  Otherwise those that do are scored exactly (all of them, if a slab has more than two).
+// it.  Otherwise those that do are scored exactly; where more than two of a slab do, the slab's workgroup scores all of its
+// centroids before it reports (equal rows, a key of zeros: 12 us a call; left to the last workgroup they took 34 us at 64 units of 1024
+// centroids, 117 at 8 of 4096).
 // Which key is displaced and where it goes does not depend on the new key's bucket: every
 // workgroup reads that state up front (the loads overlap the scoring), slab 0 copies the displaced
 // row to its bucket, and the last workgroup, which runs after all of these reads, writes the new
@@ -560,8 +566,9 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
   // goes straight into its bucket, res_ids is not touched and pos_new may be null (idx gets -2).
   __shared__ double s_x[kD];
   __shared__ __align__(16) T s_xt[kD];
-  __shared__ float s_lo[kPushThreads / 64], s_top[kPushThreads / 64], s_hi[2];
-  __shared__ int s_n, s_id[2], s_state[6], s_list[2 * 64];
+  __shared__ float s_lo[kPushThreads / 64], s_hi[2];
+  __shared__ double s_best[kPushThreads / 64];
+  __shared__ int s_n, s_id[2], s_state[6], s_list[2 * 64], s_best_id[kPushThreads / 64];
   const int slab = blockIdx.x, unit = blockIdx.y, h = unit % Hkv, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = tid & 15, grp = tid >> 4;
   SAAP_TRACE(0);
@@ -642,9 +649,11 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
   Vec8<T> xv;
   xv.load(s_xt + sub * 8);
   const float xn2 = sum16(xv.dot(xv));
-  // |fp32 score - exact score| <= 128 2^-24 |x| |c|, with head-room of four for the order of the sum, and the addition of the bias;
-  // products below the smallest fp32 number may be lost.  Norms that are themselves next to nothing bound nothing.
-  constexpr float kTol = 4.0f * 128.0f * 5.9604645e-8f, kTiny = 1e-30f;
+  // |fp32 score - exact score| <= 128 2^-24 |x| |c|, with head-room of four for the order of the sum, and the addition of the bias.
+  // Products and sums below the smallest normal fp32 number (1.2e-38, 128 of each) may be lost, from scores and from the squares of
+  // norms.
+  constexpr float kTol = 4.0f * 128.0f * 5.9604645e-8f, kLost = 4e-36f;
+  const float x_bound = kTol * sqrtf(xn2 + kLost);
   float lo = -INFINITY, top[3] = {-INFINITY, -INFINITY, -INFINITY};
   int top_id[2] = {-1, -1};
   for (int it = 0; it < cpl; ++it) {
@@ -658,10 +667,12 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
     if (it + 1 < cpl) load_rows(it + 1);
     const int b = row0 + it * kPushSlab + grp + 16 * sub;
     if (sub < kPushRows && b < B) {
-      if (bu) score += bu[b];
-      const float err = n2 > kTiny && xn2 > kTiny ? kTol * sqrtf(xn2) * sqrtf(n2) + 2.5e-7f * fabsf(score) + 2e-36f : INFINITY;
+      const float add = bu ? bu[b] : 0.f;
+      const bool never = add == -INFINITY && fabsf(score) < INFINITY;      // whatever the product is exactly
+      score += add;
+      const float err = x_bound * sqrtf(n2 + kLost) + 2.5e-7f * fabsf(score) + kLost;
       const bool known = fabsf(score) < INFINITY && err < INFINITY;        // infinities and NaN: nothing is known
-      const float up = known ? score + err : INFINITY, down = known ? score - err : -INFINITY;
+      const float up = known ? score + err : never ? -INFINITY : INFINITY, down = known ? score - err : -INFINITY;
       lo = fmaxf(lo, down);
       if (up > top[0]) {
         top[2] = top[1];
@@ -680,11 +691,8 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
   }
   SAAP_TRACE(2);
   {
-    const float wave_lo = wave_max(lo), wave_top = wave_max(top[0]);
-    if (lane == 0) {
-      s_lo[wave] = wave_lo;
-      s_top[wave] = wave_top;
-    }
+    const float wave_lo = wave_max(lo);
+    if (lane == 0) s_lo[wave] = wave_lo;
   }
   __syncthreads();
   lo = fmaxf(fmaxf(s_lo[0], s_lo[1]), fmaxf(s_lo[2], s_lo[3]));
@@ -699,19 +707,44 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
     }
   if (top_id[1] >= 0 && top[2] >= lo && top[2] > -INFINITY) atomicAdd(&s_n, 1);
   __syncthreads();
+  const int n_slab = min(s_n, 3);
+  double best = 0.0;                             // of the exact scores
+  int best_id = -1;
+  if (n_slab > 2) {
+    for (int i = tid; i < kPushSlab * cpl && row0 + i < B; i += kPushThreads) {
+      asm volatile("" ::: "memory");             // hoisted out of the loop, the key's doubles would hold 256 registers
+      double t = score_row<T>(cu + (size_t)(row0 + i) * kD, s_x);
+      if (bu) t += (double)bu[row0 + i];
+      take_better(best, best_id, t, row0 + i);
+    }
+    wave_best(best, best_id);
+    if (lane == 0) {
+      s_best[wave] = best;
+      s_best_id[wave] = best_id;
+    }
+    __syncthreads();
+  }
   if (wave != 0) return;
   SAAP_TRACE(3);
-  int n_cand = s_n, id0 = s_id[0];
+  int n_cand = n_slab;                           // listed, not scored yet
+  unsigned long long scored = 0;                 // slabs (lanes) with an exact best
+  if (n_slab > 2) {
+    n_cand = 0;
+    scored = 1ull;
+#pragma unroll
+    for (int w = 1; w < kPushThreads / 64; ++w) take_better(best, best_id, s_best[w], s_best_id[w]);
+  }
+  int id0 = n_cand > 0 ? s_id[0] : -1;
   const int id1 = n_cand > 1 ? s_id[1] : -1;
-  unsigned long long whole = n_cand > 2;         // slabs of which every centroid is scored exactly
   if (P > 1) {
     if (lane == 0) {
-      const float hi0 = n_cand > 2 ? fmaxf(fmaxf(s_top[0], s_top[1]), fmaxf(s_top[2], s_top[3])) : s_hi[0], hi1 = n_cand > 1 ? s_hi[1] : -INFINITY;
+      const float hi0 = n_cand > 0 ? s_hi[0] : -INFINITY, hi1 = n_cand > 1 ? s_hi[1] : -INFINITY;
       auto pair = [](unsigned a, unsigned b) { return (unsigned long long)b << 32 | a; };
       unsigned long long* mine = reinterpret_cast<unsigned long long*>(part + (size_t)unit * P + slab);
+      const unsigned long long middle = n_slab > 2 ? (unsigned long long)__double_as_longlong(best) : pair(__float_as_uint(hi1), (unsigned)id0);
       __hip_atomic_store(mine, pair(__float_as_uint(lo), __float_as_uint(hi0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(mine + 1, pair(__float_as_uint(hi1), (unsigned)id0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(mine + 2, pair((unsigned)id1, (unsigned)n_cand), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(mine + 1, middle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(mine + 2, pair((unsigned)(n_slab > 2 ? best_id : id1), (unsigned)n_slab), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // every load above has returned and every store has been acknowledged before the arrival counts
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -728,10 +761,12 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
     const unsigned long long q2 = __hip_atomic_load(q + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool mine = lane < P;
     const float hi0 = __uint_as_float((unsigned)(q0 >> 32)), hi1 = __uint_as_float((unsigned)q1);
-    const int n = (int)(q2 >> 32);
+    const int n = mine ? (int)(q2 >> 32) : 0;
     lo = wave_max(mine ? __uint_as_float((unsigned)q0) : -INFINITY);
-    const bool one = mine && n <= 2 && hi0 >= lo, two = mine && n == 2 && hi1 >= lo;
-    whole = __ballot(mine && n > 2 && hi0 >= lo);
+    scored = __ballot(n > 2);
+    best = __longlong_as_double((long long)q1);
+    best_id = n > 2 ? (int)(unsigned)q2 : -1;
+    const bool one = (n == 1 || n == 2) && hi0 >= lo, two = n == 2 && hi1 >= lo;
     const unsigned long long first = __ballot(one), second = __ballot(two), below = (1ull << lane) - 1ull;
     n_cand = __popcll(first) + __popcll(second);
     if (one) s_list[__popcll(first & below)] = (int)(q1 >> 32);
@@ -740,34 +775,17 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
     id0 = s_list[0];
     SAAP_TRACE(5);
     if (lane == 0) __hip_atomic_store(&counters[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    if (lane == 0) {
-      s_list[0] = id0;
-      s_list[1] = id1;
-    }
-    n_cand = whole ? 0 : n_cand;
+  } else if (lane == 0) {
+    s_list[0] = id0;
+    s_list[1] = id1;
   }
-  int best_id = id0;
-  if (whole || n_cand != 1) {                    // more than one may be the largest
+  if (scored == 0 && n_cand < 2) {
+    best_id = n_cand ? id0 : 0;                  // none: every score is -infinity, the lowest id of equal ones
+  } else {                                       // more than one may be the largest
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    double best = 0.0;
-    best_id = -1;
-    const int lists = (n_cand + 63) / 64, per_slab = kPushSlab / 64 * cpl, rounds = lists + __popcll(whole) * per_slab;
-    int from = -1;
-    for (int r = 0; r < rounds; ++r) {
-      asm volatile("" ::: "memory");             // hoisted out of the loop, the key's doubles would hold 256 registers
-      int bc = -1;
-      if (r < lists) {
-        if (64 * r + lane < n_cand) bc = s_list[64 * r + lane];
-      } else {
-        const int q = (r - lists) % per_slab;
-        if (q == 0) {                            // the next slab
-          from = (__ffsll(whole) - 1) * 64 * per_slab;
-          whole &= whole - 1ull;
-        }
-        bc = from + 64 * q + lane;
-      }
-      if (bc < 0 || bc >= B) continue;
+    for (int i = lane; i < n_cand; i += 64) {
+      asm volatile("" ::: "memory");
+      const int bc = s_list[i];
       double t = score_row<T>(cu + (size_t)bc * kD, s_x);
       if (bu) t += (double)bu[bc];
       take_better(best, best_id, t, bc);

@@ -57,3 +57,45 @@ def test_bucket_of_an_appended_key(dtype, S, Hkv, B, kind, biased):
         grown = (ln - before).cpu()
         assert flag[0].item() == 1 or torch.equal(grown.nonzero()[:, 2].view(S, Hkv), torch.from_numpy(want).long())
         ln.copy_(before)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("S,Hkv,B", [(1, 2, 100), (2, 2, 300), (64, 8, 600), (1, 2, 4100)])
+@pytest.mark.parametrize("kind", ["some masked", "all masked", "one left", "+inf", "zero key", "zero key biased", "equal rows", "masked zeros", "lowest"])
+def test_scores_that_are_known_or_equal(dtype, S, Hkv, B, kind):
+    """Biases of infinity, keys of zeros, whole slabs of equal rows: no candidate, one and many in a slab, in one slab and in all."""
+    g = torch.Generator().manual_seed(B)
+    c, x = torch.randn(Hkv, B, 128, generator=g), 3 * torch.randn(S, Hkv, 128, generator=g)
+    bias = torch.randn(Hkv, B, generator=g)
+    if kind == "some masked":
+        bias[:, ::2] = -np.inf
+    if kind in ("all masked", "one left"):
+        bias[:] = -np.inf
+    if kind == "one left":
+        bias[:, B - 3] = -5.0
+    if kind == "+inf":
+        bias[:, [B - 1, B // 2, 40]] = np.inf
+    if kind.startswith("zero key"):
+        x = 0 * x
+    if kind == "zero key":
+        bias = None
+    if kind == "equal rows":
+        c[:], bias = c[:, B // 2:B // 2 + 1].clone(), None
+    if kind == "masked zeros":
+        c[:, 7:], bias[:, ::3] = 0, -np.inf
+    if kind == "lowest":
+        bias[:] = torch.finfo(torch.float32).min
+    x, c = x.to(dtype), c.to(dtype)
+    want = ref.assign_keys(x.float().unsqueeze(2).numpy(), c.float().numpy(), None if bias is None else bias.numpy())[:, :, 0]
+    K = torch.zeros(S, Hkv, 16, 128, dtype=dtype, device=DEV)
+    off, ln, idx, Ks, Vs = saap.build_bucket_index(torch.zeros(S, Hkv, 16, dtype=torch.int32, device=DEV), K, K, B, 1)
+    x, pos = x.to(DEV), torch.full((S,), 16, dtype=torch.int32, device=DEV)
+    bias = None if bias is None else bias.to(DEV)
+    for _ in range(2):
+        before = ln.clone()
+        ids, _ = saap.append_keys(x, x, x, pos, c.to(DEV), bias, off, ln, idx, Ks, Vs)
+        assert np.array_equal(ids.cpu().numpy(), want)
+        ln.copy_(before)
+    off, ln, idx, Ks, Vs, rid = saap.build_windowed_index(torch.zeros(S, Hkv, 16, dtype=torch.int32, device=DEV), K, K, B, 1, 1, 7)
+    ids, flag = saap.window_push(x, x, x, pos, c.to(DEV), bias, off, ln, idx, Ks, Vs, rid, 1, 7)
+    assert np.array_equal(ids.cpu().numpy(), want)
