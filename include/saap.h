@@ -140,9 +140,11 @@ int32_t saap_mfma_rate_probe(const void* operands, size_t bytes, int32_t iters, 
  *   centroids  [Hkv,B,d]    dtype
  *   bias       [Hkv,B]      fp32 or NULL
  *   bucket_ids [S,Hkv,N]    int32, out
- * bf16 inputs run on the matrix cores with fp32 accumulation; rows whose best
- * two scores are closer than the accumulation error bound are re-scored in
- * double precision, so the result is the argmax defined above bit for bit.
+ * Scores come from the matrix cores with fp32 accumulation (few fp32 keys: in
+ * double precision at once); rows whose best two are closer than the
+ * accumulation error bound are re-scored in double precision, so the result is
+ * the argmax defined above bit for bit.  Where a score is not a number it is
+ * some id in [0,B), the same for the same inputs.
  */
 int32_t saap_assign_keys(const void* x, const void* centroids, const float* bias,
                          int32_t* bucket_ids,
@@ -192,8 +194,8 @@ int32_t saap_build_bucket_index_zeroed(const int32_t* bucket_ids, const void* K,
  *   new_bucket_ids [S,Hkv] int32, out
  *   overflow_flag  device int32: set to 1 if some bucket had no free slot;
  *                  that key is not stored (len unchanged), others are.
- * Workspace: SAAP_OP_APPEND_KEYS (S, Hkv, B): the centroids are scored by ceil(B/64)
- * workgroups per (sequence, head), which meet through it.
+ * Workspace: SAAP_OP_APPEND_KEYS (S, Hkv, B): the centroids are scored by up to
+ * ceil(B/128) workgroups per (sequence, head), which meet through it.
  */
 int32_t saap_append_keys(const void* x_new, const void* k_new, const void* v_new,
                          const int32_t* pos_new,

@@ -518,7 +518,7 @@ __device__ __forceinline__ void wave_best(double& best, int& best_id) {
 }
 
 // A slab's centroids that may be the key's, as exchanged between the workgroups of a unit: the largest lower bound of an exact
-// score, the n centroids whose upper bound reaches it.  n = 3: the best of the slab by exact scores.
+// score, the n centroids whose upper bound reaches it, lower id first.  n = 3: the best of the slab by exact scores.
 struct PushPartial {
   float lo, hi0;
   union {
@@ -734,11 +734,13 @@ window_push_kernel(const T* __restrict__ x_new, const T* __restrict__ k_new, con
 #pragma unroll
     for (int w = 1; w < kPushThreads / 64; ++w) take_better(best, best_id, s_best[w], s_best_id[w]);
   }
-  int id0 = n_cand > 0 ? s_id[0] : -1;
-  const int id1 = n_cand > 1 ? s_id[1] : -1;
+  // two candidates in the order of their ids, whichever came first: a score that is no number has the same outcome every time
+  const int at0 = n_cand == 2 && s_id[1] < s_id[0] ? 1 : 0;
+  int id0 = n_cand > 0 ? s_id[at0] : -1;
+  const int id1 = n_cand > 1 ? s_id[at0 ^ 1] : -1;
   if (P > 1) {
     if (lane == 0) {
-      const float hi0 = n_cand > 0 ? s_hi[0] : -INFINITY, hi1 = n_cand > 1 ? s_hi[1] : -INFINITY;
+      const float hi0 = n_cand > 0 ? s_hi[at0] : -INFINITY, hi1 = n_cand > 1 ? s_hi[at0 ^ 1] : -INFINITY;
       auto pair = [](unsigned a, unsigned b) { return (unsigned long long)b << 32 | a; };
       unsigned long long* mine = reinterpret_cast<unsigned long long*>(part + (size_t)unit * P + slab);
       const unsigned long long middle = n_slab > 2 ? (unsigned long long)__double_as_longlong(best) : pair(__float_as_uint(hi1), (unsigned)id0);

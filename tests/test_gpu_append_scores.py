@@ -99,3 +99,18 @@ def test_scores_that_are_known_or_equal(dtype, S, Hkv, B, kind):
     off, ln, idx, Ks, Vs, rid = saap.build_windowed_index(torch.zeros(S, Hkv, 16, dtype=torch.int32, device=DEV), K, K, B, 1, 1, 7)
     ids, flag = saap.window_push(x, x, x, pos, c.to(DEV), bias, off, ln, idx, Ks, Vs, rid, 1, 7)
     assert np.array_equal(ids.cpu().numpy(), want)
+
+
+def test_scores_that_are_no_numbers_have_one_outcome():
+    """The definition leaves the bucket open; the same inputs have the same one, in the range, every time."""
+    g = torch.Generator().manual_seed(0)
+    c, x = torch.randn(8, 1024, 128, generator=g), torch.randn(8, 8, 128, generator=g)
+    c[:, [5, 69, 300, 400, 401, 402]] = np.nan
+    x, c, pos = x.to(DEV), c.to(DEV), torch.full((8,), 16, dtype=torch.int32, device=DEV)
+    K = torch.zeros(8, 8, 16, 128, device=DEV)
+    off, ln, idx, Ks, Vs = saap.build_bucket_index(torch.zeros(8, 8, 16, dtype=torch.int32, device=DEV), K, K, 1024, 1)
+    before, seen = ln.clone(), []
+    for _ in range(20):
+        seen.append(saap.append_keys(x, x, x, pos, c, None, off, ln, idx, Ks, Vs)[0].clone())
+        ln.copy_(before)
+    assert all(torch.equal(s, seen[0]) for s in seen) and ((seen[0] >= 0) & (seen[0] < 1024)).all()
