@@ -6,7 +6,7 @@
 //   scale = 2^e, e the smallest integer with max|x| <= 448 * 2^e (1 for an all-zero unit)
 //   code  = round-to-nearest-even of x / scale (the chip's v_cvt_pk_fp8_f32)
 // Two launches for K and V together: per-unit maxima (atomic max on the bit pattern, which orders non-negative floats, one per
-// workgroup), and the conversion, whose last workgroup of a unit clears its maximum again.
+// workgroup), and the conversion, whose last workgroup of a unit clears its maximum again (a third launch with more than 512 units).
 #include <algorithm>
 
 #include "common.h"
@@ -15,7 +15,7 @@ namespace saap {
 namespace {
 
 constexpr int kQThreads = 256;
-constexpr int kQSlices = 64;      // workgroups per (tensor, unit) in both passes, at least (gridDim.x)
+constexpr int kQSlices = 64;      // workgroups per (tensor, unit) in both passes (gridDim.x): fewer of short units, more of a few long ones
 constexpr int kQUnroll = 4;       // 16-byte (bf16) loads a thread has in flight
 
 template <typename T>
@@ -130,15 +130,18 @@ extern "C" int32_t saap_quantize_kv(const void* Ksorted, const void* Vsorted, ui
   if (ws_bytes < SAAP_WS_HEADER_BYTES) return SAAP_WORKSPACE_TOO_SMALL;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   unsigned* amax_bits = reinterpret_cast<unsigned*>(ws);   // header words, zero on entry and on exit
-  // words between the maxima of two units: a line of 64 bytes, or two (the maximum and the count of its readers); with more units than
-  // that the maxima alone, cleared by a launch
-  auto fits = [&](int words) { return 2 * units * words * (long long)sizeof(unsigned) <= SAAP_WS_HEADER_BYTES; };
-  const int stride = fits(16) ? 16 : fits(2) ? 2 : 1;
+  // Words between the maxima of two units: a line of 64 bytes (the maximum and the count of its readers); with more units than there are
+  // lines the maxima alone, cleared by a launch of 4 us.  (Counts that share lines wait for each other: 1000 units of 1500 rows 1149 us,
+  // 365 without; 336 with fewer workgroups as well.)
+  const int stride = 2 * units * 64 <= (long long)SAAP_WS_HEADER_BYTES ? 16 : 1;
   const size_t pieces = (size_t)Ncap * kD / 8;
   // Four workgroups per compute unit where a few units have rows for them (one head of 139264 rows: 87 us with 64 workgroups to a
   // tensor, 48 with 512).
   const long long filling = 2LL * device_cus() / units, with_work = (long long)(pieces / (kQThreads * kQUnroll));
-  const dim3 grid((unsigned)std::max<long long>(kQSlices, std::min(filling, with_work)), (unsigned)units, 2);
+  // No more than have rows: a workgroup without any would read the maximum and count itself for nothing (2048 units of 54 rows: 1669 us
+  // with 64 each, 26 with two).  Many units have workgroups enough with all of their loads used.
+  const long long per_wg = stride > 1 ? kQThreads : kQThreads * kQUnroll, most = ((long long)pieces + per_wg - 1) / per_wg;
+  const dim3 grid((unsigned)std::min(most, std::max<long long>(kQSlices, std::min(filling, with_work))), (unsigned)units, 2);
   if (dtype == SAAP_BF16) {
     hipLaunchKernelGGL(absmax_kernel<bf16_t>, grid, dim3(kQThreads), 0, hs, static_cast<const bf16_t*>(Ksorted),
                        static_cast<const bf16_t*>(Vsorted), amax_bits, pieces, (int)units, stride);

@@ -22,3 +22,9 @@ def test_quantize_units(units, rows, dtype):
             want = torch.where(mx > 0, torch.exp2(torch.ceil(torch.log2(mx.double() / 448))).float(), torch.ones_like(mx))
             assert torch.equal(scale.view_as(want), want)
             assert torch.equal(codes, (x.float() / want[:, :, None, None]).to(torch.float8_e4m3fn).view(torch.uint8))
+
+
+@pytest.mark.parametrize("units,rows", [(600, 15), (600, 16), (600, 17), (1000, 64), (1000, 65), (2048, 130), (8192, 3), (64, 1040), (3, 33)])
+def test_quantize_short_units(units, rows):
+    """Fewer workgroups than usual for a unit: rows on both sides of what they take."""
+    test_quantize_units(units, rows, torch.bfloat16)
