@@ -266,10 +266,10 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
 
 // Steps 1 to 3 in one launch for contexts of up to kDirectKeys positions and kDirectBuckets buckets: workgroups of 16 waves take 1024
 // ROUNDS positions each, hold their ids, and where a unit has several workgroups each counts the others' ids for itself (the L2
-// serves them; a position takes an LDS addition, 5 us for 64 Ki of them, which is where three launches are as good: 18 and 17 us at
-// 8 heads of 65536).  8 heads of 5003 keys 8.6 us with ids loaded again for the placing, 7.9 now (26 as five launches); of 16384 keys
-// 18.0 -> 10.9, one workgroup for 16384 positions and three launches before; of 30000 keys 17.9 -> 13.7; 64 of 16384: 17.8 -> 12.8.
-constexpr int kDirectKeys = 49152, kDirectBuckets = 2048, kDirectThreads = 1024, kDirectWaves = kDirectThreads / 64;
+// serves them; a position takes an LDS addition).  A whole build, 8 heads: 16000 keys 35 us with one workgroup for 16384 positions,
+// 30 now; with three launches 20000 keys 40, 38 now, 30000 49.5, 48, and 49000 69 either way; where half of the ids are the same 43 and 43
+// at 24000, and if all are 44 and 45 (57 with an addition for each).
+constexpr int kDirectKeys = 32768, kDirectBuckets = 2048, kDirectThreads = 1024, kDirectWaves = kDirectThreads / 64;
 template <int ROUNDS>
 __global__ void __launch_bounds__(kDirectThreads)
 order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
@@ -306,15 +306,42 @@ order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, 
     if (v[k] >= 0) wave_count_add(cnt, v[k], 1u);
   if (n_parts > 1) {
     constexpr int kDeep = 8;                             // loads of a thread in flight
+    // The additions of a wave to one address wait for each other: an id that the wave meets often, the most frequent of a few out of its
+    // first 64 of 512, is counted apart.
+    constexpr int kNone = -2, kOften = 8;
     auto count_others = [&](int from, int to, int* s) {
-      for (int n = from + tid; n < to; n += kDeep * kDirectThreads) {
+      int hot = kNone, n_hot = 0;
+      auto leave_hot = [&] {
+        if (n_hot > 0 && lane == 0) atomicAdd(&s[hot], n_hot);
+        n_hot = 0;
+      };
+      for (int n = from + wave * 64; n < to; n += kDeep * kDirectThreads) {
         int u[kDeep];
 #pragma unroll
-        for (int k = 0; k < kDeep; ++k) u[k] = idu[min(n + k * kDirectThreads, N - 1)];
+        for (int k = 0; k < kDeep; ++k) u[k] = idu[min(n + lane + k * kDirectThreads, N - 1)];
 #pragma unroll
         for (int k = 0; k < kDeep; ++k)
-          if (n + k * kDirectThreads < to && u[k] >= 0 && u[k] < B) atomicAdd(&s[u[k]], 1);
+          if (n + lane + k * kDirectThreads >= to || u[k] >= B) u[k] = -1;
+        int most = max((int)__popcll(__ballot(u[0] == hot)), kOften - 1), next = hot;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int f = __builtin_amdgcn_readlane(u[0], 16 * i), c = (int)__popcll(__ballot(u[0] == f));
+          if (f >= 0 && c > most) {
+            most = c;
+            next = f;
+          }
+        }
+        if (next != hot) {
+          leave_hot();
+          hot = next;
+        }
+#pragma unroll
+        for (int k = 0; k < kDeep; ++k) {
+          n_hot += (int)__popcll(__ballot(u[k] == hot));
+          if (u[k] >= 0 && u[k] != hot) atomicAdd(&s[u[k]], 1);
+        }
       }
+      leave_hot();
     };
     count_others(lo, p0, s_before);
     count_others(p1, hi, s_after);

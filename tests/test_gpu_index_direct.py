@@ -48,3 +48,33 @@ def test_sort_in_one_launch(units, N, B, slack, window, dropped):
         assert np.array_equal(g.cpu().numpy(), w)
     if window:
         assert np.array_equal(got[5].cpu().numpy(), want[5])
+
+
+@pytest.mark.parametrize("units,N,B,slack", [(3, 8193, 24, 1), (2, 20000, 70, 0), (1, 24577, 2048, 1), (2, 32768, 1, 2), (1, 32769, 9, 1)])
+@pytest.mark.parametrize("kind", ["one id", "half one id", "two ids", "runs", "none in range", "last"])
+def test_ids_that_many_positions_share(units, N, B, slack, kind):
+    """Additions of a wave to one address: ids that most of its positions have, that change from run to run, or that no bucket has."""
+    rng = np.random.default_rng(N + B)
+    ids = rng.integers(0, B, (1, units, N)).astype(np.int32)
+    if kind == "one id":
+        ids[:] = B // 2
+    if kind == "half one id":
+        ids[rng.random(ids.shape) < 0.5] = B - 1
+    if kind == "two ids":
+        ids = np.where(rng.random(ids.shape) < 0.6, 0, B - 1).astype(np.int32)
+    if kind == "runs":
+        ids = np.broadcast_to((np.arange(N) // 300 * 7 % B).astype(np.int32), ids.shape).copy()
+    if kind == "none in range":
+        ids[rng.random(ids.shape) < 0.9] = -1
+        ids[..., N // 2:] = B
+    if kind == "last":
+        ids[:], ids[..., N - 1] = 0, B - 1
+    K = torch.zeros(1, units, N, 128, device=DEV, dtype=torch.bfloat16)
+    off, ln, idx = (t.cpu().numpy()[0] for t in saap.build_bucket_index(torch.from_numpy(ids).to(DEV), K, K, B, slack)[:3])
+    for u in range(units):
+        kept = ids[0, u][(ids[0, u] >= 0) & (ids[0, u] < B)]
+        assert np.array_equal(ln[u], np.bincount(kept, minlength=B)) and np.array_equal(np.diff(off[u]), ln[u] + slack) and off[u, 0] == 0
+        want = np.full(idx.shape[1], -1, np.int32)
+        at = np.argsort(np.where((ids[0, u] >= 0) & (ids[0, u] < B), ids[0, u], B), kind="stable")[:len(kept)]
+        want[np.arange(len(kept)) + slack * np.sort(kept)] = at
+        assert np.array_equal(idx[u], want)
