@@ -149,7 +149,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // of this lane is centroid 8*(r/4) + 4*half + r%4 of matrix tile `tile` (global tile number).
   // Two scores per step: with s <= b the second largest of {b, s, x, y} is max(s, med3(b, x, y)),
   // the largest max3(b, x, y): 2.5 vector instructions per score with the tag, not 3.
-  // last: of a ragged last slab, whose rows past the last centroid score less than any other (the lowest finite value: with a tag in
+  // last: the ragged tile, whose rows past the last centroid score less than any other (the lowest finite value: with a tag in
   // its place an infinity would be a NaN); one wins where no score compares, and the key is re-scored (id >= B below).
   auto track_pair = [&](auto last, const f32x16_t& c0, const f32x16_t& c1, int tile, int r) {
     float p0[2], p1[2];
@@ -206,7 +206,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   };
 
   const std::false_type inner;
-  const std::integral_constant<bool, RAGGED> last;       // (rows that all count are not looked at: 254 us at 1024 buckets, 258 at 1000)
+  const std::integral_constant<bool, RAGGED> last;
   f32x16_t a0, a1, b0 = {0}, b1 = {0};   // b0, b1: not read by the first step
   step(inner, 0, 0, a0, a1, b0, b1, 0, true, false);
   for (int t = 0; t < n_slabs - 1; ++t) {
@@ -217,8 +217,19 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
     __syncthreads();
     step(inner, buf ^ 1, 0, a0, a1, b0, b1, t * 2 + 1, true, true);
   }
-  step(last, (n_slabs - 1) & 1, 1, b0, b1, a0, a1, (n_slabs - 1) * 2 + 0, true, true);
-  step(last, 0, 0, a0, a1, b0, b1, (n_slabs - 1) * 2 + 1, false, true);
+  // Of the last slab's two tiles one is ragged, and where that is the first there is no second: 8 heads of 131072 keys, 1000 buckets
+  // 258 us with both looked at, 249.5 so.  With biases, whose loads the branch holds up, both are: 2 heads of 2082 keys, 48 buckets 17.5
+  // us with it, 16.4 without.
+  const int t_last = (n_slabs - 1) * 2, buf_last = (n_slabs - 1) & 1;
+  if (RAGGED && HAS_BIAS) {
+    step(last, buf_last, 1, b0, b1, a0, a1, t_last, true, true);
+    step(last, 0, 0, a0, a1, b0, b1, t_last + 1, false, true);
+  } else if (!RAGGED || B > (t_last + 1) * kCentTile) {
+    step(inner, buf_last, 1, b0, b1, a0, a1, t_last, true, true);
+    step(last, 0, 0, a0, a1, b0, b1, t_last + 1, false, true);
+  } else {
+    step(last, 0, 0, b0, b1, a0, a1, t_last, false, true);
+  }
 
   // lanes l and l+32 own the same key: merge their candidates, lower id on equal packed scores
   __shared__ unsigned s_listed, s_list_base;
