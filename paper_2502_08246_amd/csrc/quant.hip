@@ -135,9 +135,10 @@ extern "C" int32_t saap_quantize_kv(const void* Ksorted, const void* Vsorted, ui
   // 365 without; 336 with fewer workgroups as well.)
   const int stride = 2 * units * 64 <= (long long)SAAP_WS_HEADER_BYTES ? 16 : 1;
   const size_t pieces = (size_t)Ncap * kD / 8;
-  // Four workgroups per compute unit where a few units have rows for them (one head of 139264 rows: 87 us with 64 workgroups to a
-  // tensor, 48 with 512).
-  const long long filling = 2LL * device_cus() / units, with_work = (long long)(pieces / (kQThreads * kQUnroll));
+  // Up to three workgroups per compute unit where a few units have five rounds of rows for them: one head of 139264 rows 69 us with 64
+  // workgroups to a tensor, 33 with 384, 43 with 512; of 34756 rows 13.0 with 64, 11.2 with 128, 21.7 with 512, whose updates of the
+  // unit's line wait for each other.
+  const long long filling = 3LL * device_cus() / (2 * units), with_work = (long long)(pieces / (5 * kQThreads * kQUnroll));
   // No more than have rows: a workgroup without any would read the maximum and count itself for nothing (2048 units of 54 rows: 1669 us
   // with 64 each, 26 with two).  Many units have workgroups enough with all of their loads used.
   const long long per_wg = stride > 1 ? kQThreads : kQThreads * kQUnroll, most = ((long long)pieces + per_wg - 1) / per_wg;
