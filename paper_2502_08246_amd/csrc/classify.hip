@@ -604,10 +604,12 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
   if (!fs && sh.rows_per_set >= kManyRows) {
     hipLaunchKernelGGL(mlp_hidden_bf16_kernel<HIDDEN_PLANES>, g1, dim3(256), 0, hs, static_cast<const bf16_t*>(xq),
                        static_cast<const bf16_t*>(W1), b1, hbuf, sh);
-    // Tiles of 128 x 128 and 64 x 128 (as many waves, half the products) run one to a compute unit, a round of the former takes twice the
+    // Tiles of 128 x 128 and 64 x 128 (as many waves, half the products) run one to a compute unit, a round of the former takes 5/3 of the
     // time; 64 x 64 before every other compute unit has a tile.  8 weight sets, 512 units: 512 rows, 1024 buckets 20.2, 22.3 and 26.7 us
     // (one round, two, two), 552 rows, 880 buckets 30.4, 21.1 and 25.4 (two, two, two of two to a compute unit); 1264 rows, 128 buckets,
-    // 256 units 11.7, 8.6 and 9.8; 240 rows, 496 buckets, 416 units 15.2, 10.4 and 10.1.
+    // 256 units 11.7, 8.6 and 9.8; 240 rows, 496 buckets, 416 units 15.2, 10.4 and 10.1.  With the hidden layer, three rounds of the first
+    // and five of the second: 2208 rows, 4000 buckets, 512 units 60 and 67 us, 4352 rows, 2048 buckets 66.6 and 62.6, 8 sets of 1100 rows,
+    // 1024 buckets 75 and 75; two and four: 4000 rows, 2000 buckets, 448 units 48 and 61.
     auto tiles = [&](int bm, int bn) { return (long long)((sh.rows_per_set + bm - 1) / bm) * ((B + bn - 1) / bn) * Hw; };
     auto launch_rows = [&](auto wm, auto wn, auto tn) -> int32_t {
       constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TN = decltype(tn)::value;
@@ -626,7 +628,7 @@ static int32_t launch_mlp_bf16(const void* xq, const void* W1, const float* b1, 
     typedef std::integral_constant<int, 2> two;
     typedef std::integral_constant<int, 4> four;
     auto rounds = [&](int bm, int bn) { return (tiles(bm, bn) + device_cus() - 1) / device_cus(); };
-    if (2 * rounds(128, 128) <= rounds(64, 128)) return launch_rows(four{}, two{}, two{});
+    if (5 * rounds(128, 128) <= 3 * rounds(64, 128)) return launch_rows(four{}, two{}, two{});
     if (2 * tiles(64, 128) > device_cus()) return launch_rows(two{}, four{}, one{});
     return launch_rows(two{}, two{}, one{});
   }
