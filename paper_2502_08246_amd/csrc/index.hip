@@ -271,7 +271,7 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
 // at 24000, and if all are 44 and 45 (57 with an addition for each).
 constexpr int kDirectKeys = 32768, kDirectBuckets = 2048, kDirectThreads = 1024, kDirectWaves = kDirectThreads / 64;
 template <int ROUNDS>
-__global__ void __launch_bounds__(kDirectThreads)
+__global__ void __launch_bounds__(kDirectThreads, 8)      // two workgroups to a compute unit
 order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, int32_t* __restrict__ off, int32_t* __restrict__ idx,
                     int32_t* __restrict__ res_ids, int N, int Ncap, int B, int id_bits, int lo, int hi, int slack, int W, int n_sink,
                     int n_recent, int n_res) {
