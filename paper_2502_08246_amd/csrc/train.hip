@@ -368,12 +368,12 @@ gemm_f32_kernel(GemmArgs g) {
   for (int t = 0; t < TM; ++t) store_tile<EPI, 16>(g, w, m0 + wm + 32 * t, n0 + wn + col, half, acc[t]);
 }
 
-// C = A' B'; A' is M x K, B' is K x N.  Two by WN waves own a tile of 64 TM x 32 WN TN, a wave TM x TN matrix tiles of 32.  KS: the
+// C = A' B'; A' is M x K, B' is K x N.  Two by WN waves own a tile of 64 TM x 32 WN, a wave TM matrix tiles of 32.  KS: the
 // workgroup has as many such groups of waves, which share out k and add up at the end.
-template <bool TA, bool TB, int EPI, bool VEC, typename EB, int TM, int TN, int WN, int KS>
+template <bool TA, bool TB, int EPI, bool VEC, typename EB, int TM, int WN, int KS>
 __global__ void __launch_bounds__(128 * WN * KS, KS > 2 ? 1 : 2)
 gemm_kernel(GemmArgs g) {
-  constexpr int kThreads = 128 * WN, BM = 64 * TM, BN = 32 * WN * TN;
+  constexpr int kThreads = 128 * WN, BM = 64 * TM, BN = 32 * WN;
   typedef PlaneLoader<!TA, VEC, BM, kThreads, float> LoadA;
   typedef PlaneLoader<TB, VEC, BN, kThreads, EB> LoadB;
   constexpr int kUnits = LoadA::kUnits + LoadB::kUnits;
@@ -383,16 +383,14 @@ gemm_kernel(GemmArgs g) {
   const int w = blockIdx.x, n0 = blockIdx.y * BN, m0 = blockIdx.z * BM;
   const float* A = static_cast<const float*>(g.A) + (size_t)w * g.sA;
   const EB* B = static_cast<const EB*>(g.B) + (size_t)w * g.sB;
-  const int wm = wave / WN * 32 * TM, wn = wave % WN * 32 * TN;
+  const int wm = wave / WN * 32 * TM, wn = wave % WN * 32;
   const int col = lane & 31, half = lane >> 5;
   uint4* const s_ab = s_all + part * 2 * kUnits;
   const bool sums = TA && g.colsum != nullptr && blockIdx.y == 0;
   float csum = 0.f;                                             // of the thread's row of A' (TA: it is always the same)
-  f32x16_t acc[TM][TN], low[TM][TN];                            // the sums of the products of planes 0, and of the others
+  f32x16_t acc[TM], low[TM];                                    // the sums of the products of planes 0, and of the others
 #pragma unroll
-  for (int t = 0; t < TM; ++t)
-#pragma unroll
-    for (int u = 0; u < TN; ++u) acc[t][u] = low[t][u] = (f32x16_t){0};
+  for (int t = 0; t < TM; ++t) acc[t] = low[t] = (f32x16_t){0};
 
   const int oa = LoadA::offset(m0, g.M, g.K), ob = LoadB::offset(n0, g.N, g.K);
   const __amdgpu_buffer_rsrc_t ra = operand_buffer(A, g.M, g.K), rb = operand_buffer(B, g.N, g.K);
@@ -411,12 +409,10 @@ gemm_kernel(GemmArgs g) {
   auto step = [&](Staged& st, int buf, int k0_next, int end) {
     const uint4* sa = s_ab + buf * kUnits;
     const uint4* sb = sa + LoadA::kUnits;
-    bf16x8_t a[TM][3], b[TN][LoadB::kPlanes];
+    bf16x8_t a[TM][3], b[LoadB::kPlanes];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-#pragma unroll
-      for (int u = 0; u < TN; ++u)
-        if (p < LoadB::kPlanes) b[u][p] = LoadB::read(sb, p, wn + 32 * u + col, half);
+      if (p < LoadB::kPlanes) b[p] = LoadB::read(sb, p, wn + col, half);
 #pragma unroll
       for (int t = 0; t < TM; ++t) a[t][p] = LoadA::read(sa, p, wm + 32 * t + col, half);
     }
@@ -424,13 +420,11 @@ gemm_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
-      for (int t = 0; t < TM; ++t)
-#pragma unroll
-        for (int u = 0; u < TN; ++u) {
-          if (kPlaneB[i] >= LoadB::kPlanes) continue;
-          f32x16_t& sum = i < 5 ? low[t][u] : acc[t][u];
-          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kPlaneA[i]], b[u][kPlaneB[i]], sum, 0, 0, 0);
-        }
+      for (int t = 0; t < TM; ++t) {
+        if (kPlaneB[i] >= LoadB::kPlanes) continue;
+        f32x16_t& sum = i < 5 ? low[t] : acc[t];
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kPlaneA[i]], b[kPlaneB[i]], sum, 0, 0, 0);
+      }
     // moved up, the loads would get other registers than the values that they replace, and be waited for when copied over
     __builtin_amdgcn_sched_barrier(0);
     fetch(st, k0_next + 2 * kSlice);
@@ -473,21 +467,19 @@ gemm_kernel(GemmArgs g) {
   // not a number, infinite, or too large for a scaled bfloat16: as fp32 products have it
   if constexpr (KS == 1) {
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
-#pragma unroll
-      for (int u = 0; u < TN; ++u) {
-        const int tm = m0 + wm + 32 * t, tn = n0 + wn + 32 * u;
-        acc[t][u] = (acc[t][u] + low[t][u]) * kDown;
-        if (!all_finite(acc[t][u])) acc[t][u] = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
-        store_tile<EPI, 16>(g, w, tm, tn + col, half, acc[t][u]);
-      }
+    for (int t = 0; t < TM; ++t) {
+      const int tm = m0 + wm + 32 * t, tn = n0 + wn;
+      acc[t] = (acc[t] + low[t]) * kDown;
+      if (!all_finite(acc[t])) acc[t] = fp32_tile<TA, TB, VEC>(g, A, B, tm, tn);
+      store_tile<EPI, 16>(g, w, tm, tn + col, half, acc[t]);
+    }
   } else {
     // part i adds up registers 16 / KS * i and on of all parts, in order
-    static_assert(TM == 1 && TN == 1 && (KS == 2 || KS == 4), "a matrix tile per wave");
+    static_assert(TM == 1 && (KS == 2 || KS == 4), "a matrix tile per wave");
     constexpr int kWaves = kThreads / 64, kQuads = 4 / KS;
     static_assert(KS * kWaves * 4 * 64 <= KS * 2 * kUnits, "the parts' sums take the operands' place");
     float4* s = reinterpret_cast<float4*>(s_all);               // [part][wave][four registers][lane]
-    const f32x16_t mine = acc[0][0] + low[0][0];
+    const f32x16_t mine = acc[0] + low[0];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       s[((part * kWaves + wave) * 4 + q) * 64 + lane] = make_float4(mine[4 * q], mine[4 * q + 1], mine[4 * q + 2], mine[4 * q + 3]);
@@ -616,13 +608,13 @@ void gemm_sized(const GemmArgs& g, int Hw, hipStream_t hs) {
     auto launch = [&](auto kernel, int bm, int bn, int threads) { hipLaunchKernelGGL(kernel, grid(bm, bn), dim3(threads), 0, hs, g); };
     const int columns = (g.N + 63) / 64;
     const bool half_empty = columns < 7 && columns % 2 == 1;      // the last tile of 128 columns, and it counts
-    if (tiled && half_empty && count(128, 64) >= 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 2, 1, 2, 1>, 128, 64, 256);
-    if (tiled && !half_empty && count(128, 128) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 2, 1, 4, 1>, 128, 128, 512);
-    if (tiled && count(64, 64) > 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 1>, 64, 64, 256);
+    if (tiled && half_empty && count(128, 64) >= 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 2, 2, 1>, 128, 64, 256);
+    if (tiled && !half_empty && count(128, 128) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 2, 4, 1>, 128, 128, 512);
+    if (tiled && count(64, 64) > 2LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 2, 1>, 64, 64, 256);
     if (tiled && g.K >= 128 && count(64, 64) <= device_cus() && count(32, 32) >= 2LL * device_cus())
-      return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 4>, 64, 64, 1024);
-    if (tiled && g.K >= 64 && 2 * count(32, 32) >= 5LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 2>, 64, 64, 512);
-    if (tiled && count(64, 64) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 1, 2, 1>, 64, 64, 256);
+      return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 2, 4>, 64, 64, 1024);
+    if (tiled && g.K >= 64 && 2 * count(32, 32) >= 5LL * device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 2, 2>, 64, 64, 512);
+    if (tiled && count(64, 64) >= device_cus()) return launch(gemm_kernel<TA, TB, EPI, VEC, EB, 1, 2, 1>, 64, 64, 256);
   }
   for (long long m = 0; m < g.M; m += kMostTiles * 32)
     for (long long n = 0; n < g.N; n += kMostTiles * 32) {
