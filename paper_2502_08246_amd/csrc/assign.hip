@@ -783,8 +783,8 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
     s_kid[tid] = 0x7fffffff;
   }
   __syncthreads();
-  // Up to eight close keys, as most workgroups have: every centroid in double precision, a thread per pair of the tile, takes half as
-  // long as the second walk and its candidates (2500 keys, 256 / 1024 centroids: 53.7 / 194 us in all with it, 45 / 162 so).
+  // Up to eight close keys, as most workgroups have: every centroid in double precision takes half as long as the second walk and its
+  // candidates, or less (2500 keys, 256 / 1024 centroids: 53.7 / 194 us in all with it, 35 to 40 / 120 to 134 so).
   const bool few = s_close <= 8u;
   if (few) {
     if (ks.close && half == 0 && B > 1) s_list[atomicAdd(&s_odd, 1u)] = row;
@@ -833,8 +833,62 @@ assign_f32_kernel(const float* __restrict__ x, const float* __restrict__ cent, c
     }
     __syncthreads();
   }
-  // every centroid, 32 keys at a time: a thread has a centroid of the tile and four of the keys (or one, of eight)
+  // One or two keys: a thread to a centroid, rows straight from memory (5 us a key and 256 centroids; 15 for up to eight keys from
+  // tiles).
   const int n_listed = (int)s_odd;
+  if (n_listed <= 2) {
+    double* const s_x = reinterpret_cast<double*>(s_cscore);             // [kD], and the waves' best
+    double* const s_wbest = s_x + kD;
+    int* const s_wid = s_cand;
+    static_assert(kF32Cand >= kD + 4, "room for them");
+    for (int i = 0; i < n_listed; ++i) {
+      const size_t g = (size_t)unit * N + s_list[i];
+      if (tid < kD) s_x[tid] = (double)x[g * kD + tid];
+      __syncthreads();
+      double most = 0.0;
+      int most_id = -1;
+      auto take = [&](double o, int o_id) {
+        if (better(o, o_id, most, most_id)) {
+          most = o;
+          most_id = o_id;
+        }
+      };
+      for (int b = tid; b < B; b += 256) {
+        asm volatile("" ::: "memory");                   // hoisted out of the loop, the key's doubles would hold 256 registers
+        const float4* c = reinterpret_cast<const float4*>(cu + (size_t)b * kD);
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          float4 v[16];
+#pragma unroll
+          for (int j = 0; j < 16; ++j) v[j] = c[16 * q + j];
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const double* xs = s_x + 64 * q + 4 * j;
+            t = fma(xs[0], (double)v[j].x, t);
+            t = fma(xs[1], (double)v[j].y, t);
+            t = fma(xs[2], (double)v[j].z, t);
+            t = fma(xs[3], (double)v[j].w, t);
+          }
+        }
+        if (bu) t += (double)bu[b];
+        take(t, b);
+      }
+      for (int n = 1; n < 64; n <<= 1) take(__shfl_xor(most, n), __shfl_xor(most_id, n));
+      if (lane == 0) {
+        s_wbest[wave] = most;
+        s_wid[wave] = most_id;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        for (int w = 1; w < 4; ++w) take(s_wbest[w], s_wid[w]);
+        ids[g] = most_id;
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  // every centroid, 32 keys at a time: a thread has a centroid of the tile and four of the keys (or one, of eight)
   float* const s_keys = &s_c[1][0];                      // [kScanKeys][kD]
   static_assert(kScanKeys * kD <= kCentTile * kF32Pitch, "room for them");
   for (int first = 0; first < n_listed; first += kScanKeys) {
@@ -931,8 +985,8 @@ extern "C" int32_t saap_assign_keys(const void* x, const void* centroids, const 
   if (dtype == SAAP_F32) {
     // A workgroup per key that scores it exactly, or matrix instructions for 128 keys of a (sequence, head) at a time: both take a time
     // that grows with the centroids, the former with the keys (2048 keys, 64 / 256 / 1024 centroids 11.1 / 34 / 119 us), the latter with
-    // the rounds of two workgroups per compute unit, however few keys they hold (10.7 / 30 / 108 us a round without close keys, 16 /
-    // 45 / 162 with some).  512 sequences of 8 heads, 64 centroids: one key each 19 us exactly, 90 otherwise, four 62 and 89; 64 of 8 heads,
+    // the rounds of two workgroups per compute unit, however few keys they hold (10.7 / 30 / 106 us a round without close keys, 14 to
+    // 17 / 35 to 40 / 120 to 134 with some).  512 sequences of 8 heads, 64 centroids: one key each 19 us exactly, 90 otherwise, four 62 and 89; 64 of 8 heads,
     // eight keys each 19 and 15 to 20.
     const long long wgs_of_unit = (N + kF32Keys - 1) / kF32Keys, rounds = (wgs_of_unit * units + 2 * cus - 1) / (2 * cus);
     if (rows <= 8ll * cus * rounds) {

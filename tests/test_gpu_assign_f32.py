@@ -54,9 +54,10 @@ def test_keys_scored_against_every_centroid(B, kind):
     assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV), None if bias is None else bias.to(DEV)).cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("close", [1, 8, 9, 127])
+@pytest.mark.parametrize("close", [1, 2, 3, 8, 9, 127])
 def test_few_close_keys_and_many(close):
-    """Up to eight close keys of a workgroup are scored against every centroid, more of them against the centroids they list."""
+    """Up to eight close keys of a workgroup are scored against every centroid, one or two of them another way than more, and more than eight against the
+    centroids they list."""
     g = torch.Generator().manual_seed(close)
     c = torch.randn(1, 300, 128, generator=g)
     c[:, 7] = c[:, 250] * (1 + 2.0 ** -22)
