@@ -60,6 +60,8 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
                    float* __restrict__ cmax, int32_t* __restrict__ ids, int32_t* __restrict__ flagged,
                    unsigned* __restrict__ n_flagged, size_t list_cap, int Hkv, int N, int B, float tol) {
   __shared__ __align__(16) bf16_t s_c[2][kSlab * kPitch];
+  // Biases of a slab.  They are read until the slab after the next is being stored: four in turn.
+  __shared__ __align__(16) float s_bias[HAS_BIAS ? 4 : 1][HAS_BIAS ? kSlab : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int unit = blockIdx.y, h = unit % Hkv;
   const int col = lane & 31, half = lane >> 5;
@@ -104,14 +106,23 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // buckets: 187 us in all, 20 now).  A loop without the rows' 64-bit addresses is the faster one besides: 8 heads of 131072 keys, 1024
   // buckets, 257 -> 251 us.
   u32x4_t stage[kSlab / 16];
+  float stage_bias = 0.f;
   const __amdgpu_buffer_rsrc_t rows_of_c = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(cu), 0, (int)((unsigned)B * (kD * 2)), 0x00027000);
   auto fetch = [&](int t) {
 #pragma unroll
     for (int i = 0; i < kSlab / 16; ++i)
       stage[i] = __builtin_amdgcn_raw_buffer_load_b128(rows_of_c, (int)((unsigned)t * (kSlab * kD * 2) + (tid + i * 256) * 16), 0, 0);
+    if constexpr (HAS_BIAS) stage_bias = bias[(size_t)h * B + min(t * kSlab + lane, B - 1)];      // (every wave the same)
   };
   float norm2 = 0.f;                             // NORMS: the largest squared norm of the rows that the thread's row of lanes has stored
-  auto stash = [&](int buf) {
+  // Rows past the last centroid score the lowest finite value.  An infinite score would be a NaN with a tag in its low bits and displace
+  // others: a bias of -infinity (a masked bucket) or nearly so is cut down to what leaves room for the product; keys whose best two
+  // scores come from such biases find them equal and are re-scored.  That happens on the biases' way to LDS, once for a workgroup: loaded
+  // by each lane for each tile they held up the ranking (8 heads of 131072 keys, 1024 buckets 414 us, 283 so, 254 without biases).
+  constexpr float kLowest = -3.402823466e38f, kMostBias = 1.7e38f;
+  auto stash = [&](int buf, int t) {
+    if constexpr (HAS_BIAS)
+      s_bias[t & 3][lane] = t * kSlab + lane < B ? __builtin_amdgcn_fmed3f(stage_bias, -kMostBias, kMostBias) : kLowest;
 #pragma unroll
     for (int i = 0; i < kSlab / 16; ++i) {
       const int piece = tid + i * 256, r = piece >> 4, pc = piece & 15;
@@ -124,12 +135,11 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
     }
   };
   fetch(0);
-  stash(0);
+  stash(0, 0);
   fetch(min(1, n_slabs - 1));
   __syncthreads();
 
   const uint32_t keep = 0xFFFFFFF0u;
-  constexpr float kLowest = -3.402823466e38f;
   float best[2], second[2];
   int best_tile[2];
 #pragma unroll
@@ -151,18 +161,17 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   // the largest max3(b, x, y): 2.5 vector instructions per score with the tag, not 3.
   // last: the ragged tile, whose rows past the last centroid score less than any other (the lowest finite value: with a tag in
   // its place an infinity would be a NaN); one wins where no score compares, and the key is re-scored (id >= B below).
-  auto track_pair = [&](auto last, const f32x16_t& c0, const f32x16_t& c1, int tile, int r) {
+  auto track_pair = [&](auto last, const f32x16_t& c0, const f32x16_t& c1, const float (&add)[16], int tile, int r) {
     float p0[2], p1[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       float s0 = c0[r + u], s1 = c1[r + u];
-      const int b = tile * kCentTile + 8 * ((r + u) / 4) + 4 * half + ((r + u) % 4);
       if (HAS_BIAS) {
-        const float bv = bias[(size_t)h * B + (b < B ? b : 0)];
-        s0 += bv;
-        s1 += bv;
+        s0 += add[r + u];
+        s1 += add[r + u];
       }
       if constexpr (decltype(last)::value) {
+        const int b = tile * kCentTile + 8 * ((r + u) / 4) + 4 * half + ((r + u) % 4);
         s0 = b < B ? s0 : kLowest;
         s1 = b < B ? s1 : kLowest;
       }
@@ -183,6 +192,14 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
                   int tile_old, bool has_new, bool has_old) {
     const float old0 = best[0], old1 = best[1];
     bf16x8_t a = a_frag(buf, sub, 0);
+    float add[16];                               // the old tile's biases: register r's centroid is 8*(r/4) + 4*half + r%4 of it
+    if (HAS_BIAS && has_old) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(&s_bias[tile_old >> 1 & 3][(tile_old & 1) * kCentTile + 8 * i + 4 * half]);
+        add[4 * i] = v.x; add[4 * i + 1] = v.y; add[4 * i + 2] = v.z; add[4 * i + 3] = v.w;
+      }
+    }
     if (has_new) {
       n0 = (f32x16_t){0};
       n1 = (f32x16_t){0};
@@ -196,7 +213,7 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
         n1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xb[1][st], n1, 0, 0, 0);
         a = a_next;
       }
-      if (has_old) track_pair(last, o0, o1, tile_old, 2 * st);
+      if (has_old) track_pair(last, o0, o1, add, tile_old, 2 * st);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (has_old) {
@@ -206,25 +223,21 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
   };
 
   const std::false_type inner;
-  const std::integral_constant<bool, RAGGED> last;
+  const std::integral_constant<bool, RAGGED && !HAS_BIAS> last;          // (biases see to it)
   f32x16_t a0, a1, b0 = {0}, b1 = {0};   // b0, b1: not read by the first step
   step(inner, 0, 0, a0, a1, b0, b1, 0, true, false);
   for (int t = 0; t < n_slabs - 1; ++t) {
     const int buf = t & 1;
     step(inner, buf, 1, b0, b1, a0, a1, t * 2 + 0, true, true);
-    stash(buf ^ 1);
+    stash(buf ^ 1, t + 1);
     fetch(min(t + 2, n_slabs - 1));
     __syncthreads();
     step(inner, buf ^ 1, 0, a0, a1, b0, b1, t * 2 + 1, true, true);
   }
   // Of the last slab's two tiles one is ragged, and where that is the first there is no second: 8 heads of 131072 keys, 1000 buckets
-  // 258 us with both looked at, 249.5 so.  With biases, whose loads the branch holds up, both are: 2 heads of 2082 keys, 48 buckets 17.5
-  // us with it, 16.4 without.
+  // 258 us with both looked at, 249.5 so.
   const int t_last = (n_slabs - 1) * 2, buf_last = (n_slabs - 1) & 1;
-  if (RAGGED && HAS_BIAS) {
-    step(last, buf_last, 1, b0, b1, a0, a1, t_last, true, true);
-    step(last, 0, 0, a0, a1, b0, b1, t_last + 1, false, true);
-  } else if (!RAGGED || B > (t_last + 1) * kCentTile) {
+  if (!RAGGED || B > (t_last + 1) * kCentTile) {
     step(inner, buf_last, 1, b0, b1, a0, a1, t_last, true, true);
     step(last, 0, 0, a0, a1, b0, b1, t_last + 1, false, true);
   } else {
@@ -273,8 +286,10 @@ assign_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cent
       const size_t g = (size_t)unit * N + row;
       ids[g] = id;
       // error bound of the fp32 accumulation plus the 4 mantissa bits used for the register tag (of a score of zero: all that it has)
-      const float thr = tol_c * sqrtf(xnorm2[rt]) + 5e-6f * fabsf(nb) + 4e-36f;
-      if (!(nb - ns > thr) || id >= B) {
+      const float from_product = tol_c * sqrtf(xnorm2[rt]);
+      const float thr = from_product + 5e-6f * fabsf(nb) + 4e-36f;
+      // (products near the end of fp32's range may have overflowed, with a bias or without)
+      if (!(nb - ns > thr) || id >= B || !(from_product < tol * 1e38f)) {
         listed[rt] = true;
         slot[rt] = atomicAdd(&s_listed, 1u);
       }
@@ -560,7 +575,8 @@ assign_rescore_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ c
     if (tid < kGroupKeys) {
       float m = s_max[0][tid];
       for (int w = 1; w < kRescoreWaves; ++w) m = fmaxf(m, s_max[w][tid]);
-      // two fp32 scores are compared: the same bound as for the first matrix pass
+      // two fp32 scores are compared: the same bound as for the first matrix pass (a maximum of +infinity may be a finite one's overflow)
+      m = fminf(m, 3.402823466e38f);
       s_lim[tid] = m - (tol * norm * sqrtf(xnorm2) + 5e-6f * fabsf(m));
     }
     __syncthreads();

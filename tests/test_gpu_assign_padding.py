@@ -36,6 +36,20 @@ def test_empty_rows_of_the_last_slab(B, kind, biased, dtype):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("N", [130, 2500])
+@pytest.mark.parametrize("B", [5, 16, 64, 100, 200])
+@pytest.mark.parametrize("kind", ["one +inf", "two +inf", "last +inf", "some -inf", "all -inf", "some lowest", "all lowest", "highest"])
+def test_bf16_biases_at_the_end_of_the_range(N, B, kind):
+    g = torch.Generator().manual_seed(N + B)
+    c, x = torch.randn(2, B, 128, generator=g).to(torch.bfloat16), torch.randn(2, 2, N, 128, generator=g).to(torch.bfloat16)
+    bias = torch.randn(2, B, generator=g)
+    most = torch.finfo(torch.float32).max
+    value = {"+inf": np.inf, "-inf": -np.inf, "lowest": -most, "highest": most}[kind.split()[-1]]
+    bias[0, {"one": [3], "two": [B - 1, 2], "last": [B - 1], "some": list(range(0, B, 3)), "all": list(range(B)), "highest": [1, 4]}[kind.split()[0]]] = value
+    want = ref.assign_keys(x.float().numpy(), c.float().numpy(), bias.numpy())
+    assert np.array_equal(saap.assign_keys(x.to(DEV), c.to(DEV), bias.to(DEV)).cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("N", [130, 2500])                # scored exactly at once; on the matrix cores
 @pytest.mark.parametrize("B", [16, 200])
 @pytest.mark.parametrize("kind", ["one +inf", "two +inf", "some -inf", "all -inf", "some lowest", "all lowest", "sum beyond the largest"])
