@@ -267,8 +267,8 @@ scatter_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ slic
 // Steps 1 to 3 in one launch for contexts of up to kDirectKeys positions and kDirectBuckets buckets: workgroups of 16 waves take 1024
 // ROUNDS positions each, hold their ids, and where a unit has several workgroups each counts the others' ids for itself (the L2
 // serves them; a position takes an LDS addition).  A whole build, 8 heads: 16000 keys 35 us with one workgroup for 16384 positions,
-// 30 now; with three launches 20000 keys 40, 38 now, 30000 49.5, 48, and 49000 69 either way; where half of the ids are the same 43 and 43
-// at 24000, and if all are 44 and 45 (57 with an addition for each).
+// 30 now; with three launches 20000 keys 40, 37.5 now, 30000 49.5, 47.5, and 49000 69 either way; where half of the ids are the same 43 and
+// 44.5 at 24000, and if all are 44 and 45.5 (57 with an addition for each).
 constexpr int kDirectKeys = 32768, kDirectBuckets = 2048, kDirectThreads = 1024, kDirectWaves = kDirectThreads / 64;
 template <int ROUNDS>
 __global__ void __launch_bounds__(kDirectThreads, 8)      // two workgroups to a compute unit
@@ -306,8 +306,8 @@ order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, 
     if (v[k] >= 0) wave_count_add(cnt, v[k], 1u);
   if (n_parts > 1) {
     constexpr int kDeep = 8;                             // loads of a thread in flight
-    // The additions of a wave to one address wait for each other: an id that the wave meets often, the most frequent of a few out of its
-    // first 64 of 512, is counted apart.
+    // The additions of a wave to one address wait for each other: an id that the wave meets often, in the first 64 of 512, is counted
+    // apart.
     constexpr int kNone = -2, kOften = 8;
     auto count_others = [&](int from, int to, int* s) {
       int hot = kNone, n_hot = 0;
@@ -322,10 +322,12 @@ order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, 
 #pragma unroll
         for (int k = 0; k < kDeep; ++k)
           if (n + lane + k * kDirectThreads >= to || u[k] >= B) u[k] = -1;
-        int most = max((int)__popcll(__ballot(u[0] == hot)), kOften - 1), next = hot;
+        // (the most frequent of the one so far and those of two lanes)
+        int most = max(hot == kNone ? 0 : (int)__popcll(__ballot(u[0] == hot)), kOften - 1), next = kNone;
+        if (hot != kNone && most >= kOften) next = hot;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int f = __builtin_amdgcn_readlane(u[0], 16 * i), c = (int)__popcll(__ballot(u[0] == f));
+        for (int i = 0; i < 2; ++i) {
+          const int f = __builtin_amdgcn_readlane(u[0], 32 * i), c = (int)__popcll(__ballot(u[0] == f));
           if (f >= 0 && c > most) {
             most = c;
             next = f;
@@ -334,6 +336,12 @@ order_direct_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ len, 
         if (next != hot) {
           leave_hot();
           hot = next;
+        }
+        if (hot == kNone) {                              // as a rule: nothing more than the additions
+#pragma unroll
+          for (int k = 0; k < kDeep; ++k)
+            if (u[k] >= 0) atomicAdd(&s[u[k]], 1);
+          continue;
         }
 #pragma unroll
         for (int k = 0; k < kDeep; ++k) {
